@@ -17,6 +17,14 @@
 
 namespace tlc {
 
+// How a kernel reaches the five partitions of a range: one float4 per
+// partition slice (m % 4 == 0, 16-byte aligned output), aligned float4 cells
+// off the slice grid (aligned output, m % 4 != 0), or one quartic byte per
+// lane with scalar accesses (unaligned output).
+constexpr int kPathVec = 0;
+constexpr int kPathShift = 1;
+constexpr int kPathByte = 2;
+
 // ---------------------------------------------------------------- index scan
 // A start entry: (stream byte << 8 | how far into its expansion) with the
 // launch's epoch above it, published with an agent-scope atomic store like

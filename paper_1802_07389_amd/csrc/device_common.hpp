@@ -99,15 +99,27 @@ __device__ __forceinline__ ScanU32 block_scan_max_u32(uint32_t v, uint32_t* lds)
   return r;
 }
 
-// How a kernel reaches the five partitions of a tile: one float4 per
-// partition slice (m % 4 == 0, 16-byte aligned tensors), aligned float4
-// cells off the slice grid (aligned tensors, m % 4 != 0), or one quartic
-// byte per lane with scalar accesses (unaligned tensors).
-constexpr int kPathVec = 0;
-constexpr int kPathShift = 1;
-constexpr int kPathByte = 2;
+// Four floats at any dword address: gfx950 loads and stores 16 bytes there
+// with the same instruction as at aligned ones, so tensors that are views
+// into a flat buffer, and partitions that start anywhere (m % 4 != 0), need
+// no path of their own.  (Before, such tensors went value by value, and
+// partitions off the 16-byte grid through LDS atomics: on a 7,340,037-value
+// view the max pass took 35 us and the encoder 46 us.)
+typedef float tlc_f4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ld4(const float* p) {
+  const tlc_f4 v = *reinterpret_cast<const tlc_f4*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st4(float* p, float4 v) {
+  tlc_f4 w;
+  w.x = v.x;
+  w.y = v.y;
+  w.z = v.z;
+  w.w = v.w;
+  *reinterpret_cast<tlc_f4*>(p) = w;
+}
 
-// Streaming float4 accesses (16-byte aligned addresses) with the
+// The same as streaming accesses, with the
 // nontemporal hint, for tensors read or written once per kernel and far
 // larger than the caches.  Measured on gfx950: the max reduction reads
 // 25 % faster with it, the 8-bit kernels (contiguous read/write streams,
@@ -118,7 +130,6 @@ constexpr int kPathByte = 2;
 // loads or stores slowed it or the decode that follows.  The hint changes
 // neither values nor visibility: the next kernel on the stream sees the
 // stores.
-typedef float tlc_f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 ld_stream(const float* p) {
   const tlc_f4 v = __builtin_nontemporal_load(reinterpret_cast<const tlc_f4*>(p));
   return make_float4(v.x, v.y, v.z, v.w);
@@ -192,42 +203,16 @@ __device__ __forceinline__ uint32_t quantize_one(float acc, float M, float U,
   return pos ? 2u : (neg ? 0u : 1u);
 }
 
-// Quartic byte j < m: quantizes the five accumulated values r[j + k*m]
-// (contiguous partitions, p0 most significant; elements past n are the zero
-// padding of Section 3.2, step 4) and returns the byte.  A value with q = 0
-// keeps acc as its residual, which the buffer already holds, so only q != 0
-// writes back.  kX (after the check pass has given M): the buffer still
-// holds the previous residual, acc = x + r is formed here (step 1 of
-// Section 3.1) and every value's residual is stored.
-template <bool kX = false>
-__device__ __forceinline__ uint32_t quantize_byte(const float* __restrict__ x,
-                                                  float* __restrict__ r, uint64_t n,
-                                                  uint64_t m, uint64_t j, float M, float U) {
-  uint32_t code = 0u;
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const uint64_t e = k * m + j;
-    uint32_t t = 0u;
-    if (e < n) {
-      float o;
-      t = quantize_one(kX ? x[e] + r[e] : r[e], M, U, o);
-      if (kX || t != 1u) r[e] = o;
-    }
-    code = code * 3u + t;
-  }
-  return code;
-}
-
-// Quartic bytes j .. j+3 (j % 4 == 0) with m % 4 == 0 and r 16-byte
-// aligned (and x, with kX): every partition slice is one float4.
+// Quartic bytes j .. j+3 (j % 4 == 0): every partition slice is one float4.
 // group4_full says whether all twenty values exist (only the last groups
-// reach into the padding of p4); load_group4 fetches the five slices (the
-// sums x + r with kX) and quantize_group4_loaded quantizes them, stores
-// back a slice if one of its values has q != 0 (every slice with kX), and
-// returns the four bytes packed little-endian.  Split so a caller can keep
-// the loads of several groups in flight at once.
+// reach into the padding of p4) and all four bytes lie before m;
+// load_group4 fetches the five slices (the sums x + r with kX) and
+// quantize_group4_loaded quantizes them, stores back a slice if one of its
+// values has q != 0 (every slice with kX), and returns the four bytes packed
+// little-endian.  Split so a caller can keep the loads of several groups in
+// flight at once.
 __device__ __forceinline__ bool group4_full(uint64_t n, uint64_t m, uint64_t j) {
-  return 4 * m + j + 4 <= n;
+  return 4 * m + j + 4 <= n && j + 4 <= m;
 }
 
 template <bool kX = false>
@@ -235,11 +220,11 @@ __device__ __forceinline__ void load_group4(const float* __restrict__ x,
                                             const float* __restrict__ r, uint64_t m,
                                             uint64_t j, float4 (&a)[5]) {
 #pragma unroll
-  for (int k = 0; k < 5; ++k) a[k] = *reinterpret_cast<const float4*>(r + k * m + j);
+  for (int k = 0; k < 5; ++k) a[k] = ld4(r + k * m + j);
   if (kX) {
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const float4 b = *reinterpret_cast<const float4*>(x + k * m + j);
+      const float4 b = ld4(x + k * m + j);
       a[k] = make_float4(b.x + a[k].x, b.y + a[k].y, b.z + a[k].z, b.w + a[k].w);
     }
   }
@@ -261,33 +246,47 @@ __device__ __forceinline__ uint32_t quantize_group4_loaded(float* __restrict__ r
     code[1] = code[1] * 3u + t1;
     code[2] = code[2] * 3u + t2;
     code[3] = code[3] * 3u + t3;
-    if (kX || ((t0 ^ 1u) | (t1 ^ 1u) | (t2 ^ 1u) | (t3 ^ 1u)))
-      *reinterpret_cast<float4*>(r + k * m + j) = o;
+    if (kX || ((t0 ^ 1u) | (t1 ^ 1u) | (t2 ^ 1u) | (t3 ^ 1u))) st4(r + k * m + j, o);
   }
   return code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
 }
 
-// The group by single bytes (any group, including those in the padding).
+// Any group value by value (contiguous partitions, p0 most significant;
+// elements past n are the zero padding of Section 3.2, step 4; a byte past m
+// gives 0): the last groups of a tensor.  All loads come before the first
+// use.  A value with q = 0 keeps acc as its residual, which the buffer
+// already holds without kX, so only q != 0 writes back there.
 template <bool kX = false>
-__device__ __forceinline__ uint32_t quantize_group4_bytes(const float* __restrict__ x,
-                                                          float* __restrict__ r, uint64_t n,
-                                                          uint64_t m, uint64_t j, float M,
-                                                          float U) {
+__device__ __forceinline__ uint32_t quantize_group4_edge(const float* __restrict__ x,
+                                                         float* __restrict__ r, uint64_t n,
+                                                         uint64_t m, uint64_t j, float M,
+                                                         float U) {
+  float a[5][4];
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint64_t e = k * m + j + c;
+      a[k][c] = j + c < m && e < n ? (kX ? x[e] + r[e] : r[e]) : 0.0f;
+    }
   uint32_t w = 0u;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) w |= quantize_byte<kX>(x, r, n, m, j + c, M, U) << (8 * c);
+  for (int c = 0; c < 4; ++c) {
+    uint32_t code = 0u;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const uint64_t e = k * m + j + c;
+      uint32_t t = 0u;
+      if (j + c < m && e < n) {
+        float o;
+        t = quantize_one(a[k][c], M, U, o);
+        if (kX || t != 1u) r[e] = o;
+      }
+      code = code * 3u + t;
+    }
+    w |= code << (8 * c);
+  }
   return w;
-}
-
-template <bool kX = false>
-__device__ __forceinline__ uint32_t quantize_group4(const float* __restrict__ x,
-                                                    float* __restrict__ r, uint64_t n,
-                                                    uint64_t m, uint64_t j, float M,
-                                                    float U) {
-  if (!group4_full(n, m, j)) return quantize_group4_bytes<kX>(x, r, n, m, j, M, U);
-  float4 a[5];
-  load_group4<kX>(x, r, m, j, a);
-  return quantize_group4_loaded<kX>(r, m, j, a, M, U);
 }
 
 // ---------------------------------------------------------------- stochastic mode
@@ -302,13 +301,14 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
                                                  uint32_t c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
-    const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-    const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    // one 32 x 32 -> 64 multiply each (v_mad_u64_u32), not a low and a high one
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
     c0 = n0;
-    c1 = lo1;
+    c1 = (uint32_t)p1;
     c2 = n2;
-    c3 = lo0;
+    c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;
   }
@@ -328,12 +328,14 @@ __device__ __forceinline__ Philox4 element_words(uint64_t b, uint64_t step, uint
 }
 
 // Stochastic 3-value quantization of one value: sign(x) kept with
-// probability |x|/M, i.e. when u*M < |x| for u = (w >> 8) * 2^-24; the
-// product of a 24-bit integer and an fp32 is exact in double, so the
-// decision is exact.  Returns the trit q + 1.
+// probability |x|/M, i.e. when u*M < |x| for u = (w >> 8) * 2^-24.  The fused
+// multiply-add rounds u*M - |x| once, from its exact value, and rounding
+// keeps the sign (a negative difference too small for a float becomes -0, a
+// zero one +0), so its sign bit is the exact decision; M = 0 (all zeros)
+// keeps nothing.  Returns the trit q + 1.
 __device__ __forceinline__ uint32_t stochastic_trit(float x, float M, uint32_t w) {
-  const double u = (double)(w >> 8) * (1.0 / 16777216.0);
-  const bool keep = (M > 0.0f) && (u * (double)M < fabs((double)x));
+  const float u = (float)(w >> 8) * 0x1p-24f;  // both exact
+  const bool keep = (int32_t)__float_as_uint(__builtin_fmaf(u, M, -fabsf(x))) < 0;
   return keep ? (x > 0.0f ? 2u : 0u) : 1u;
 }
 

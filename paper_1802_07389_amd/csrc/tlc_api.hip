@@ -141,8 +141,8 @@ struct tlc_ctx {
   TileRec* recs = nullptr;
   uint64_t* chunk_agg = nullptr;  // chunk summaries, scanned in place into chunk prefixes
   uint64_t* local_pre = nullptr;  // every tile's prefix within its chunk
-  uint2* fix = nullptr;           // per tile kFixCap deferred residuals
-  uint16_t* summ = nullptr;       // per float4 of the buffer: top half of max |acc|
+  uint16_t* bound = nullptr;      // per 32 values of the buffer: top half of max |acc|
+  uint8_t* trits = nullptr;       // per four values: their trits
   // pinned host memory: status readback, batch results, descriptor staging
   HostReadback* rb = nullptr;
   EncResult* host_results = nullptr;
@@ -446,7 +446,7 @@ int check_usable(tlc_ctx* c, const char* fn) {
 }
 
 // Absmax blocks given to one tensor of a batch (proportional to its size,
-// `items` float4 pairs or single values).
+// `items` float4 pairs).
 uint32_t batch_absmax_blocks(size_t items) {
   size_t b = ceil_div(items, (size_t)kThreads * 4);
   return (uint32_t)std::max<size_t>(1, std::min<size_t>(b, kAbsmaxMaxBlocks));
@@ -493,7 +493,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->start_words = mm / kDecRange + max_tensors + 2;
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
   //         start | enc descs | dec descs | tile records | chunk summaries |
-  //         tile prefixes in their chunks | fix lists | float4 summaries | slots
+  //         tile prefixes in their chunks | line bounds | trits | slots
   // (the batch results follow the control block, so that one copy reads both)
   static_assert(sizeof(Ctrl) % alignof(EncResult) == 0, "results follow the control block");
   const size_t off_res = sizeof(Ctrl);
@@ -518,10 +518,10 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   off = round_up(off + (tiles1 / 64 + 1) * sizeof(uint64_t), 256);
   const size_t off_local = off;
   off = round_up(off + tiles1 * sizeof(uint64_t), 256);
-  const size_t off_fix = off;
-  off = round_up(off + tiles1 * (size_t)kFixCap * sizeof(uint2), 256);
-  const size_t off_summ = off;
-  off = round_up(off + (max_n / 4) * sizeof(uint16_t), 256);
+  const size_t off_bound = off;
+  off = round_up(off + ceil_div(max_n, (size_t)32) * sizeof(uint16_t), 256);
+  const size_t off_trits = off;
+  off = round_up(off + ceil_div(max_n, (size_t)4) + 64, 256);  // 64: whole words past the last
   const size_t off_slots = off;
   const size_t total = round_up(off + tiles1 * (size_t)kEncTile, 256);
   e = hipMalloc(&c->ws, total);
@@ -542,10 +542,10 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->recs = (TileRec*)(base + off_recs);
   c->chunk_agg = (uint64_t*)(base + off_chunks);
   c->local_pre = (uint64_t*)(base + off_local);
-  c->fix = (uint2*)(base + off_fix);
-  c->summ = (uint16_t*)(base + off_summ);
+  c->bound = (uint16_t*)(base + off_bound);
+  c->trits = base + off_trits;
   c->slots = base + off_slots;
-  e = hipMemset(c->ws, 0, total);
+  e = hipMemset(c->ws, 0, off_recs);  // the rest is written before it is read
   if (e == hipSuccess) e = hipDeviceSynchronize();
   // pinned readback block, laid out as the workspace's head: the control
   // block's slot, then the batch results
@@ -617,12 +617,7 @@ namespace {
 // writing, and the writing pass leaves a tensor whose scale is bad
 // untouched, so the buffer keeps its values on TLC_E_NONFINITE;
 // TLC_OPT_IN_PLACE_FEEDBACK drops the check pass.
-// With summ (the three-pass float4 path) after a check pass, the writing
-// pass quantizes every value and leaves trits in summ (*trit set); in place
-// it leaves acc and bounds.
-int launch_max_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint16_t* summ,
-                      uint32_t* np, bool* trit = nullptr) {
-  if (trit) *trit = false;
+int launch_max_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint32_t* np) {
   const uint32_t* guard = nullptr;
   uint32_t guard_np = 0;
   if (r && !(c->options & TLC_OPT_IN_PLACE_FEEDBACK)) {
@@ -632,11 +627,36 @@ int launch_max_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, u
     if (st) return st;
     guard = c->partials_chk;
   }
-  const bool quantize = summ != nullptr && guard != nullptr;
-  if (trit) *trit = quantize;
-  return timed_launch(c, quantize ? TLC_KERNEL_ACCUM_QUANTIZE : TLC_KERNEL_ABSMAX, [&] {
-    return launch_accum_absmax(x, r, n, c->partials, np, summ, guard, guard_np, s, quantize,
-                               c->stream);
+  return timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
+    return launch_accum_absmax(x, r, n, c->partials, np, guard, guard_np, s, nullptr, c->stream);
+  });
+}
+
+// Steps 1, a and b for one tensor: residuals in r, trits in the workspace,
+// err and M in the control block and in hm.  Default policy: the check pass
+// (8n bytes), then the writing pass (12n).  In place: the sums with the max
+// pass (12n), then the lines that can hold a q != 0.
+int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s,
+                           HostMirror hm) {
+  uint32_t np = 0;
+  int st;
+  if (c->options & TLC_OPT_IN_PLACE_FEEDBACK) {
+    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
+      return launch_accum_absmax(x, r, n, c->partials, &np, nullptr, 0, s, c->bound, c->stream);
+    });
+    if (st) return st;
+    return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
+      return launch_quantize_lines(r, n, s, c->partials, np, c->bound, c->trits, c->ctrl, hm,
+                                   c->stream);
+    });
+  }
+  st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
+    return launch_absmax_check(x, r, n, c->partials_chk, &np, c->stream);
+  });
+  if (st) return st;
+  return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
+    return launch_accum_quantize(x, r, n, s, c->partials_chk, np, c->trits, c->ctrl, hm,
+                                 c->stream);
   });
 }
 
@@ -680,24 +700,14 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
 
   arm_results(&c->rb->enc, 1);
   const uint32_t ntiles = (uint32_t)ceil_div(m, kEncTile);
-  // The three passes' float4 path: after the check pass the max pass
-  // quantizes every value and keeps 2-bit trits per value in summ; in place
-  // it keeps a bound per float4 there, and the quantizer skips float4s of
-  // the buffer whose bound is below U.
-  // (The bounds take the float4 slices of the partitions, so m % 4 == 0;
-  // the trits are kept per float4 of the buffer and serve any m.)
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
-  uint16_t* summ = (ntiles >= kThreePassMinTiles && aligned16(tensor) && aligned16(residual) &&
-                    (m % 4 == 0 || !in_place))
-                       ? c->summ
-                       : nullptr;
   if (ntiles < kThreePassMinTiles) {  // small tensor: one chained pass
     // default policy: the check pass, then the chained tiles form acc = x + r
     // themselves; in place: step 1 into the buffer first, as for large tensors
     uint32_t np = 0;
     const uint32_t* partials = c->partials;
     if (in_place) {
-      st = launch_max_passes(c, tensor, residual, n, s, nullptr, &np);
+      st = launch_max_passes(c, tensor, residual, n, s, &np);
     } else {
       partials = c->partials_chk;
       st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
@@ -719,13 +729,10 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
     c->enc_ticket_base += ntiles;
     return finish_compress(c, "tlc_compress", bytes_len, scale, true);
   }
-  uint32_t np = 0;
-  bool trit = false;
-  st = launch_max_passes(c, tensor, residual, n, s, summ, &np, &trit);
+  st = launch_quantize_passes(c, tensor, residual, n, s, enc_mirror(c));
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
-    return launch_quant_encode(residual, n, (uint32_t)m, s, c->partials, np, c->slots, c->recs,
-                               c->fix, summ, trit, c->ctrl, enc_mirror(c), c->stream);
+    return launch_quant_encode(n, (uint32_t)m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
   });
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
@@ -734,7 +741,7 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_COMPACT, [&] {
     return launch_zre_compact(c->recs, c->chunk_agg, c->local_pre, c->slots, (uint32_t)m, bytes,
-                              c->fix, residual, n, c->ctrl, enc_mirror(c), c->stream);
+                              c->ctrl, enc_mirror(c), c->stream);
   });
   if (st) return st;
   return finish_compress(c, "tlc_compress", bytes_len, scale, true);
@@ -765,7 +772,7 @@ int compress_int8(tlc_ctx* c, const float* tensor, float* residual, size_t n, fl
   int st = dev.status();
   if (st) return st;
   uint32_t np = 0;
-  st = launch_max_passes(c, tensor, residual, n, s, nullptr, &np);
+  st = launch_max_passes(c, tensor, residual, n, s, &np);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_INT8_QUANT, [&] {
     return launch_int8_quant(tensor, residual, n, s, c->partials, np, bytes, c->ctrl,
@@ -817,14 +824,26 @@ TLC_API int tlc_compress_ex(tlc_ctx* c, int mode, const float* tensor, float* re
   DeviceScope dev(c->device);
   st = dev.status();
   if (st) return st;
-  float* r = stoch ? nullptr : residual;  // the stochastic mode has no error feedback
-  uint32_t np = 0;
-  st = launch_max_passes(c, tensor, r, n, s, nullptr, &np);
-  if (st) return st;
-  st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
-    return launch_quant_pack(tensor, r, n, (uint32_t)m, s, stoch ? 1 : 0, seed, step,
-                             c->partials, np, bytes, c->ctrl, c->stream);
-  });
+  if (stoch) {  // no error feedback: max |x|, then trits of x
+    uint32_t np = 0;
+    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
+      return launch_accum_absmax(tensor, nullptr, n, c->partials, &np, nullptr, 0, s, nullptr,
+                                 c->stream);
+    });
+    if (st) return st;
+    st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
+      hipError_t e = launch_stochastic_trits(tensor, n, s, seed, step, c->partials, np, c->trits,
+                                             c->ctrl, c->stream);
+      if (e != hipSuccess) return e;
+      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, c->stream);
+    });
+  } else {
+    st = launch_quantize_passes(c, tensor, residual, n, s, HostMirror{});
+    if (st) return st;
+    st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
+      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, c->stream);
+    });
+  }
   if (st) return st;
   st = sync_and_read(c);
   if (st) return st;
@@ -902,10 +921,7 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
     e.s = s[t];
     e.tile0 = tiles;
     e.blk0 = blocks;
-    const bool ral = aligned16(residuals[t]);
-    const bool al = ral && aligned16(tensors[t]);
-    e.nblk = batch_absmax_blocks(al ? ns[t] / 4 : ns[t]);
-    e.vec = ((e.m % 4 == 0 && ral) ? 1u : 0u) | (ral ? 2u : 0u) | (al ? 4u : 0u);
+    e.nblk = batch_absmax_blocks(ns[t] / 4);
     blocks += e.nblk;
     tiles += (uint32_t)ceil_div(e.m, kEncTile);
     d.push_back(e);

@@ -80,29 +80,20 @@ struct EncDesc {
   uint32_t tile0;  // first encoder tile (global tile numbering of the launch)
   uint32_t blk0;   // first absmax block / partial maximum of this tensor
   uint32_t nblk;   // absmax blocks of this tensor
-  uint32_t vec;    // bit 0: m % 4 == 0 and r 16-byte aligned; bit 1: r aligned;
-                   // bit 2: x and r aligned (float4 accumulation)
-  uint32_t pad[2];
+  uint32_t pad[3];
 };
 static_assert(sizeof(EncDesc) == 64, "EncDesc is 64 bytes");
 
 // Per-tile record of the single-tensor encoder's first pass: the zero-run
 // summary of the whole tile (RunSum bits), the length of its leading run of
-// 121 bytes, how many bytes it wrote into its slot (its encoding from the
-// first non-121 byte on), and how many residuals it left in its fix list.
+// 121 bytes and how many bytes it wrote into its slot (its encoding from the
+// first non-121 byte on).
 struct TileRec {
   uint64_t agg;
   uint16_t lead;  // <= kEncTile
   uint16_t len;   // <= kEncTile
-  uint32_t nfix;  // <= kFixCap
+  uint32_t pad;
 };
-static_assert(sizeof(TileRec) == 16, "TileRec is 16 bytes");
-
-// Residuals with q != 0 that a first-pass tile of the float4 path leaves to
-// the compaction pass, as (k * kEncTile + position in the tile, value
-// bits): a few scattered stores cost far less in a pass of their own than
-// mixed into the first pass's read stream.  Further ones are stored at once.
-constexpr uint32_t kFixCap = 256;
 static_assert(sizeof(TileRec) == 16, "TileRec is 16 bytes");
 
 // One stream of a batched decode or of a decode-sum.
@@ -150,21 +141,25 @@ inline void launch_k(void (*kernel)(Formals...), dim3 grid, dim3 block, hipStrea
 // The check pass: partial maxima of |x + r|, nothing written.
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st);
-// summ (may be NULL): per float4 of r, the top half of its largest |acc|;
-// only written on the float4 path (x and r 16-byte aligned).  guard (may
+// Step 1 into the buffer (r NULL: none) and the partial maxima.  guard (may
 // be NULL): the check pass's guard_np partial maxima; if they give a bad
 // scale (with s), nothing is written and the partials mark the tensor bad.
-// trit: after the check pass (guard) on the float4 path, the pass quantizes
-// every value (final residuals in r, 2-bit trits in summ, one byte per
-// float4) and launch_quant_encode(trit) only packs the trits.
-hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n,
-                               uint32_t* partials, uint32_t* nblocks, uint16_t* summ,
-                               const uint32_t* guard, uint32_t guard_np, float s, bool trit,
-                               hipStream_t st);
-hipError_t launch_quant_encode(float* r, uint64_t n, uint32_t m, float s,
-                               const uint32_t* partials, uint32_t npartials, uint8_t* slots,
-                               TileRec* recs, uint2* fix, const uint16_t* summ, bool trit,
-                               Ctrl* ctrl, HostMirror hm, hipStream_t st);
+// bound (may be NULL): per 32 values of r, the top half of the largest |acc|.
+hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
+                               uint32_t* nblocks, const uint32_t* guard, uint32_t guard_np,
+                               float s, uint16_t* bound, hipStream_t st);
+// Eq. 2 for a large tensor: final residuals in r and 2-bit trits, one byte per
+// four values.  After the check pass (its partials): from x + r; in place
+// (the max pass's partials and bounds): from r.
+hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s,
+                                 const uint32_t* partials, uint32_t np, uint8_t* trits,
+                                 Ctrl* ctrl, HostMirror hm, hipStream_t st);
+hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* partials,
+                                 uint32_t np, const uint16_t* bound, uint8_t* trits, Ctrl* ctrl,
+                                 HostMirror hm, hipStream_t st);
+// The tiles' own encodings from the trits.
+hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* recs,
+                               const uint8_t* trits, const Ctrl* ctrl, hipStream_t st);
 // x != NULL: the tiles form acc = x + r themselves from the check pass's
 // partials (r still holds the previous residual); x == NULL: r holds acc.
 hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uint32_t m,
@@ -176,11 +171,12 @@ hipError_t launch_zre_chunks(const TileRec* recs, uint32_t ntiles, uint64_t* loc
                              uint64_t* chunk_agg, Ctrl* ctrl, hipStream_t st);
 hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
                               const uint64_t* local_pre, const uint8_t* slots, uint32_t m,
-                              uint8_t* out, const uint2* fix, float* r, uint64_t n, Ctrl* ctrl,
-                              HostMirror hm, hipStream_t st);
-hipError_t launch_quant_pack(const float* x, float* r, uint64_t n, uint32_t m, float s,
-                             int stochastic, uint64_t seed, uint64_t step,
-                             const uint32_t* partials, uint32_t npartials, uint8_t* out,
+                              uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st);
+// Comparison modes: stochastic trits of x, and the quartic bytes of any trits.
+hipError_t launch_stochastic_trits(const float* x, uint64_t n, float s, uint64_t seed,
+                                   uint64_t step, const uint32_t* partials, uint32_t np,
+                                   uint8_t* trits, Ctrl* ctrl, hipStream_t st);
+hipError_t launch_quant_pack(uint64_t n, uint32_t m, const uint8_t* trits, uint8_t* out,
                              Ctrl* ctrl, hipStream_t st);
 hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s,
                              const uint32_t* partials, uint32_t npartials, uint8_t* out,
