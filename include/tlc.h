@@ -173,7 +173,8 @@ int tlc_compress_ex(tlc_ctx* ctx, int mode, const float* tensor, float* residual
 int tlc_decompress_ex(tlc_ctx* ctx, int mode, const uint8_t* bytes, size_t bytes_len,
                       float scale, size_t n, float* out, int accumulate);
 
-/* Encode `count` tensors in one pass (two launches, one synchronisation):
+/* Encode `count` tensors in one pass (one launch, or two where a tensor has
+ * more than 1,310,720 values; one synchronisation):
  * for every t, exactly tlc_compress(ctx, tensors[t], residuals[t], ns[t],
  * s[t], bytes[t], caps[t], &bytes_len[t], &scales[t]).  All arrays are host
  * arrays of `count` entries; the pointers in them are device pointers, and
@@ -225,8 +226,8 @@ typedef struct tlc_result {
   uint32_t reserved; /* 0 */
 } tlc_result;
 
-/* Largest n tlc_compress_noalloc accepts: 2^23 values (at most 410 encoder
- * tiles, whose scratch is 8 KiB of device memory). */
+/* Largest n tlc_compress_noalloc accepts: 2^23 values (the scratch, 16 KiB of
+ * device memory, holds a status word for each of their encoder tiles). */
 #define TLC_NOALLOC_MAX_N ((size_t)8388608u)
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -244,7 +245,7 @@ typedef struct tlc_result {
  * returned at once, and nothing runs); read *result after the stream has
  * reached it.  No device or pinned memory is allocated, and no library
  * routine that allocates is called: the scratch (a control block, partial
- * maxima, look-back status words) is a static device array of 8 KiB per
+ * maxima, look-back status words) is a static device array of 16 KiB per
  * device, located once per device on the first call there.  Every call on
  * a device shares that array and clears it first, so calls that may
  * overlap on one device (other streams, other host threads) race and must

@@ -26,6 +26,21 @@ __device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > 
 __device__ __forceinline__ void host_put(uint32_t* p, uint32_t v) {
   if (p) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+// A whole result in one 16-byte store: a batch's hundreds of results cross the
+// bus one store each (three word stores per tensor kept 335 blocks from
+// storing anything else for up to 14 us).  The host checks every word by
+// itself, so it need not arrive as one.
+__device__ __forceinline__ void host_put_all(EncResult* h, uint32_t err, uint32_t len,
+                                             float scale) {
+  if (!h) return;
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  u4 w;
+  w.x = err;
+  w.y = len;
+  w.z = __float_as_uint(scale);
+  w.w = 0u;
+  *reinterpret_cast<volatile u4*>(h) = w;
+}
 __device__ __forceinline__ void host_put_result(EncResult* h, uint32_t err, float scale) {
   if (h) {
     host_put(&h->err, err);
@@ -99,6 +114,22 @@ __device__ __forceinline__ ScanU32 block_scan_max_u32(uint32_t v, uint32_t* lds)
   return r;
 }
 
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)uniform32((uint32_t)v) | ((uint64_t)uniform32((uint32_t)(v >> 32)) << 32);
+}
+// A pointer into global memory that is the same in every lane.  The address
+// space is said outright: a pointer read from LDS would otherwise be taken for
+// one that may point into LDS, and every access made a flat one.
+template <class T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  typedef __attribute__((address_space(1))) T G;
+  return (T*)(G*)uniform64(reinterpret_cast<uint64_t>(p));
+}
+
 // Four floats at any dword address: gfx950 loads and stores 16 bytes there
 // with the same instruction as at aligned ones, so tensors that are views
 // into a flat buffer, and partitions that start anywhere (m % 4 != 0), need
@@ -156,29 +187,21 @@ struct Scale {
 };
 
 // rint(fl(a / M)) for |a| <= M is 1 exactly when fl(a / M) > 0.5, i.e. (the
-// tie at 0.5 + 2^-25 rounds down to the even 0.5) when a > M * (0.5 +
-// 2^-25).  That product has at most 49 significant bits, so it is exact in
-// double; U is the smallest float above it.  The test a >= U therefore
-// gives the same q as an IEEE divide followed by round-half-even, and by
-// symmetry a <= -U gives q = -1.  M = 0 makes U the smallest subnormal, so
-// q = 0 for the (all-zero) tensor.
+// tie at 0.5 + 2^-25 rounds down to the even 0.5) when a > T = M * (0.5 +
+// 2^-25).  U is the smallest float above T, so the test a >= U gives the same
+// q as an IEEE divide followed by round-half-even, and by symmetry a <= -U
+// gives q = -1.  M * 2^-25 lies between half and one unit in the last place
+// of M / 2, so for M >= 2^-125 U is the float after M / 2; below, where floats
+// are k * 2^-149 with k their bit pattern, T lies in [k / 2, k / 2 + 1/2) and U
+// is floor(k / 2) + 1 (M = 0: the smallest subnormal, so q = 0 for the
+// all-zero tensor).
 __device__ __forceinline__ float quant_threshold(float M) {
-  const double h = 0.5000000298023223876953125;  // 0.5 + 2^-25
-  const double T = (double)M * h;
-  float f = __double2float_rn(T);
-  if ((double)f <= T) f = __uint_as_float(__float_as_uint(f) + 1u);
-  return f;
+  const uint32_t k = __float_as_uint(M);
+  return __uint_as_float((k < 0x01000000u ? k >> 1 : k - 0x00800000u) + 1u);
 }
 
-// M and U from the partial maxima of one tensor (all kT threads of the
-// block).
-template <int kT = kThreads>
-__device__ __forceinline__ Scale finish_scale(const uint32_t* __restrict__ partials,
-                                              uint32_t np, float s, uint32_t* lds) {
-  static_assert(kT % 64 == 0, "whole waves");
-  uint32_t v = 0;
-  for (uint32_t i = threadIdx.x; i < np; i += kT) v = max(v, partials[i]);
-  const uint32_t A = block_max<kT / 64>(v, lds);
+// M and U from the bit pattern of max|acc|.
+__device__ __forceinline__ Scale scale_of(uint32_t A, float s) {
   Scale sc;
   sc.M = 0.0f;
   sc.U = 0.0f;
@@ -192,101 +215,36 @@ __device__ __forceinline__ Scale finish_scale(const uint32_t* __restrict__ parti
   return sc;
 }
 
-// q = round(acc / M) in {-1, 0, 1} (returned as the trit q + 1) and the
-// residual acc - M*q.  M*q is exact, so acc - M, acc + M and acc are the
-// bit patterns of acc - M*q for q = 1, -1, 0 (acc - (+0) == acc, -0 kept).
+// The same from the partial maxima of one tensor (all kT threads of the
+// block).
+template <int kT = kThreads>
+__device__ __forceinline__ Scale finish_scale(const uint32_t* __restrict__ partials,
+                                              uint32_t np, float s, uint32_t* lds) {
+  static_assert(kT % 64 == 0, "whole waves");
+  uint32_t v = 0;
+  for (uint32_t i = threadIdx.x; i < np; i += kT) v = max(v, partials[i]);
+  return scale_of(block_max<kT / 64>(v, lds), s);
+}
+
+// q = round(acc / M) in {-1, 0, 1} as a float: |acc| >= U, with acc's sign.
+// The residual acc - M*q is one fused multiply-add: the product is exact, so
+// it is the subtraction, and for q = +0 it adds -0, which keeps every acc
+// (-0.0 too).
+__device__ __forceinline__ float quantize_q(float acc, float U) {
+  const float one = __uint_as_float(0x3f800000u | (__float_as_uint(acc) & 0x80000000u));
+  return fabsf(acc) >= U ? one : 0.0f;
+}
+__device__ __forceinline__ float residual_of(float acc, float q, float M) {
+  return __builtin_fmaf(-q, M, acc);
+}
+
+// The same with the trit q + 1.
 __device__ __forceinline__ uint32_t quantize_one(float acc, float M, float U,
                                                  float& res) {
   const bool pos = acc >= U;
   const bool neg = acc <= -U;
   res = pos ? acc - M : (neg ? acc + M : acc);
   return pos ? 2u : (neg ? 0u : 1u);
-}
-
-// Quartic bytes j .. j+3 (j % 4 == 0): every partition slice is one float4.
-// group4_full says whether all twenty values exist (only the last groups
-// reach into the padding of p4) and all four bytes lie before m;
-// load_group4 fetches the five slices (the sums x + r with kX) and
-// quantize_group4_loaded quantizes them, stores back a slice if one of its
-// values has q != 0 (every slice with kX), and returns the four bytes packed
-// little-endian.  Split so a caller can keep the loads of several groups in
-// flight at once.
-__device__ __forceinline__ bool group4_full(uint64_t n, uint64_t m, uint64_t j) {
-  return 4 * m + j + 4 <= n && j + 4 <= m;
-}
-
-template <bool kX = false>
-__device__ __forceinline__ void load_group4(const float* __restrict__ x,
-                                            const float* __restrict__ r, uint64_t m,
-                                            uint64_t j, float4 (&a)[5]) {
-#pragma unroll
-  for (int k = 0; k < 5; ++k) a[k] = ld4(r + k * m + j);
-  if (kX) {
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      const float4 b = ld4(x + k * m + j);
-      a[k] = make_float4(b.x + a[k].x, b.y + a[k].y, b.z + a[k].z, b.w + a[k].w);
-    }
-  }
-}
-
-template <bool kX = false>
-__device__ __forceinline__ uint32_t quantize_group4_loaded(float* __restrict__ r, uint64_t m,
-                                                           uint64_t j, const float4 (&a)[5],
-                                                           float M, float U) {
-  uint32_t code[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    float4 o;
-    const uint32_t t0 = quantize_one(a[k].x, M, U, o.x);
-    const uint32_t t1 = quantize_one(a[k].y, M, U, o.y);
-    const uint32_t t2 = quantize_one(a[k].z, M, U, o.z);
-    const uint32_t t3 = quantize_one(a[k].w, M, U, o.w);
-    code[0] = code[0] * 3u + t0;
-    code[1] = code[1] * 3u + t1;
-    code[2] = code[2] * 3u + t2;
-    code[3] = code[3] * 3u + t3;
-    if (kX || ((t0 ^ 1u) | (t1 ^ 1u) | (t2 ^ 1u) | (t3 ^ 1u))) st4(r + k * m + j, o);
-  }
-  return code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
-}
-
-// Any group value by value (contiguous partitions, p0 most significant;
-// elements past n are the zero padding of Section 3.2, step 4; a byte past m
-// gives 0): the last groups of a tensor.  All loads come before the first
-// use.  A value with q = 0 keeps acc as its residual, which the buffer
-// already holds without kX, so only q != 0 writes back there.
-template <bool kX = false>
-__device__ __forceinline__ uint32_t quantize_group4_edge(const float* __restrict__ x,
-                                                         float* __restrict__ r, uint64_t n,
-                                                         uint64_t m, uint64_t j, float M,
-                                                         float U) {
-  float a[5][4];
-#pragma unroll
-  for (int k = 0; k < 5; ++k)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint64_t e = k * m + j + c;
-      a[k][c] = j + c < m && e < n ? (kX ? x[e] + r[e] : r[e]) : 0.0f;
-    }
-  uint32_t w = 0u;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    uint32_t code = 0u;
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      const uint64_t e = k * m + j + c;
-      uint32_t t = 0u;
-      if (j + c < m && e < n) {
-        float o;
-        t = quantize_one(a[k][c], M, U, o);
-        if (kX || t != 1u) r[e] = o;
-      }
-      code = code * 3u + t;
-    }
-    w |= code << (8 * c);
-  }
-  return w;
 }
 
 // ---------------------------------------------------------------- stochastic mode

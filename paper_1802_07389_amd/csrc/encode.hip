@@ -290,201 +290,41 @@ __global__ __launch_bounds__(kThreads) void tlc_quantize_lines_kernel(
   }
 }
 
-// One block of the batch's max passes.  kStore false: the check pass.
-// guard (kStore): the check pass's partial maxima, same block numbering.
-template <bool kStore>
-__device__ __forceinline__ void accum_absmax_batch_block(const EncDesc* __restrict__ descs,
-                                                         uint32_t count,
-                                                         uint32_t* __restrict__ partials,
-                                                         const uint32_t* __restrict__ guard,
-                                                         uint32_t* lds) {
-  const uint32_t t =
-      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.blk0; });
-  const EncDesc& d = descs[t];
-  const uint32_t blk = blockIdx.x - d.blk0;
-  if (kStore && refused_by_guard(guard ? guard + d.blk0 : nullptr, d.nblk, d.s, lds,
-                                 &partials[blockIdx.x]))
-    return;
-  const uint32_t mx = absmax_part<true, kStore>(d.x, d.r, d.n, blk, d.nblk);
-  const uint32_t bm = block_max(mx, lds);
-  if (threadIdx.x == 0) partials[blockIdx.x] = bm;
-}
-
+// The max passes of a batch's tensors of more than one tile: the check pass
+// or, in place, step 1 into the buffers.
 __global__ __launch_bounds__(kThreads) void tlc_absmax_check_batch_kernel(
     const EncDesc* __restrict__ descs, uint32_t count, uint32_t* __restrict__ partials) {
   __shared__ uint32_t lds[kWaves];
-  accum_absmax_batch_block<false>(descs, count, partials, nullptr, lds);
+  const uint32_t t =
+      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.blk0; });
+  const EncDesc& d = descs[t];
+  const uint32_t bm =
+      block_max(absmax_part<true, false>(d.x, d.r, d.n, blockIdx.x - d.blk0, d.nblk), lds);
+  if (threadIdx.x == 0) partials[blockIdx.x] = bm;
 }
 
 __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_batch_kernel(
-    const EncDesc* __restrict__ descs, uint32_t count, uint32_t* __restrict__ partials,
-    const uint32_t* __restrict__ guard) {
+    const EncDesc* __restrict__ descs, uint32_t count, uint32_t* __restrict__ partials) {
   __shared__ uint32_t lds[kWaves];
-  accum_absmax_batch_block<true>(descs, count, partials, guard, lds);
+  const uint32_t t =
+      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.blk0; });
+  const EncDesc& d = descs[t];
+  const uint32_t bm =
+      block_max(absmax_part<true, true>(d.x, d.r, d.n, blockIdx.x - d.blk0, d.nblk), lds);
+  if (threadIdx.x == 0) partials[blockIdx.x] = bm;
 }
 
-// ---------------------------------------------------------------- Eq. 2, 3.2
 // ---------------------------------------------------------------- Eq. 2, 3.2, 3.3
+template <int kW>
 struct EncShared {
-  uint32_t red[kWaves];
-  uint32_t fault;
-  uint32_t red2[kWaves];
-  uint32_t lead;   // the tile's first non-121 byte (first pass)
-  RunSum wave[kWaves];
-  RunSum excl;
+  uint32_t red[kW];
+  uint32_t red2[kW];
+  uint32_t lead;   // the tile's first non-121 byte
   __align__(16) uint8_t q[kEncTile];
   __align__(16) uint8_t out[kEncTile + 16];
 };
 
-static_assert(kEncTile / kThreads == 16, "one uint4 of quartic bytes per thread");
 constexpr int kGroupsPerThread = kEncTile / 4 / kThreads;  // groups of 4 bytes per thread
-
-// Phase 1 of a tile (Eq. 2, residual write-back, quartic pack): the block
-// quantizes the 5 * tile_bytes accumulated values of quartic bytes
-// [q0, q0 + tile_bytes), held in the buffer r, and leaves the bytes in q
-// (LDS).  Threads take groups of 4 bytes, interleaved so every load and store
-// instruction is coalesced.  In a whole tile whose every group lies before n,
-// all of a thread's groups are loaded, without branches between them, before
-// the first is quantized: one memory round trip per tile instead of one per
-// group, at the cost of registers, for grids small enough to stay resident
-// (the chained and batched encoders).  Ends with a barrier.
-template <bool kX>
-__device__ __forceinline__ void quantize_tile(const float* __restrict__ x, float* __restrict__ r,
-                                              uint64_t n, uint32_t m, const Scale& sc,
-                                              uint64_t q0, uint32_t tile_bytes, uint8_t* q) {
-  if (tile_bytes == (uint32_t)kEncTile && group4_full(n, m, q0 + kEncTile - 4u)) {
-    float4 v[kGroupsPerThread][5];
-#pragma unroll
-    for (int it = 0; it < kGroupsPerThread; ++it)
-      load_group4<kX>(x, r, m, q0 + (threadIdx.x + kThreads * it) * 4u, v[it]);
-#pragma unroll
-    for (int it = 0; it < kGroupsPerThread; ++it) {
-      const uint32_t g = threadIdx.x + kThreads * it;
-      *reinterpret_cast<uint32_t*>(q + g * 4u) =
-          quantize_group4_loaded<kX>(r, m, q0 + g * 4u, v[it], sc.M, sc.U);
-    }
-  } else {
-    // The thread's groups g = threadIdx.x + kThreads * it: the next group's
-    // ten loads are issued before the current group is quantized, so a
-    // tile takes about one memory round trip per thread instead of one per
-    // group (the groups' values are disjoint).  A group reaching into the
-    // padding of p4 or past m goes value by value.
-    auto ok = [&](uint32_t g) {
-      return g * 4u < tile_bytes && group4_full(n, m, q0 + g * 4u);
-    };
-    float4 cur[5];
-    if (ok(threadIdx.x)) load_group4<kX>(x, r, m, q0 + threadIdx.x * 4u, cur);
-#pragma unroll 1
-    for (uint32_t g = threadIdx.x; g * 4u < tile_bytes; g += kThreads) {
-      const uint64_t j = q0 + g * 4u;
-      float4 nxt[5];
-      const bool next = ok(g + kThreads);
-      if (next) load_group4<kX>(x, r, m, j + 4u * kThreads, nxt);
-      *reinterpret_cast<uint32_t*>(q + g * 4u) =
-          ok(g) ? quantize_group4_loaded<kX>(r, m, j, cur, sc.M, sc.U)
-                : quantize_group4_edge<kX>(x, r, n, m, j, sc.M, sc.U);
-      if (next) {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) cur[k] = nxt[k];
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Encodes tile `lt` (kEncTile quartic bytes) of one tensor of a batch whose
-// scale is sc.  Phase 1: quantize_tile.  Phase 2: each thread takes
-// kEncTile/256 consecutive bytes and summarises them as a RunSum; the block
-// scans the summaries, the tile gets its prefix by decoupled look-back
-// (status slot floor + lt; slot floor is the tensor's first tile), and
-// every thread zero-run encodes its bytes from its own prefix into LDS; the
-// block then copies the tile's output into the stream.  The last tile
-// stores the stream length in res->len.
-template <bool kX>
-__device__ __forceinline__ void encode_tile(const float* __restrict__ x, float* __restrict__ r,
-                                            uint64_t n, uint32_t m, const Scale& sc,
-                                            uint32_t lt, uint32_t floor,
-                                            uint8_t* __restrict__ out,
-                                            uint64_t* __restrict__ status, uint32_t epoch,
-                                            Ctrl* __restrict__ ctrl, EncResult* res,
-                                            EncResult* hres, uint32_t* hfault,
-                                            EncShared& sh) {
-  constexpr int kBytes = kEncTile / kThreads;  // zero-run bytes per thread
-  static_assert(kBytes % 16 == 0, "threads read whole uint4s of quartic bytes");
-
-  // ---- phase 1: Eq. 1-2, residual write-back, quartic pack
-  const uint64_t q0 = (uint64_t)lt * kEncTile;
-  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
-  quantize_tile<kX>(x, r, n, m, sc, q0, tile_bytes, sh.q);
-
-  // ---- phase 2: Section 3.3
-  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-  const uint32_t lo = threadIdx.x * kBytes;
-  const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
-  const uint32_t nz = cnt ? nonzero_group_mask(sh.q, lo, cnt) : 0u;
-  const RunSum sum = rs_mask_summary(nz, cnt);
-
-  const RunSum incl = wave_incl_scan_rs(sum);
-  const RunSum excl_lane = wave_prev_lane_rs(incl);
-  if (lane == 63) sh.wave[wid] = incl;
-  __syncthreads();
-  RunSum wpre = rs_identity();
-  RunSum agg = rs_identity();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    if ((uint32_t)w < wid) wpre = rs_combine(wpre, sh.wave[w]);
-    agg = rs_combine(agg, sh.wave[w]);
-  }
-
-  if (wid == 0) {
-    bool fault = false;
-    uint64_t ex = rs_to_payload(rs_identity());
-    if (lt == 0) {
-      if (lane == 0)
-        status_publish(&status[floor], EncSW::pack(rs_to_payload(agg), kFlagPrefix, epoch));
-    } else {
-      ex = lookback_wave<EncSW>(status, floor, floor + lt, rs_to_payload(agg), ex, epoch,
-                                EncOp(), &fault);
-    }
-    if (lane == 0) {
-      sh.excl = rs_from_payload(ex);
-      sh.fault = fault ? 1u : 0u;
-      if (fault) {
-        __hip_atomic_store(&ctrl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        host_put(hfault, 1u);
-      }
-    }
-  }
-  __syncthreads();
-  if (sh.fault) return;
-
-  const RunSum tex = sh.excl;
-  const RunSum P = rs_combine(rs_combine(tex, wpre), excl_lane);
-  const uint32_t tile_begin = rs_emitted(tex);
-  uint32_t o = rs_emitted(P) - tile_begin;
-  uint32_t phi = rs_phase(P);
-  auto put = [&](uint32_t c) {
-    if (o < sizeof(sh.out)) sh.out[o] = (uint8_t)c;
-    ++o;
-  };
-  phi = rs_mask_walk(nz, cnt, phi, [&](uint32_t i) { return (uint32_t)sh.q[lo + i]; }, put);
-  if (cnt && q0 + lo + cnt == m && phi) put(rs_code(phi));  // stream ends in a run
-
-  const bool last_tile = q0 + kEncTile >= m;
-  const RunSum tincl = rs_combine(tex, agg);
-  const uint32_t tile_end = last_tile ? rs_total(tincl) : rs_emitted(tincl);
-  __syncthreads();
-  // a tile emits at most kEncTile + 1 bytes; the clamps only keep a logic
-  // error from writing outside the m-byte output buffer
-  const uint32_t count =
-      tile_end >= tile_begin ? umin32(tile_end - tile_begin, kEncTile + 1) : 0u;
-  for (uint32_t i = threadIdx.x; i < count; i += kThreads)
-    if (tile_begin + i < m) out[tile_begin + i] = sh.out[i];
-  if (last_tile && threadIdx.x == 0) {
-    res->len = tile_end;
-    if (hres) host_put(&hres->len, tile_end);
-  }
-}
 
 // ---------------------------------------------------------------- single tensor, three passes
 // A single tensor is encoded without any wait between tiles:
@@ -659,7 +499,7 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
   constexpr int kHalves = kEncTile / kT / 16;
   constexpr uint32_t kBytes = 16u * kHalves;  // quartic bytes per thread
   static_assert(kHalves == 1 || kHalves == 2, "one or two pieces of 16 bytes per thread");
-  __shared__ EncShared sh;
+  __shared__ EncShared<kW> sh;
   __shared__ uint32_t s_lut[5][256];
   const uint32_t t = blockIdx.x;
   const uint64_t q0 = (uint64_t)t * kEncTile;
@@ -833,18 +673,53 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_chunk_kernel(
 // ends the stream and the stream length.  Every write is clamped to
 // the m-byte output (the stream never exceeds m bytes; the clamp only
 // contains a logic error).
+// kOwnPrefix (at most kOwnPrefixTiles tiles): no pass B; the block combines
+// the summaries of all tiles before its first one itself, a few per thread.
+template <bool kOwnPrefix>
 __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
     const TileRec* __restrict__ recs, const uint64_t* __restrict__ chunk_pre,
     const uint64_t* __restrict__ local_pre, const uint8_t* __restrict__ slots, uint32_t m,
     uint32_t ntiles, uint8_t* __restrict__ out, Ctrl* __restrict__ ctrl, HostMirror hm) {
   if (ctrl->enc.err) return;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t t = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const uint32_t t0 = blockIdx.x * kWaves;
+  const uint32_t t = t0 + (threadIdx.x >> 6);
+  RunSum P;
+  if constexpr (kOwnPrefix) {
+    __shared__ uint64_t s_wave[kWaves];
+    constexpr uint32_t kPer = kOwnPrefixTiles / kThreads;
+    RunSum sum = rs_identity();
+#pragma unroll
+    for (uint32_t i = 0; i < kPer; ++i) {  // tiles kPer * thread + i, in order
+      const uint32_t u = kPer * threadIdx.x + i;
+      RunSum a = rs_identity();
+      if (u < t0) a.v = recs[u].agg;
+      sum = rs_combine(sum, a);
+    }
+    sum = wave_incl_scan_rs(sum);
+    if (lane == 63) s_wave[threadIdx.x >> 6] = sum.v;
+    __syncthreads();
+    P = rs_identity();
+#pragma unroll 1
+    for (uint32_t i = 0; i < kWaves; ++i) {
+      RunSum b;
+      b.v = s_wave[i];
+      P = rs_combine(P, b);
+    }
+#pragma unroll 1
+    for (uint32_t u = t0; u < t && u < ntiles; ++u) {  // the block's own earlier tiles
+      RunSum b;
+      b.v = recs[u].agg;
+      P = rs_combine(P, b);
+    }
+  }
   if (t >= ntiles) return;  // whole waves; nothing below synchronises the block
-  RunSum cp, lp;
-  cp.v = chunk_pre[t / kChunkTiles];
-  lp.v = local_pre[t];
-  const RunSum P = rs_combine(cp, lp);
+  if constexpr (!kOwnPrefix) {
+    RunSum cp, lp;
+    cp.v = chunk_pre[t / kChunkTiles];
+    lp.v = local_pre[t];
+    P = rs_combine(cp, lp);
+  }
   const TileRec rec = recs[t];
   const uint64_t q0 = (uint64_t)t * kEncTile;
   const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
@@ -879,61 +754,434 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
   }
 }
 
-// A small tensor in one pass: tiles taken in order from the ticket and
-// chained by decoupled look-back (status slot = tile).  With few tiles the
-// look-back rarely waits, and this saves the two small passes' launches.
-// kX (the default error policy): partials are the check pass's, the buffer
-// still holds the previous residual, and the tiles form acc = x + r
-// themselves (no writing max pass before them).
-template <bool kX>
-__global__ __launch_bounds__(kThreads) void tlc_quant_encode_chained_kernel(
-    const float* __restrict__ x, float* __restrict__ r, uint64_t n, uint32_t m, float s,
-    const uint32_t* __restrict__ partials, uint32_t np, uint8_t* __restrict__ out,
-    uint64_t* __restrict__ status, uint32_t ticket_base, uint32_t epoch,
-    Ctrl* __restrict__ ctrl, HostMirror hm) {
-  __shared__ EncShared sh;
-  __shared__ uint32_t s_tile;
-  if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
-  const Scale sc = finish_scale(partials, np, s, sh.red);  // includes a barrier
-  const uint32_t tile = s_tile;
-  if (tile == 0 && threadIdx.x == 0) {
-    ctrl->enc.err = sc.bad;
-    ctrl->enc.scale = sc.M;
-    host_put_result(hm.res, sc.bad, sc.M);
+// ---------------------------------------------------------------- small tensors
+// A tile of a small tensor, or of one tensor of a batch, in one go: kT threads
+// of kG groups of four quartic bytes each.  Every thread loads the values of
+// its own bytes (five slices of x and r per group) before anything else, so
+// the tile takes one round trip to memory; the values then stay in registers
+// for M, Eq. 2, the residuals and the quartic bytes.
+//
+// M: a tensor of one tile is all in its block.  Of a tensor of at most
+// kExchangeTiles tiles, every tile publishes its largest |acc| in a word of
+// its own and reads the others' (nothing is written before all have come), so
+// that no check pass runs before.  Tiles take tickets in order and a tensor's
+// are consecutive, so a tile only waits for tiles that run already or are next
+// to start, at most kExchangeTiles - 1 of them.  A longer tensor's M comes
+// from a check pass (partials).
+//
+// The zero-run encoding is the first pass's (from the gaps between non-121
+// bytes, from the tile's first one on).  Its place in the stream and the
+// leading run's codes need the tiles before: every tile publishes its summary
+// and, with at most kExchangeTiles, reads all summaries before its own at
+// once; in a longer tensor they are chained by decoupled look-back.
+//
+// Bound by latency (a few dependent round trips and some 1500 instructions per
+// wave): tiles of 2048 quartic bytes spread a million values over 103 blocks.
+template <int kT, int kG>
+struct TileShared {
+  uint32_t red[kT / 64];
+  uint32_t red2[kT / 64];
+  uint32_t lead;   // the tile's first non-121 byte
+  uint32_t fault;
+  // what the first waves read of the other tiles: maxima, then summaries
+  uint64_t wave[kExchangeTiles / 64];
+  LookShared<kT / 64> look;
+  __align__(16) uint8_t out[kT * kG * 4 + 16];
+};
+
+// Where one tensor of a launch lies and where its results go.
+struct TileJob {
+  const float* x;  // null: r holds the sums already
+  float* r;
+  uint8_t* out;
+  uint64_t n;
+  uint32_t m;
+  float s;
+  const uint32_t* partials;  // the check pass's (more than kExchangeTiles tiles)
+  uint32_t np;
+  uint32_t floor;  // status slot of the tensor's first tile
+  EncResult* res;
+  EncResult* hres;
+};
+
+// Waits until every one of the `count` (<= 64 * waves) words p[lane index] has
+// ready(word); each lane gets its own word, lanes past count get 0.  False
+// when the wait runs past kSpinLimit.
+template <class Ready>
+__device__ __forceinline__ bool wait_words(const uint64_t* p, bool mine, Ready ready,
+                                           uint64_t* w) {
+  *w = 0u;
+  for (uint32_t spins = 0;; ++spins) {
+    if (mine) *w = status_read(p);
+    if (__ballot(mine && !ready(*w)) == 0u) return true;
+    if (spins > kSpinLimit) return false;
+    __builtin_amdgcn_s_sleep(1);
   }
-  if (sc.bad) return;  // NaN/Inf or overflow: no stream (the buffer as it was, or acc)
-  encode_tile<kX>(x, r, n, m, sc, tile, 0, out, status, epoch, ctrl, &ctrl->enc, hm.res,
-                         hm.fault, sh);
 }
 
-// kX as for the chained kernel (partials: the check pass's).
-template <bool kX>
-__global__ __launch_bounds__(kThreads) void tlc_quant_encode_batch_kernel(
-    const EncDesc* __restrict__ descs, uint32_t count, const uint32_t* __restrict__ partials,
-    EncResult* __restrict__ results, uint64_t* __restrict__ status, uint32_t ticket_base,
-    uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
-  __shared__ EncShared sh;
-  __shared__ uint32_t s_tile;
-  if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
-  __syncthreads();
-  const uint32_t T = s_tile;
-  const uint32_t t = find_desc(descs, count, T, [](const EncDesc& d) { return d.tile0; });
-  const EncDesc d = descs[t];
-  const Scale sc = finish_scale(partials + d.blk0, d.nblk, d.s, sh.red);
-  const uint32_t lt = T - d.tile0;
-  EncResult* hres = hm.res ? hm.res + t : nullptr;
-  if (lt == 0 && threadIdx.x == 0) {
-    results[t].err = sc.bad;
-    results[t].scale = sc.M;
-    host_put_result(hres, sc.bad, sc.M);
-    if (sc.bad) {
-      results[t].len = 0u;
-      if (hres) host_put(&hres->len, 0u);
+template <int kT, int kG>
+__device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool in_place,
+                                            uint64_t* __restrict__ status,
+                                            uint64_t* __restrict__ maxima, uint32_t epoch,
+                                            Ctrl* __restrict__ ctrl, uint32_t* hfault,
+                                            TileShared<kT, kG>& sh) {
+  constexpr int kW = kT / 64;
+  constexpr uint32_t kBytes = 4u * kG;        // quartic bytes per thread
+  constexpr uint32_t kTile = kT * kBytes;
+  static_assert(kBytes <= 16, "the gap forms take at most 16 bytes per thread");
+  constexpr uint32_t kReaders = kExchangeTiles / 64;  // waves that read a tensor's words
+  static_assert(kReaders <= kW && kExchangeTiles % 64 == 0, "a word per lane");
+  const uint64_t n = J.n, m = J.m;
+  const uint64_t q0 = (uint64_t)lt * kTile;
+  const uint32_t tile_bytes = (uint32_t)umin64(kTile, m - q0);
+  const uint32_t tiles = (uint32_t)((m + kTile - 1) / kTile);
+  const bool chained = m > (uint64_t)kExchangeTiles * kSmallTile;
+  const bool last_tile = q0 + kTile >= m;
+  const uint32_t lo = threadIdx.x * kBytes;
+  const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  auto fault_out = [&]() {
+    __hip_atomic_store(&ctrl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    host_put(hfault, 1u);
+  };
+  if (threadIdx.x == 0) sh.fault = 0u;  // read after several barriers
+
+  // ---- step 1: acc = x + r, the thread's 20 * kG values; 0 past the end.
+  // Of partition k the tile holds the first lim[k] of the block's bytes'
+  // values (all but the last tile: all of them), from a place that is the same
+  // for the whole block.
+  uint32_t lim[5], least = kTile;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const uint64_t base = (uint64_t)k * m + q0;
+    lim[k] = n > base ? (uint32_t)umin64(n - base, tile_bytes) : 0u;
+    least = umin32(least, lim[k]);
+  }
+  auto part = [&](int k) { return lim[k] ? (uint64_t)k * m + q0 : 0u; };  // in bounds in any case
+  float4 v[kG][5], b[kG][5];
+  bool full[kG];
+#pragma unroll
+  for (int g = 0; g < kG; ++g) {
+    const uint32_t i = lo + 4u * g;
+    full[g] = i + 4u <= least;
+    if (full[g]) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) v[g][k] = ld4(J.r + part(k) + i);
+      if (J.x) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) b[g][k] = ld4(J.x + part(k) + i);
+      }
+    } else if (i < tile_bytes) {
+      // the group at the end, without branches: a value that does not exist
+      // is read as the last one that does, and zeroed below
+      auto one = [&](const float* p, int k, uint32_t c) {
+        return (p + part(k))[umin32(i + c, lim[k] ? lim[k] - 1u : 0u)];
+      };
+#pragma unroll
+      for (int k = 0; k < 5; ++k)
+        v[g][k] = make_float4(one(J.r, k, 0), one(J.r, k, 1), one(J.r, k, 2), one(J.r, k, 3));
+      if (J.x) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+          b[g][k] = make_float4(one(J.x, k, 0), one(J.x, k, 1), one(J.x, k, 2), one(J.x, k, 3));
+      }
     }
   }
-  if (sc.bad) return;  // this tensor is refused; the others go on
-  encode_tile<kX>(d.x, d.r, d.n, d.m, sc, lt, d.tile0, d.out, status, epoch, ctrl, &results[t],
-                  hres, hm.fault, sh);
+#pragma unroll
+  for (int g = 0; g < kG; ++g) {
+    const uint32_t i = lo + 4u * g;
+    if (i < tile_bytes) {
+      if (J.x) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+          v[g][k] = make_float4(b[g][k].x + v[g][k].x, b[g][k].y + v[g][k].y,
+                                b[g][k].z + v[g][k].z, b[g][k].w + v[g][k].w);
+      }
+      if (!full[g]) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+          v[g][k] = make_float4(i < lim[k] ? v[g][k].x : 0.f, i + 1u < lim[k] ? v[g][k].y : 0.f,
+                                i + 2u < lim[k] ? v[g][k].z : 0.f,
+                                i + 3u < lim[k] ? v[g][k].w : 0.f);
+      }
+    }
+  }
+
+  // ---- Eq. 1
+  Scale sc;
+  if (!chained) {
+    uint32_t mx = 0u;
+#pragma unroll
+    for (int g = 0; g < kG; ++g) {
+      if (cnt > 4u * g) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+          mx = max(mx, max(max(abs_bits(v[g][k].x), abs_bits(v[g][k].y)),
+                           max(abs_bits(v[g][k].z), abs_bits(v[g][k].w))));
+      }
+    }
+    mx = block_max<kW>(mx, sh.red);
+    if (tiles > 1u) {
+      if (threadIdx.x == 0)
+        status_publish(&maxima[J.floor + lt], ((uint64_t)epoch << 32) | mx);
+      if (wid < kReaders) {
+        uint64_t w;
+        const bool ok = wait_words(
+            &maxima[J.floor + threadIdx.x], threadIdx.x < tiles,
+            [&](uint64_t v) { return (uint32_t)(v >> 32) == epoch; }, &w);
+        const uint32_t wm = wave_max((uint32_t)w);
+        if (lane == 0) {
+          sh.wave[wid] = wm;
+          if (!ok) {
+            sh.fault = 1u;
+            fault_out();
+          }
+        }
+      }
+      __syncthreads();
+      if (sh.fault) return;  // nothing is written yet
+#pragma unroll
+      for (uint32_t i = 0; i < kReaders; ++i) mx = max(mx, (uint32_t)sh.wave[i]);
+    }
+    sc = scale_of(mx, J.s);
+  } else {
+    sc = finish_scale<kT>(J.partials, J.np, J.s, sh.red);
+  }
+  // one of the last tile's threads reports for the whole tensor
+  if (sc.bad && last_tile && threadIdx.x == 0) {
+    J.res->err = 1u;
+    J.res->len = 0u;
+    J.res->scale = 0.0f;
+    host_put_all(J.hres, 1u, 0u, 0.0f);
+  }
+  auto store = [&](int g, int k, const float4& o) {
+    const uint32_t i = lo + 4u * g;
+    float* p = J.r + part(k) + i;
+    if (full[g]) {
+      st4(p, o);
+    } else {
+      if (i < lim[k]) p[0] = o.x;
+      if (i + 1u < lim[k]) p[1] = o.y;
+      if (i + 2u < lim[k]) p[2] = o.z;
+      if (i + 3u < lim[k]) p[3] = o.w;
+    }
+  };
+  if (sc.bad) {
+    // NaN/Inf or overflow: no stream, the buffer as it was or, in place, the
+    // sums (which it holds already where x is null)
+    if (in_place && J.x) {
+#pragma unroll
+      for (int g = 0; g < kG; ++g)
+        if (cnt > 4u * g)
+#pragma unroll
+          for (int k = 0; k < 5; ++k) store(g, k, v[g][k]);
+    }
+    return;
+  }
+
+  // ---- Eq. 2, residuals, quartic pack: a byte is 121 + sum of 3^(4-k) * q_k,
+  // exact in floats, and padding is q = -1 (trit 0)
+  uint32_t w[kG];
+#pragma unroll
+  for (int g = 0; g < kG; ++g) {
+    w[g] = 0x79797979u;
+    if (cnt > 4u * g) {
+      float c0 = 121.f, c1 = 121.f, c2 = 121.f, c3 = 121.f;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        const float wt = (float)trit_weight(k);
+        const float4 a = v[g][k];
+        float4 q = make_float4(quantize_q(a.x, sc.U), quantize_q(a.y, sc.U),
+                               quantize_q(a.z, sc.U), quantize_q(a.w, sc.U));
+        store(g, k, make_float4(residual_of(a.x, q.x, sc.M), residual_of(a.y, q.y, sc.M),
+                                residual_of(a.z, q.z, sc.M), residual_of(a.w, q.w, sc.M)));
+        if (!full[g]) {
+          const uint32_t i = lo + 4u * g;
+          q.x = i < lim[k] ? q.x : -1.f;
+          q.y = i + 1u < lim[k] ? q.y : -1.f;
+          q.z = i + 2u < lim[k] ? q.z : -1.f;
+          q.w = i + 3u < lim[k] ? q.w : -1.f;
+        }
+        c0 = __builtin_fmaf(q.x, wt, c0);
+        c1 = __builtin_fmaf(q.y, wt, c1);
+        c2 = __builtin_fmaf(q.z, wt, c2);
+        c3 = __builtin_fmaf(q.w, wt, c3);
+      }
+      w[g] = __builtin_amdgcn_cvt_pk_u8_f32(
+          c3, 3u, __builtin_amdgcn_cvt_pk_u8_f32(
+                      c2, 2u, __builtin_amdgcn_cvt_pk_u8_f32(
+                                  c1, 1u, __builtin_amdgcn_cvt_pk_u8_f32(c0, 0u, 0u))));
+    }
+  }
+
+  // ---- Section 3.3 inside the tile, as in tlc_quant_encode_kernel
+  uint32_t nz = 0u;
+#pragma unroll
+  for (int g = 0; g < kG; ++g) nz |= nonzero_byte_mask4(w[g]) << (4 * g);
+  nz &= (1u << cnt) - 1u;
+  const uint32_t last = nz ? lo + 32u - (uint32_t)__builtin_clz(nz) : 0u;  // position + 1
+  const ScanU32 pm = block_scan_max_u32<kW>(last, sh.red2);
+  const int prev = (int)pm.excl - 1;  // the previous non-121 byte, -1 if none
+  if (nz != 0u && prev < 0) sh.lead = lo + (uint32_t)__builtin_ctz(nz);
+  const uint32_t trail = tile_bytes - pm.total;  // 121s after the last non-121 byte
+  const uint32_t mine = rs_gaps_len(nz, lo, prev) +
+                        (nz != 0u && last == pm.total ? trail / kRunMax : 0u);
+  // every output byte that is not a remainder code or a non-121 byte is a 255
+#pragma unroll
+  for (int g = 0; g < kG; ++g)
+    reinterpret_cast<uint32_t*>(sh.out)[kG * threadIdx.x + g] = ~0u;
+  if (threadIdx.x < 4u) reinterpret_cast<uint32_t*>(sh.out)[kG * kT + threadIdx.x] = ~0u;
+  const ScanU32 off = block_scan_u32<kW>(mine, sh.red);
+  const bool some = pm.total != 0u;
+  const uint32_t lead = some ? sh.lead : tile_bytes;
+  const RunSum agg =
+      some ? rs_combine(rs_zero_run(lead), rs_make(0u, 0u, trail % kRunMax, off.total))
+           : rs_zero_run(tile_bytes);
+  // the tiles after this one can go on before it has emitted anything
+  if (tiles > 1u && threadIdx.x == 0)
+    status_publish(&status[J.floor + lt],
+                   EncSW::pack(rs_to_payload(agg), lt == 0 ? kFlagPrefix : kFlagAgg, epoch));
+  uint32_t o = off.excl;
+  auto put = [&](uint32_t c) {
+    if (o < sizeof(sh.out)) sh.out[o] = (uint8_t)c;
+    ++o;
+  };
+  // the bytes as one 64-bit value: an array indexed at run time would be moved
+  // to LDS, at a place each wave computes from the dispatch packet, which lies
+  // in host memory (in a batch of 335 tensors the waves waited up to 14 us)
+  uint64_t bytes = w[0];
+  if (kG > 1) bytes |= (uint64_t)w[kG > 1 ? 1 : 0] << 32;
+  rs_gaps_emit(nz, lo, prev, [bytes](uint32_t i) { return (uint32_t)(bytes >> (8u * i)) & 255u; },
+               put, [&](uint32_t k) { o += k; });
+  static_assert(kG <= 2, "the thread's bytes fit 64 bits");
+  RunSum P = rs_identity();
+  if (lt != 0) {
+    if (!chained) {
+      if (wid < kReaders) {  // lane i of wave w reads tile 64w + i's summary
+        uint64_t w;
+        const bool mine = threadIdx.x < lt;
+        const bool ok = wait_words(
+            &status[J.floor + threadIdx.x], mine,
+            [&](uint64_t v) { return EncSW::epoch(v) == epoch && EncSW::flag(v) != 0u; }, &w);
+        RunSum a = rs_identity();
+        if (mine) a = rs_from_payload(EncSW::payload(w));
+        a = wave_incl_scan_rs(a);
+        if (lane == 63) {
+          sh.wave[wid] = a.v;
+          if (!ok) {
+            sh.fault = 1u;
+            fault_out();
+          }
+        }
+      }
+    } else {
+      P = rs_from_payload(lookback_block<EncSW, kW>(
+          status, J.floor, J.floor + lt, rs_to_payload(agg), rs_to_payload(rs_identity()), epoch,
+          EncOp(), sh.look, &sh.fault));
+      if (sh.fault) {
+        if (threadIdx.x == 0) fault_out();
+        return;
+      }
+    }
+    if (!chained) {
+      __syncthreads();
+      if (sh.fault) return;
+#pragma unroll 1
+      for (uint32_t i = 0; i < kReaders; ++i) {
+        RunSum a;
+        a.v = sh.wave[i];
+        P = rs_combine(P, a);
+      }
+    }
+  } else {
+    __syncthreads();
+  }
+
+  // ---- the tile's part of the stream; the clamps only keep a logic error
+  // from writing outside the m-byte output buffer
+  const uint32_t at0 = rs_emitted(P);
+  const uint32_t grown = rs_phase(P) + lead;  // the open run after the leading 121s
+  const uint32_t n255 = grown / kRunMax, rho = grown % kRunMax;
+  const uint32_t code = (some && rho) ? 1u : 0u;
+  for (uint32_t i = threadIdx.x; i < n255; i += kT)
+    if (at0 + i < m) J.out[at0 + i] = (uint8_t)kFullChunk;
+  if (code && threadIdx.x == 0 && at0 + n255 < m) J.out[at0 + n255] = (uint8_t)rs_code(rho);
+  const uint32_t at = at0 + n255 + code;
+  const uint32_t len = umin32(off.total, kTile);
+  for (uint32_t i = threadIdx.x; i < len; i += kT)
+    if (at + i < m) J.out[at + i] = sh.out[i];
+  if (last_tile && threadIdx.x == 0) {  // a run that ends the stream; the length
+    const RunSum T = rs_combine(P, agg);
+    const uint32_t total = rs_total(T);
+    if (rs_phase(T) && total >= 1u && total - 1u < m)
+      J.out[total - 1u] = (uint8_t)rs_code(rs_phase(T));
+    J.res->err = 0u;
+    J.res->len = total;
+    J.res->scale = sc.M;
+    host_put_all(J.hres, 0u, total, sc.M);
+  }
+}
+
+// One tensor.  A chained one takes tiles of twice the size (kT 512): its
+// look-back is half as long (8,388,608 values: 42 against 51 us).
+template <int kT>
+__global__ __launch_bounds__(kT) void tlc_quant_encode_chained_kernel(
+    const float* __restrict__ x, float* __restrict__ r, uint64_t n, uint32_t m, float s,
+    bool in_place, const uint32_t* __restrict__ partials, uint32_t np, uint8_t* __restrict__ out,
+    uint64_t* __restrict__ status, uint64_t* __restrict__ maxima, uint32_t ticket_base,
+    uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
+  __shared__ TileShared<kT, kTileGroups> sh;
+  __shared__ uint32_t s_tile;
+  uint32_t tile = 0u;
+  if (gridDim.x > 1u) {
+    if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
+    __syncthreads();
+    tile = uniform32(s_tile);
+  }
+  const TileJob J = {x, r, out, n, m, s, partials, np, 0u, &ctrl->enc, hm.res};
+  encode_tile<kT, kTileGroups>(J, tile, in_place, status, maxima, epoch, ctrl, hm.fault, sh);
+}
+
+// Many tensors: block (or, where a tensor has more than one tile, ticket) T
+// belongs to the last descriptor whose tile0 is <= T.  kOneTile: every tensor
+// has one, so that is descriptor T.
+template <bool kOneTile>
+__global__ __launch_bounds__(kTileThreads) void tlc_quant_encode_batch_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, const uint16_t* __restrict__ owner,
+    bool in_place, const uint32_t* __restrict__ partials, EncResult* __restrict__ results,
+    uint64_t* __restrict__ status, uint64_t* __restrict__ maxima, uint32_t ticket_base,
+    uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
+  __shared__ TileShared<kTileThreads, kTileGroups> sh;
+  __shared__ uint32_t s_tile;
+  __shared__ EncDesc s_desc;
+  uint32_t T = blockIdx.x, t = T;
+  if (!kOneTile) {
+    if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
+    __syncthreads();
+    T = s_tile;
+    t = owner[T];
+  }
+  // one read of the descriptor per block: it may lie in host memory
+  if (threadIdx.x < sizeof(EncDesc) / 4)
+    reinterpret_cast<uint32_t*>(&s_desc)[threadIdx.x] =
+        reinterpret_cast<const uint32_t*>(descs + t)[threadIdx.x];
+  __syncthreads();
+  const uint32_t lt = uniform32(T - s_desc.tile0), ut = uniform32(t);
+  // in place, a tensor with a max pass has its sums in the buffer
+  const TileJob J = {
+      in_place && s_desc.nblk ? nullptr : uniform_ptr(s_desc.x),
+      uniform_ptr(s_desc.r),
+      uniform_ptr(s_desc.out),
+      uniform64(s_desc.n),
+      uniform32(s_desc.m),
+      s_desc.s,
+      partials + uniform32(s_desc.blk0),
+      uniform32(s_desc.nblk),
+      uniform32(s_desc.tile0),
+      results + ut,
+      hm.res ? hm.res + ut : nullptr};
+  encode_tile<kTileThreads, kTileGroups>(J, lt, in_place, status, maxima, epoch, ctrl, hm.fault,
+                                         sh);
 }
 
 // ---------------------------------------------------------------- comparison modes
@@ -1072,16 +1320,19 @@ hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* 
   return hipGetLastError();
 }
 
-hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uint32_t m,
-                                       float s, const uint32_t* partials, uint32_t npartials,
-                                       uint8_t* out, uint64_t* status, uint32_t ntiles,
+hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uint32_t m, float s,
+                                       bool in_place, const uint32_t* partials, uint32_t np,
+                                       uint8_t* out, uint64_t* status, uint64_t* maxima,
                                        uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                        HostMirror hm, hipStream_t st) {
-#define TLC_LAUNCH(X)                                                                         \
-  launch_k(tlc_quant_encode_chained_kernel<X>, ntiles, kThreads, st, x, r, n, m, s, partials, \
-           npartials, out, status, ticket_base, epoch, ctrl, hm)
-  if (x != nullptr) TLC_LAUNCH(true); else TLC_LAUNCH(false);
-#undef TLC_LAUNCH
+  const uint32_t tiles = small_tiles(m);
+  if (tiles > kExchangeTiles)
+    launch_k(tlc_quant_encode_chained_kernel<2 * kTileThreads>, (tiles + 1u) / 2u,
+             2 * kTileThreads, st, x, r, n, m, s, in_place, partials, np, out, status, maxima,
+             ticket_base, epoch, ctrl, hm);
+  else
+    launch_k(tlc_quant_encode_chained_kernel<kTileThreads>, tiles, kTileThreads, st, x, r, n, m, s,
+             in_place, partials, np, out, status, maxima, ticket_base, epoch, ctrl, hm);
   return hipGetLastError();
 }
 
@@ -1097,36 +1348,35 @@ hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
                               const uint64_t* local_pre, const uint8_t* slots, uint32_t m,
                               uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   const uint32_t ntiles = (uint32_t)((m + kEncTile - 1) / kEncTile);
-  launch_k(tlc_zre_compact_kernel, (ntiles + kWaves - 1) / kWaves, kThreads, st,
-      recs, chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
+  if (!zre_chunked(m))
+    launch_k(tlc_zre_compact_kernel<true>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
+             chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
+  else
+    launch_k(tlc_zre_compact_kernel<false>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
+             chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
   return hipGetLastError();
 }
 
-hipError_t launch_absmax_check_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_blocks, uint32_t* partials, hipStream_t st) {
-  launch_k(tlc_absmax_check_batch_kernel, total_blocks, kThreads, st, descs, count, partials);
+hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t total_blocks,
+                               bool in_place, uint32_t* partials, hipStream_t st) {
+  if (in_place)
+    launch_k(tlc_accum_absmax_batch_kernel, total_blocks, kThreads, st, descs, count, partials);
+  else
+    launch_k(tlc_absmax_check_batch_kernel, total_blocks, kThreads, st, descs, count, partials);
   return hipGetLastError();
 }
 
-hipError_t launch_accum_absmax_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_blocks, uint32_t* partials,
-                                     const uint32_t* guard, hipStream_t st) {
-  launch_k(tlc_accum_absmax_batch_kernel, total_blocks, kThreads, st, descs, count, partials,
-                                                                   guard);
-  return hipGetLastError();
-}
-
-hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_tiles, const uint32_t* partials,
-                                     bool fused, EncResult* results, uint64_t* status,
+hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count, const uint16_t* owner,
+                                     uint32_t tiles, bool in_place, const uint32_t* partials,
+                                     EncResult* results, uint64_t* status, uint64_t* maxima,
                                      uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                      HostMirror hm, hipStream_t st) {
-  if (fused)
-    launch_k(tlc_quant_encode_batch_kernel<true>, total_tiles, kThreads, st,
-        descs, count, partials, results, status, ticket_base, epoch, ctrl, hm);
+  if (tiles == count)
+    launch_k(tlc_quant_encode_batch_kernel<true>, tiles, kTileThreads, st, descs, count, owner,
+             in_place, partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
   else
-    launch_k(tlc_quant_encode_batch_kernel<false>, total_tiles, kThreads, st,
-        descs, count, partials, results, status, ticket_base, epoch, ctrl, hm);
+    launch_k(tlc_quant_encode_batch_kernel<false>, tiles, kTileThreads, st, descs, count, owner,
+             in_place, partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
   return hipGetLastError();
 }
 

@@ -147,4 +147,76 @@ __device__ uint64_t lookback_wave(uint64_t* status, uint32_t floor, uint32_t til
   return failed ? identity : run;
 }
 
+// The same by a whole block of kW waves, which poll kW windows of 64
+// predecessors at a time (wave 0 the nearest): with hundreds of tiles that
+// publish at about the same time, a tile a few windows away from the nearest
+// inclusive prefix needs one round instead of several.  The caller has
+// published the tile's aggregate.  Every thread returns the exclusive prefix
+// and reads *fault after a barrier.
+template <int kW>
+struct LookShared {
+  uint64_t fold[kW];
+  uint32_t state[kW];  // 0: whole window folded, 1: up to a prefix, 2: gave up
+};
+
+template <class SW, int kW, class Op>
+__device__ uint64_t lookback_block(uint64_t* status, uint32_t floor, uint32_t tile, uint64_t agg,
+                                   uint64_t identity, uint32_t epoch, Op op,
+                                   LookShared<kW>& sh, uint32_t* fault) {
+  const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  uint64_t run = identity;
+  uint32_t end = 0u;  // 1: a prefix was reached, 2: gave up
+  for (int64_t base = (int64_t)tile - 1; end == 0u; base -= 64 * kW) {
+    const int64_t idx = base - 64 * (int64_t)wid - (int64_t)lane;
+    uint64_t val = identity;
+    uint32_t p = 64u, state = 0u;
+    for (uint32_t spins = 0;; ++spins) {
+      bool ready = true, is_prefix = true, is_fault = false;
+      if (idx >= (int64_t)floor) {
+        const uint64_t w = status_read(&status[idx]);
+        const uint32_t f = SW::flag(w);
+        ready = SW::epoch(w) == epoch && f != 0u;
+        is_prefix = ready && f == kFlagPrefix;
+        is_fault = ready && f == kFlagFault;
+        val = SW::payload(w);
+      }
+      const uint64_t pmask = __ballot(is_prefix);
+      p = pmask ? (uint32_t)(__ffsll((unsigned long long)pmask) - 1) : 64u;
+      const bool need = lane <= p;
+      if (__ballot(is_fault && need)) state = 2u;
+      if (state == 2u || __ballot(!ready && need) == 0u) break;
+      if (spins > kSpinLimit) {
+        state = 2u;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (state == 0u && p < 64u) state = 1u;
+    const uint64_t fold =
+        readlane64(wave_incl_scan(lane <= p ? val : identity, identity, OpLaterFirst<Op>{op}), 63);
+    __syncthreads();  // the last round's words have been read
+    if (lane == 0) {
+      sh.fold[wid] = fold;
+      sh.state[wid] = state;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int w = 0; w < kW && end == 0u; ++w) {
+      if (sh.state[w] == 2u) {
+        end = 2u;
+      } else {
+        run = op(sh.fold[w], run);
+        end = sh.state[w];
+      }
+    }
+  }
+  if (threadIdx.x == 0) {
+    *fault = end == 2u ? 1u : 0u;
+    status_publish(&status[tile], end == 2u ? SW::pack(0, kFlagFault, epoch)
+                                            : SW::pack(op(run, agg), kFlagPrefix, epoch));
+  }
+  __syncthreads();
+  return run;
+}
+
 }  // namespace tlc

@@ -18,17 +18,17 @@ namespace {
 // flag), the check pass's partial maxima (at most kAbsmaxMaxBlocks; the
 // next kAbsmaxMaxBlocks words are spare), then one look-back status word
 // per encoder tile
-// (n <= TLC_NOALLOC_MAX_N gives at most 410 tiles, all on the chained
-// path) and two spare words.
+// (n <= TLC_NOALLOC_MAX_N gives at most 820 tiles), two spare words and one
+// word per tile for the maxima of at most kExchangeTiles tiles.
 constexpr uint32_t kNoallocMaxTiles =
-    (uint32_t)(((TLC_NOALLOC_MAX_N + 4) / 5 + kEncTile - 1) / kEncTile);
-static_assert(kNoallocMaxTiles < kThreePassMinTiles, "the chained path takes every size");
+    (uint32_t)(((TLC_NOALLOC_MAX_N + 4) / 5 + kSmallTile - 1) / kSmallTile);
 constexpr size_t kOffPartialsChk = sizeof(Ctrl);
 constexpr size_t kOffPartials = kOffPartialsChk + kAbsmaxMaxBlocks * sizeof(uint32_t);
 constexpr size_t kOffStatus = kOffPartials + kAbsmaxMaxBlocks * sizeof(uint32_t);
 constexpr size_t kStatusWords = kNoallocMaxTiles + 2;
-constexpr size_t kScratchBytes = 8192;  // the size the header states
-static_assert(kOffStatus + kStatusWords * sizeof(uint64_t) <= kScratchBytes, "layout fits");
+constexpr size_t kOffMaxima = kOffStatus + kStatusWords * sizeof(uint64_t);
+constexpr size_t kScratchBytes = 16384;  // the size the header states
+static_assert(kOffMaxima + kExchangeTiles * sizeof(uint64_t) <= kScratchBytes, "layout fits");
 
 // In host code `scratch` names a host-side stand-in; its device address
 // comes from hipGetSymbolAddress, once per device.
@@ -48,6 +48,8 @@ __global__ __launch_bounds__(kThreads) void tlc_noalloc_begin_kernel(
   for (uint32_t i = threadIdx.x; i < sizeof(Ctrl) / sizeof(uint32_t); i += kThreads) ctrl[i] = 0u;
   uint64_t* status = reinterpret_cast<uint64_t*>(scr + kOffStatus);
   for (uint32_t i = threadIdx.x; i < words; i += kThreads) status[i] = 0u;
+  uint64_t* maxima = reinterpret_cast<uint64_t*>(scr + kOffMaxima);
+  for (uint32_t i = threadIdx.x; i < kExchangeTiles; i += kThreads) maxima[i] = 0u;
   if (threadIdx.x == 0) {
     res->status = TLC_OK;
     res->bytes_len = 0u;
@@ -118,16 +120,18 @@ TLC_API int tlc_compress_noalloc(const float* tensor, float* residual, size_t n,
   uint32_t* partials_chk = reinterpret_cast<uint32_t*>(scr + kOffPartialsChk);
   uint64_t* status = reinterpret_cast<uint64_t*>(scr + kOffStatus);
   hipStream_t st = (hipStream_t)hip_stream;
-  const uint32_t ntiles = (uint32_t)((m + kEncTile - 1) / kEncTile);  // <= kNoallocMaxTiles
+  const uint32_t ntiles = small_tiles((uint32_t)m);  // <= kNoallocMaxTiles
 
   tlc_noalloc_begin_kernel<<<1, kThreads, 0, st>>>(scr, ntiles + 2u, result);
   e = hipGetLastError();
   if (e == hipSuccess && n) {
     uint32_t np = 0;
-    e = launch_absmax_check(tensor, residual, n, partials_chk, &np, st);
+    if (ntiles > kExchangeTiles)
+      e = launch_absmax_check(tensor, residual, n, partials_chk, &np, st);
     if (e == hipSuccess)
-      e = launch_quant_encode_chained(tensor, residual, n, (uint32_t)m, s, partials_chk, np,
-                                      bytes, status, ntiles, 0u, 1u, ctrl, HostMirror{}, st);
+      e = launch_quant_encode_chained(tensor, residual, n, (uint32_t)m, s, false, partials_chk, np,
+                                      bytes, status, reinterpret_cast<uint64_t*>(scr + kOffMaxima), 0u,
+                                      1u, ctrl, HostMirror{}, st);
     if (e == hipSuccess) {
       tlc_noalloc_end_kernel<<<1, 64, 0, st>>>(scr, result);
       e = hipGetLastError();

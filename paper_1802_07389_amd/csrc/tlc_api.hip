@@ -127,7 +127,7 @@ struct tlc_ctx {
   uint32_t* partials = nullptr;
   uint32_t* partials_chk = nullptr;  // the check pass's partial maxima
   size_t partials_cap = 0;
-  uint64_t* enc_status = nullptr;
+  uint64_t* enc_status = nullptr;  // enc_status_words words, then as many for the maxima
   size_t enc_status_words = 0;
   uint64_t* dec_status = nullptr;
   size_t dec_status_words = 0;
@@ -147,7 +147,9 @@ struct tlc_ctx {
   HostReadback* rb = nullptr;
   EncResult* host_results = nullptr;
   HostReadback* rb_dev = nullptr;  // the same pinned memory, as the device addresses it
-  uint8_t* staging = nullptr;  // kStagingSlots slots of max_tensors * 64 bytes
+  uint8_t* staging = nullptr;  // kStagingSlots slots: descriptors, then the tiles' owners
+  size_t slot_bytes = 0;
+  uint8_t* staging_dev = nullptr;  // the same, as the device addresses it
   hipEvent_t staging_done[kStagingSlots] = {};
   bool staging_used[kStagingSlots] = {};
   int staging_next = 0;
@@ -164,6 +166,7 @@ struct tlc_ctx {
   std::vector<EncDesc> enc_host;
   std::vector<DecDesc> dec_host;
   std::vector<size_t> which;
+  std::vector<uint16_t> owner;  // the tensor of each encoder tile (capacity enc_status_words)
   std::vector<Span> spans;  // address ranges of a batched call (3 per tensor)
   std::vector<Span> enc_spans_ok, dec_spans_ok;  // the last batched calls that passed
   std::vector<hipEvent_t> free_events;
@@ -304,15 +307,23 @@ int next_dec_epoch(tlc_ctx* c, uint32_t* out) {
 // pinned staging slot.  A slot is reused only after its previous copy has
 // executed, so back-to-back asynchronous calls cannot overwrite a
 // descriptor table that is still in flight.
-int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes) {
-  const int slot = c->staging_next;
-  c->staging_next = (slot + 1) % kStagingSlots;
-  if (c->staging_used[slot]) {
-    hipError_t e = hipEventSynchronize(c->staging_done[slot]);
+int take_slot(tlc_ctx* c, const void* src, size_t bytes, int* slot) {
+  *slot = c->staging_next;
+  c->staging_next = (*slot + 1) % kStagingSlots;
+  if (c->staging_used[*slot]) {
+    hipError_t e = hipEventSynchronize(c->staging_done[*slot]);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize(staging)");
+    c->staging_used[*slot] = false;
   }
-  uint8_t* host = c->staging + (size_t)slot * c->max_tensors * 64;
-  memcpy(host, src, bytes);
+  memcpy(c->staging + (size_t)*slot * c->slot_bytes, src, bytes);
+  return TLC_OK;
+}
+
+int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes) {
+  int slot = 0;
+  int st = take_slot(c, src, bytes, &slot);
+  if (st) return st;
+  const uint8_t* host = c->staging + (size_t)slot * c->slot_bytes;
   hipError_t e = hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipEventRecord(c->staging_done[slot], c->stream);
   if (e != hipSuccess) {
@@ -320,6 +331,21 @@ int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes) {
     return hip_fail(e, "descriptor upload");
   }
   c->staging_used[slot] = true;
+  return TLC_OK;
+}
+
+// The descriptors and the tiles' owners in a pinned slot, as the device
+// addresses it, for kernels that read them there; the caller waits for those
+// kernels' results, so the slot needs no event.
+int stage(tlc_ctx* c, const void* src, size_t bytes, const void* own, size_t own_bytes,
+          const void** dev, const void** dev_own) {
+  int slot = 0;
+  int st = take_slot(c, src, bytes, &slot);
+  if (st) return st;
+  const size_t at = (size_t)slot * c->slot_bytes, off = c->max_tensors * 64;
+  memcpy(c->staging + at + off, own, own_bytes);
+  *dev = c->staging_dev + at;
+  *dev_own = c->staging_dev + at + off;
   return TLC_OK;
 }
 
@@ -401,7 +427,9 @@ int wait_results(tlc_ctx* c, const EncResult* r, uint32_t count) {
       collect_timings(c);
       return TLC_OK;
     }
-    if ((spin & 255u) == 0u) {
+    // a query costs the host 5 to 20 us, more than a small encode: the first
+    // one comes after about a millisecond of polling
+    if ((spin & 32767u) == 0u) {
       const hipError_t q = hipStreamQuery(c->stream);
       if (q == hipSuccess) break;
       if (q != hipErrorNotReady) return hip_fail(q, "hipStreamQuery");
@@ -488,7 +516,8 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->partials_cap =
       std::max<size_t>(kAbsmaxMaxBlocks, max_n / ((size_t)kThreads * 4) + max_tensors + 1);
   const size_t tiles1 = ceil_div(quartic_len(max_n), (size_t)kEncTile);  // one tensor
-  c->enc_status_words = mm / kEncTile + max_tensors + 2;
+  c->enc_status_words = mm / kSmallTile + max_tensors + 2;
+  c->slot_bytes = round_up(max_tensors * 64 + c->enc_status_words * sizeof(uint16_t), 64);
   c->dec_status_words = mm / kZreBatchTile + max_tensors + 2;  // the smaller tile
   c->start_words = mm / kDecRange + max_tensors + 2;
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
@@ -503,7 +532,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   const size_t off_partials_chk = off;
   off = round_up(off + c->partials_cap * sizeof(uint32_t), 256);
   const size_t off_enc = off;
-  off = round_up(off + c->enc_status_words * sizeof(uint64_t), 256);
+  off = round_up(off + 2 * c->enc_status_words * sizeof(uint64_t), 256);  // and the maxima
   const size_t off_dec = off;
   off = round_up(off + c->dec_status_words * sizeof(uint64_t), 256);
   const size_t off_start = off;
@@ -545,7 +574,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->bound = (uint16_t*)(base + off_bound);
   c->trits = base + off_trits;
   c->slots = base + off_slots;
-  e = hipMemset(c->ws, 0, off_recs);  // the rest is written before it is read
+  e = hipMemset(c->ws, 0, total);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   // pinned readback block, laid out as the workspace's head: the control
   // block's slot, then the batch results
@@ -557,8 +586,8 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
         reinterpret_cast<EncResult*>(reinterpret_cast<uint8_t*>(c->rb) + sizeof(Ctrl));
   if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->rb_dev, c->rb, 0);
   if (e == hipSuccess)
-    e = hipHostMalloc((void**)&c->staging, kStagingSlots * max_tensors * 64,
-                      hipHostMallocDefault);
+    e = hipHostMalloc((void**)&c->staging, kStagingSlots * c->slot_bytes, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&c->staging_dev, c->staging, 0);
   for (int i = 0; i < kStagingSlots && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&c->staging_done[i], hipEventDisableTiming);
   if (e != hipSuccess) {
@@ -575,6 +604,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
     c->enc_host.reserve(max_tensors);
     c->dec_host.reserve(max_tensors);
     c->which.reserve(max_tensors);
+    c->owner.reserve(c->enc_status_words);
     c->spans.reserve(3 * max_tensors);
     c->enc_spans_ok.reserve(3 * max_tensors);
     c->dec_spans_ok.reserve(3 * max_tensors);
@@ -702,31 +732,26 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
   const uint32_t ntiles = (uint32_t)ceil_div(m, kEncTile);
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
   if (ntiles < kThreePassMinTiles) {  // small tensor: one chained pass
-    // default policy: the check pass, then the chained tiles form acc = x + r
-    // themselves; in place: step 1 into the buffer first, as for large tensors
+    const uint32_t tiles = small_tiles((uint32_t)m);
     uint32_t np = 0;
-    const uint32_t* partials = c->partials;
-    if (in_place) {
-      st = launch_max_passes(c, tensor, residual, n, s, &np);
-    } else {
-      partials = c->partials_chk;
+    if (tiles > kExchangeTiles) {
       st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
         return launch_absmax_check(tensor, residual, n, c->partials_chk, &np, c->stream);
       });
+      if (st) return st;
     }
-    if (st) return st;
     uint32_t epoch = 0;
-    st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, c->enc_status_words, nullptr,
-                    &epoch);
+    st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, 2 * c->enc_status_words,
+                    nullptr, &epoch);
     if (st) return st;
     st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_CHAINED, [&] {
-      return launch_quant_encode_chained(in_place ? nullptr : tensor, residual, n, (uint32_t)m,
-                                         s, partials, np, bytes, c->enc_status, ntiles,
-                                         c->enc_ticket_base, epoch, c->ctrl, enc_mirror(c),
-                                         c->stream);
+      return launch_quant_encode_chained(tensor, residual, n, (uint32_t)m, s, in_place,
+                                         c->partials_chk, np, bytes, c->enc_status,
+                                         c->enc_status + c->enc_status_words, c->enc_ticket_base,
+                                         epoch, c->ctrl, enc_mirror(c), c->stream);
     });
     if (st) return st;
-    c->enc_ticket_base += ntiles;
+    if (tiles > 1u) c->enc_ticket_base += tiles;  // a lone tile takes no ticket
     return finish_compress(c, "tlc_compress", bytes_len, scale, true);
   }
   st = launch_quantize_passes(c, tensor, residual, n, s, enc_mirror(c));
@@ -735,10 +760,12 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
     return launch_quant_encode(n, (uint32_t)m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
   });
   if (st) return st;
-  st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
-    return launch_zre_chunks(c->recs, ntiles, c->local_pre, c->chunk_agg, c->ctrl, c->stream);
-  });
-  if (st) return st;
+  if (zre_chunked((uint32_t)m)) {
+    st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
+      return launch_zre_chunks(c->recs, ntiles, c->local_pre, c->chunk_agg, c->ctrl, c->stream);
+    });
+    if (st) return st;
+  }
   st = timed_launch(c, TLC_KERNEL_ZRE_COMPACT, [&] {
     return launch_zre_compact(c->recs, c->chunk_agg, c->local_pre, c->slots, (uint32_t)m, bytes,
                               c->ctrl, enc_mirror(c), c->stream);
@@ -909,23 +936,34 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
   std::vector<size_t>& which = c->which;  // batch position of each launched tensor
   d.clear();
   which.clear();
-  uint32_t blocks = 0, tiles = 0;
-  for (size_t t = 0; t < count; ++t) {
-    if (ns[t] == 0) continue;
-    EncDesc e = {};
-    e.x = tensors[t];
-    e.r = residuals[t];
-    e.out = bytes[t];
-    e.n = ns[t];
-    e.m = (uint32_t)quartic_len(ns[t]);
-    e.s = s[t];
-    e.tile0 = tiles;
-    e.blk0 = blocks;
-    e.nblk = batch_absmax_blocks(ns[t] / 4);
-    blocks += e.nblk;
-    tiles += (uint32_t)ceil_div(e.m, kEncTile);
-    d.push_back(e);
-    which.push_back(t);
+  // the tensors with a max pass first (blk0 counts its blocks), then the
+  // others of more than one tile, so that the small ones fill the gaps
+  uint32_t blocks = 0, tiles = 0, nbig = 0;
+  c->owner.clear();
+  for (int kind = 0; kind < 3; ++kind) {
+    for (size_t t = 0; t < count; ++t) {
+      const size_t m = quartic_len(ns[t]);
+      const size_t k = ceil_div(m, (size_t)kSmallTile);
+      if (m == 0 || (k > kExchangeTiles ? 0 : (k > 1 ? 1 : 2)) != kind) continue;
+      EncDesc e = {};
+      e.x = tensors[t];
+      e.r = residuals[t];
+      e.out = bytes[t];
+      e.n = ns[t];
+      e.m = (uint32_t)m;
+      e.s = s[t];
+      e.tile0 = tiles;
+      if (kind == 0) {
+        e.blk0 = blocks;
+        e.nblk = batch_absmax_blocks(ns[t] / 4);
+        blocks += e.nblk;
+        ++nbig;
+      }
+      tiles += (uint32_t)k;
+      c->owner.insert(c->owner.end(), k, (uint16_t)d.size());
+      d.push_back(e);
+      which.push_back(t);
+    }
   }
   if (d.empty()) return TLC_OK;
   if (blocks > c->partials_cap || tiles > c->enc_status_words)
@@ -934,36 +972,41 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
   st = dev.status();
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
-  st = upload(c, c->enc_descs, d.data(), cnt * sizeof(EncDesc));
-  if (st) return st;
-  arm_results(c->host_results, cnt);
-  // default policy: the check pass, then every tile forms acc = x + r itself
-  // from its tensor (no writing max pass); in place: step 1 into the buffers
-  // with the partial maxima of the sums, then the tiles quantize the buffers
-  const bool check = !(c->options & TLC_OPT_IN_PLACE_FEEDBACK);
-  if (check) {
-    st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK_BATCH, [&] {
-      return launch_absmax_check_batch(c->enc_descs, cnt, blocks, c->partials_chk, c->stream);
-    });
-  } else {
-    st = timed_launch(c, TLC_KERNEL_ABSMAX_BATCH, [&] {
-      return launch_accum_absmax_batch(c->enc_descs, cnt, blocks, c->partials, nullptr,
-                                       c->stream);
-    });
+  const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
+  const EncDesc* descs = c->enc_descs;
+  const uint16_t* owner = nullptr;
+  if (nbig) {
+    st = upload(c, c->enc_descs, d.data(), cnt * sizeof(EncDesc));
+    if (st) return st;
   }
-  if (st) return st;
+  {
+    // every block reads one descriptor, once: straight from the pinned copy,
+    // which is free again when the call returns (every result needs its own)
+    const EncDesc* pinned = nullptr;
+    st = stage(c, d.data(), cnt * sizeof(EncDesc), c->owner.data(),
+               c->owner.size() * sizeof(uint16_t), (const void**)&pinned, (const void**)&owner);
+    if (st) return st;
+    if (!nbig) descs = pinned;
+  }
+  arm_results(c->host_results, cnt);
+  if (nbig) {
+    st = timed_launch(c, in_place ? TLC_KERNEL_ABSMAX_BATCH : TLC_KERNEL_ABSMAX_CHECK_BATCH, [&] {
+      return launch_absmax_batch(descs, nbig, blocks, in_place, c->partials_chk, c->stream);
+    });
+    if (st) return st;
+  }
   uint32_t epoch = 0;
-  st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, c->enc_status_words, nullptr,
+  st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, 2 * c->enc_status_words, nullptr,
                   &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_BATCH, [&] {
-    return launch_quant_encode_batch(c->enc_descs, cnt, tiles,
-                                     check ? c->partials_chk : c->partials, check,
-                                     c->enc_results, c->enc_status, c->enc_ticket_base, epoch,
-                                     c->ctrl, batch_mirror(c), c->stream);
+    return launch_quant_encode_batch(descs, cnt, owner, tiles, in_place, c->partials_chk,
+                                     c->enc_results, c->enc_status,
+                                     c->enc_status + c->enc_status_words, c->enc_ticket_base,
+                                     epoch, c->ctrl, batch_mirror(c), c->stream);
   });
   if (st) return st;
-  c->enc_ticket_base += tiles;
+  if (tiles != cnt) c->enc_ticket_base += tiles;
   st = wait_results(c, c->host_results, cnt);
   if (st) return st;
   if (c->rb->fault) {
@@ -1250,7 +1293,7 @@ TLC_API int tlc_ctx_set_epochs(tlc_ctx* c, uint32_t enc_epoch, uint32_t dec_epoc
   // every epoch-tagged word: status words, range starts and the
   // single-stream verdict (a word from an earlier use of an epoch must not
   // match)
-  hipError_t e = hipMemsetAsync(c->enc_status, 0, c->enc_status_words * sizeof(uint64_t),
+  hipError_t e = hipMemsetAsync(c->enc_status, 0, 2 * c->enc_status_words * sizeof(uint64_t),
                                 c->stream);
   if (e == hipSuccess)
     e = hipMemsetAsync(c->dec_status, 0, c->dec_status_words * sizeof(uint64_t), c->stream);

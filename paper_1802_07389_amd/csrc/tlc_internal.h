@@ -22,10 +22,28 @@ constexpr int kZreBatchBytesPerThread = 32;
 constexpr int kZreBatchTile = kThreads * kZreBatchBytesPerThread;  // 8192
 constexpr int kEncTile = 4096;            // quartic bytes per encoder tile
 constexpr int kDecRange = 4096;           // quartic bytes per expand/dequantize block
-constexpr uint32_t kAbsmaxMaxBlocks = 256;  // partial maxima per encode (one block per CU)
+// Encoder tiles of small tensors and batches: 256 threads of eight quartic
+// bytes.  The tiles of a tensor of at most kExchangeTiles (1,310,720 values)
+// exchange their maxima and summaries among themselves; a longer one has a
+// check pass and a look-back.  (The waiting blocks of one launch number at
+// most kExchangeTiles - 1, so launches on other streams find room beside them:
+// the card holds more than a thousand such blocks.)
+constexpr int kTileThreads = kThreads;
+constexpr int kTileGroups = 2;
+constexpr uint32_t kSmallTile = kTileThreads * kTileGroups * 4;  // 2048 quartic bytes
+constexpr uint32_t kExchangeTiles = 128;
+inline uint32_t small_tiles(uint32_t m) { return (m + kSmallTile - 1) / kSmallTile; }
 // Tensors of at least this many encoder tiles take the three-pass encoder
-// (no waits between tiles); smaller ones the single chained pass.
-constexpr uint32_t kThreePassMinTiles = 512;
+// (no waits between tiles); smaller ones, whose tiles can exchange what they
+// need (kExchangeTiles of half the size), a single launch.
+constexpr uint32_t kThreePassMinTiles = kExchangeTiles / 2 + 1;
+constexpr uint32_t kAbsmaxMaxBlocks = 256;  // partial maxima per encode (one block per CU)
+// Up to this many tiles the compaction finds its prefixes without the chunk
+// pass: two summaries per thread.
+constexpr uint32_t kOwnPrefixTiles = 512;
+inline bool zre_chunked(uint32_t m) {
+  return (m + (uint32_t)kEncTile - 1) / kEncTile > kOwnPrefixTiles;
+}
 
 // Per-tensor encode result (device), written by the encoder's tiles.
 struct EncResult {
@@ -160,11 +178,12 @@ hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* 
 // The tiles' own encodings from the trits.
 hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* recs,
                                const uint8_t* trits, const Ctrl* ctrl, hipStream_t st);
-// x != NULL: the tiles form acc = x + r themselves from the check pass's
-// partials (r still holds the previous residual); x == NULL: r holds acc.
-hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uint32_t m,
-                                       float s, const uint32_t* partials, uint32_t npartials,
-                                       uint8_t* out, uint64_t* status, uint32_t ntiles,
+// A small tensor in one launch (after the check pass, its partials, when it
+// has more than kExchangeTiles tiles).  in_place: a refused tensor is left
+// with the sums.  status, maxima: a word per tile each.
+hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uint32_t m, float s,
+                                       bool in_place, const uint32_t* partials, uint32_t np,
+                                       uint8_t* out, uint64_t* status, uint64_t* maxima,
                                        uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                        HostMirror hm, hipStream_t st);
 hipError_t launch_zre_chunks(const TileRec* recs, uint32_t ntiles, uint64_t* local_pre,
@@ -183,15 +202,15 @@ hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s,
                              Ctrl* ctrl, hipStream_t st);
 hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out,
                                int accumulate, hipStream_t st);
-hipError_t launch_absmax_check_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_blocks, uint32_t* partials, hipStream_t st);
-hipError_t launch_accum_absmax_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_blocks, uint32_t* partials,
-                                     const uint32_t* guard, hipStream_t st);
-// fused: as x != NULL for the chained encoder (partials: the check pass's).
-hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count,
-                                     uint32_t total_tiles, const uint32_t* partials,
-                                     bool fused, EncResult* results, uint64_t* status,
+// The max pass of the first `count` tensors (those of more than kExchangeTiles
+// tiles): the check pass or, in place, step 1 into the buffers.
+hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t total_blocks,
+                               bool in_place, uint32_t* partials, hipStream_t st);
+// owner: the tensor of each of the `tiles` tiles (not read when every tensor
+// has one).  partials: the max pass's.
+hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count, const uint16_t* owner,
+                                     uint32_t tiles, bool in_place, const uint32_t* partials,
+                                     EncResult* results, uint64_t* status, uint64_t* maxima,
                                      uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                      HostMirror hm, hipStream_t st);
 // One stream's decode.  Small decodes (at most kFusedMaxBlocks blocks in
