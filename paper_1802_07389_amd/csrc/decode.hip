@@ -17,14 +17,6 @@
 
 namespace tlc {
 
-// How a kernel reaches the five partitions of a range: one float4 per
-// partition slice (m % 4 == 0, 16-byte aligned output), aligned float4 cells
-// off the slice grid (aligned output, m % 4 != 0), or one quartic byte per
-// lane with scalar accesses (unaligned output).
-constexpr int kPathVec = 0;
-constexpr int kPathShift = 1;
-constexpr int kPathByte = 2;
-
 // ---------------------------------------------------------------- index scan
 // A start entry: (stream byte << 8 | how far into its expansion) with the
 // launch's epoch above it, published with an agent-scope atomic store like
@@ -185,17 +177,45 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_index_kernel(
                                  hm.corrupt, sh);
 }
 
+// Reads descriptor t once for the block (it may lie in host memory) and gives
+// every thread its fields as scalars.  Holds a barrier.
+__device__ __forceinline__ DecDesc block_desc(const DecDesc* __restrict__ descs, uint32_t t,
+                                              DecDesc* lds) {
+  if (threadIdx.x < sizeof(DecDesc) / 4)
+    reinterpret_cast<uint32_t*>(lds)[threadIdx.x] =
+        reinterpret_cast<const uint32_t*>(descs + t)[threadIdx.x];
+  __syncthreads();
+  DecDesc d = *lds;
+  d.C = uniform_ptr(d.C);
+  d.out = uniform_ptr(d.out);
+  d.n = uniform64(d.n);
+  d.c = uniform32(d.c);
+  d.m = uniform32(d.m);
+  d.tile0 = uniform32(d.tile0);
+  d.range0 = uniform32(d.range0);
+  return d;
+}
+
+// One scan tile per block.  kOneTile: every stream has one (the common batch),
+// so that block t is stream t's and waits for nobody; otherwise tiles are
+// taken from the ticket, and owner says whose each is.  (A binary search over
+// the descriptors took nine dependent loads.)
+template <bool kOneTile>
 __global__ __launch_bounds__(kThreads) void tlc_zre_index_batch_kernel(
-    const DecDesc* __restrict__ descs, uint32_t count, uint64_t* __restrict__ start,
-    uint64_t* __restrict__ status, uint32_t ticket_base, uint32_t epoch,
-    Ctrl* __restrict__ ctrl, HostMirror hm) {
+    const DecDesc* __restrict__ descs, const uint16_t* __restrict__ owner,
+    uint64_t* __restrict__ start, uint64_t* __restrict__ status, uint32_t ticket_base,
+    uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ IdxShared sh;
   __shared__ uint32_t s_tile;
-  if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->dec_ticket) - ticket_base;
-  __syncthreads();
-  const uint32_t T = s_tile;
-  const uint32_t t = find_desc(descs, count, T, [](const DecDesc& d) { return d.tile0; });
-  const DecDesc d = descs[t];
+  __shared__ DecDesc s_desc;
+  uint32_t T = blockIdx.x, t = T;
+  if (!kOneTile) {
+    if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->dec_ticket) - ticket_base;
+    __syncthreads();
+    T = uniform32(s_tile);
+    t = owner[T];
+  }
+  const DecDesc d = block_desc(descs, t, &s_desc);
   index_tile<kZreBatchBytesPerThread>(d.C, d.c, d.m, start + d.range0, status, d.tile0,
                                       T - d.tile0, epoch, ctrl, hm.fault, hm.corrupt, sh);
 }
@@ -396,23 +416,21 @@ __device__ __forceinline__ void dequant_partition_shifted(const uint8_t* s_q, ui
 
 // Unpacks the base-3 digits of quartic bytes s_q[0, qn) (global bytes
 // q0 + jl), dequantizes (Eq. 3) and stores or accumulates into the five
-// partitions of out.  kPathShift: aligned float4 cells partition by
-// partition (aligned out; the large outputs also take the nontemporal
-// hint).  kPathVec: each lane takes 4 bytes and their five float4 slices
-// at once (aligned out, m % 4 == 0; fewer dependent memory round trips per
-// block, which is what outputs that fit the cache are bound by).
-// kPathByte: one quartic byte per lane with scalar accesses.
-template <int kPath, bool kAcc, bool kNT = false>
+// partitions of out.  Each lane takes 4 bytes and their five float4 slices
+// at once, at any dword address (few dependent memory round trips per
+// block, which is what outputs that fit the cache are bound by).  kNT (large
+// outputs): float4 cells partition by partition with the nontemporal hint.
+template <bool kAcc, bool kNT>
 __device__ __forceinline__ void dequant_range(const uint8_t* s_q, uint64_t q0, uint32_t qn,
                                               uint64_t n, uint64_t m, float M,
                                               float* __restrict__ out, bool dense) {
-  if (kPath == kPathShift) {
+  if (kNT) {
     dequant_partition_shifted<0, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
     dequant_partition_shifted<1, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
     dequant_partition_shifted<2, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
     dequant_partition_shifted<3, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
     dequant_partition_shifted<4, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-  } else if (kPath == kPathVec) {
+  } else {
 #pragma unroll
     for (int g = 0; g < kDecRange / (4 * kThreads); ++g) {
       const uint32_t jl = 4u * (threadIdx.x + kThreads * g);
@@ -422,11 +440,11 @@ __device__ __forceinline__ void dequant_range(const uint8_t* s_q, uint64_t q0, u
       uint32_t t[4][5];
 #pragma unroll
       for (int cc = 0; cc < 4; ++cc) digits5((w >> (8 * cc)) & 0xffu, t[cc]);
-      if (4 * m + j + 4 <= n) {
+      if (4 * m + j + 4 <= n && j + 4 <= m) {
         float4 o[5];
         if (kAcc) {
 #pragma unroll
-          for (int k = 0; k < 5; ++k) o[k] = *reinterpret_cast<const float4*>(out + k * m + j);
+          for (int k = 0; k < 5; ++k) o[k] = ld4(out + k * m + j);
         }
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
@@ -440,37 +458,21 @@ __device__ __forceinline__ void dequant_range(const uint8_t* s_q, uint64_t q0, u
             o[k].z = trit_value(t[2][k], M);
             o[k].w = trit_value(t[3][k], M);
           }
-          if (store) *reinterpret_cast<float4*>(out + k * m + j) = o[k];
+          if (store) st4(out + k * m + j, o[k]);
         }
-      } else {  // the group whose p4 slice reaches into the padding
+      } else {  // a group that reaches past m or into the padding
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
 #pragma unroll
           for (int cc = 0; cc < 4; ++cc) {
             const uint64_t e = k * m + j + cc;
-            if (e < n) {
+            if (j + cc < m && e < n) {
               if (kAcc)
                 acc_trit_at(out, e, t[cc][k], M);
               else
                 out[e] = trit_value(t[cc][k], M);
             }
           }
-        }
-      }
-    }
-  } else {
-    for (uint32_t jl = threadIdx.x; jl < qn; jl += kThreads) {
-      const uint64_t j = q0 + jl;
-      uint32_t t[5];
-      digits5(s_q[jl], t);
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        const uint64_t e = k * m + j;
-        if (e < n) {
-          if (kAcc)
-            acc_trit_at(out, e, t[k], M);
-          else
-            out[e] = trit_value(t[k], M);
         }
       }
     }
@@ -533,7 +535,7 @@ __device__ bool wait_verdict(uint32_t epoch, Ctrl* ctrl, uint32_t* hfault) {
 // tile's verdict before it stores anything: a corrupt stream leaves out
 // untouched.  The scan's latency then overlaps the expanding blocks' work
 // and no kernel boundary separates the two steps.
-template <int kPath, bool kAcc, bool kNT, bool kFused>
+template <bool kAcc, bool kNT, bool kFused>
 __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
     const uint8_t* __restrict__ C, uint32_t c, uint64_t* __restrict__ start,
     uint64_t* __restrict__ status, uint32_t ntiles, uint32_t ticket_base, uint64_t n,
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
   const uint64_t q0 = (uint64_t)k * kDecRange;
   const uint32_t qn = (uint32_t)umin64(kDecRange, m - q0);
   const bool last = q0 + kDecRange >= m;
-  constexpr bool kPre = kPath == kPathShift && kAcc && kNT;
+  constexpr bool kPre = kAcc && kNT;
   // large outputs: the first two partitions' loads go out before the
   // expansion (on gfx950 15 us of 410 on a 2^28-value decode; outputs that
   // fit the cache gained nothing)
@@ -607,31 +609,26 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
     dequant_partition_shifted<3, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
     dequant_partition_shifted<4, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
   } else {
-    dequant_range<kPath, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_range<kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
   }
 }
 
+// One range per block; owner: whose it is.
 template <bool kAcc>
 __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_batch_kernel(
-    const DecDesc* __restrict__ descs, uint32_t count, const uint64_t* __restrict__ start,
-    uint32_t epoch, const Ctrl* __restrict__ ctrl) {
+    const DecDesc* __restrict__ descs, const uint16_t* __restrict__ owner,
+    const uint64_t* __restrict__ start, uint32_t epoch, const Ctrl* __restrict__ ctrl) {
   __shared__ uint32_t red[kWaves];
+  __shared__ DecDesc s_desc;
   __shared__ __align__(16) uint8_t s_q[kDecRange];
   if (ctrl->dec_bad_epoch == epoch) return;  // a corrupt stream: no output written
-  const uint32_t t =
-      find_desc(descs, count, blockIdx.x, [](const DecDesc& d) { return d.range0; });
-  const DecDesc d = descs[t];
+  const DecDesc d = block_desc(descs, owner[blockIdx.x], &s_desc);
   const uint32_t k = blockIdx.x - d.range0;
   const uint64_t q0 = (uint64_t)k * kDecRange;
   const uint32_t qn = (uint32_t)umin64(kDecRange, (uint64_t)d.m - q0);
   const bool dense =
       expand_range(d.C, d.c, start + d.range0, k, d.m, qn, s_q, red) > kDenseLiterals;
-  if (d.vec & 1u)
-    dequant_range<kPathVec, kAcc>(s_q, q0, qn, d.n, d.m, d.scale, d.out, dense);
-  else if (d.vec & 2u)
-    dequant_range<kPathShift, kAcc>(s_q, q0, qn, d.n, d.m, d.scale, d.out, dense);
-  else
-    dequant_range<kPathByte, kAcc>(s_q, q0, qn, d.n, d.m, d.scale, d.out, dense);
+  dequant_range<kAcc, false>(s_q, q0, qn, d.n, d.m, d.scale, d.out, dense);
 }
 
 // ---------------------------------------------------------------- aggregation
@@ -723,14 +720,14 @@ __device__ __forceinline__ void wave_expand(const SumSlice& sl, const SliceWords
 // wave into its own LDS range, with one block barrier per group; the next
 // group's bytes load while the current group is summed, and the groups'
 // LDS ranges alternate between two sets.
-template <bool kVec, bool kAcc>
+template <bool kAcc>
 __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
     const DecDesc* __restrict__ descs, uint32_t count, const uint64_t* __restrict__ start,
     uint64_t n, uint64_t m, float* __restrict__ out, uint32_t epoch,
     const Ctrl* __restrict__ ctrl) {
-  constexpr int kPer = kVec ? kDecRange / kThreads / 4 : kDecRange / kThreads;  // slots
-  constexpr int kW = kVec ? 4 : 1;                                              // bytes/slot
-  constexpr uint32_t kZeroWord = kVec ? 0x79797979u : kZeroGroup;  // a slot of zero groups
+  constexpr int kW = 4;                              // bytes per slot
+  constexpr int kPer = kDecRange / kThreads / kW;    // slots
+  constexpr uint32_t kZeroWord = 0x79797979u;        // a slot of zero groups
   __shared__ __align__(16) uint8_t s_q[2][kWaves][kDecRange];
   __shared__ SumSlice s_sl[kSumChunk];
   if (ctrl->dec_bad_epoch == epoch) return;  // a corrupt stream: out untouched
@@ -742,8 +739,9 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
   // slot g covers quartic bytes jl(g) .. jl(g) + kW - 1 and their 5 partitions
   float acc[kPer][5][kW];
   auto jl_of = [&](int g) -> uint32_t {
-    return kVec ? 4u * (threadIdx.x + kThreads * g) : threadIdx.x + kThreads * g;
+    return 4u * (threadIdx.x + kThreads * g);
   };
+  auto whole = [&](uint64_t j) { return 4 * m + j + 4 <= n && j + 4 <= m; };
   if (kAcc) {
 #pragma unroll
     for (int g = 0; g < kPer; ++g) {
@@ -752,17 +750,17 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
       const uint64_t j = q0 + jl;
 #pragma unroll
       for (int kk = 0; kk < 5; ++kk) {
-        if (kVec && 4 * m + j + 4 <= n) {
-          const float4 v = *reinterpret_cast<const float4*>(out + kk * m + j);
+        if (whole(j)) {
+          const float4 v = ld4(out + kk * m + j);
           acc[g][kk][0] = v.x;
-          acc[g][kk][kW > 1 ? 1 : 0] = v.y;
-          acc[g][kk][kW > 2 ? 2 : 0] = v.z;
-          acc[g][kk][kW > 3 ? 3 : 0] = v.w;
+          acc[g][kk][1] = v.y;
+          acc[g][kk][2] = v.z;
+          acc[g][kk][3] = v.w;
         } else {
 #pragma unroll
           for (int cc = 0; cc < kW; ++cc) {
             const uint64_t e = kk * m + j + cc;
-            acc[g][kk][cc] = e < n ? out[e] : 0.0f;
+            acc[g][kk][cc] = j + cc < m && e < n ? out[e] : 0.0f;
           }
         }
       }
@@ -800,7 +798,7 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
         for (int g = 0; g < kPer; ++g) {
           const uint32_t jl = jl_of(g);
           if (jl >= qn) continue;
-          const uint32_t w = kVec ? *reinterpret_cast<const uint32_t*>(sq + jl) : sq[jl];
+          const uint32_t w = *reinterpret_cast<const uint32_t*>(sq + jl);
           if (!dense && w == kZeroWord) continue;  // every term +-0: no value changes
 #pragma unroll
           for (int cc = 0; cc < kW; ++cc) {
@@ -830,15 +828,14 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
     const uint64_t j = q0 + jl;
 #pragma unroll
     for (int kk = 0; kk < 5; ++kk) {
-      if (kVec && 4 * m + j + 4 <= n) {
-        *reinterpret_cast<float4*>(out + kk * m + j) =
-            make_float4(acc[g][kk][0], acc[g][kk][kW > 1 ? 1 : 0], acc[g][kk][kW > 2 ? 2 : 0],
-                        acc[g][kk][kW > 3 ? 3 : 0]);
+      if (whole(j)) {
+        st4(out + kk * m + j,
+            make_float4(acc[g][kk][0], acc[g][kk][1], acc[g][kk][2], acc[g][kk][3]));
       } else {
 #pragma unroll
         for (int cc = 0; cc < kW; ++cc) {
           const uint64_t e = kk * m + j + cc;
-          if (e < n) out[e] = acc[g][kk][cc];
+          if (j + cc < m && e < n) out[e] = acc[g][kk][cc];
         }
       }
     }
@@ -849,10 +846,6 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_sum_kernel(
 // Outputs of at least this size decode with nontemporal hints (twice the
 // 256 MB last-level cache of the part).
 constexpr uint64_t kNtMinBytes = 512ull << 20;
-
-static inline bool aligned16(const void* p) {
-  return (reinterpret_cast<uintptr_t>(p) & 15u) == 0u;
-}
 
 hipError_t launch_zre_index(const uint8_t* C, uint32_t c, uint32_t m, uint64_t* start,
                             uint64_t* status, uint32_t ntiles, uint32_t ticket_base,
@@ -866,66 +859,61 @@ hipError_t launch_expand_dequant(const uint8_t* C, uint32_t c, uint64_t* start,
                                  uint64_t* status, uint32_t ticket_base, uint64_t n, uint64_t m,
                                  float scale, float* out, int accumulate, uint32_t epoch,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st) {
-  const bool al = aligned16(out);
-  const bool nt = al && n * sizeof(float) >= kNtMinBytes;
+  const bool nt = n * sizeof(float) >= kNtMinBytes;
   const bool fused = decode_fused(c, m);
   const uint32_t ntiles = fused ? decode_index_tiles(c, m) : 0u;
   const uint32_t blocks = ntiles + decode_ranges(m);
-#define TLC_LAUNCH(V, A, N, F)                                                              \
-  launch_k(tlc_expand_dequant_kernel<V, A, N, F>, blocks, kThreads, st, C, c, start, status, \
+#define TLC_LAUNCH(A, N, F)                                                                \
+  launch_k(tlc_expand_dequant_kernel<A, N, F>, blocks, kThreads, st, C, c, start, status, \
            ntiles, ticket_base, n, m, scale, out, epoch, ctrl, hm)
-#define TLC_LAUNCH2(V, A, N) \
-  if (fused) TLC_LAUNCH(V, A, N, true); else TLC_LAUNCH(V, A, N, false)
   if (nt) {
     // outputs of 512 MiB or more have far more blocks than a fused launch takes
-    if (accumulate) TLC_LAUNCH(kPathShift, true, true, false);
-    else TLC_LAUNCH(kPathShift, false, true, false);
-  } else if (al && m % 4 == 0) {
-    if (accumulate) { TLC_LAUNCH2(kPathVec, true, false); } else { TLC_LAUNCH2(kPathVec, false, false); }
-  } else if (al) {
-    if (accumulate) { TLC_LAUNCH2(kPathShift, true, false); } else { TLC_LAUNCH2(kPathShift, false, false); }
+    if (accumulate) TLC_LAUNCH(true, true, false); else TLC_LAUNCH(false, true, false);
+  } else if (fused) {
+    if (accumulate) TLC_LAUNCH(true, false, true); else TLC_LAUNCH(false, false, true);
   } else {
-    if (accumulate) { TLC_LAUNCH2(kPathByte, true, false); } else { TLC_LAUNCH2(kPathByte, false, false); }
+    if (accumulate) TLC_LAUNCH(true, false, false); else TLC_LAUNCH(false, false, false);
   }
-#undef TLC_LAUNCH2
 #undef TLC_LAUNCH
   return hipGetLastError();
 }
 
-hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, uint32_t total_tiles,
-                                  uint64_t* start, uint64_t* status, uint32_t ticket_base,
-                                  uint32_t epoch, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
-  launch_k(tlc_zre_index_batch_kernel, total_tiles, kThreads, st, descs, count, start, status,
-           ticket_base, epoch, ctrl, hm);
+hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, const uint16_t* owner,
+                                  uint32_t tiles, uint64_t* start, uint64_t* status,
+                                  uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl, HostMirror hm,
+                                  hipStream_t st) {
+  if (tiles == count)
+    launch_k(tlc_zre_index_batch_kernel<true>, tiles, kThreads, st, descs, owner, start, status,
+             ticket_base, epoch, ctrl, hm);
+  else
+    launch_k(tlc_zre_index_batch_kernel<false>, tiles, kThreads, st, descs, owner, start, status,
+             ticket_base, epoch, ctrl, hm);
   return hipGetLastError();
 }
 
-hipError_t launch_expand_dequant_batch(const DecDesc* descs, uint32_t count,
+hipError_t launch_expand_dequant_batch(const DecDesc* descs, const uint16_t* owner,
                                        uint32_t total_ranges, const uint64_t* start,
                                        int accumulate, uint32_t epoch, const Ctrl* ctrl,
                                        hipStream_t st) {
   if (accumulate)
-    launch_k(tlc_expand_dequant_batch_kernel<true>, total_ranges, kThreads, st, descs, count,
-                                                                             start, epoch, ctrl);
+    launch_k(tlc_expand_dequant_batch_kernel<true>, total_ranges, kThreads, st, descs, owner,
+             start, epoch, ctrl);
   else
-    launch_k(tlc_expand_dequant_batch_kernel<false>, total_ranges, kThreads, st,
-        descs, count, start, epoch, ctrl);
+    launch_k(tlc_expand_dequant_batch_kernel<false>, total_ranges, kThreads, st, descs, owner,
+             start, epoch, ctrl);
   return hipGetLastError();
 }
 
 hipError_t launch_expand_sum(const DecDesc* descs, uint32_t count, const uint64_t* start,
-                             uint64_t n, uint64_t m, float* out, int vec, int accumulate,
-                             uint32_t epoch, const Ctrl* ctrl, hipStream_t st) {
+                             uint64_t n, uint64_t m, float* out, int accumulate, uint32_t epoch,
+                             const Ctrl* ctrl, hipStream_t st) {
   const uint32_t blocks = (uint32_t)((m + kDecRange - 1) / kDecRange);
-#define TLC_LAUNCH(V, A)                                                                 \
-  launch_k(tlc_expand_sum_kernel<V, A>, blocks, kThreads, st, descs, count, start, n, m, out, \
-                                                           epoch, ctrl)
-  if (vec) {
-    if (accumulate) TLC_LAUNCH(true, true); else TLC_LAUNCH(true, false);
-  } else {
-    if (accumulate) TLC_LAUNCH(false, true); else TLC_LAUNCH(false, false);
-  }
-#undef TLC_LAUNCH
+  if (accumulate)
+    launch_k(tlc_expand_sum_kernel<true>, blocks, kThreads, st, descs, count, start, n, m, out,
+             epoch, ctrl);
+  else
+    launch_k(tlc_expand_sum_kernel<false>, blocks, kThreads, st, descs, count, start, n, m, out,
+             epoch, ctrl);
   return hipGetLastError();
 }
 

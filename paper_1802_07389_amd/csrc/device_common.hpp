@@ -150,6 +150,15 @@ __device__ __forceinline__ void st4(float* p, float4 v) {
   *reinterpret_cast<tlc_f4*>(p) = w;
 }
 
+// Four bytes at any address, the same way.
+typedef uint32_t tlc_u4b __attribute__((aligned(1)));
+__device__ __forceinline__ uint32_t ld_word(const uint8_t* p) {
+  return *reinterpret_cast<const tlc_u4b*>(p);
+}
+__device__ __forceinline__ void st_word(uint8_t* p, uint32_t w) {
+  *reinterpret_cast<tlc_u4b*>(p) = w;
+}
+
 // The same as streaming accesses, with the
 // nontemporal hint, for tensors read or written once per kernel and far
 // larger than the caches.  Measured on gfx950: the max reduction reads

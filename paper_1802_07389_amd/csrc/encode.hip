@@ -178,31 +178,15 @@ __global__ __launch_bounds__(kThreads) void tlc_absmax_check_kernel(
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
-// The guard of a writing pass: with the check pass's partial maxima (guard
-// != nullptr), a tensor whose scale would be NaN/Inf or overflow is left
-// untouched, and the pass posts a partial that makes every later kernel
-// refuse it as well.  Returns true when the block must stop.  Ends with a
-// barrier when it reads the guard.
-__device__ __forceinline__ bool refused_by_guard(const uint32_t* __restrict__ guard,
-                                                 uint32_t guard_np, float s, uint32_t* lds,
-                                                 uint32_t* __restrict__ partial) {
-  if (guard == nullptr) return false;
-  const Scale g = finish_scale(guard, guard_np, s, lds);
-  __syncthreads();  // lds is reused by the caller
-  if (!g.bad) return false;
-  if (threadIdx.x == 0) *partial = 0xffffffffu;
-  return true;
-}
-
-template <bool kResid, bool kBound>
+// Step 1 into the buffer and its max pass (in place, large tensors), or the
+// max pass of a tensor without one.
+template <bool kResid>
 __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_kernel(
     const float* __restrict__ x, float* __restrict__ r, uint64_t n,
-    uint32_t* __restrict__ partials, const uint32_t* __restrict__ guard, uint32_t guard_np,
-    float s, uint16_t* __restrict__ bound) {
+    uint32_t* __restrict__ partials, uint16_t* __restrict__ bound) {
   __shared__ uint32_t lds[kWaves];
-  if (refused_by_guard(guard, guard_np, s, lds, &partials[blockIdx.x])) return;
   const uint32_t mx = block_max(
-      absmax_part<kResid, kResid, kBound>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
+      absmax_part<kResid, kResid, kResid>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
@@ -1228,11 +1212,14 @@ __global__ __launch_bounds__(kThreads) void tlc_stochastic_trits_kernel(
 // The quartic bytes of all values from their trits, one tile per block.
 __global__ __launch_bounds__(kThreads) void tlc_quant_pack_kernel(
     uint64_t n, uint32_t m, const uint8_t* __restrict__ trits, uint8_t* __restrict__ out,
-    Ctrl* __restrict__ ctrl) {
+    Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ uint32_t s_lut[5][256];
   __shared__ __align__(16) uint8_t s_q[kEncTile];
   const uint32_t bad = ctrl->enc.err;
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->enc.len = bad ? 0u : m;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctrl->enc.len = bad ? 0u : m;
+    host_put_all(hm.res, bad, bad ? 0u : m, ctrl->enc.scale);
+  }
   if (bad) return;
   const uint64_t q0 = (uint64_t)blockIdx.x * kEncTile;
   const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
@@ -1275,18 +1262,12 @@ hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint3
 }
 
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, const uint32_t* guard, uint32_t guard_np,
-                               float s, uint16_t* bound, hipStream_t st) {
-  const uint32_t blocks = absmax_blocks(n);
-  if (guard && guard_np != blocks) return hipErrorInvalidValue;  // same launch as the check
-  *nblocks = blocks;
-#define TLC_LAUNCH(R, B)                                                                     \
-  launch_k(tlc_accum_absmax_kernel<R, B>, blocks, kThreads, st, x, r, n, partials, guard, \
-           guard_np, s, bound)
-  if (r == nullptr) TLC_LAUNCH(false, false);  // no error buffer: max |x|
-  else if (bound) TLC_LAUNCH(true, true);
-  else TLC_LAUNCH(true, false);
-#undef TLC_LAUNCH
+                               uint32_t* nblocks, uint16_t* bound, hipStream_t st) {
+  *nblocks = absmax_blocks(n);
+  if (r)
+    launch_k(tlc_accum_absmax_kernel<true>, *nblocks, kThreads, st, x, r, n, partials, bound);
+  else
+    launch_k(tlc_accum_absmax_kernel<false>, *nblocks, kThreads, st, x, r, n, partials, bound);
   return hipGetLastError();
 }
 
@@ -1393,9 +1374,9 @@ hipError_t launch_stochastic_trits(const float* x, uint64_t n, float s, uint64_t
 }
 
 hipError_t launch_quant_pack(uint64_t n, uint32_t m, const uint8_t* trits, uint8_t* out,
-                             Ctrl* ctrl, hipStream_t st) {
+                             Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   const uint32_t blocks = (uint32_t)((m + kEncTile - 1) / kEncTile);
-  launch_k(tlc_quant_pack_kernel, blocks, kThreads, st, n, m, trits, out, ctrl);
+  launch_k(tlc_quant_pack_kernel, blocks, kThreads, st, n, m, trits, out, ctrl, hm);
   return hipGetLastError();
 }
 

@@ -4,9 +4,8 @@
 //
 //   tlc_int8_quant_kernel    code = rint(acc / D) clamped to [-127, 127]
 //                            (0 when D == 0), residual acc - code * D,
-//                            one int8 byte per value; acc is the buffer
-//                            that tlc_accum_absmax_kernel has accumulated
-//                            (error feedback) or the tensor itself
+//                            one int8 byte per value; acc = x + r after the
+//                            check pass (error feedback) or the tensor itself
 //   tlc_int8_dequant_kernel  out = code * D, or out + code * D
 //
 // Both are elementwise streams: a block covers kI8Rows rows of 1024 values;
@@ -58,162 +57,148 @@ __device__ __forceinline__ uint32_t int8_one(float acc, float D, float& res) {
   return int8_byte(code);
 }
 
-// kVec: the values read (r or x) 16-byte aligned, out 4-byte aligned.
-// kResid: error feedback, acc = r (already x + r) and r is rewritten, x is
-// unused; otherwise acc = x and r is unused.
-template <bool kVec, bool kResid>
+// kResid: error feedback, acc = x + r is formed here once the check pass has
+// given M (8n + 13n bytes; storing the sums in a max pass and reading them
+// again took 8n + 12n + 9n: 128 + 103 us on 2^26 values) and r is rewritten;
+// otherwise acc = x and r is unused.  A refused tensor is left alone, or with
+// its sums (in_place).  Any alignment.
+template <bool kResid>
 __global__ __launch_bounds__(kThreads) void tlc_int8_quant_kernel(
-    const float* __restrict__ x, float* __restrict__ r, uint64_t n, float s,
+    const float* __restrict__ x, float* __restrict__ r, uint64_t n, float s, bool in_place,
     const uint32_t* __restrict__ partials, uint32_t np, uint8_t* __restrict__ out,
-    Ctrl* __restrict__ ctrl) {
+    Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ uint32_t red[kWaves];
   const Scale sc = finish_scale(partials, np, s, red);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const uint32_t len = sc.bad ? 0u : (uint32_t)n;
     ctrl->enc.err = sc.bad;
     ctrl->enc.scale = sc.M;
-    ctrl->enc.len = sc.bad ? 0u : (uint32_t)n;
+    ctrl->enc.len = len;
+    host_put_all(hm.res, sc.bad, len, sc.M);
   }
-  if (sc.bad) return;  // NaN/Inf or overflow: no bytes, the buffer keeps acc
+  if (sc.bad && !(kResid && in_place)) return;  // NaN/Inf or overflow: no bytes
   const float D = int8_step(sc.M);
   const uint64_t base = (uint64_t)blockIdx.x * kI8Row * kI8Rows;
-  const float* __restrict__ src = kResid ? r : x;
-  if (kVec) {
 #pragma unroll 1
-    for (int h = 0; h < kI8Rows; h += kI8Batch) {
-      float4 a[kI8Batch];
-      bool full[kI8Batch];
+  for (int h = 0; h < kI8Rows; h += kI8Batch) {
+    float4 a[kI8Batch], b[kI8Batch];
+    bool full[kI8Batch];
+#pragma unroll
+    for (int i = 0; i < kI8Batch; ++i) {
+      const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
+      full[i] = e + 4u <= n;
+      if (full[i]) a[i] = ld_stream(x + e);
+    }
+    if (kResid) {
 #pragma unroll
       for (int i = 0; i < kI8Batch; ++i) {
         const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
-        full[i] = e + 4u <= n;
-        if (full[i]) a[i] = ld_stream(src + e);
+        if (full[i]) b[i] = ld_stream(r + e);
       }
+    }
 #pragma unroll
-      for (int i = 0; i < kI8Batch; ++i) {
-        const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
-        if (full[i]) {
-          float4 o;
-          const uint32_t w = int8_one<kResid>(a[i].x, D, o.x) |
-                             int8_one<kResid>(a[i].y, D, o.y) << 8 |
-                             int8_one<kResid>(a[i].z, D, o.z) << 16 |
-                             int8_one<kResid>(a[i].w, D, o.w) << 24;
-          if (kResid) st_stream(r + e, o);
-          *reinterpret_cast<uint32_t*>(out + e) = w;
-        } else {
+    for (int i = 0; i < kI8Batch; ++i) {
+      const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
+      if (full[i]) {
+        float4 v = a[i], o;
+        if (kResid)
+          v = make_float4(__fadd_rn(v.x, b[i].x), __fadd_rn(v.y, b[i].y), __fadd_rn(v.z, b[i].z),
+                          __fadd_rn(v.w, b[i].w));
+        if (sc.bad) {
+          st_stream(r + e, v);
+          continue;
+        }
+        const uint32_t w = int8_one<kResid>(v.x, D, o.x) | int8_one<kResid>(v.y, D, o.y) << 8 |
+                           int8_one<kResid>(v.z, D, o.z) << 16 |
+                           int8_one<kResid>(v.w, D, o.w) << 24;
+        if (kResid) st_stream(r + e, o);
+        st_word(out + e, w);
+      } else {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            if (e + c < n) {
-              float o = 0.0f;
-              out[e + c] = (uint8_t)int8_one<kResid>(src[e + c], D, o);
-              if (kResid) r[e + c] = o;
-            }
+        for (int c = 0; c < 4; ++c) {
+          if (e + c < n) {
+            const float v = kResid ? __fadd_rn(x[e + c], r[e + c]) : x[e + c];
+            float o = v;
+            if (!sc.bad) out[e + c] = (uint8_t)int8_one<kResid>(v, D, o);
+            if (kResid) r[e + c] = o;
           }
         }
       }
-    }
-  } else {
-    for (uint32_t k = threadIdx.x; k < kI8Row * kI8Rows; k += kThreads) {
-      const uint64_t e = base + k;
-      if (e >= n) break;
-      float o = 0.0f;
-      out[e] = (uint8_t)int8_one<kResid>(src[e], D, o);
-      if (kResid) r[e] = o;
     }
   }
 }
 
-// kVec: C 4-byte aligned, out 16-byte aligned.
-template <bool kVec, bool kAcc>
+template <bool kAcc>
 __global__ __launch_bounds__(kThreads) void tlc_int8_dequant_kernel(
     const uint8_t* __restrict__ C, uint64_t n, float M, float* __restrict__ out) {
   const float D = int8_step(M);
   const uint64_t base = (uint64_t)blockIdx.x * kI8Row * kI8Rows;
-  if (kVec) {
 #pragma unroll 1
-    for (int h = 0; h < kI8Rows; h += kI8Batch) {
-      uint32_t w[kI8Batch];
-      float4 o[kI8Batch];
-      bool full[kI8Batch];
+  for (int h = 0; h < kI8Rows; h += kI8Batch) {
+    uint32_t w[kI8Batch];
+    float4 o[kI8Batch];
+    bool full[kI8Batch];
 #pragma unroll
-      for (int i = 0; i < kI8Batch; ++i) {
-        const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
-        full[i] = e + 4u <= n;
-        if (full[i]) {
-          w[i] = *reinterpret_cast<const uint32_t*>(C + e);
-          if (kAcc) o[i] = ld_stream(out + e);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < kI8Batch; ++i) {
-        const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
-        if (full[i]) {
-          float4 res;
-          if (kAcc) {
-            res = make_float4(int8_acc(o[i].x, w[i], D), int8_acc(o[i].y, w[i] >> 8, D),
-                              int8_acc(o[i].z, w[i] >> 16, D), int8_acc(o[i].w, w[i] >> 24, D));
-          } else {
-            res = make_float4(int8_value(w[i], D), int8_value(w[i] >> 8, D),
-                              int8_value(w[i] >> 16, D), int8_value(w[i] >> 24, D));
-          }
-          st_stream(out + e, res);
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            if (e + c < n)
-              out[e + c] = kAcc ? int8_acc(out[e + c], C[e + c], D) : int8_value(C[e + c], D);
-          }
-        }
+    for (int i = 0; i < kI8Batch; ++i) {
+      const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
+      full[i] = e + 4u <= n;
+      if (full[i]) {
+        w[i] = ld_word(C + e);
+        if (kAcc) o[i] = ld_stream(out + e);
       }
     }
-  } else {
-    for (uint32_t k = threadIdx.x; k < kI8Row * kI8Rows; k += kThreads) {
-      const uint64_t e = base + k;
-      if (e >= n) break;
-      out[e] = kAcc ? int8_acc(out[e], C[e], D) : int8_value(C[e], D);
+#pragma unroll
+    for (int i = 0; i < kI8Batch; ++i) {
+      const uint64_t e = base + (uint64_t)(h + i) * kI8Row + 4u * threadIdx.x;
+      if (full[i]) {
+        float4 res;
+        if (kAcc) {
+          res = make_float4(int8_acc(o[i].x, w[i], D), int8_acc(o[i].y, w[i] >> 8, D),
+                            int8_acc(o[i].z, w[i] >> 16, D), int8_acc(o[i].w, w[i] >> 24, D));
+        } else {
+          res = make_float4(int8_value(w[i], D), int8_value(w[i] >> 8, D),
+                            int8_value(w[i] >> 16, D), int8_value(w[i] >> 24, D));
+        }
+        st_stream(out + e, res);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (e + c < n)
+            out[e + c] = kAcc ? int8_acc(out[e + c], C[e + c], D) : int8_value(C[e + c], D);
+        }
+      }
     }
   }
 }
 
 // ---------------------------------------------------------------- launchers
 namespace {
-inline bool aligned(const void* p, uintptr_t a) {
-  return (reinterpret_cast<uintptr_t>(p) & (a - 1u)) == 0u;
-}
 inline uint32_t int8_blocks(uint64_t n) {
   const uint64_t per = (uint64_t)kI8Row * kI8Rows;
   return (uint32_t)((n + per - 1) / per);
 }
 }  // namespace
 
-hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s,
+hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s, bool in_place,
                              const uint32_t* partials, uint32_t npartials, uint8_t* out,
-                             Ctrl* ctrl, hipStream_t st) {
+                             Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   const uint32_t blocks = int8_blocks(n);
-  const bool vec = aligned(r ? r : x, 16) && aligned(out, 4);
-  if (r) x = nullptr;  // the buffer already holds x + r
-#define TLC_LAUNCH(V, R)                                                                 \
-  launch_k(tlc_int8_quant_kernel<V, R>, blocks, kThreads, st, x, r, n, s, partials, npartials, \
-                                                           out, ctrl)
-  if (r) {
-    if (vec) TLC_LAUNCH(true, true); else TLC_LAUNCH(false, true);
-  } else {
-    if (vec) TLC_LAUNCH(true, false); else TLC_LAUNCH(false, false);
-  }
-#undef TLC_LAUNCH
+  if (r)
+    launch_k(tlc_int8_quant_kernel<true>, blocks, kThreads, st, x, r, n, s, in_place, partials,
+             npartials, out, ctrl, hm);
+  else
+    launch_k(tlc_int8_quant_kernel<false>, blocks, kThreads, st, x, r, n, s, in_place, partials,
+             npartials, out, ctrl, hm);
   return hipGetLastError();
 }
 
 hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out,
                                int accumulate, hipStream_t st) {
   const uint32_t blocks = int8_blocks(n);
-  const bool vec = aligned(C, 4) && aligned(out, 16);
-#define TLC_LAUNCH(V, A) launch_k(tlc_int8_dequant_kernel<V, A>, blocks, kThreads, st, C, n, M, out)
-  if (accumulate) {
-    if (vec) TLC_LAUNCH(true, true); else TLC_LAUNCH(false, true);
-  } else {
-    if (vec) TLC_LAUNCH(true, false); else TLC_LAUNCH(false, false);
-  }
-#undef TLC_LAUNCH
+  if (accumulate)
+    launch_k(tlc_int8_dequant_kernel<true>, blocks, kThreads, st, C, n, M, out);
+  else
+    launch_k(tlc_int8_dequant_kernel<false>, blocks, kThreads, st, C, n, M, out);
   return hipGetLastError();
 }
 

@@ -49,8 +49,6 @@ bool overlap(const void* a, size_t an, const void* b, size_t bn) {
   return an && bn && pa < pb + bn && pb < pa + an;
 }
 
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0u; }
-
 const char* const kKernelNames[TLC_KERNEL_COUNT] = {
     "tlc_accum_absmax_kernel",       "tlc_quant_encode_kernel",
     "tlc_zre_index_kernel",          "tlc_expand_dequant_kernel",
@@ -135,6 +133,7 @@ struct tlc_ctx {
   size_t start_words = 0;
   EncDesc* enc_descs = nullptr;
   DecDesc* dec_descs = nullptr;
+  uint16_t* dec_owner = nullptr;  // the stream of each scan tile of a summed decode
   EncResult* enc_results = nullptr;
   // single-tensor encoder: per-tile slots and records, chunk summaries
   uint8_t* slots = nullptr;
@@ -148,7 +147,7 @@ struct tlc_ctx {
   EncResult* host_results = nullptr;
   HostReadback* rb_dev = nullptr;  // the same pinned memory, as the device addresses it
   uint8_t* staging = nullptr;  // kStagingSlots slots: descriptors, then the tiles' owners
-  size_t slot_bytes = 0;
+  size_t slot_bytes = 0, owner_cap = 0;
   uint8_t* staging_dev = nullptr;  // the same, as the device addresses it
   hipEvent_t staging_done[kStagingSlots] = {};
   bool staging_used[kStagingSlots] = {};
@@ -166,7 +165,7 @@ struct tlc_ctx {
   std::vector<EncDesc> enc_host;
   std::vector<DecDesc> dec_host;
   std::vector<size_t> which;
-  std::vector<uint16_t> owner;  // the tensor of each encoder tile (capacity enc_status_words)
+  std::vector<uint16_t> owner;  // the tensor of each encoder tile (capacity owner_cap)
   std::vector<Span> spans;  // address ranges of a batched call (3 per tensor)
   std::vector<Span> enc_spans_ok, dec_spans_ok;  // the last batched calls that passed
   std::vector<hipEvent_t> free_events;
@@ -319,10 +318,17 @@ int take_slot(tlc_ctx* c, const void* src, size_t bytes, int* slot) {
   return TLC_OK;
 }
 
-int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes) {
+// own (may be NULL): owners to follow the descriptors in the same copy.
+int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes, const void* own = nullptr,
+           size_t own_bytes = 0) {
   int slot = 0;
   int st = take_slot(c, src, bytes, &slot);
   if (st) return st;
+  if (own_bytes) {
+    const size_t off = c->max_tensors * 64;
+    memcpy(c->staging + (size_t)slot * c->slot_bytes + off, own, own_bytes);
+    bytes = off + own_bytes;
+  }
   const uint8_t* host = c->staging + (size_t)slot * c->slot_bytes;
   hipError_t e = hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipEventRecord(c->staging_done[slot], c->stream);
@@ -335,29 +341,27 @@ int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes) {
 }
 
 // The descriptors and the tiles' owners in a pinned slot, as the device
-// addresses it, for kernels that read them there; the caller waits for those
-// kernels' results, so the slot needs no event.
+// addresses it, for kernels that read them there.  The caller either waits
+// for those kernels' results or records the slot's event after them
+// (hold_slot).
 int stage(tlc_ctx* c, const void* src, size_t bytes, const void* own, size_t own_bytes,
-          const void** dev, const void** dev_own) {
-  int slot = 0;
-  int st = take_slot(c, src, bytes, &slot);
+          const void** dev, const void** dev_own, int* slot) {
+  int st = take_slot(c, src, bytes, slot);
   if (st) return st;
-  const size_t at = (size_t)slot * c->slot_bytes, off = c->max_tensors * 64;
+  const size_t at = (size_t)*slot * c->slot_bytes, off = c->max_tensors * 64;
   memcpy(c->staging + at + off, own, own_bytes);
   *dev = c->staging_dev + at;
   *dev_own = c->staging_dev + at + off;
   return TLC_OK;
 }
 
-// Copies the control block's readback fields to the pinned block, then
-// waits.
-int sync_and_read(tlc_ctx* c) {
-  hipError_t e =
-      hipMemcpyAsync(c->rb, c->ctrl, sizeof(HostReadback), hipMemcpyDeviceToHost, c->stream);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(readback)");
-  e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  collect_timings(c);
+int hold_slot(tlc_ctx* c, int slot) {
+  const hipError_t e = hipEventRecord(c->staging_done[slot], c->stream);
+  if (e != hipSuccess) {
+    c->broken = true;
+    return hip_fail(e, "hipEventRecord(staging)");
+  }
+  c->staging_used[slot] = true;
   return TLC_OK;
 }
 
@@ -449,12 +453,10 @@ int wait_results(tlc_ctx* c, const EncResult* r, uint32_t count) {
   return TLC_OK;
 }
 
-// Waits for an encode and reports its result (the stream length and M);
-// mirrored: the kernels wrote it into the readback (enc_mirror), which
-// arm_result prepared.
-int finish_compress(tlc_ctx* c, const char* fn, size_t* bytes_len, float* scale,
-                    bool mirrored = false) {
-  int st = mirrored ? wait_results(c, &c->rb->enc, 1) : sync_and_read(c);
+// Waits for an encode and reports its result (the stream length and M): the
+// kernels write it into the readback (enc_mirror), which arm_results prepared.
+int finish_compress(tlc_ctx* c, const char* fn, size_t* bytes_len, float* scale) {
+  int st = wait_results(c, &c->rb->enc, 1);
   if (st) return st;
   if (c->rb->fault) {
     c->broken = true;
@@ -517,11 +519,13 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
       std::max<size_t>(kAbsmaxMaxBlocks, max_n / ((size_t)kThreads * 4) + max_tensors + 1);
   const size_t tiles1 = ceil_div(quartic_len(max_n), (size_t)kEncTile);  // one tensor
   c->enc_status_words = mm / kSmallTile + max_tensors + 2;
-  c->slot_bytes = round_up(max_tensors * 64 + c->enc_status_words * sizeof(uint16_t), 64);
   c->dec_status_words = mm / kZreBatchTile + max_tensors + 2;  // the smaller tile
   c->start_words = mm / kDecRange + max_tensors + 2;
+  // a slot's owners: an encoder's tiles, or a decoder's ranges and scan tiles
+  c->owner_cap = std::max(c->enc_status_words, c->start_words + c->dec_status_words);
+  c->slot_bytes = round_up(max_tensors * 64 + c->owner_cap * sizeof(uint16_t), 64);
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
-  //         start | enc descs | dec descs | tile records | chunk summaries |
+  //         start | enc descs | dec descs | scan tiles' owners | tile records | chunk summaries |
   //         tile prefixes in their chunks | line bounds | trits | slots
   // (the batch results follow the control block, so that one copy reads both)
   static_assert(sizeof(Ctrl) % alignof(EncResult) == 0, "results follow the control block");
@@ -540,7 +544,8 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   const size_t off_edesc = off;
   off = round_up(off + max_tensors * sizeof(EncDesc), 256);
   const size_t off_ddesc = off;
-  off = round_up(off + max_tensors * sizeof(DecDesc), 256);
+  // (as in a staging slot: the owners follow max_tensors descriptors)
+  off = round_up(off + max_tensors * sizeof(DecDesc) + c->dec_status_words * sizeof(uint16_t), 256);
   const size_t off_recs = off;
   off = round_up(off + tiles1 * sizeof(TileRec), 256);
   const size_t off_chunks = off;
@@ -567,6 +572,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->start = (uint64_t*)(base + off_start);
   c->enc_descs = (EncDesc*)(base + off_edesc);
   c->dec_descs = (DecDesc*)(base + off_ddesc);
+  c->dec_owner = (uint16_t*)(base + off_ddesc + max_tensors * sizeof(DecDesc));
   c->enc_results = (EncResult*)(base + off_res);
   c->recs = (TileRec*)(base + off_recs);
   c->chunk_agg = (uint64_t*)(base + off_chunks);
@@ -604,7 +610,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
     c->enc_host.reserve(max_tensors);
     c->dec_host.reserve(max_tensors);
     c->which.reserve(max_tensors);
-    c->owner.reserve(c->enc_status_words);
+    c->owner.reserve(c->owner_cap);
     c->spans.reserve(3 * max_tensors);
     c->enc_spans_ok.reserve(3 * max_tensors);
     c->dec_spans_ok.reserve(3 * max_tensors);
@@ -642,23 +648,15 @@ TLC_API int tlc_ctx_destroy(tlc_ctx* c) {
 // ---------------------------------------------------------------- encode
 namespace {
 
-// Step 1 and Eq. 1 for one tensor (r may be NULL: no error buffer).  With
-// the default error policy a check pass first reduces max|x + r| without
-// writing, and the writing pass leaves a tensor whose scale is bad
-// untouched, so the buffer keeps its values on TLC_E_NONFINITE;
-// TLC_OPT_IN_PLACE_FEEDBACK drops the check pass.
-int launch_max_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint32_t* np) {
-  const uint32_t* guard = nullptr;
-  uint32_t guard_np = 0;
-  if (r && !(c->options & TLC_OPT_IN_PLACE_FEEDBACK)) {
-    int st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
-      return launch_absmax_check(x, r, n, c->partials_chk, &guard_np, c->stream);
+// Eq. 1 for one tensor without a byte written: the check pass, or max |x|
+// where there is no error buffer.
+int launch_max_pass(tlc_ctx* c, const float* x, const float* r, size_t n, uint32_t* np) {
+  if (r)
+    return timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
+      return launch_absmax_check(x, r, n, c->partials, np, c->stream);
     });
-    if (st) return st;
-    guard = c->partials_chk;
-  }
   return timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-    return launch_accum_absmax(x, r, n, c->partials, np, guard, guard_np, s, nullptr, c->stream);
+    return launch_accum_absmax(x, nullptr, n, c->partials, np, nullptr, c->stream);
   });
 }
 
@@ -672,7 +670,7 @@ int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float
   int st;
   if (c->options & TLC_OPT_IN_PLACE_FEEDBACK) {
     st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-      return launch_accum_absmax(x, r, n, c->partials, &np, nullptr, 0, s, c->bound, c->stream);
+      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, c->stream);
     });
     if (st) return st;
     return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
@@ -752,7 +750,7 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
     });
     if (st) return st;
     if (tiles > 1u) c->enc_ticket_base += tiles;  // a lone tile takes no ticket
-    return finish_compress(c, "tlc_compress", bytes_len, scale, true);
+    return finish_compress(c, "tlc_compress", bytes_len, scale);
   }
   st = launch_quantize_passes(c, tensor, residual, n, s, enc_mirror(c));
   if (st) return st;
@@ -771,7 +769,7 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
                               c->ctrl, enc_mirror(c), c->stream);
   });
   if (st) return st;
-  return finish_compress(c, "tlc_compress", bytes_len, scale, true);
+  return finish_compress(c, "tlc_compress", bytes_len, scale);
 }
 
 namespace {
@@ -799,14 +797,14 @@ int compress_int8(tlc_ctx* c, const float* tensor, float* residual, size_t n, fl
   int st = dev.status();
   if (st) return st;
   uint32_t np = 0;
-  st = launch_max_passes(c, tensor, residual, n, s, &np);
+  st = launch_max_pass(c, tensor, residual, n, &np);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_INT8_QUANT, [&] {
-    return launch_int8_quant(tensor, residual, n, s, c->partials, np, bytes, c->ctrl,
-                             c->stream);
+    return launch_int8_quant(tensor, residual, n, s, (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u,
+                             c->partials, np, bytes, c->ctrl, enc_mirror(c), c->stream);
   });
   if (st) return st;
-  st = sync_and_read(c);
+  st = sync_mirrored(c);
   if (st) return st;
   if (c->rb->enc.err)
     return fail(TLC_E_NONFINITE, "tlc_compress_ex: NaN/Inf in the input or max*s overflow");
@@ -853,26 +851,25 @@ TLC_API int tlc_compress_ex(tlc_ctx* c, int mode, const float* tensor, float* re
   if (st) return st;
   if (stoch) {  // no error feedback: max |x|, then trits of x
     uint32_t np = 0;
-    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-      return launch_accum_absmax(tensor, nullptr, n, c->partials, &np, nullptr, 0, s, nullptr,
-                                 c->stream);
-    });
+    st = launch_max_pass(c, tensor, nullptr, n, &np);
     if (st) return st;
     st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
       hipError_t e = launch_stochastic_trits(tensor, n, s, seed, step, c->partials, np, c->trits,
                                              c->ctrl, c->stream);
       if (e != hipSuccess) return e;
-      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, c->stream);
+      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, enc_mirror(c),
+                               c->stream);
     });
   } else {
     st = launch_quantize_passes(c, tensor, residual, n, s, HostMirror{});
     if (st) return st;
     st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
-      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, c->stream);
+      return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, enc_mirror(c),
+                               c->stream);
     });
   }
   if (st) return st;
-  st = sync_and_read(c);
+  st = sync_mirrored(c);
   if (st) return st;
   if (c->rb->enc.err)
     return fail(TLC_E_NONFINITE, "tlc_compress_ex: NaN/Inf in the input or max*s overflow");
@@ -983,8 +980,10 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
     // every block reads one descriptor, once: straight from the pinned copy,
     // which is free again when the call returns (every result needs its own)
     const EncDesc* pinned = nullptr;
+    int slot = 0;
     st = stage(c, d.data(), cnt * sizeof(EncDesc), c->owner.data(),
-               c->owner.size() * sizeof(uint16_t), (const void**)&pinned, (const void**)&owner);
+               c->owner.size() * sizeof(uint16_t), (const void**)&pinned, (const void**)&owner,
+               &slot);
     if (st) return st;
     if (!nbig) descs = pinned;
   }
@@ -1154,7 +1153,6 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
     e.scale = scales[t];
     e.tile0 = tiles;
     e.range0 = ranges;
-    e.vec = aligned16(outs[t]) ? (e.m % 4 == 0 ? 1u : 2u) : 0u;
     tiles += (uint32_t)ceil_div(e.c, kZreBatchTile);
     ranges += (uint32_t)ceil_div(e.m, kDecRange);
     d.push_back(e);
@@ -1177,22 +1175,35 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   st = dev.status();
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
-  st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc));
+  // whose each range is, then (unless every stream has one) each scan tile
+  c->owner.clear();
+  for (uint32_t i = 0; i < cnt; ++i)
+    c->owner.insert(c->owner.end(), ceil_div(d[i].m, (size_t)kDecRange), (uint16_t)i);
+  if (tiles != cnt)
+    for (uint32_t i = 0; i < cnt; ++i)
+      c->owner.insert(c->owner.end(), ceil_div(d[i].c, (size_t)kZreBatchTile), (uint16_t)i);
+  const DecDesc* descs = nullptr;
+  const uint16_t* owner = nullptr;
+  int slot = 0;
+  st = stage(c, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
+             c->owner.size() * sizeof(uint16_t), (const void**)&descs, (const void**)&owner, &slot);
   if (st) return st;
   uint32_t epoch = 0;
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_INDEX_BATCH, [&] {
-    return launch_zre_index_batch(c->dec_descs, cnt, tiles, c->start, c->dec_status,
+    return launch_zre_index_batch(descs, cnt, owner + ranges, tiles, c->start, c->dec_status,
                                   c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
                                   c->stream);
   });
   if (st) return st;
-  c->dec_ticket_base += tiles;
-  return timed_launch(c, TLC_KERNEL_EXPAND_DEQUANT_BATCH, [&] {
-    return launch_expand_dequant_batch(c->dec_descs, cnt, ranges, c->start, accumulate, epoch,
-                                       c->ctrl, c->stream);
+  if (tiles != cnt) c->dec_ticket_base += tiles;
+  st = timed_launch(c, TLC_KERNEL_EXPAND_DEQUANT_BATCH, [&] {
+    return launch_expand_dequant_batch(descs, owner, ranges, c->start, accumulate, epoch, c->ctrl,
+                                       c->stream);
   });
+  if (st) return st;
+  return hold_slot(c, slot);
 }
 
 TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* bytes,
@@ -1239,22 +1250,28 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   st = dev.status();
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
-  st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc));
+  c->owner.clear();
+  if (tiles != cnt)
+    for (uint32_t i = 0; i < cnt; ++i)
+      c->owner.insert(c->owner.end(), ceil_div(d[i].c, (size_t)kZreBatchTile), (uint16_t)i);
+  // to device memory: every block of the sum reads the descriptors
+  st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
+              c->owner.size() * sizeof(uint16_t));
   if (st) return st;
+  const uint16_t* owner = c->dec_owner;
   uint32_t epoch = 0;
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_INDEX_BATCH, [&] {
-    return launch_zre_index_batch(c->dec_descs, cnt, tiles, c->start, c->dec_status,
+    return launch_zre_index_batch(c->dec_descs, cnt, owner, tiles, c->start, c->dec_status,
                                   c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
                                   c->stream);
   });
   if (st) return st;
-  c->dec_ticket_base += tiles;
-  const int vec = (m % 4 == 0 && aligned16(out)) ? 1 : 0;
+  if (tiles != cnt) c->dec_ticket_base += tiles;
   return timed_launch(c, TLC_KERNEL_EXPAND_SUM, [&] {
-    return launch_expand_sum(c->dec_descs, cnt, c->start, n, m, out, vec, accumulate, epoch,
-                             c->ctrl, c->stream);
+    return launch_expand_sum(c->dec_descs, cnt, c->start, n, m, out, accumulate, epoch, c->ctrl,
+                             c->stream);
   });
 }
 

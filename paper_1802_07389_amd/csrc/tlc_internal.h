@@ -124,8 +124,7 @@ struct DecDesc {
   float scale;
   uint32_t tile0;   // first index-scan tile (global numbering of the launch)
   uint32_t range0;  // first start-index entry / expand block of this stream
-  uint32_t vec;     // 1: m % 4 == 0 and out 16-byte aligned; 2: only out aligned
-  uint32_t pad[4];
+  uint32_t pad[5];
 };
 static_assert(sizeof(DecDesc) == 64, "DecDesc is 64 bytes");
 
@@ -159,13 +158,11 @@ inline void launch_k(void (*kernel)(Formals...), dim3 grid, dim3 block, hipStrea
 // The check pass: partial maxima of |x + r|, nothing written.
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st);
-// Step 1 into the buffer (r NULL: none) and the partial maxima.  guard (may
-// be NULL): the check pass's guard_np partial maxima; if they give a bad
-// scale (with s), nothing is written and the partials mark the tensor bad.
-// bound (may be NULL): per 32 values of r, the top half of the largest |acc|.
+// In place: step 1 into the buffer (r NULL: max |x| alone) and the partial
+// maxima; bound (with r): per 32 values of r, the top half of the largest
+// |acc|.
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, const uint32_t* guard, uint32_t guard_np,
-                               float s, uint16_t* bound, hipStream_t st);
+                               uint32_t* nblocks, uint16_t* bound, hipStream_t st);
 // Eq. 2 for a large tensor: final residuals in r and 2-bit trits, one byte per
 // four values.  After the check pass (its partials): from x + r; in place
 // (the max pass's partials and bounds): from r.
@@ -196,10 +193,11 @@ hipError_t launch_stochastic_trits(const float* x, uint64_t n, float s, uint64_t
                                    uint64_t step, const uint32_t* partials, uint32_t np,
                                    uint8_t* trits, Ctrl* ctrl, hipStream_t st);
 hipError_t launch_quant_pack(uint64_t n, uint32_t m, const uint8_t* trits, uint8_t* out,
-                             Ctrl* ctrl, hipStream_t st);
-hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s,
+                             Ctrl* ctrl, HostMirror hm, hipStream_t st);
+// x + r after the check pass (its partials), or x alone (r NULL).
+hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s, bool in_place,
                              const uint32_t* partials, uint32_t npartials, uint8_t* out,
-                             Ctrl* ctrl, hipStream_t st);
+                             Ctrl* ctrl, HostMirror hm, hipStream_t st);
 hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out,
                                int accumulate, hipStream_t st);
 // The max pass of the first `count` tensors (those of more than kExchangeTiles
@@ -243,16 +241,19 @@ hipError_t launch_expand_dequant(const uint8_t* C, uint32_t c, uint64_t* start,
                                  uint64_t* status, uint32_t ticket_base, uint64_t n, uint64_t m,
                                  float scale, float* out, int accumulate, uint32_t epoch,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st);
-hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, uint32_t total_tiles,
-                                  uint64_t* start, uint64_t* status, uint32_t ticket_base,
-                                  uint32_t epoch, Ctrl* ctrl, HostMirror hm, hipStream_t st);
-hipError_t launch_expand_dequant_batch(const DecDesc* descs, uint32_t count,
+// owner: the stream of each scan tile (not read when every stream has one),
+// of each range.
+hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, const uint16_t* owner,
+                                  uint32_t tiles, uint64_t* start, uint64_t* status,
+                                  uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl, HostMirror hm,
+                                  hipStream_t st);
+hipError_t launch_expand_dequant_batch(const DecDesc* descs, const uint16_t* owner,
                                        uint32_t total_ranges, const uint64_t* start,
                                        int accumulate, uint32_t epoch, const Ctrl* ctrl,
                                        hipStream_t st);
 hipError_t launch_expand_sum(const DecDesc* descs, uint32_t count, const uint64_t* start,
-                             uint64_t n, uint64_t m, float* out, int vec, int accumulate,
-                             uint32_t epoch, const Ctrl* ctrl, hipStream_t st);
+                             uint64_t n, uint64_t m, float* out, int accumulate, uint32_t epoch,
+                             const Ctrl* ctrl, hipStream_t st);
 
 // Epoch widths of the two look-back status layouts.
 constexpr uint32_t kEncEpochMax = (1u << 23) - 1u;
