@@ -39,6 +39,32 @@ __device__ __forceinline__ uint32_t verdict_word(uint32_t epoch, bool bad) {
   return (epoch << 1) | (bad ? 1u : 0u);
 }
 
+// `cnt` stream bytes from p on (at most kN), packed four to a word, byte i in
+// bits 8 * (i % 4) of w[i / 4]; bytes past cnt are 0.  The loads are of the
+// aligned dwords that hold the bytes, all issued together: each holds at least
+// one byte of the stream, so none leaves the pages that it lies in.  (Guarded
+// byte loads, each waited for before the next, kept the batched scan of short
+// streams at 16 us.)
+template <int kN>
+__device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ p, uint32_t cnt,
+                                           uint32_t (&w)[kN / 4]) {
+#pragma unroll
+  for (int q = 0; q < kN / 4; ++q) w[q] = 0u;
+  if (cnt == 0u) return;
+  const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(p) & 3u);
+  const uint32_t* base = reinterpret_cast<const uint32_t*>(p - sh);
+  const uint32_t last = (sh + cnt - 1u) >> 2;
+  uint32_t r[kN / 4 + 1];
+#pragma unroll
+  for (int q = 0; q < kN / 4 + 1; ++q) r[q] = base[umin32((uint32_t)q, last)];
+#pragma unroll
+  for (int q = 0; q < kN / 4; ++q) {
+    const uint32_t x = __builtin_amdgcn_alignbyte(r[q + 1], r[q], sh);
+    const uint32_t left = cnt > 4u * q ? cnt - 4u * q : 0u;
+    w[q] = left >= 4u ? x : (x & ((1u << (8u * left)) - 1u));
+  }
+}
+
 struct IdxShared {
   uint32_t red[kWaves];
   uint32_t fault;
@@ -52,8 +78,10 @@ struct IdxShared {
 // records (its index, how far into its expansion that position lies) in
 // start[k], so each expanding block finds its part of the stream with one
 // load.  The stream's last tile flags the launch's epoch as corrupt when
-// the expansion total is not exactly m.
-template <int kBytes>
+// the expansion total is not exactly m.  kVerdict: it also publishes its
+// verdict, for a launch whose other blocks wait for it (only there: hundreds
+// of streams' stores to the one word took the batched scan 10 us).
+template <int kBytes, bool kVerdict = false>
 __device__ __forceinline__ void index_tile(const uint8_t* __restrict__ C, uint32_t c, uint32_t m,
                                            uint64_t* __restrict__ start,
                                            uint64_t* __restrict__ status, uint32_t floor,
@@ -77,14 +105,7 @@ __device__ __forceinline__ void index_tile(const uint8_t* __restrict__ C, uint32
       w[4 * h + 3] = v.w;
     }
   } else {
-#pragma unroll
-    for (int q = 0; q < kBytes / 4; ++q) {
-      uint32_t x = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if ((uint32_t)(4 * q + i) < cnt) x |= (uint32_t)C[j0 + 4 * q + i] << (8 * i);
-      w[q] = x;
-    }
+    load_bytes<kBytes>(C + j0, cnt, w);
   }
   // one quartic byte per stream byte and the runs' extra bytes word by
   // word (the zero bytes past cnt add nothing)
@@ -121,7 +142,7 @@ __device__ __forceinline__ void index_tile(const uint8_t* __restrict__ C, uint32
         __hip_atomic_store(&ctrl->dec_corrupt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         host_put(hcorrupt, 1u);
       }
-      if (last_tile)
+      if (kVerdict && last_tile)
         __hip_atomic_store(&ctrl->dec_verdict, verdict_word(epoch, bad), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -299,10 +320,10 @@ __device__ __forceinline__ uint32_t expand_range(const uint8_t* __restrict__ C, 
   const Slice sl = slice_of(starts, k, m, c);
   const uint32_t lo = threadIdx.x * kSliceBytes;
   const uint32_t cnt = lo < sl.count ? umin32(kSliceBytes, sl.count - lo) : 0u;
-  uint8_t b[kSliceBytes];
-#pragma unroll
-  for (int i = 0; i < kSliceBytes; ++i) b[i] = (uint32_t)i < cnt ? C[sl.i0 + lo + i] : (uint8_t)0;
-  return expand_slice([&](int i) -> uint32_t { return b[i]; }, cnt, sl.skip, qn, s_q, red);
+  uint32_t w[kSliceBytes / 4];
+  load_bytes<kSliceBytes>(C + sl.i0 + lo, cnt, w);
+  return expand_slice([&](int i) -> uint32_t { return (w[i / 4] >> (8 * (i % 4))) & 255u; }, cnt,
+                      sl.skip, qn, s_q, red);
 }
 
 // ---------------------------------------------------------------- Eq. 3
@@ -552,7 +573,7 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
     __syncthreads();
     const uint32_t T = s_t;
     if (T < ntiles) {
-      index_tile<kZreBatchBytesPerThread>(C, c, (uint32_t)m, start, status, 0, T, epoch, ctrl,
+      index_tile<kZreBatchBytesPerThread, true>(C, c, (uint32_t)m, start, status, 0, T, epoch, ctrl,
                                           hm.fault, hm.corrupt, ish);
       return;
     }
@@ -591,12 +612,11 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
   }
   const uint32_t lo = threadIdx.x * kSliceBytes;
   const uint32_t cnt = lo < sl.count ? umin32(kSliceBytes, sl.count - lo) : 0u;
-  uint8_t b[kSliceBytes];
-#pragma unroll
-  for (int i = 0; i < kSliceBytes; ++i) b[i] = (uint32_t)i < cnt ? C[sl.i0 + lo + i] : (uint8_t)0;
+  uint32_t w[kSliceBytes / 4];
+  load_bytes<kSliceBytes>(C + sl.i0 + lo, cnt, w);
   const bool dense =
-      expand_slice([&](int i) -> uint32_t { return b[i]; }, cnt, sl.skip, qn, s_q, red) >
-      kDenseLiterals;
+      expand_slice([&](int i) -> uint32_t { return (w[i / 4] >> (8 * (i % 4))) & 255u; }, cnt,
+                   sl.skip, qn, s_q, red) > kDenseLiterals;
   if constexpr (kFused) {
     if (threadIdx.x == 0) s_ok = wait_verdict(epoch, ctrl, hm.fault) ? 1u : 0u;
     __syncthreads();

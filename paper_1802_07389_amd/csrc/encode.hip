@@ -1126,25 +1126,25 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_chained_kernel(
   encode_tile<kT, kTileGroups>(J, tile, in_place, status, maxima, epoch, ctrl, hm.fault, sh);
 }
 
-// Many tensors: block (or, where a tensor has more than one tile, ticket) T
-// belongs to the last descriptor whose tile0 is <= T.  kOneTile: every tensor
-// has one, so that is descriptor T.
-template <bool kOneTile>
+// Many tensors: the first `shared` tiles, of tensors of more than one, go by
+// ticket, and owner says whose each is; every other block has a tensor of its
+// own, in descriptor order, and takes none (hundreds of blocks queue for the
+// one counter).
 __global__ __launch_bounds__(kTileThreads) void tlc_quant_encode_batch_kernel(
-    const EncDesc* __restrict__ descs, uint32_t count, const uint16_t* __restrict__ owner,
+    const EncDesc* __restrict__ descs, uint32_t shared, const uint16_t* __restrict__ owner,
     bool in_place, const uint32_t* __restrict__ partials, EncResult* __restrict__ results,
     uint64_t* __restrict__ status, uint64_t* __restrict__ maxima, uint32_t ticket_base,
     uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ TileShared<kTileThreads, kTileGroups> sh;
   __shared__ uint32_t s_tile;
   __shared__ EncDesc s_desc;
-  uint32_t T = blockIdx.x, t = T;
-  if (!kOneTile) {
+  uint32_t T = blockIdx.x;
+  if (T < shared) {
     if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
     __syncthreads();
-    T = s_tile;
-    t = owner[T];
+    T = uniform32(s_tile);
   }
+  const uint32_t t = owner[T];
   // one read of the descriptor per block: it may lie in host memory
   if (threadIdx.x < sizeof(EncDesc) / 4)
     reinterpret_cast<uint32_t*>(&s_desc)[threadIdx.x] =
@@ -1347,17 +1347,13 @@ hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t to
   return hipGetLastError();
 }
 
-hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count, const uint16_t* owner,
+hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t shared, const uint16_t* owner,
                                      uint32_t tiles, bool in_place, const uint32_t* partials,
                                      EncResult* results, uint64_t* status, uint64_t* maxima,
                                      uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                      HostMirror hm, hipStream_t st) {
-  if (tiles == count)
-    launch_k(tlc_quant_encode_batch_kernel<true>, tiles, kTileThreads, st, descs, count, owner,
-             in_place, partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
-  else
-    launch_k(tlc_quant_encode_batch_kernel<false>, tiles, kTileThreads, st, descs, count, owner,
-             in_place, partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
+  launch_k(tlc_quant_encode_batch_kernel, tiles, kTileThreads, st, descs, shared, owner, in_place,
+           partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
   return hipGetLastError();
 }
 

@@ -935,7 +935,7 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
   which.clear();
   // the tensors with a max pass first (blk0 counts its blocks), then the
   // others of more than one tile, so that the small ones fill the gaps
-  uint32_t blocks = 0, tiles = 0, nbig = 0;
+  uint32_t blocks = 0, tiles = 0, nbig = 0, shared = 0;
   c->owner.clear();
   for (int kind = 0; kind < 3; ++kind) {
     for (size_t t = 0; t < count; ++t) {
@@ -957,6 +957,7 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
         ++nbig;
       }
       tiles += (uint32_t)k;
+      if (kind < 2) shared = tiles;
       c->owner.insert(c->owner.end(), k, (uint16_t)d.size());
       d.push_back(e);
       which.push_back(t);
@@ -999,13 +1000,13 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
                   &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_BATCH, [&] {
-    return launch_quant_encode_batch(descs, cnt, owner, tiles, in_place, c->partials_chk,
+    return launch_quant_encode_batch(descs, shared, owner, tiles, in_place, c->partials_chk,
                                      c->enc_results, c->enc_status,
                                      c->enc_status + c->enc_status_words, c->enc_ticket_base,
                                      epoch, c->ctrl, batch_mirror(c), c->stream);
   });
   if (st) return st;
-  if (tiles != cnt) c->enc_ticket_base += tiles;
+  c->enc_ticket_base += shared;
   st = wait_results(c, c->host_results, cnt);
   if (st) return st;
   if (c->rb->fault) {

@@ -204,9 +204,9 @@ hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out
 // tiles): the check pass or, in place, step 1 into the buffers.
 hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t total_blocks,
                                bool in_place, uint32_t* partials, hipStream_t st);
-// owner: the tensor of each of the `tiles` tiles (not read when every tensor
-// has one).  partials: the max pass's.
-hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t count, const uint16_t* owner,
+// owner: the tensor of each of the `tiles` tiles; the first `shared` are those
+// of tensors of more than one.  partials: the max pass's.
+hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t shared, const uint16_t* owner,
                                      uint32_t tiles, bool in_place, const uint32_t* partials,
                                      EncResult* results, uint64_t* status, uint64_t* maxima,
                                      uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
