@@ -258,9 +258,9 @@ int tlc_compress_noalloc(const float* tensor, float* residual, size_t n, float s
 
 /* TLC_OPT_IN_PLACE_FEEDBACK: take step 1 of error accumulation (Section
  * 3.1, Fig. 3: the tensor is added into the buffer) as done in the
- * residual itself before Eq. 1 is known.  The encoders then read tensor and
- * residual once instead of twice (12 instead of 20 bytes per value for the
- * 3-value modes); every result is the same, except that after
+ * residual itself before Eq. 1 is known.  The encoders of large tensors then
+ * read tensor and residual once instead of twice (12 instead of 20 bytes per
+ * value for the 3-value modes); every result is the same, except that after
  * TLC_E_NONFINITE the residual holds tensor + residual instead of being
  * left unchanged.  For callers that check their tensors for NaN/Inf
  * themselves, or reset the residual after such an error. */
@@ -298,8 +298,9 @@ const char* tlc_last_error_string(void);
 
 /* ---- per-kernel timing (HIP events on the context's stream) ----------- */
 
-#define TLC_KERNEL_ABSMAX 0         /* step 1 into the residual, partial max (Eq. 1) */
-#define TLC_KERNEL_QUANT_ENCODE 1   /* Eq. 1-2, residual, quartic pack, each tile's own
+#define TLC_KERNEL_ABSMAX 0         /* in place: step 1 into the residual, partial max (Eq. 1);
+                                       without a residual: partial max */
+#define TLC_KERNEL_QUANT_ENCODE 1   /* large tensors: quartic pack from trits, each tile's own
                                        zero-run encoding */
 #define TLC_KERNEL_ZRE_INDEX 2      /* zero-run scan: where each output range starts
                                        (a small stream's scan runs in the next kernel) */
@@ -310,16 +311,16 @@ const char* tlc_last_error_string(void);
 #define TLC_KERNEL_ZRE_INDEX_BATCH 6
 #define TLC_KERNEL_EXPAND_DEQUANT_BATCH 7
 #define TLC_KERNEL_EXPAND_SUM 8     /* multi-stream expansion + summed dequantization */
-#define TLC_KERNEL_QUANT_PACK 9     /* comparison modes: quantize + quartic pack */
+#define TLC_KERNEL_QUANT_PACK 9     /* comparison modes: (stochastic trits and) quartic pack */
 #define TLC_KERNEL_INT8_QUANT 10    /* 8-bit comparator: codes and residual */
 #define TLC_KERNEL_INT8_DEQUANT 11  /* 8-bit comparator: decode */
 #define TLC_KERNEL_ZRE_CHUNKS 12    /* zero-run encoding: summaries of tile chunks */
 #define TLC_KERNEL_ZRE_COMPACT 13   /* zero-run encoding: tiles compacted into the stream */
-#define TLC_KERNEL_QUANT_ENCODE_CHAINED 14 /* a small tensor's encode in one chained pass */
+#define TLC_KERNEL_QUANT_ENCODE_CHAINED 14 /* a small tensor's whole encode */
 #define TLC_KERNEL_ABSMAX_CHECK 15  /* partial max of |tensor + residual|, nothing written */
 #define TLC_KERNEL_ABSMAX_CHECK_BATCH 16
-#define TLC_KERNEL_ACCUM_QUANTIZE 17 /* after the check pass: step 1, Eq. 2 and the residual
-                                        for every value, 2-bit trits (large tensors) */
+#define TLC_KERNEL_ACCUM_QUANTIZE 17 /* large tensors: Eq. 2, the residuals and 2-bit trits
+                                        (after the check pass, with step 1) */
 #define TLC_KERNEL_COUNT 18
 
 /* Enable (on != 0) or disable recording of a start/stop event pair around

@@ -1,32 +1,29 @@
 // encode.hip -- gfx950 encode kernels of the 3LC path.
 //
+//   tlc_quant_encode_chained_kernel, tlc_quant_encode_batch_kernel
+//       a small tensor, or many tensors, in one launch: tiles hold their sums
+//       in registers until M is known, and exchange maxima and summaries
+//                                                   (Sections 3.1-3.3)
 //   tlc_absmax_check_kernel / _batch_kernel
 //       partial maxima of |tensor + buffer|, nothing written: lets the
 //       default error policy refuse NaN/Inf before the buffer changes
-//   tlc_accum_absmax_kernel / _batch_kernel
-//       step 1 of error accumulation (the tensor is added into the buffer,
-//       in place) and partial maxima of the sums               (Section 3.1,
-//                                                               Fig. 3, Eq. 1)
 //   tlc_accum_quantize_kernel
-//       after the check pass, on large aligned tensors: acc = x + r,
-//       3-value quantization, the residual stored in place and 2-bit
-//       trits for the quartic pack                  (Section 3.1, Eq. 1-2)
-//   tlc_quant_encode_kernel, tlc_zre_chunk(_scan)_kernel, tlc_zre_compact_kernel
-//       one tensor: M, 3-value quantization of the buffer, residual
-//       write-back where q != 0 (or the quartic pack from the writing
-//       pass's trits), each tile's own zero-run encoding; then a scan of the
-//       tile summaries and the compaction into one stream
-//                                              (Eq. 1-2, Sections 3.2-3.3)
-//   tlc_quant_encode_chained_kernel, tlc_quant_encode_batch_kernel
-//       a small tensor, or many tensors, in one pass: tiles chained by
-//       decoupled look-back
+//       after the check pass, on large tensors: acc = x + r, 3-value
+//       quantization, the residual stored in place and 2-bit trits for the
+//       quartic pack                                (Section 3.1, Eq. 1-2)
+//   tlc_accum_absmax_kernel / _batch_kernel, tlc_quantize_lines_kernel
+//       the same in place: the tensor is added into the buffer with partial
+//       maxima of the sums (Fig. 3, Eq. 1), then the lines that can hold a
+//       q != 0 are quantized
+//   tlc_quant_encode_kernel, tlc_zre_chunk_kernel, tlc_zre_compact_kernel
+//       the quartic pack from the trits and each tile's own zero-run encoding;
+//       then a scan of the tile summaries and the compaction into one stream
+//                                                   (Sections 3.2-3.3)
 //
-// The batch kernels run many tensors in one launch: every block maps its
-// index (absmax) or its ticket (encoder) to a tensor through the sorted
-// first-block / first-tile fields of the tensor descriptors, then runs the
-// same max reduction and tile quantization as the single-tensor kernels.
-// Everything is HBM streaming; nothing is a dense contraction, so there is
-// no MFMA.
+// The batch kernels run many tensors in one launch: every block reads the
+// descriptor of its tensor, then runs the single-tensor device code.
+// Everything is HBM streaming or bound by latency; nothing is a dense
+// contraction, so there is no MFMA.
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -43,9 +40,8 @@ __device__ __forceinline__ uint32_t line_max(uint32_t v) {
 
 // ---------------------------------------------------------------- Eq. 1
 // Step 1 and Eq. 1 in one read of the tensor: with kResid the buffer
-// becomes acc = x + r (the quantizer then reads only the buffer and writes
-// back just the values with q != 0, whose residual differs from acc);
-// without, acc = x and nothing is written.  max |acc| is taken on the bit
+// becomes acc = x + r (the quantizer then rewrites only what can hold a
+// q != 0); without, acc = x and nothing is written.  max |acc| is taken on the bit
 // patterns with the sign cleared: for non-negative IEEE values integer
 // order equals numeric order, so the u32 max is exact and independent of
 // reduction order, and any NaN/Inf makes the result >= 0x7f800000.  Block
@@ -63,7 +59,10 @@ __device__ __forceinline__ uint32_t line_max(uint32_t v) {
 // (|acc| < (h + 1) * 2^16 as bit patterns), so the pass that follows can skip
 // every line whose h lies below the top half of its threshold U: all its
 // values have q = 0 and keep acc.
-template <bool kResid = true, bool kStore = kResid, bool kBound = false>
+//
+// kKeep: plain loads, which leave what they read in the last-level cache for
+// the writing pass (where both tensors fit it).
+template <bool kResid = true, bool kStore = kResid, bool kBound = false, bool kKeep = false>
 __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
                                                 float* __restrict__ r, uint64_t n,
                                                 uint32_t blk, uint32_t nblk,
@@ -74,14 +73,15 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
   const uint64_t tid = (uint64_t)blk * kThreads + threadIdx.x;
   const uint64_t stride = (uint64_t)nblk * kThreads;
   const uint64_t nv = n >> 2;
+  auto ld = [](const float* p) { return kKeep ? ld4(p) : ld_stream(p); };
   uint64_t i = tid;
   for (; i + 3 * stride < nv; i += 4 * stride) {
     float4 a[4], b[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) a[u] = ld_stream(x + 4 * (i + u * stride));
+    for (int u = 0; u < 4; ++u) a[u] = ld(x + 4 * (i + u * stride));
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      b[u] = kResid ? ld_stream(r + 4 * (i + u * stride)) : make_float4(0, 0, 0, 0);
+      b[u] = kResid ? ld(r + 4 * (i + u * stride)) : make_float4(0, 0, 0, 0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float4 v = kResid ? make_float4(a[u].x + b[u].x, a[u].y + b[u].y,
@@ -100,9 +100,9 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
   for (; i - (threadIdx.x & 63u) < nv; i += stride) {  // whole waves (line_max)
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < nv) {
-      v = ld_stream(x + 4 * i);
+      v = ld(x + 4 * i);
       if (kResid) {
-        const float4 b = ld_stream(r + 4 * i);
+        const float4 b = ld(r + 4 * i);
         v = make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);
         if (kStore) st_stream(r + 4 * i, v);
       }
@@ -169,12 +169,14 @@ __device__ __forceinline__ void accum_quantize_part(const float* __restrict__ x,
 
 // Partial maxima of |x + r| that write nothing: the check pass that lets
 // the default error policy refuse NaN/Inf before the buffer is touched.
+template <bool kKeep>
 __global__ __launch_bounds__(kThreads) void tlc_absmax_check_kernel(
     const float* __restrict__ x, const float* __restrict__ r, uint64_t n,
     uint32_t* __restrict__ partials) {
   __shared__ uint32_t lds[kWaves];
   const uint32_t mx = block_max(
-      absmax_part<true, false>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x), lds);
+      absmax_part<true, false, false, kKeep>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x),
+      lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
@@ -1254,10 +1256,21 @@ uint32_t absmax_blocks(uint64_t n) {
 }
 }  // namespace
 
+// Tensors whose values and buffer fit the 256 MB last-level cache are read with
+// plain loads by the check pass: the writing pass then finds them there (check
+// + writing pass, three tensors in turn, nontemporal against plain loads: 12M
+// values 16.8 + 27.8 against 18.4 + 22.9 us, 25.6M 32.8 + 53.8 against 35.6 +
+// 46.1, 33M 40.5 + 69.0 against 47.3 + 59.9; 45M, which do not fit, 54.4 + 91.9
+// against 62.6 + 83.1, and 2^28 lose 40 us).
+constexpr uint64_t kCacheBytes = 256ull << 20;
+
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st) {
   *nblocks = absmax_blocks(n);
-  launch_k(tlc_absmax_check_kernel, *nblocks, kThreads, st, x, r, n, partials);
+  if (n * 2 * sizeof(float) <= kCacheBytes)
+    launch_k(tlc_absmax_check_kernel<true>, *nblocks, kThreads, st, x, r, n, partials);
+  else
+    launch_k(tlc_absmax_check_kernel<false>, *nblocks, kThreads, st, x, r, n, partials);
   return hipGetLastError();
 }
 

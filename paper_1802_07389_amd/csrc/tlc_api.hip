@@ -1055,6 +1055,28 @@ int check_stream(const char* fn, size_t t, const uint8_t* bytes, size_t len, flo
 
 }  // namespace
 
+namespace {
+
+// Numbers the streams' scan tiles; returns how many there are.
+uint32_t place_scan_tiles(std::vector<DecDesc>& d, bool wide) {
+  const size_t tile = wide ? kZreTile : kZreBatchTile;
+  size_t tiles = 0;
+  for (DecDesc& e : d) {
+    e.tile0 = (uint32_t)tiles;
+    tiles += ceil_div((size_t)e.c, tile);
+  }
+  return (uint32_t)tiles;
+}
+
+// Appends the stream of each scan tile to the call's owners.
+void add_scan_owners(tlc_ctx* c, const std::vector<DecDesc>& d, uint32_t tiles) {
+  for (size_t i = 0; i < d.size(); ++i)
+    c->owner.insert(c->owner.end(), (i + 1 < d.size() ? d[i + 1].tile0 : tiles) - d[i].tile0,
+                    (uint16_t)i);
+}
+
+}  // namespace
+
 TLC_API int tlc_decompress(tlc_ctx* c, const uint8_t* bytes, size_t bytes_len, float scale,
                            size_t n, float* out, int accumulate) {
   int st = check_usable(c, "tlc_decompress");
@@ -1134,7 +1156,8 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   size_t total_n = 0;
   std::vector<DecDesc>& d = c->dec_host;
   d.clear();
-  uint32_t tiles = 0, ranges = 0;
+  uint32_t ranges = 0;
+  uint64_t stream_bytes = 0;
   for (size_t t = 0; t < count; ++t) {
     if (ns[t] > c->max_n)
       return fail(TLC_E_INVALID, "tlc_decompress_batch: stream %zu: n = %zu too large", t,
@@ -1152,9 +1175,8 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
     e.c = (uint32_t)bytes_len[t];
     e.m = (uint32_t)quartic_len(ns[t]);
     e.scale = scales[t];
-    e.tile0 = tiles;
     e.range0 = ranges;
-    tiles += (uint32_t)ceil_div(e.c, kZreBatchTile);
+    stream_bytes += e.c;
     ranges += (uint32_t)ceil_div(e.m, kDecRange);
     d.push_back(e);
   }
@@ -1170,6 +1192,8 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   if (spans_conflict_cached(c->spans, c->dec_spans_ok))
     return fail(TLC_E_INVALID, "tlc_decompress_batch: an output overlaps another stream's "
                                "output or bytes");
+  const bool wide = batch_scan_wide(stream_bytes, d.size());
+  const uint32_t tiles = place_scan_tiles(d, wide);
   if (tiles > c->dec_status_words || ranges > c->start_words)
     return fail(TLC_E_INVALID, "tlc_decompress_batch: batch exceeds the context's workspace");
   DeviceScope dev(c->device);
@@ -1180,9 +1204,7 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   c->owner.clear();
   for (uint32_t i = 0; i < cnt; ++i)
     c->owner.insert(c->owner.end(), ceil_div(d[i].m, (size_t)kDecRange), (uint16_t)i);
-  if (tiles != cnt)
-    for (uint32_t i = 0; i < cnt; ++i)
-      c->owner.insert(c->owner.end(), ceil_div(d[i].c, (size_t)kZreBatchTile), (uint16_t)i);
+  if (tiles != cnt) add_scan_owners(c, d, tiles);
   const DecDesc* descs = nullptr;
   const uint16_t* owner = nullptr;
   int slot = 0;
@@ -1193,8 +1215,8 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_INDEX_BATCH, [&] {
-    return launch_zre_index_batch(descs, cnt, owner + ranges, tiles, c->start, c->dec_status,
-                                  c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
+    return launch_zre_index_batch(descs, cnt, owner + ranges, tiles, wide, c->start,
+                                  c->dec_status, c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
                                   c->stream);
   });
   if (st) return st;
@@ -1226,7 +1248,7 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   const uint32_t nranges = (uint32_t)ceil_div(m, kDecRange);
   std::vector<DecDesc>& d = c->dec_host;
   d.clear();
-  uint32_t tiles = 0;
+  uint64_t stream_bytes = 0;
   for (size_t t = 0; t < count; ++t) {
     bool skip = false;
     st = check_stream("tlc_decompress_sum", t, bytes[t], bytes_len[t], scales[t], n, out, &skip);
@@ -1239,12 +1261,13 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
     e.c = (uint32_t)bytes_len[t];
     e.m = (uint32_t)m;
     e.scale = scales[t];
-    e.tile0 = tiles;
     e.range0 = (uint32_t)t * nranges;
-    tiles += (uint32_t)ceil_div(e.c, kZreBatchTile);
+    stream_bytes += e.c;
     d.push_back(e);
   }
   if (d.empty()) return TLC_OK;
+  const bool wide = batch_scan_wide(stream_bytes, d.size());
+  const uint32_t tiles = place_scan_tiles(d, wide);
   if (tiles > c->dec_status_words || (size_t)count * nranges > c->start_words)
     return fail(TLC_E_INVALID, "tlc_decompress_sum: streams exceed the context's workspace");
   DeviceScope dev(c->device);
@@ -1252,9 +1275,7 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
   c->owner.clear();
-  if (tiles != cnt)
-    for (uint32_t i = 0; i < cnt; ++i)
-      c->owner.insert(c->owner.end(), ceil_div(d[i].c, (size_t)kZreBatchTile), (uint16_t)i);
+  if (tiles != cnt) add_scan_owners(c, d, tiles);
   // to device memory: every block of the sum reads the descriptors
   st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
               c->owner.size() * sizeof(uint16_t));
@@ -1264,8 +1285,8 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_INDEX_BATCH, [&] {
-    return launch_zre_index_batch(c->dec_descs, cnt, owner, tiles, c->start, c->dec_status,
-                                  c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
+    return launch_zre_index_batch(c->dec_descs, cnt, owner, tiles, wide, c->start,
+                                  c->dec_status, c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
                                   c->stream);
   });
   if (st) return st;
