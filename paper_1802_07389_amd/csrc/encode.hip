@@ -31,7 +31,7 @@
 namespace tlc {
 
 // Max over the eight lanes of a line (quad_perm 1,0,3,2 and 2,3,0,1, then
-// row_half_mirror), in each of them; every lane of the wave active.
+// row_half_mirror), in each of them; all eight lanes active.
 __device__ __forceinline__ uint32_t line_max(uint32_t v) {
   v = umax32(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true));
   v = umax32(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true));
@@ -75,7 +75,10 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
   const uint64_t nv = n >> 2;
   auto ld = [](const float* p) { return kKeep ? ld4(p) : ld_stream(p); };
   uint64_t i = tid;
-  for (; i + 3 * stride < nv; i += 4 * stride) {
+  // with bounds a line's eight lanes leave the loop together: line_max needs
+  // all of them, also where nv % 8 cuts the last line off
+  auto four = [&](uint64_t j) { return (kBound ? j | 7u : j) + 3 * stride < nv; };
+  for (; four(i); i += 4 * stride) {
     float4 a[4], b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) a[u] = ld(x + 4 * (i + u * stride));

@@ -55,6 +55,32 @@ def test_flat_passes(ctx, options, kind, extra, offset, r_offset):
     assert np.array_equal(g.bits(r_gpu), g.bits(r_ref))
 
 
+@pytest.mark.parametrize("n", [4 * 1021 + 2, 4 * 524285 + 1])
+@pytest.mark.parametrize("lane", range(8))
+def test_in_place_line_bounds(ctx, n, lane):
+    """One float4 of each 128-byte line reaches half the scale: the line's bound
+    has to hold it also where n cuts the unrolled loop of the max pass inside a
+    line (n / 4 three short of a multiple of its step, 4 * 256 float4s a block)."""
+    import gpuutil as g
+    from paper_1802_07389_amd import tlc
+    x = workloads.normal([85, n], n, 1e-5)
+    x[4 * lane + 1::32] = F32(0.02)
+    r = workloads.normal([86, n], n, 1e-5)
+    for mode in (tlc.TLC_MODE_3LC, tlc.TLC_MODE_NO_ZRE):
+        r_ref = r.copy()
+        encode = oracle.compress if mode == tlc.TLC_MODE_3LC else oracle.compress_nozre
+        st, C_ref, M_ref = encode(x, r_ref, 1.5)
+        xd, rd = g.to_dev(x), g.to_dev(r)
+        ctx.set_options(1)
+        try:
+            data, M = ctx.compress_mode(mode, xd, rd, 1.5)
+        finally:
+            ctx.set_options(0)
+        assert st == 0 and F32(M).tobytes() == F32(M_ref).tobytes()
+        assert np.array_equal(data.cpu().numpy(), C_ref)
+        assert np.array_equal(g.bits(rd.cpu().numpy()), g.bits(r_ref))
+
+
 @pytest.mark.parametrize("options", [0, 1], ids=["default", "in_place"])
 @pytest.mark.parametrize("where", [0, -1])
 def test_refused_tensor_off_the_grid(ctx, options, where):
