@@ -1025,7 +1025,13 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
       scales[t] = r.scale;
     }
   }
-  if (worst) fail(worst, "tlc_compress_batch: NaN/Inf or overflow in at least one tensor");
+  if (worst) {
+    // a refused tensor with a max pass is reported by its last tile, which
+    // waits for no other: blocks yet to start still read the pinned slot
+    st = sync_mirrored(c);
+    if (st) return st;
+    fail(worst, "tlc_compress_batch: NaN/Inf or overflow in at least one tensor");
+  }
   return worst;
 }
 

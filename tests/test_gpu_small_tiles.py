@@ -83,3 +83,35 @@ def test_batch_of_all_kinds(ctx, options):
         for t in range(len(sizes)):
             check(g, xb[t], rs[t], 1.75, (stat[t], bufs[t][:lens[t]].cpu().numpy(), scales[t],
                                           rd[t].cpu().numpy()), bool(options))
+
+
+def test_decodes_right_after_a_refused_batch(ctx):
+    """A refused tensor with a max pass: the descriptor slots that the decodes
+    after it take over are no longer read by its blocks."""
+    import torch
+
+    import gpuutil as g
+    from paper_1802_07389_amd import tlc
+    n = EDGE + 50_001
+    big, r = workloads.normal([96, n], n), np.zeros(n, F32)
+    big[0] = np.inf
+    x, small = workloads.normal([97, 0], 3000), np.zeros(3000, F32)
+    r_ref = small.copy()
+    _, C, M = oracle.compress(x, r_ref, 1.5)
+    _, want = oracle.decompress(C, M, 3000, np.zeros(3000, F32))
+    bd, rd, xd = g.to_dev(big), g.to_dev(r), g.to_dev(x)
+    data = torch.from_numpy(C).cuda()
+    outs = [[torch.zeros(3000, device="cuda") for _ in range(3)] for _ in range(6)]
+    for _ in range(3):
+        sd = g.to_dev(small)
+        with pytest.raises(tlc.TLCError):
+            ctx.compress_batch([bd, xd], [rd, sd], 1.5)
+        for o in outs:
+            ctx.decompress_batch([data] * 3, [M] * 3, o)
+        ctx.sync()
+        assert np.array_equal(g.bits(sd.cpu().numpy()), g.bits(r_ref))
+        assert not rd.any()
+        for o in outs:
+            for t in o:
+                assert np.array_equal(g.bits(t.cpu().numpy()), g.bits(want))
+                t.zero_()
