@@ -753,10 +753,10 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
 // M: a tensor of one tile is all in its block.  Of a tensor of at most
 // kExchangeTiles tiles, every tile publishes its largest |acc| in a word of
 // its own and reads the others' (nothing is written before all have come), so
-// that no check pass runs before.  Tiles take tickets in order and a tensor's
-// are consecutive, so a tile only waits for tiles that run already or are next
-// to start, at most kExchangeTiles - 1 of them.  A longer tensor's M comes
-// from a check pass (partials).
+// that no check pass runs before.  Those that follow it may not have started:
+// a tile that has waited a while reads their values itself (help_maxima), so
+// that any number of resident blocks will do.  A longer tensor's M comes from
+// a check pass (partials).
 //
 // The zero-run encoding is the first pass's (from the gaps between non-121
 // bytes, from the tile's first one on).  Its place in the stream and the
@@ -772,6 +772,7 @@ struct TileShared {
   uint32_t red2[kT / 64];
   uint32_t lead;   // the tile's first non-121 byte
   uint32_t fault;
+  uint32_t help;   // some tile's maximum has not come
   // what the first waves read of the other tiles: maxima, then summaries
   uint64_t wave[kExchangeTiles / 64];
   LookShared<kT / 64> look;
@@ -793,19 +794,72 @@ struct TileJob {
   EncResult* hres;
 };
 
-// Waits until every one of the `count` (<= 64 * waves) words p[lane index] has
-// ready(word); each lane gets its own word, lanes past count get 0.  False
-// when the wait runs past kSpinLimit.
+// Waits until every lane's word *p (of the lanes with `mine`) has ready(word);
+// each lane gets its own word, the others 0.  False when the wait runs past
+// `limit` polls.
 template <class Ready>
 __device__ __forceinline__ bool wait_words(const uint64_t* p, bool mine, Ready ready,
-                                           uint64_t* w) {
+                                           uint32_t limit, uint64_t* w) {
   *w = 0u;
   for (uint32_t spins = 0;; ++spins) {
     if (mine) *w = status_read(p);
     if (__ballot(mine && !ready(*w)) == 0u) return true;
-    if (spins > kSpinLimit) return false;
+    if (spins >= limit) return false;
     __builtin_amdgcn_s_sleep(1);
   }
+}
+
+// The polls (about a microsecond each) before a tile stops waiting for the
+// others' maxima.  The stress build helps at the first poll that misses one.
+#ifdef TLC_DELAY_INJECT
+constexpr uint32_t kHelpPolls = 0u;
+#else
+constexpr uint32_t kHelpPolls = 1u << 12;
+#endif
+
+// The largest |acc| of a whole tensor by one block, for a tile whose wait for
+// the others' maxima has run out: those it waits for may not have started, and
+// where few blocks are resident (a stream with few CUs, other launches that
+// wait) they cannot start before it ends.  A maximum that is still missing is
+// taken from the tile's values and published for everybody.  That tile writes
+// its buffer only after it has published: where its word is still missing
+// after the values have been read, they were the ones before the call; where
+// it has come in between, it counts and what was read does not.
+template <int kT>
+__device__ __forceinline__ uint32_t help_maxima(const TileJob& J, uint32_t tile_values,
+                                                uint32_t tiles, uint64_t* __restrict__ maxima,
+                                                uint32_t epoch, uint32_t* red, uint64_t* word) {
+  uint32_t mx = 0u;
+#pragma unroll 1
+  for (uint32_t t = 0; t < tiles; ++t) {
+    __syncthreads();  // *word and red are free
+    if (threadIdx.x == 0) *word = status_read(&maxima[t]);
+    __syncthreads();
+    if ((uint32_t)(*word >> 32) != epoch) {
+      const uint64_t q0 = (uint64_t)t * tile_values;
+      const uint32_t len = (uint32_t)umin64(tile_values, J.m - q0);
+      uint32_t v = 0u;
+#pragma unroll 1
+      for (int k = 0; k < 5; ++k) {
+        const uint64_t base = (uint64_t)k * J.m + q0;
+        const uint32_t lim = J.n > base ? (uint32_t)umin64(J.n - base, len) : 0u;
+        for (uint32_t i = threadIdx.x; i < lim; i += kT)
+          v = max(v, abs_bits(J.x[base + i] + J.r[base + i]));
+      }
+      v = block_max<kT / 64>(v, red);  // every thread's values are read
+      if (threadIdx.x == 0) {
+        uint64_t w = status_read(&maxima[t]);
+        if ((uint32_t)(w >> 32) != epoch) {
+          w = ((uint64_t)epoch << 32) | v;
+          status_publish(&maxima[t], w);
+        }
+        *word = w;
+      }
+      __syncthreads();
+    }
+    mx = max(mx, (uint32_t)*word);
+  }
+  return mx;
 }
 
 template <int kT, int kG>
@@ -833,7 +887,7 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
     __hip_atomic_store(&ctrl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     host_put(hfault, 1u);
   };
-  if (threadIdx.x == 0) sh.fault = 0u;  // read after several barriers
+  if (threadIdx.x == 0) sh.fault = sh.help = 0u;  // read after a barrier
 
   // ---- step 1: acc = x + r, the thread's 20 * kG values; 0 past the end.
   // Of partition k the tile holds the first lim[k] of the block's bytes'
@@ -917,20 +971,21 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
         uint64_t w;
         const bool ok = wait_words(
             &maxima[J.floor + threadIdx.x], threadIdx.x < tiles,
-            [&](uint64_t v) { return (uint32_t)(v >> 32) == epoch; }, &w);
+            [&](uint64_t v) { return (uint32_t)(v >> 32) == epoch; }, kHelpPolls, &w);
         const uint32_t wm = wave_max((uint32_t)w);
         if (lane == 0) {
           sh.wave[wid] = wm;
-          if (!ok) {
-            sh.fault = 1u;
-            fault_out();
-          }
+          if (!ok) sh.help = 1u;
         }
       }
       __syncthreads();
-      if (sh.fault) return;  // nothing is written yet
+      if (sh.help) {
+        mx = help_maxima<kT>(J, kTile, tiles, maxima + J.floor, epoch, sh.red, &sh.wave[0]);
+        __syncthreads();  // sh.wave is written again below
+      } else {
 #pragma unroll
-      for (uint32_t i = 0; i < kReaders; ++i) mx = max(mx, (uint32_t)sh.wave[i]);
+        for (uint32_t i = 0; i < kReaders; ++i) mx = max(mx, (uint32_t)sh.wave[i]);
+      }
     }
     sc = scale_of(mx, J.s);
   } else {
@@ -1051,7 +1106,8 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
         const bool mine = threadIdx.x < lt;
         const bool ok = wait_words(
             &status[J.floor + threadIdx.x], mine,
-            [&](uint64_t v) { return EncSW::epoch(v) == epoch && EncSW::flag(v) != 0u; }, &w);
+            [&](uint64_t v) { return EncSW::epoch(v) == epoch && EncSW::flag(v) != 0u; },
+            kSpinLimit, &w);
         RunSum a = rs_identity();
         if (mine) a = rs_from_payload(EncSW::payload(w));
         a = wave_incl_scan_rs(a);
@@ -1122,7 +1178,7 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_chained_kernel(
   __shared__ TileShared<kT, kTileGroups> sh;
   __shared__ uint32_t s_tile;
   uint32_t tile = 0u;
-  if (gridDim.x > 1u) {
+  if (m > kT * kTileGroups * 4u) {  // more than one tile
     if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->enc_ticket) - ticket_base;
     __syncthreads();
     tile = uniform32(s_tile);
@@ -1267,6 +1323,14 @@ uint32_t absmax_blocks(uint64_t n) {
 // against 62.6 + 83.1, and 2^28 lose 40 us).
 constexpr uint64_t kCacheBytes = 256ull << 20;
 
+#ifdef TLC_DELAY_INJECT
+// Stress build only: blocks per launch of a small tensor's encode (0: all).
+static uint32_t g_stress_blocks = 0u;
+extern "C" __attribute__((visibility("default"))) void tlc_stress_blocks(uint32_t blocks) {
+  g_stress_blocks = blocks;
+}
+#endif
+
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st) {
   *nblocks = absmax_blocks(n);
@@ -1323,13 +1387,23 @@ hipError_t launch_quant_encode_chained(const float* x, float* r, uint64_t n, uin
                                        uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
                                        HostMirror hm, hipStream_t st) {
   const uint32_t tiles = small_tiles(m);
-  if (tiles > kExchangeTiles)
-    launch_k(tlc_quant_encode_chained_kernel<2 * kTileThreads>, (tiles + 1u) / 2u,
-             2 * kTileThreads, st, x, r, n, m, s, in_place, partials, np, out, status, maxima,
-             ticket_base, epoch, ctrl, hm);
-  else
-    launch_k(tlc_quant_encode_chained_kernel<kTileThreads>, tiles, kTileThreads, st, x, r, n, m, s,
-             in_place, partials, np, out, status, maxima, ticket_base, epoch, ctrl, hm);
+  const bool chained = tiles > kExchangeTiles;
+  const uint32_t blocks = chained ? (tiles + 1u) / 2u : tiles;
+  // one launch; the stress build can launch fewer blocks at a time, each
+  // launch ending before the next one starts, as if no more were resident
+  uint32_t each = blocks;
+#ifdef TLC_DELAY_INJECT
+  if (g_stress_blocks) each = std::min(blocks, g_stress_blocks);
+#endif
+  for (uint32_t b = 0; b < blocks; b += each) {
+    const uint32_t grid = std::min(each, blocks - b);
+    if (chained)
+      launch_k(tlc_quant_encode_chained_kernel<2 * kTileThreads>, grid, 2 * kTileThreads, st, x, r,
+               n, m, s, in_place, partials, np, out, status, maxima, ticket_base, epoch, ctrl, hm);
+    else
+      launch_k(tlc_quant_encode_chained_kernel<kTileThreads>, grid, kTileThreads, st, x, r, n, m, s,
+               in_place, partials, np, out, status, maxima, ticket_base, epoch, ctrl, hm);
+  }
   return hipGetLastError();
 }
 

@@ -11,10 +11,10 @@
 //
 // The L2 caches of the eight XCDs are not coherent with each other, so
 // status words are only touched with agent-scope atomics.  Tiles are taken
-// in order from an atomic ticket, so a look-back only ever waits for tiles
-// that already run (the small-tensor encoder also reads the words of the
-// tiles that follow, at most kExchangeTiles - 1, which fit the chip at once),
-// and every wait is bounded (kSpinLimit) so each wave exits.
+// in order from an atomic ticket, so a tile only ever waits for tiles that
+// already run (the small-tensor encoder also reads the words of tiles that
+// follow; it does their part itself when they do not come), and every wait is
+// bounded (kSpinLimit) so each wave exits.
 #pragma once
 
 #include <hip/hip_runtime.h>

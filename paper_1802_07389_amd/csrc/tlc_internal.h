@@ -25,9 +25,7 @@ constexpr int kDecRange = 4096;           // quartic bytes per expand/dequantize
 // Encoder tiles of small tensors and batches: 256 threads of eight quartic
 // bytes.  The tiles of a tensor of at most kExchangeTiles (1,310,720 values)
 // exchange their maxima and summaries among themselves; a longer one has a
-// check pass and a look-back.  (The waiting blocks of one launch number at
-// most kExchangeTiles - 1, so launches on other streams find room beside them:
-// the card holds more than a thousand such blocks.)
+// check pass and a look-back.
 constexpr int kTileThreads = kThreads;
 constexpr int kTileGroups = 2;
 constexpr uint32_t kSmallTile = kTileThreads * kTileGroups * 4;  // 2048 quartic bytes

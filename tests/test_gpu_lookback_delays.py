@@ -68,6 +68,44 @@ def encode_check(ctx, x, r, s, tag):
     return C_ref, M_ref
 
 
+@pytest.fixture
+def few_blocks(dt):
+    """Sets how many blocks of a small tensor's encode are launched at a time
+    (each launch ends before the next one starts), as if no more fitted."""
+    yield dt.lib.tlc_stress_blocks
+    dt.lib.tlc_stress_blocks(0)
+
+
+@pytest.mark.parametrize("options", [0, 1], ids=["default", "in_place"])
+@pytest.mark.parametrize("blocks", [0, 1, 2, 50])
+def test_exchanging_tiles(dt, ctx, few_blocks, blocks, options):
+    """Tensors of 2 to 128 tiles, whose tiles exchange maxima and summaries:
+    with all blocks in one launch, and with so few at a time that the tiles a
+    block waits for have not started (it then reads their values itself)."""
+    import torch
+    ctx.set_options(options)
+    few_blocks(blocks)
+    try:
+        for k, n in enumerate([5 * 2048 * 128, 5 * 2048 * 128 - 3, 700_001, 5 * 2048 + 1]):
+            # the largest value in the first tile, the last one and between
+            x = workloads.normal([95, k], n, 1e-3)
+            x[(n - 1) * k // 3] = F32(0.25)
+            encode_check(ctx, x, workloads.normal([96, k], n, 1e-4), 1.25 + k / 8,
+                         f"{n} values, {blocks} blocks at a time")
+        x[n // 2] = np.nan  # refused by every tile
+        r = workloads.normal([96, 9], n, 1e-4)
+        rd = torch.from_numpy(r.copy()).cuda()
+        with pytest.raises(dt.TLCError) as e:
+            ctx.compress(torch.from_numpy(x).cuda(), rd, 1.5)
+        assert e.value.code == dt.TLC_E_NONFINITE
+        left = rd.cpu().numpy()
+        want = r if not options else x + r
+        ok = np.isfinite(want)
+        assert np.array_equal(bits(left)[ok], bits(want)[ok])
+    finally:
+        ctx.set_options(0)
+
+
 def test_chained_and_three_pass_encoders(dt, ctx):
     # 400 tiles on the chained path (tile tickets + decoupled look-back)
     n = 400 * 4096 * 5 - 3
