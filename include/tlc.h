@@ -173,9 +173,9 @@ int tlc_compress_ex(tlc_ctx* ctx, int mode, const float* tensor, float* residual
 int tlc_decompress_ex(tlc_ctx* ctx, int mode, const uint8_t* bytes, size_t bytes_len,
                       float scale, size_t n, float* out, int accumulate);
 
-/* Encode `count` tensors in one pass (one launch, or two where a tensor has
- * more than 1,310,720 values; one synchronisation):
- * for every t, exactly tlc_compress(ctx, tensors[t], residuals[t], ns[t],
+/* Encode `count` tensors (in one launch; those of more than 1,310,720 values
+ * in four launches of their own, together, or five each above 41,943,040; one
+ * synchronisation): for every t, exactly tlc_compress(ctx, tensors[t], residuals[t], ns[t],
  * s[t], bytes[t], caps[t], &bytes_len[t], &scales[t]).  All arrays are host
  * arrays of `count` entries; the pointers in them are device pointers, and
  * buffers of different tensors must not overlap.  Argument errors reject the

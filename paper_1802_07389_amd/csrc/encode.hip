@@ -20,8 +20,9 @@
 //       then a scan of the tile summaries and the compaction into one stream
 //                                                   (Sections 3.2-3.3)
 //
-// The batch kernels run many tensors in one launch: every block reads the
-// descriptor of its tensor, then runs the single-tensor device code.
+// The batch kernels (and the _many_ ones, for the tensors of a batch that are
+// too large for its one launch) run many tensors in one launch: every block
+// reads the descriptor of its tensor, then runs the single-tensor device code.
 // Everything is HBM streaming or bound by latency; nothing is a dense
 // contraction, so there is no MFMA.
 #include <algorithm>
@@ -170,6 +171,13 @@ __device__ __forceinline__ void accum_quantize_part(const float* __restrict__ x,
   }
 }
 
+// A refused tensor, in place: the buffer gets the sums.
+__device__ __forceinline__ void store_sums(const float* __restrict__ x, float* __restrict__ r,
+                                           uint64_t n, uint32_t blk, uint32_t nblk) {
+  for (uint64_t e = (uint64_t)blk * kThreads + threadIdx.x; e < n; e += (uint64_t)nblk * kThreads)
+    r[e] = x[e] + r[e];
+}
+
 // Partial maxima of |x + r| that write nothing: the check pass that lets
 // the default error policy refuse NaN/Inf before the buffer is touched.
 template <bool kKeep>
@@ -199,12 +207,12 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_kernel(
 // a and b of Section 3.1 with Eq. 2): the check pass's partial maxima give M
 // (Eq. 1), then every value's acc = x + r is quantized, its residual stored in
 // place and q + 1 kept as a 2-bit trit (accum_quantize_part).  A scale that is
-// NaN/Inf or overflows leaves the buffer untouched.  Block 0 reports M and the
-// verdict.
+// NaN/Inf or overflows leaves the buffer untouched, or with the sums
+// (in_place).  Block 0 reports M and the verdict.
 __global__ __launch_bounds__(kThreads) void tlc_accum_quantize_kernel(
     const float* __restrict__ x, float* __restrict__ r, uint64_t n, uint8_t* __restrict__ trits,
-    const uint32_t* __restrict__ partials, uint32_t np, float s, Ctrl* __restrict__ ctrl,
-    HostMirror hm) {
+    const uint32_t* __restrict__ partials, uint32_t np, float s, bool in_place,
+    Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ uint32_t lds[kWaves];
   const Scale sc = finish_scale(partials, np, s, lds);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -212,7 +220,10 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_quantize_kernel(
     ctrl->enc.scale = sc.M;
     host_put_result(hm.res, sc.bad, sc.M);
   }
-  if (sc.bad) return;
+  if (sc.bad) {
+    if (in_place) store_sums(x, r, n, blockIdx.x, gridDim.x);
+    return;
+  }
   accum_quantize_part(x, r, n, blockIdx.x, gridDim.x, sc.M, sc.U, trits);
 }
 
@@ -226,32 +237,23 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_quantize_kernel(
 constexpr int kLineSlots = 4;
 constexpr uint32_t kLineMaxBlocks = 2048;  // eight per CU, all resident
 
-__global__ __launch_bounds__(kThreads) void tlc_quantize_lines_kernel(
-    float* __restrict__ r, uint64_t n, uint8_t* __restrict__ trits,
-    const uint16_t* __restrict__ bound, const uint32_t* __restrict__ partials, uint32_t np,
-    float s, Ctrl* __restrict__ ctrl, HostMirror hm) {
-  __shared__ uint32_t lds[kWaves];
-  const Scale sc = finish_scale(partials, np, s, lds);
+__device__ __forceinline__ void quantize_lines_part(float* __restrict__ r, uint64_t n,
+                                                    uint32_t blk, uint32_t nblk, const Scale& sc,
+                                                    const uint16_t* __restrict__ bound,
+                                                    uint8_t* __restrict__ trits) {
   const uint64_t nv = n >> 2;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctrl->enc.err = sc.bad;
-    ctrl->enc.scale = sc.M;
-    host_put_result(hm.res, sc.bad, sc.M);
-    if (!sc.bad && (n & 3u)) {  // the last n % 4 values
-      uint32_t tb = 0u;
-      for (uint64_t e = nv << 2; e < n; ++e) {
-        float o;
-        tb |= quantize_one(r[e], sc.M, sc.U, o) << (2u * (uint32_t)(e & 3u));
-        r[e] = o;
-      }
-      trits[nv] = (uint8_t)tb;
+  if (blk == 0 && threadIdx.x == 0 && (n & 3u)) {  // the last n % 4 values
+    uint32_t tb = 0u;
+    for (uint64_t e = nv << 2; e < n; ++e) {
+      float o;
+      tb |= quantize_one(r[e], sc.M, sc.U, o) << (2u * (uint32_t)(e & 3u));
+      r[e] = o;
     }
+    trits[nv] = (uint8_t)tb;
   }
-  if (sc.bad) return;
   const uint32_t hU = __float_as_uint(sc.U) >> 16;
-  const uint64_t step = (uint64_t)gridDim.x * kThreads * kLineSlots;
-  for (uint64_t i0 = (uint64_t)blockIdx.x * kThreads * kLineSlots + threadIdx.x; i0 < nv;
-       i0 += step) {
+  const uint64_t step = (uint64_t)nblk * kThreads * kLineSlots;
+  for (uint64_t i0 = (uint64_t)blk * kThreads * kLineSlots + threadIdx.x; i0 < nv; i0 += step) {
     bool take[kLineSlots];
     float4 v[kLineSlots];
 #pragma unroll
@@ -279,28 +281,112 @@ __global__ __launch_bounds__(kThreads) void tlc_quantize_lines_kernel(
   }
 }
 
-// The max passes of a batch's tensors of more than one tile: the check pass
-// or, in place, step 1 into the buffers.
-__global__ __launch_bounds__(kThreads) void tlc_absmax_check_batch_kernel(
-    const EncDesc* __restrict__ descs, uint32_t count, uint32_t* __restrict__ partials) {
+__global__ __launch_bounds__(kThreads) void tlc_quantize_lines_kernel(
+    float* __restrict__ r, uint64_t n, uint8_t* __restrict__ trits,
+    const uint16_t* __restrict__ bound, const uint32_t* __restrict__ partials, uint32_t np,
+    float s, Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ uint32_t lds[kWaves];
-  const uint32_t t =
-      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.blk0; });
-  const EncDesc& d = descs[t];
-  const uint32_t bm =
-      block_max(absmax_part<true, false>(d.x, d.r, d.n, blockIdx.x - d.blk0, d.nblk), lds);
-  if (threadIdx.x == 0) partials[blockIdx.x] = bm;
+  const Scale sc = finish_scale(partials, np, s, lds);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctrl->enc.err = sc.bad;
+    ctrl->enc.scale = sc.M;
+    host_put_result(hm.res, sc.bad, sc.M);
+  }
+  if (sc.bad) return;
+  quantize_lines_part(r, n, blockIdx.x, gridDim.x, sc, bound, trits);
+}
+
+// The max and the writing passes over a batch's middle tensors, laid end to end
+// (v0 counts from the first one's start, in kManyValues).  Groups of blocks take
+// equal shares of the whole, and a group's blocks stride over each tensor in
+// its share together: equal work wherever the tensors end.  (A share of the
+// blocks for each tensor left blocks over or doubled them up on a CU: 130
+// tensors of 1M values 625 to 673 us, three of 25M 345 with 258 blocks and 279
+// with 255.  A stretch of its own for each block costs a tenth to a fifth of
+// the bandwidth, many tensors in a group a tail each.)  Partial maxima: one per
+// block, group and tensor, a tensor's from number blk0 on.
+template <class Part>
+__device__ __forceinline__ void for_many(const EncDesc* __restrict__ descs, uint32_t count,
+                                         uint32_t units, uint32_t groups, Part&& part) {
+  const uint32_t per = gridDim.x / groups;  // blocks of a group
+  const uint32_t g = blockIdx.x / per, b = blockIdx.x - g * per;
+  const uint32_t u0 = (uint32_t)((uint64_t)units * g / groups);
+  const uint32_t u1 = (uint32_t)((uint64_t)units * (g + 1u) / groups);
+  if (u0 >= u1) return;
+  uint32_t t = find_desc(descs, count, u0, [](const EncDesc& d) { return d.v0; });
+#pragma unroll 1
+  for (; t < count; ++t) {
+    const EncDesc& d = descs[t];
+    if (d.v0 >= u1) break;
+    const uint64_t lo = (uint64_t)(umax32(u0, d.v0) - d.v0) * kManyValues;
+    const uint64_t hi = umin64(d.n, (uint64_t)(u1 - d.v0) * kManyValues);
+    part(t, d, lo, hi > lo ? hi - lo : 0u, (g + t) * (kAbsmaxMaxBlocks / groups) + b, b, per);
+    __syncthreads();  // the part's LDS is free again
+  }
+}
+
+template <bool kKeep>
+__global__ __launch_bounds__(kThreads) void tlc_absmax_check_batch_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, uint32_t units, uint32_t groups,
+    uint32_t* __restrict__ partials) {
+  __shared__ uint32_t lds[kWaves];
+  for_many(descs, count, units, groups,
+           [&](uint32_t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
+               uint32_t nblk) {
+             const uint32_t bm = block_max(
+                 absmax_part<true, false, false, kKeep>(uniform_ptr(d.x) + lo,
+                                                        uniform_ptr(d.r) + lo, n, blk, nblk),
+                 lds);
+             if (threadIdx.x == 0) partials[slot] = bm;
+           });
 }
 
 __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_batch_kernel(
-    const EncDesc* __restrict__ descs, uint32_t count, uint32_t* __restrict__ partials) {
+    const EncDesc* __restrict__ descs, uint32_t count, uint32_t units, uint32_t groups,
+    uint32_t* __restrict__ partials, uint16_t* __restrict__ bound) {
   __shared__ uint32_t lds[kWaves];
-  const uint32_t t =
-      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.blk0; });
-  const EncDesc& d = descs[t];
-  const uint32_t bm =
-      block_max(absmax_part<true, true>(d.x, d.r, d.n, blockIdx.x - d.blk0, d.nblk), lds);
-  if (threadIdx.x == 0) partials[blockIdx.x] = bm;
+  for_many(descs, count, units, groups,
+           [&](uint32_t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
+               uint32_t nblk) {
+             const uint64_t at = (uint64_t)d.v0 * kManyValues + lo;
+             const uint32_t bm =
+                 block_max(absmax_part<true, true, true>(uniform_ptr(d.x) + lo,
+                                                         uniform_ptr(d.r) + lo, n, blk, nblk,
+                                                         bound + at / 32),
+                           lds);
+             if (threadIdx.x == 0) partials[slot] = bm;
+           });
+}
+
+// kLines: after the in-place max pass.
+template <bool kLines>
+__global__ __launch_bounds__(kThreads) void tlc_quantize_many_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, uint32_t units, uint32_t groups,
+    const uint32_t* __restrict__ partials, bool in_place, const uint16_t* __restrict__ bound,
+    uint8_t* __restrict__ trits, EncResult* __restrict__ results, HostMirror hm) {
+  __shared__ uint32_t lds[kWaves];
+  for_many(descs, count, units, groups,
+           [&](uint32_t t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
+               uint32_t nblk) {
+             const Scale sc = finish_scale(partials + d.blk0, d.nblk, d.s, lds);
+             if (slot == d.blk0 && threadIdx.x == 0) {  // its first group's first block
+               results[t].err = sc.bad;
+               results[t].scale = sc.M;
+               host_put_result(hm.res ? hm.res + t : nullptr, sc.bad, sc.M);
+             }
+             const float* x = uniform_ptr(d.x) + lo;
+             float* r = uniform_ptr(d.r) + lo;
+             const uint64_t at = (uint64_t)d.v0 * kManyValues + lo;
+             if constexpr (kLines) {
+               if (!sc.bad)
+                 quantize_lines_part(r, n, blk, nblk, sc, bound + at / 32, trits + at / 4);
+             } else {
+               if (!sc.bad)
+                 accum_quantize_part(x, r, n, blk, nblk, sc.M, sc.U, trits + at / 4);
+               else if (in_place)
+                 store_sums(x, r, n, blk, nblk);
+             }
+           });
 }
 
 // ---------------------------------------------------------------- Eq. 2, 3.2, 3.3
@@ -481,16 +567,24 @@ constexpr int kTritThreads = 128;
 constexpr uint32_t kTritTwoWaveMinTiles = 8192;
 
 template <int kT>
-__global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
-    uint64_t n, uint32_t m, uint8_t* __restrict__ slots, TileRec* __restrict__ recs,
-    const uint8_t* __restrict__ trits, const Ctrl* __restrict__ ctrl) {
+struct TritTileShared {
+  EncShared<kT / 64> enc;
+  uint32_t lut[5][256];
+};
+
+// Tile t of a tensor: its slot and record.  err: the tensor was refused.
+template <int kT>
+__device__ __forceinline__ void encode_trit_tile(uint64_t n, uint32_t m, uint32_t t,
+                                                 const uint8_t* __restrict__ trits,
+                                                 const uint32_t* err, uint8_t* __restrict__ slot,
+                                                 TileRec* __restrict__ rec_out,
+                                                 TritTileShared<kT>& shared) {
   constexpr int kW = kT / 64;
   constexpr int kHalves = kEncTile / kT / 16;
   constexpr uint32_t kBytes = 16u * kHalves;  // quartic bytes per thread
   static_assert(kHalves == 1 || kHalves == 2, "one or two pieces of 16 bytes per thread");
-  __shared__ EncShared<kW> sh;
-  __shared__ uint32_t s_lut[5][256];
-  const uint32_t t = blockIdx.x;
+  EncShared<kW>& sh = shared.enc;
+  uint32_t(&s_lut)[5][256] = shared.lut;
   const uint64_t q0 = (uint64_t)t * kEncTile;
   const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
   // an interior tile (whole, every value before n): each thread packs its
@@ -505,7 +599,7 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
     load_trits<kT>(trits, n, m, q0, tile_bytes, h);
   init_trit_luts<kT>(s_lut);
   __syncthreads();  // the tables
-  if (ctrl->enc.err) return;  // NaN/Inf or overflow: no stream (every block returns)
+  if (*err) return;  // NaN/Inf or overflow: no stream (every block returns)
   const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
   uint4 w[kHalves];
   uint32_t nz[kHalves];  // non-121 bytes of each piece, spread: bit 2i for its byte i
@@ -579,7 +673,7 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
   const uint32_t len = umin32(off.total, tile_bytes);
   __syncthreads();
   for (uint32_t i = 16u * threadIdx.x; i < len; i += 16u * kT)
-    *reinterpret_cast<uint4*>(slots + q0 + i) = *reinterpret_cast<const uint4*>(sh.out + i);
+    *reinterpret_cast<uint4*>(slot + i) = *reinterpret_cast<const uint4*>(sh.out + i);
   if (threadIdx.x == 0) {
     TileRec rec;
     if (pm.total == 0u) {  // all 121: one run
@@ -592,8 +686,32 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
       rec.len = (uint16_t)len;
     }
     rec.pad = 0u;
-    recs[t] = rec;
+    *rec_out = rec;
   }
+}
+
+template <int kT>
+__global__ __launch_bounds__(kT) void tlc_quant_encode_kernel(
+    uint64_t n, uint32_t m, uint8_t* __restrict__ slots, TileRec* __restrict__ recs,
+    const uint8_t* __restrict__ trits, const Ctrl* __restrict__ ctrl) {
+  __shared__ TritTileShared<kT> sh;
+  const uint32_t t = blockIdx.x;
+  encode_trit_tile<kT>(n, m, t, trits, &ctrl->enc.err, slots + (uint64_t)t * kEncTile, recs + t,
+                       sh);
+}
+
+// The tiles of a batch's middle tensors, numbered through (tile0).
+__global__ __launch_bounds__(kThreads) void tlc_quant_encode_many_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, uint8_t* __restrict__ slots,
+    TileRec* __restrict__ recs, const uint8_t* __restrict__ trits,
+    const EncResult* __restrict__ results) {
+  __shared__ TritTileShared<kThreads> sh;
+  const uint32_t t =
+      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.tile0; });
+  const EncDesc& d = descs[t];
+  encode_trit_tile<kThreads>(d.n, d.m, blockIdx.x - d.tile0,
+                             trits + (uint64_t)d.v0 * (kManyValues / 4), &results[t].err,
+                             slots + (uint64_t)blockIdx.x * kEncTile, recs + blockIdx.x, sh);
 }
 
 // Pass B: one wave per chunk of 64 tiles: every tile's prefix within its
@@ -662,29 +780,30 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_chunk_kernel(
 // ends the stream and the stream length.  Every write is clamped to
 // the m-byte output (the stream never exceeds m bytes; the clamp only
 // contains a logic error).
-// kOwnPrefix (at most kOwnPrefixTiles tiles): no pass B; the block combines
-// the summaries of all tiles before its first one itself, a few per thread.
-template <bool kOwnPrefix>
-__global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
+// kPer > 0 (at most kPer * kThreads tiles): no pass B; the block combines the
+// summaries of all tiles before its first one itself, kPer per thread.
+template <uint32_t kPer>
+__device__ __forceinline__ void compact_tiles(
     const TileRec* __restrict__ recs, const uint64_t* __restrict__ chunk_pre,
     const uint64_t* __restrict__ local_pre, const uint8_t* __restrict__ slots, uint32_t m,
-    uint32_t ntiles, uint8_t* __restrict__ out, Ctrl* __restrict__ ctrl, HostMirror hm) {
-  if (ctrl->enc.err) return;
+    uint32_t ntiles, uint32_t t0, uint8_t* __restrict__ out, EncResult* __restrict__ res,
+    EncResult* hres) {
+  if (res->err) return;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t t0 = blockIdx.x * kWaves;
   const uint32_t t = t0 + (threadIdx.x >> 6);
   RunSum P;
-  if constexpr (kOwnPrefix) {
+  if constexpr (kPer != 0u) {
     __shared__ uint64_t s_wave[kWaves];
-    constexpr uint32_t kPer = kOwnPrefixTiles / kThreads;
-    RunSum sum = rs_identity();
+    RunSum a[kPer];
 #pragma unroll
     for (uint32_t i = 0; i < kPer; ++i) {  // tiles kPer * thread + i, in order
       const uint32_t u = kPer * threadIdx.x + i;
-      RunSum a = rs_identity();
-      if (u < t0) a.v = recs[u].agg;
-      sum = rs_combine(sum, a);
+      a[i] = rs_identity();
+      if (u < t0) a[i].v = recs[u].agg;
     }
+    RunSum sum = a[0];
+#pragma unroll
+    for (uint32_t i = 1; i < kPer; ++i) sum = rs_combine(sum, a[i]);
     sum = wave_incl_scan_rs(sum);
     if (lane == 63) s_wave[threadIdx.x >> 6] = sum.v;
     __syncthreads();
@@ -703,7 +822,7 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
     }
   }
   if (t >= ntiles) return;  // whole waves; nothing below synchronises the block
-  if constexpr (!kOwnPrefix) {
+  if constexpr (kPer == 0u) {
     RunSum cp, lp;
     cp.v = chunk_pre[t / kChunkTiles];
     lp.v = local_pre[t];
@@ -738,9 +857,32 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
     const uint32_t total = rs_total(T);
     if (rs_phase(T) && total >= 1u && total - 1u < m)
       out[total - 1u] = (uint8_t)rs_code(rs_phase(T));
-    ctrl->enc.len = total;
-    if (hm.res) host_put(&hm.res->len, total);
+    res->len = total;
+    if (hres) host_put(&hres->len, total);
   }
+}
+
+template <uint32_t kPer>
+__global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
+    const TileRec* __restrict__ recs, const uint64_t* __restrict__ chunk_pre,
+    const uint64_t* __restrict__ local_pre, const uint8_t* __restrict__ slots, uint32_t m,
+    uint32_t ntiles, uint8_t* __restrict__ out, Ctrl* __restrict__ ctrl, HostMirror hm) {
+  compact_tiles<kPer>(recs, chunk_pre, local_pre, slots, m, ntiles, blockIdx.x * kWaves, out,
+                      &ctrl->enc, hm.res);
+}
+
+// A batch's middle tensors of at most kPer * kThreads tiles: cblk0 counts the
+// compaction's blocks.
+template <uint32_t kPer>
+__global__ __launch_bounds__(kThreads) void tlc_zre_compact_many_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, const TileRec* __restrict__ recs,
+    const uint8_t* __restrict__ slots, EncResult* __restrict__ results, HostMirror hm) {
+  const uint32_t t =
+      find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.cblk0; });
+  const EncDesc& d = descs[t];
+  compact_tiles<kPer>(recs + d.tile0, nullptr, nullptr, slots + (uint64_t)d.tile0 * kEncTile, d.m,
+                      (d.m + kEncTile - 1) / kEncTile, (blockIdx.x - d.cblk0) * kWaves,
+                      uniform_ptr(d.out), results + t, hm.res ? hm.res + t : nullptr);
 }
 
 // ---------------------------------------------------------------- small tensors
@@ -755,8 +897,9 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
 // its own and reads the others' (nothing is written before all have come), so
 // that no check pass runs before.  Those that follow it may not have started:
 // a tile that has waited a while reads their values itself (help_maxima), so
-// that any number of resident blocks will do.  A longer tensor's M comes from
-// a check pass (partials).
+// that any number of resident blocks will do.  A longer tensor (of a
+// no-allocation call only) takes kT 512 and has its M from a check pass
+// (partials).
 //
 // The zero-run encoding is the first pass's (from the gaps between non-121
 // bytes, from the tile's first one on).  Its place in the stream and the
@@ -781,13 +924,13 @@ struct TileShared {
 
 // Where one tensor of a launch lies and where its results go.
 struct TileJob {
-  const float* x;  // null: r holds the sums already
+  const float* x;
   float* r;
   uint8_t* out;
   uint64_t n;
   uint32_t m;
   float s;
-  const uint32_t* partials;  // the check pass's (more than kExchangeTiles tiles)
+  const uint32_t* partials;  // the check pass's (kT 512)
   uint32_t np;
   uint32_t floor;  // status slot of the tensor's first tile
   EncResult* res;
@@ -878,7 +1021,7 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
   const uint64_t q0 = (uint64_t)lt * kTile;
   const uint32_t tile_bytes = (uint32_t)umin64(kTile, m - q0);
   const uint32_t tiles = (uint32_t)((m + kTile - 1) / kTile);
-  const bool chained = m > (uint64_t)kExchangeTiles * kSmallTile;
+  constexpr bool kChained = kT > kTileThreads;
   const bool last_tile = q0 + kTile >= m;
   const uint32_t lo = threadIdx.x * kBytes;
   const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
@@ -910,10 +1053,8 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
     if (full[g]) {
 #pragma unroll
       for (int k = 0; k < 5; ++k) v[g][k] = ld4(J.r + part(k) + i);
-      if (J.x) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k) b[g][k] = ld4(J.x + part(k) + i);
-      }
+      for (int k = 0; k < 5; ++k) b[g][k] = ld4(J.x + part(k) + i);
     } else if (i < tile_bytes) {
       // the group at the end, without branches: a value that does not exist
       // is read as the last one that does, and zeroed below
@@ -923,23 +1064,19 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
 #pragma unroll
       for (int k = 0; k < 5; ++k)
         v[g][k] = make_float4(one(J.r, k, 0), one(J.r, k, 1), one(J.r, k, 2), one(J.r, k, 3));
-      if (J.x) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k)
-          b[g][k] = make_float4(one(J.x, k, 0), one(J.x, k, 1), one(J.x, k, 2), one(J.x, k, 3));
-      }
+      for (int k = 0; k < 5; ++k)
+        b[g][k] = make_float4(one(J.x, k, 0), one(J.x, k, 1), one(J.x, k, 2), one(J.x, k, 3));
     }
   }
 #pragma unroll
   for (int g = 0; g < kG; ++g) {
     const uint32_t i = lo + 4u * g;
     if (i < tile_bytes) {
-      if (J.x) {
 #pragma unroll
-        for (int k = 0; k < 5; ++k)
-          v[g][k] = make_float4(b[g][k].x + v[g][k].x, b[g][k].y + v[g][k].y,
-                                b[g][k].z + v[g][k].z, b[g][k].w + v[g][k].w);
-      }
+      for (int k = 0; k < 5; ++k)
+        v[g][k] = make_float4(b[g][k].x + v[g][k].x, b[g][k].y + v[g][k].y,
+                              b[g][k].z + v[g][k].z, b[g][k].w + v[g][k].w);
       if (!full[g]) {
 #pragma unroll
         for (int k = 0; k < 5; ++k)
@@ -952,7 +1089,7 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
 
   // ---- Eq. 1
   Scale sc;
-  if (!chained) {
+  if constexpr (!kChained) {
     uint32_t mx = 0u;
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
@@ -1012,8 +1149,8 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
   };
   if (sc.bad) {
     // NaN/Inf or overflow: no stream, the buffer as it was or, in place, the
-    // sums (which it holds already where x is null)
-    if (in_place && J.x) {
+    // sums
+    if (in_place) {
 #pragma unroll
       for (int g = 0; g < kG; ++g)
         if (cnt > 4u * g)
@@ -1100,7 +1237,7 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
   static_assert(kG <= 2, "the thread's bytes fit 64 bits");
   RunSum P = rs_identity();
   if (lt != 0) {
-    if (!chained) {
+    if constexpr (!kChained) {
       if (wid < kReaders) {  // lane i of wave w reads tile 64w + i's summary
         uint64_t w;
         const bool mine = threadIdx.x < lt;
@@ -1120,15 +1257,15 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
         }
       }
     } else {
-      P = rs_from_payload(lookback_block<EncSW, kW>(
-          status, J.floor, J.floor + lt, rs_to_payload(agg), rs_to_payload(rs_identity()), epoch,
-          EncOp(), sh.look, &sh.fault));
+      P = rs_from_payload(lookback_block<EncSW, kW>(status, lt, rs_to_payload(agg),
+                                                    rs_to_payload(rs_identity()), epoch, EncOp(),
+                                                    sh.look, &sh.fault));
       if (sh.fault) {
         if (threadIdx.x == 0) fault_out();
         return;
       }
     }
-    if (!chained) {
+    if constexpr (!kChained) {
       __syncthreads();
       if (sh.fault) return;
 #pragma unroll 1
@@ -1168,7 +1305,10 @@ __device__ __forceinline__ void encode_tile(const TileJob& J, uint32_t lt, bool 
 }
 
 // One tensor.  A chained one takes tiles of twice the size (kT 512): its
-// look-back is half as long (8,388,608 values: 42 against 51 us).
+// look-back is half as long (8,388,608 values: 42 against 51 us).  (Tensors of
+// this size in a context take the three passes, alone or in a batch: chained in
+// the batch's launch, ten of 2M values took 131 us, four of 8M 197, one of 25.6M
+// 166; before the exchange, in 4096-byte tiles, 108, 148 and 126.)
 template <int kT>
 __global__ __launch_bounds__(kT) void tlc_quant_encode_chained_kernel(
     const float* __restrict__ x, float* __restrict__ r, uint64_t n, uint32_t m, float s,
@@ -1193,9 +1333,9 @@ __global__ __launch_bounds__(kT) void tlc_quant_encode_chained_kernel(
 // one counter).
 __global__ __launch_bounds__(kTileThreads) void tlc_quant_encode_batch_kernel(
     const EncDesc* __restrict__ descs, uint32_t shared, const uint16_t* __restrict__ owner,
-    bool in_place, const uint32_t* __restrict__ partials, EncResult* __restrict__ results,
-    uint64_t* __restrict__ status, uint64_t* __restrict__ maxima, uint32_t ticket_base,
-    uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
+    bool in_place, EncResult* __restrict__ results, uint64_t* __restrict__ status,
+    uint64_t* __restrict__ maxima, uint32_t ticket_base, uint32_t epoch, Ctrl* __restrict__ ctrl,
+    HostMirror hm) {
   __shared__ TileShared<kTileThreads, kTileGroups> sh;
   __shared__ uint32_t s_tile;
   __shared__ EncDesc s_desc;
@@ -1212,16 +1352,15 @@ __global__ __launch_bounds__(kTileThreads) void tlc_quant_encode_batch_kernel(
         reinterpret_cast<const uint32_t*>(descs + t)[threadIdx.x];
   __syncthreads();
   const uint32_t lt = uniform32(T - s_desc.tile0), ut = uniform32(t);
-  // in place, a tensor with a max pass has its sums in the buffer
   const TileJob J = {
-      in_place && s_desc.nblk ? nullptr : uniform_ptr(s_desc.x),
+      uniform_ptr(s_desc.x),
       uniform_ptr(s_desc.r),
       uniform_ptr(s_desc.out),
       uniform64(s_desc.n),
       uniform32(s_desc.m),
       s_desc.s,
-      partials + uniform32(s_desc.blk0),
-      uniform32(s_desc.nblk),
+      nullptr,
+      0u,
       uniform32(s_desc.tile0),
       results + ut,
       hm.res ? hm.res + ut : nullptr};
@@ -1315,14 +1454,12 @@ uint32_t absmax_blocks(uint64_t n) {
 }
 }  // namespace
 
-// Tensors whose values and buffer fit the 256 MB last-level cache are read with
+// Tensors whose values and buffer fit the last-level cache are read with
 // plain loads by the check pass: the writing pass then finds them there (check
 // + writing pass, three tensors in turn, nontemporal against plain loads: 12M
 // values 16.8 + 27.8 against 18.4 + 22.9 us, 25.6M 32.8 + 53.8 against 35.6 +
 // 46.1, 33M 40.5 + 69.0 against 47.3 + 59.9; 45M, which do not fit, 54.4 + 91.9
 // against 62.6 + 83.1, and 2^28 lose 40 us).
-constexpr uint64_t kCacheBytes = 256ull << 20;
-
 #ifdef TLC_DELAY_INJECT
 // Stress build only: blocks per launch of a small tensor's encode (0: all).
 static uint32_t g_stress_blocks = 0u;
@@ -1352,10 +1489,10 @@ hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* p
 }
 
 hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s,
-                                 const uint32_t* partials, uint32_t np, uint8_t* trits,
-                                 Ctrl* ctrl, HostMirror hm, hipStream_t st) {
+                                 bool in_place, const uint32_t* partials, uint32_t np,
+                                 uint8_t* trits, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   launch_k(tlc_accum_quantize_kernel, absmax_blocks(n), kThreads, st, x, r, n, trits, partials,
-           np, s, ctrl, hm);
+           np, s, in_place, ctrl, hm);
   return hipGetLastError();
 }
 
@@ -1420,30 +1557,55 @@ hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
                               uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   const uint32_t ntiles = (uint32_t)((m + kEncTile - 1) / kEncTile);
   if (!zre_chunked(m))
-    launch_k(tlc_zre_compact_kernel<true>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
+    launch_k(tlc_zre_compact_kernel<kOwnPrefixTiles / kThreads>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
              chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
   else
-    launch_k(tlc_zre_compact_kernel<false>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
+    launch_k(tlc_zre_compact_kernel<0u>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
              chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
   return hipGetLastError();
 }
 
-hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t total_blocks,
-                               bool in_place, uint32_t* partials, hipStream_t st) {
-  if (in_place)
-    launch_k(tlc_accum_absmax_batch_kernel, total_blocks, kThreads, st, descs, count, partials);
-  else
-    launch_k(tlc_absmax_check_batch_kernel, total_blocks, kThreads, st, descs, count, partials);
+hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_place,
+                              uint32_t* partials, uint16_t* bound, uint8_t* trits, uint8_t* slots,
+                              TileRec* recs, EncResult* results, HostMirror hm, int pass,
+                              hipStream_t st) {
+  constexpr uint32_t kBlocks = kAbsmaxMaxBlocks;  // one per CU, as for a tensor alone
+  if (pass == 0) {
+    if (p.lines)
+      launch_k(tlc_accum_absmax_batch_kernel, kBlocks, kThreads, st, descs, p.count, p.units,
+               p.groups, partials, bound);
+    else if (p.values * 2 * sizeof(float) <= kCacheBytes)
+      launch_k(tlc_absmax_check_batch_kernel<true>, kBlocks, kThreads, st, descs, p.count, p.units,
+               p.groups, partials);
+    else
+      launch_k(tlc_absmax_check_batch_kernel<false>, kBlocks, kThreads, st, descs, p.count,
+               p.units, p.groups, partials);
+  } else if (pass == 1) {
+    if (p.lines)
+      launch_k(tlc_quantize_many_kernel<true>, kLineMaxBlocks, kThreads, st, descs, p.count,
+               p.units, p.groups, partials, in_place, bound, trits, results, hm);
+    else
+      launch_k(tlc_quantize_many_kernel<false>, kBlocks, kThreads, st, descs, p.count, p.units,
+               p.groups, partials, in_place, bound, trits, results, hm);
+  } else if (pass == 2) {
+    launch_k(tlc_quant_encode_many_kernel, p.tiles, kThreads, st, descs, p.count, slots, recs,
+             trits, results);
+  } else if (p.most_tiles <= kOwnPrefixTiles) {
+    launch_k(tlc_zre_compact_many_kernel<kOwnPrefixTiles / kThreads>, p.compact_blocks, kThreads,
+             st, descs, p.count, recs, slots, results, hm);
+  } else {
+    launch_k(tlc_zre_compact_many_kernel<kManyMaxTiles / kThreads>, p.compact_blocks, kThreads, st,
+             descs, p.count, recs, slots, results, hm);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t shared, const uint16_t* owner,
-                                     uint32_t tiles, bool in_place, const uint32_t* partials,
-                                     EncResult* results, uint64_t* status, uint64_t* maxima,
-                                     uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
-                                     HostMirror hm, hipStream_t st) {
+                                     uint32_t tiles, bool in_place, EncResult* results,
+                                     uint64_t* status, uint64_t* maxima, uint32_t ticket_base,
+                                     uint32_t epoch, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   launch_k(tlc_quant_encode_batch_kernel, tiles, kTileThreads, st, descs, shared, owner, in_place,
-           partials, results, status, maxima, ticket_base, epoch, ctrl, hm);
+           results, status, maxima, ticket_base, epoch, ctrl, hm);
   return hipGetLastError();
 }
 

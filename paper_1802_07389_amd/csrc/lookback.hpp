@@ -149,12 +149,12 @@ __device__ uint64_t lookback_wave(uint64_t* status, uint32_t floor, uint32_t til
   return failed ? identity : run;
 }
 
-// The same by a whole block of kW waves, which poll kW windows of 64
-// predecessors at a time (wave 0 the nearest): with hundreds of tiles that
-// publish at about the same time, a tile a few windows away from the nearest
-// inclusive prefix needs one round instead of several.  The caller has
-// published the tile's aggregate.  Every thread returns the exclusive prefix
-// and reads *fault after a barrier.
+// The same by a whole block of kW waves for a scan of at most 64 * kW + 1
+// tiles from word 0 on: the waves poll 64 predecessors each (wave 0 the
+// nearest) at the same time, so that with hundreds of tiles that publish at
+// about the same time none takes several rounds.  The caller has published
+// the tile's aggregate.  Every thread returns the exclusive prefix and reads
+// *fault after a barrier.
 template <int kW>
 struct LookShared {
   uint64_t fold[kW];
@@ -162,56 +162,54 @@ struct LookShared {
 };
 
 template <class SW, int kW, class Op>
-__device__ uint64_t lookback_block(uint64_t* status, uint32_t floor, uint32_t tile, uint64_t agg,
-                                   uint64_t identity, uint32_t epoch, Op op,
-                                   LookShared<kW>& sh, uint32_t* fault) {
+__device__ uint64_t lookback_block(uint64_t* status, uint32_t tile, uint64_t agg,
+                                   uint64_t identity, uint32_t epoch, Op op, LookShared<kW>& sh,
+                                   uint32_t* fault) {
   const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+  const int idx = (int)tile - 1 - (int)(64u * wid + lane);
+  uint64_t val = identity;
+  uint32_t p = 64u, state = 0u;
+  for (uint32_t spins = 0;; ++spins) {
+    bool ready = true, is_prefix = true, is_fault = false;
+    if (idx >= 0) {  // lanes before the first tile act as an (ignored) prefix
+      const uint64_t w = status_read(&status[idx]);
+      const uint32_t f = SW::flag(w);
+      ready = SW::epoch(w) == epoch && f != 0u;
+      is_prefix = ready && f == kFlagPrefix;
+      is_fault = ready && f == kFlagFault;
+      val = SW::payload(w);
+    }
+    const uint64_t pmask = __ballot(is_prefix);
+    p = pmask ? (uint32_t)(__ffsll((unsigned long long)pmask) - 1) : 64u;
+    const bool need = lane <= p;
+    if (__ballot(is_fault && need)) state = 2u;
+    if (state == 2u || __ballot(!ready && need) == 0u) break;
+    if (spins > kSpinLimit) {
+      state = 2u;
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  if (state == 0u && p < 64u) state = 1u;
+  const uint64_t fold =
+      readlane64(wave_incl_scan(lane <= p ? val : identity, identity, OpLaterFirst<Op>{op}), 63);
+  if (lane == 0) {
+    sh.fold[wid] = fold;
+    sh.state[wid] = state;
+  }
+  __syncthreads();
   uint64_t run = identity;
   uint32_t end = 0u;  // 1: a prefix was reached, 2: gave up
-  for (int64_t base = (int64_t)tile - 1; end == 0u; base -= 64 * kW) {
-    const int64_t idx = base - 64 * (int64_t)wid - (int64_t)lane;
-    uint64_t val = identity;
-    uint32_t p = 64u, state = 0u;
-    for (uint32_t spins = 0;; ++spins) {
-      bool ready = true, is_prefix = true, is_fault = false;
-      if (idx >= (int64_t)floor) {
-        const uint64_t w = status_read(&status[idx]);
-        const uint32_t f = SW::flag(w);
-        ready = SW::epoch(w) == epoch && f != 0u;
-        is_prefix = ready && f == kFlagPrefix;
-        is_fault = ready && f == kFlagFault;
-        val = SW::payload(w);
-      }
-      const uint64_t pmask = __ballot(is_prefix);
-      p = pmask ? (uint32_t)(__ffsll((unsigned long long)pmask) - 1) : 64u;
-      const bool need = lane <= p;
-      if (__ballot(is_fault && need)) state = 2u;
-      if (state == 2u || __ballot(!ready && need) == 0u) break;
-      if (spins > kSpinLimit) {
-        state = 2u;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    if (state == 0u && p < 64u) state = 1u;
-    const uint64_t fold =
-        readlane64(wave_incl_scan(lane <= p ? val : identity, identity, OpLaterFirst<Op>{op}), 63);
-    __syncthreads();  // the last round's words have been read
-    if (lane == 0) {
-      sh.fold[wid] = fold;
-      sh.state[wid] = state;
-    }
-    __syncthreads();
 #pragma unroll 1
-    for (int w = 0; w < kW && end == 0u; ++w) {
-      if (sh.state[w] == 2u) {
-        end = 2u;
-      } else {
-        run = op(sh.fold[w], run);
-        end = sh.state[w];
-      }
+  for (int w = 0; w < kW && end == 0u; ++w) {
+    if (sh.state[w] == 2u) {
+      end = 2u;
+    } else {
+      run = op(sh.fold[w], run);
+      end = sh.state[w];
     }
   }
+  if (end == 0u) end = 2u;  // more tiles than the windows hold
   if (threadIdx.x == 0) {
     *fault = end == 2u ? 1u : 0u;
     status_publish(&status[tile], end == 2u ? SW::pack(0, kFlagFault, epoch)

@@ -29,6 +29,8 @@ constexpr size_t kStatusWords = kNoallocMaxTiles + 2;
 constexpr size_t kOffMaxima = kOffStatus + kStatusWords * sizeof(uint64_t);
 constexpr size_t kScratchBytes = 16384;  // the size the header states
 static_assert(kOffMaxima + kExchangeTiles * sizeof(uint64_t) <= kScratchBytes, "layout fits");
+static_assert((kNoallocMaxTiles + 1) / 2 <= 64 * (2 * kTileThreads / 64) + 1,
+              "a chained tensor's look-back takes one round (lookback_block)");
 
 // In host code `scratch` names a host-side stand-in; its device address
 // comes from hipGetSymbolAddress, once per device.

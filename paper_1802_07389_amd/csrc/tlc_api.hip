@@ -475,11 +475,13 @@ int check_usable(tlc_ctx* c, const char* fn) {
   return TLC_OK;
 }
 
-// Absmax blocks given to one tensor of a batch (proportional to its size,
-// `items` float4 pairs).
-uint32_t batch_absmax_blocks(size_t items) {
-  size_t b = ceil_div(items, (size_t)kThreads * 4);
-  return (uint32_t)std::max<size_t>(1, std::min<size_t>(b, kAbsmaxMaxBlocks));
+// How a batched encode takes a tensor of m quartic bytes (exchange: the most
+// tiles that exchange their maxima in this call).
+enum BatchKind { kMiddle, kShared, kLone, kLarge };
+BatchKind batch_kind(size_t m, uint32_t exchange) {
+  if (m <= kSmallTile) return kLone;
+  if (m <= (size_t)exchange * kSmallTile) return kShared;
+  return m > (size_t)kManyMaxTiles * kEncTile ? kLarge : kMiddle;
 }
 
 }  // namespace
@@ -515,9 +517,16 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   // Bounds over any call: the sum of m_t is at most max_n/5 + tensors, and a
   // tensor has at most m_t/tile + 1 tiles.
   const size_t mm = max_n / 5 + max_tensors;
+  // a batch's middle tensors: how many there can be
+  const size_t many =
+      std::min(max_tensors, max_n / ((size_t)kManyMinTiles * kSmallTile * 5) + 1);
   c->partials_cap =
-      std::max<size_t>(kAbsmaxMaxBlocks, max_n / ((size_t)kThreads * 4) + max_tensors + 1);
+      std::max<size_t>(3 * kAbsmaxMaxBlocks,
+                       (many + kManyMaxGroups) * (kAbsmaxMaxBlocks / kManyMaxGroups));
   const size_t tiles1 = ceil_div(quartic_len(max_n), (size_t)kEncTile);  // one tensor
+  // the middle tensors' tiles in all (each rounds its bytes and its tiles up)
+  const size_t tiles2 = tiles1 + 2 * many;
+  const size_t values2 = max_n + 2 * many * kManyValues;
   c->enc_status_words = mm / kSmallTile + max_tensors + 2;
   c->dec_status_words = mm / kZreBatchTile + max_tensors + 2;  // the smaller tile
   c->start_words = mm / kDecRange + max_tensors + 2;
@@ -547,17 +556,17 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   // (as in a staging slot: the owners follow max_tensors descriptors)
   off = round_up(off + max_tensors * sizeof(DecDesc) + c->dec_status_words * sizeof(uint16_t), 256);
   const size_t off_recs = off;
-  off = round_up(off + tiles1 * sizeof(TileRec), 256);
+  off = round_up(off + tiles2 * sizeof(TileRec), 256);
   const size_t off_chunks = off;
   off = round_up(off + (tiles1 / 64 + 1) * sizeof(uint64_t), 256);
   const size_t off_local = off;
   off = round_up(off + tiles1 * sizeof(uint64_t), 256);
   const size_t off_bound = off;
-  off = round_up(off + ceil_div(max_n, (size_t)32) * sizeof(uint16_t), 256);
+  off = round_up(off + ceil_div(values2, (size_t)32) * sizeof(uint16_t), 256);
   const size_t off_trits = off;
-  off = round_up(off + ceil_div(max_n, (size_t)4) + 64, 256);  // 64: whole words past the last
+  off = round_up(off + ceil_div(values2, (size_t)4) + 64, 256);  // 64: whole words past the last
   const size_t off_slots = off;
-  const size_t total = round_up(off + tiles1 * (size_t)kEncTile, 256);
+  const size_t total = round_up(off + tiles2 * (size_t)kEncTile, 256);
   e = hipMalloc(&c->ws, total);
   if (e != hipSuccess) {
     delete c;
@@ -660,15 +669,22 @@ int launch_max_pass(tlc_ctx* c, const float* x, const float* r, size_t n, uint32
   });
 }
 
+// Below this the writing pass finds the tensor and the buffer in the last-level
+// cache, and the two passes of the default policy are the faster ones in place
+// too (a refused tensor is then left with the sums): 2M values 28 against 33
+// us, 10M 51 against 54, 18M 81 against 83.
+constexpr size_t kInPlaceMinValues = 20000000;
+
 // Steps 1, a and b for one tensor: residuals in r, trits in the workspace,
 // err and M in the control block and in hm.  Default policy: the check pass
-// (8n bytes), then the writing pass (12n).  In place: the sums with the max
-// pass (12n), then the lines that can hold a q != 0.
+// (8n bytes), then the writing pass (12n).  In place, from kInPlaceMinValues on:
+// the sums with the max pass (12n), then the lines that can hold a q != 0.
 int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s,
                            HostMirror hm) {
   uint32_t np = 0;
   int st;
-  if (c->options & TLC_OPT_IN_PLACE_FEEDBACK) {
+  const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
+  if (in_place && n >= kInPlaceMinValues) {
     st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
       return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, c->stream);
     });
@@ -683,9 +699,47 @@ int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float
   });
   if (st) return st;
   return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
-    return launch_accum_quantize(x, r, n, s, c->partials_chk, np, c->trits, c->ctrl, hm,
-                                 c->stream);
+    return launch_accum_quantize(x, r, n, s, in_place, c->partials_chk, np, c->trits, c->ctrl,
+                                 hm, c->stream);
   });
+}
+
+// The three passes of one tensor.
+int launch_three_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint8_t* bytes,
+                        HostMirror hm) {
+  const uint32_t m = (uint32_t)quartic_len(n);
+  int st = launch_quantize_passes(c, x, r, n, s, hm);
+  if (st) return st;
+  st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
+    return launch_quant_encode(n, m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
+  });
+  if (st) return st;
+  if (zre_chunked(m)) {
+    st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
+      return launch_zre_chunks(c->recs, (uint32_t)ceil_div(m, kEncTile), c->local_pre,
+                               c->chunk_agg, c->ctrl, c->stream);
+    });
+    if (st) return st;
+  }
+  return timed_launch(c, TLC_KERNEL_ZRE_COMPACT, [&] {
+    return launch_zre_compact(c->recs, c->chunk_agg, c->local_pre, c->slots, m, bytes, c->ctrl, hm,
+                              c->stream);
+  });
+}
+
+// The three passes of a batch's middle tensors (descriptors d[0 .. plan.count)
+// in device memory).
+int launch_many_passes(tlc_ctx* c, const ManyPlan& plan, bool in_place, HostMirror hm) {
+  const int ids[4] = {plan.lines ? TLC_KERNEL_ABSMAX_BATCH : TLC_KERNEL_ABSMAX_CHECK_BATCH,
+                      TLC_KERNEL_ACCUM_QUANTIZE, TLC_KERNEL_QUANT_ENCODE, TLC_KERNEL_ZRE_COMPACT};
+  for (int pass = 0; pass < 4; ++pass) {
+    const int st = timed_launch(c, ids[pass], [&] {
+      return launch_encode_many(c->enc_descs, plan, in_place, c->partials_chk, c->bound, c->trits,
+                                c->slots, c->recs, c->enc_results, hm, pass, c->stream);
+    });
+    if (st) return st;
+  }
+  return TLC_OK;
 }
 
 }  // namespace
@@ -752,22 +806,7 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
     if (tiles > 1u) c->enc_ticket_base += tiles;  // a lone tile takes no ticket
     return finish_compress(c, "tlc_compress", bytes_len, scale);
   }
-  st = launch_quantize_passes(c, tensor, residual, n, s, enc_mirror(c));
-  if (st) return st;
-  st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
-    return launch_quant_encode(n, (uint32_t)m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
-  });
-  if (st) return st;
-  if (zre_chunked((uint32_t)m)) {
-    st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
-      return launch_zre_chunks(c->recs, ntiles, c->local_pre, c->chunk_agg, c->ctrl, c->stream);
-    });
-    if (st) return st;
-  }
-  st = timed_launch(c, TLC_KERNEL_ZRE_COMPACT, [&] {
-    return launch_zre_compact(c->recs, c->chunk_agg, c->local_pre, c->slots, (uint32_t)m, bytes,
-                              c->ctrl, enc_mirror(c), c->stream);
-  });
+  st = launch_three_passes(c, tensor, residual, n, s, bytes, enc_mirror(c));
   if (st) return st;
   return finish_compress(c, "tlc_compress", bytes_len, scale);
 }
@@ -878,6 +917,39 @@ TLC_API int tlc_compress_ex(tlc_ctx* c, int mode, const float* tensor, float* re
   return TLC_OK;
 }
 
+namespace {
+
+// The tensors of a batch that take one launch: `count` descriptors, the
+// owners in c->owner, results from number `first` on.
+int launch_few(tlc_ctx* c, const EncDesc* d, uint32_t count, uint32_t shared, uint32_t tiles,
+               bool in_place, uint32_t first, HostMirror hm) {
+  // every block reads one descriptor, once: straight from the pinned copy,
+  // which is free again when the call returns (every result needs its own)
+  const EncDesc* descs = nullptr;
+  const uint16_t* owner = nullptr;
+  int slot = 0;
+  int st = stage(c, d, count * sizeof(EncDesc), c->owner.data(),
+                 c->owner.size() * sizeof(uint16_t), (const void**)&descs, (const void**)&owner,
+                 &slot);
+  if (st) return st;
+  uint32_t epoch = 0;
+  st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, 2 * c->enc_status_words, nullptr,
+                  &epoch);
+  if (st) return st;
+  st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_BATCH, [&] {
+    return launch_quant_encode_batch(descs, shared, owner, tiles, in_place,
+                                     c->enc_results + first, c->enc_status,
+                                     c->enc_status + c->enc_status_words, c->enc_ticket_base,
+                                     epoch, c->ctrl, HostMirror{hm.res + first, hm.fault},
+                                     c->stream);
+  });
+  if (st) return st;
+  c->enc_ticket_base += shared;
+  return TLC_OK;
+}
+
+}  // namespace
+
 TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* tensors,
                                float* const* residuals, const size_t* ns, const float* s,
                                uint8_t* const* bytes, const size_t* caps, size_t* bytes_len,
@@ -933,15 +1005,29 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
   std::vector<size_t>& which = c->which;  // batch position of each launched tensor
   d.clear();
   which.clear();
-  // the tensors with a max pass first (blk0 counts its blocks), then the
-  // others of more than one tile, so that the small ones fill the gaps
-  uint32_t blocks = 0, tiles = 0, nbig = 0, shared = 0;
+  // the middle tensors, whose three passes go together; those of the one launch:
+  // of several tiles, then the small ones, which fill the gaps; the large ones
+  ManyPlan plan = {};
+  uint64_t wide = 0;  // values of the tensors that exchange among many tiles
+  for (size_t t = 0; t < count; ++t) {
+    const size_t m = quartic_len(ns[t]);
+    if (batch_kind(m, kExchangeTiles) == kMiddle) plan.values += ns[t];
+    if (batch_kind(m, kExchangeTiles) == kShared && batch_kind(m, kManyMinTiles) != kShared)
+      wide += ns[t];
+  }
+  const bool join = wide * 2 * sizeof(float) > kCacheBytes;
+  const uint32_t exchange = join ? kManyMinTiles : kExchangeTiles;
+  if (join) plan.values += wide;
+  plan.lines =
+      (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u && plan.values >= kInPlaceMinValues;
+  uint32_t tiles = 0, shared = 0;
   c->owner.clear();
-  for (int kind = 0; kind < 3; ++kind) {
+  for (int kind = kMiddle; kind <= kLarge; ++kind) {
     for (size_t t = 0; t < count; ++t) {
       const size_t m = quartic_len(ns[t]);
-      const size_t k = ceil_div(m, (size_t)kSmallTile);
-      if (m == 0 || (k > kExchangeTiles ? 0 : (k > 1 ? 1 : 2)) != kind) continue;
+      if (m == 0 || batch_kind(m, exchange) != kind) continue;
+      which.push_back(t);
+      if (kind == kLarge) continue;
       EncDesc e = {};
       e.x = tensors[t];
       e.r = residuals[t];
@@ -949,64 +1035,68 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
       e.n = ns[t];
       e.m = (uint32_t)m;
       e.s = s[t];
-      e.tile0 = tiles;
-      if (kind == 0) {
-        e.blk0 = blocks;
-        e.nblk = batch_absmax_blocks(ns[t] / 4);
-        blocks += e.nblk;
-        ++nbig;
+      if (kind == kMiddle) {
+        e.tile0 = plan.tiles;
+        e.v0 = plan.units;
+        e.cblk0 = plan.compact_blocks;
+        const uint32_t k = (uint32_t)ceil_div(m, (size_t)kEncTile);
+        plan.tiles += k;
+        plan.most_tiles = std::max(plan.most_tiles, k);
+        plan.compact_blocks += (uint32_t)ceil_div(k, (size_t)(kThreads / 64));
+        plan.units += (uint32_t)(ceil_div(ns[t], kManyValues) + 1);
+        ++plan.count;
+      } else {
+        const uint32_t k = small_tiles((uint32_t)m);
+        e.tile0 = tiles;
+        tiles += k;
+        if (kind == kShared) shared = tiles;
+        c->owner.insert(c->owner.end(), k, (uint16_t)(d.size() - plan.count));
       }
-      tiles += (uint32_t)k;
-      if (kind < 2) shared = tiles;
-      c->owner.insert(c->owner.end(), k, (uint16_t)d.size());
       d.push_back(e);
-      which.push_back(t);
     }
   }
-  if (d.empty()) return TLC_OK;
-  if (blocks > c->partials_cap || tiles > c->enc_status_words)
+  if (which.empty()) return TLC_OK;
+  // the groups of blocks that a middle tensor's units fall to (for_many)
+  plan.groups = 1;
+  while (2 * plan.groups <= std::min(plan.count, kManyMaxGroups)) plan.groups *= 2;
+  const uint32_t per = kAbsmaxMaxBlocks / plan.groups;  // partial maxima of a group and tensor
+  const auto group_of = [&](uint32_t u) {
+    uint32_t g = (uint32_t)((uint64_t)u * plan.groups / plan.units);
+    while (g + 1 < plan.groups && (uint64_t)plan.units * (g + 1) / plan.groups <= u) ++g;
+    return g;
+  };
+  for (uint32_t i = 0; i < plan.count; ++i) {
+    const uint32_t end = i + 1 < plan.count ? d[i + 1].v0 : plan.units;
+    const uint32_t g0 = group_of(d[i].v0), g1 = group_of(end - 1);
+    d[i].blk0 = (g0 + i) * per;
+    d[i].nblk = (g1 - g0 + 1) * per;
+  }
+  if ((plan.count + plan.groups) * per > c->partials_cap || tiles > c->enc_status_words)
     return fail(TLC_E_INVALID, "tlc_compress_batch: batch exceeds the context's workspace");
   DeviceScope dev(c->device);
   st = dev.status();
   if (st) return st;
-  const uint32_t cnt = (uint32_t)d.size();
+  const uint32_t cnt = (uint32_t)which.size();
+  const uint32_t few = (uint32_t)d.size() - plan.count;  // tensors of the one launch
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
-  const EncDesc* descs = c->enc_descs;
-  const uint16_t* owner = nullptr;
-  if (nbig) {
-    st = upload(c, c->enc_descs, d.data(), cnt * sizeof(EncDesc));
-    if (st) return st;
-  }
-  {
-    // every block reads one descriptor, once: straight from the pinned copy,
-    // which is free again when the call returns (every result needs its own)
-    const EncDesc* pinned = nullptr;
-    int slot = 0;
-    st = stage(c, d.data(), cnt * sizeof(EncDesc), c->owner.data(),
-               c->owner.size() * sizeof(uint16_t), (const void**)&pinned, (const void**)&owner,
-               &slot);
-    if (st) return st;
-    if (!nbig) descs = pinned;
-  }
+  const HostMirror hm = batch_mirror(c);
   arm_results(c->host_results, cnt);
-  if (nbig) {
-    st = timed_launch(c, in_place ? TLC_KERNEL_ABSMAX_BATCH : TLC_KERNEL_ABSMAX_CHECK_BATCH, [&] {
-      return launch_absmax_batch(descs, nbig, blocks, in_place, c->partials_chk, c->stream);
-    });
+  if (few) {  // first: the others' launches are issued while it runs
+    st = launch_few(c, d.data() + plan.count, few, shared, tiles, in_place, plan.count, hm);
     if (st) return st;
   }
-  uint32_t epoch = 0;
-  st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, 2 * c->enc_status_words, nullptr,
-                  &epoch);
-  if (st) return st;
-  st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_BATCH, [&] {
-    return launch_quant_encode_batch(descs, shared, owner, tiles, in_place, c->partials_chk,
-                                     c->enc_results, c->enc_status,
-                                     c->enc_status + c->enc_status_words, c->enc_ticket_base,
-                                     epoch, c->ctrl, batch_mirror(c), c->stream);
-  });
-  if (st) return st;
-  c->enc_ticket_base += shared;
+  if (plan.count) {
+    st = upload(c, c->enc_descs, d.data(), plan.count * sizeof(EncDesc));
+    if (st) return st;
+    st = launch_many_passes(c, plan, in_place, hm);
+    if (st) return st;
+  }
+  for (uint32_t i = (uint32_t)d.size(); i < cnt; ++i) {
+    const size_t t = which[i];
+    st = launch_three_passes(c, tensors[t], residuals[t], ns[t], s[t], bytes[t],
+                             HostMirror{hm.res + i, hm.fault});
+    if (st) return st;
+  }
   st = wait_results(c, c->host_results, cnt);
   if (st) return st;
   if (c->rb->fault) {
@@ -1026,8 +1116,8 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
     }
   }
   if (worst) {
-    // a refused tensor with a max pass is reported by its last tile, which
-    // waits for no other: blocks yet to start still read the pinned slot
+    // a refused tensor is reported as soon as its maxima are known: blocks yet
+    // to start still read the pinned slot
     st = sync_mirrored(c);
     if (st) return st;
     fail(worst, "tlc_compress_batch: NaN/Inf or overflow in at least one tensor");

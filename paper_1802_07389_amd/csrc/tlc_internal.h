@@ -24,8 +24,7 @@ constexpr int kEncTile = 4096;            // quartic bytes per encoder tile
 constexpr int kDecRange = 4096;           // quartic bytes per expand/dequantize block
 // Encoder tiles of small tensors and batches: 256 threads of eight quartic
 // bytes.  The tiles of a tensor of at most kExchangeTiles (1,310,720 values)
-// exchange their maxima and summaries among themselves; a longer one has a
-// check pass and a look-back.
+// exchange their maxima and summaries among themselves.
 constexpr int kTileThreads = kThreads;
 constexpr int kTileGroups = 2;
 constexpr uint32_t kSmallTile = kTileThreads * kTileGroups * 4;  // 2048 quartic bytes
@@ -35,6 +34,7 @@ inline uint32_t small_tiles(uint32_t m) { return (m + kSmallTile - 1) / kSmallTi
 // (no waits between tiles); smaller ones, whose tiles can exchange what they
 // need (kExchangeTiles of half the size), a single launch.
 constexpr uint32_t kThreePassMinTiles = kExchangeTiles / 2 + 1;
+constexpr uint64_t kCacheBytes = 256ull << 20;  // the last-level cache
 constexpr uint32_t kAbsmaxMaxBlocks = 256;  // partial maxima per encode (one block per CU)
 // Up to this many tiles the compaction finds its prefixes without the chunk
 // pass: two summaries per thread.
@@ -85,7 +85,26 @@ struct HostMirror {
   uint32_t* corrupt = nullptr;
 };
 
-// One tensor of a batched encode (device copy of the host's description).
+// A batch's tensors of more than kExchangeTiles small tiles and at most
+// kManyMaxTiles of kEncTile (41,943,040 values) go through the three passes
+// together: their trits and bounds start at multiples of kManyValues values of
+// the workspace, with as many to spare after each (trit words are read past
+// the end).  Larger ones go one after the other: their passes fill the chip.
+// (One after the other, four of 12M values took 225 us, together 196.)
+// Tensors of kManyMinTiles to kExchangeTiles small tiles join them where they
+// don't fit the last-level cache together: the one launch holds a tile's
+// values in registers while it waits, which costs more than the check pass's
+// second read once the chip is full (64 tensors of 1M values: 265 us; before
+// the exchange, in place, 235).
+constexpr uint32_t kManyMaxTiles = 2048;
+constexpr uint32_t kManyMinTiles = 32;
+constexpr uint32_t kManyValues = 1024;
+// Groups of blocks over them: as many as tensors, rounded down to a power of
+// two, and at most this (130 tensors of 1M values: 16 groups 483 us, 32 474, 64
+// 491, 256 554).
+constexpr uint32_t kManyMaxGroups = 32;
+
+// One tensor of a batched encode.
 struct EncDesc {
   const float* x;
   float* r;
@@ -94,9 +113,12 @@ struct EncDesc {
   uint32_t m;
   float s;
   uint32_t tile0;  // first encoder tile (global tile numbering of the launch)
-  uint32_t blk0;   // first absmax block / partial maximum of this tensor
-  uint32_t nblk;   // absmax blocks of this tensor
-  uint32_t pad[3];
+  // the three passes only:
+  uint32_t blk0;   // first partial maximum of the max pass
+  uint32_t nblk;   // how many
+  uint32_t v0;     // first trit, in kManyValues
+  uint32_t cblk0;  // first block of the compaction
+  uint32_t pad;
 };
 static_assert(sizeof(EncDesc) == 64, "EncDesc is 64 bytes");
 
@@ -162,9 +184,10 @@ hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint3
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, uint16_t* bound, hipStream_t st);
 // Eq. 2 for a large tensor: final residuals in r and 2-bit trits, one byte per
-// four values.  After the check pass (its partials): from x + r; in place
-// (the max pass's partials and bounds): from r.
-hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s,
+// four values.  After the check pass (its partials): from x + r (in_place: a
+// refused tensor is left with the sums); after the in-place max pass (its
+// partials and bounds): from r.
+hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s, bool in_place,
                                  const uint32_t* partials, uint32_t np, uint8_t* trits,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st);
 hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* partials,
@@ -198,17 +221,24 @@ hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s, bool
                              Ctrl* ctrl, HostMirror hm, hipStream_t st);
 hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out,
                                int accumulate, hipStream_t st);
-// The max pass of the first `count` tensors (those of more than kExchangeTiles
-// tiles): the check pass or, in place, step 1 into the buffers.
-hipError_t launch_absmax_batch(const EncDesc* descs, uint32_t count, uint32_t total_blocks,
-                               bool in_place, uint32_t* partials, hipStream_t st);
+// Pass 0 (max), 1 (quantize), 2 (tiles) or 3 (compaction) of a batch's middle
+// tensors; descs in device memory, results by descriptor.
+struct ManyPlan {
+  uint32_t count, tiles, compact_blocks, most_tiles;
+  uint32_t units, groups;  // kManyValues each; equal shares of them (a power of two)
+  uint64_t values;
+  bool lines;  // the in-place max pass and lines, not the check and writing pass
+};
+hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_place,
+                              uint32_t* partials, uint16_t* bound, uint8_t* trits, uint8_t* slots,
+                              TileRec* recs, EncResult* results, HostMirror hm, int pass,
+                              hipStream_t st);
 // owner: the tensor of each of the `tiles` tiles; the first `shared` are those
-// of tensors of more than one.  partials: the max pass's.
+// of tensors of more than one.
 hipError_t launch_quant_encode_batch(const EncDesc* descs, uint32_t shared, const uint16_t* owner,
-                                     uint32_t tiles, bool in_place, const uint32_t* partials,
-                                     EncResult* results, uint64_t* status, uint64_t* maxima,
-                                     uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl,
-                                     HostMirror hm, hipStream_t st);
+                                     uint32_t tiles, bool in_place, EncResult* results,
+                                     uint64_t* status, uint64_t* maxima, uint32_t ticket_base,
+                                     uint32_t epoch, Ctrl* ctrl, HostMirror hm, hipStream_t st);
 // One stream's decode.  Small decodes (at most kFusedMaxBlocks blocks in
 // all, so every block is resident at once) run in one launch: the first
 // blocks scan the stream (kZreBatchTile bytes each), the others expand.
