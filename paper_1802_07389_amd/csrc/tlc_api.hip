@@ -133,7 +133,6 @@ struct tlc_ctx {
   size_t start_words = 0;
   EncDesc* enc_descs = nullptr;
   DecDesc* dec_descs = nullptr;
-  uint16_t* dec_owner = nullptr;  // the stream of each scan tile of a summed decode
   EncResult* enc_results = nullptr;
   // single-tensor encoder: per-tile slots and records, chunk summaries
   uint8_t* slots = nullptr;
@@ -146,7 +145,7 @@ struct tlc_ctx {
   HostReadback* rb = nullptr;
   EncResult* host_results = nullptr;
   HostReadback* rb_dev = nullptr;  // the same pinned memory, as the device addresses it
-  uint8_t* staging = nullptr;  // kStagingSlots slots: descriptors, then the tiles' owners
+  uint8_t* staging = nullptr;  // kStagingSlots slots: a call's descriptors, then its tiles' owners
   size_t slot_bytes = 0, owner_cap = 0;
   uint8_t* staging_dev = nullptr;  // the same, as the device addresses it
   hipEvent_t staging_done[kStagingSlots] = {};
@@ -325,9 +324,8 @@ int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes, const void* own
   int st = take_slot(c, src, bytes, &slot);
   if (st) return st;
   if (own_bytes) {
-    const size_t off = c->max_tensors * 64;
-    memcpy(c->staging + (size_t)slot * c->slot_bytes + off, own, own_bytes);
-    bytes = off + own_bytes;
+    memcpy(c->staging + (size_t)slot * c->slot_bytes + bytes, own, own_bytes);
+    bytes += own_bytes;
   }
   const uint8_t* host = c->staging + (size_t)slot * c->slot_bytes;
   hipError_t e = hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, c->stream);
@@ -348,10 +346,10 @@ int stage(tlc_ctx* c, const void* src, size_t bytes, const void* own, size_t own
           const void** dev, const void** dev_own, int* slot) {
   int st = take_slot(c, src, bytes, slot);
   if (st) return st;
-  const size_t at = (size_t)*slot * c->slot_bytes, off = c->max_tensors * 64;
-  memcpy(c->staging + at + off, own, own_bytes);
+  const size_t at = (size_t)*slot * c->slot_bytes;
+  memcpy(c->staging + at + bytes, own, own_bytes);
   *dev = c->staging_dev + at;
-  *dev_own = c->staging_dev + at + off;
+  *dev_own = c->staging_dev + at + bytes;
   return TLC_OK;
 }
 
@@ -534,7 +532,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->owner_cap = std::max(c->enc_status_words, c->start_words + c->dec_status_words);
   c->slot_bytes = round_up(max_tensors * 64 + c->owner_cap * sizeof(uint16_t), 64);
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
-  //         start | enc descs | dec descs | scan tiles' owners | tile records | chunk summaries |
+  //         start | enc descs | dec descs, owners | tile records | chunk summaries |
   //         tile prefixes in their chunks | line bounds | trits | slots
   // (the batch results follow the control block, so that one copy reads both)
   static_assert(sizeof(Ctrl) % alignof(EncResult) == 0, "results follow the control block");
@@ -553,8 +551,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   const size_t off_edesc = off;
   off = round_up(off + max_tensors * sizeof(EncDesc), 256);
   const size_t off_ddesc = off;
-  // (as in a staging slot: the owners follow max_tensors descriptors)
-  off = round_up(off + max_tensors * sizeof(DecDesc) + c->dec_status_words * sizeof(uint16_t), 256);
+  off = round_up(off + c->slot_bytes, 256);  // as in a staging slot
   const size_t off_recs = off;
   off = round_up(off + tiles2 * sizeof(TileRec), 256);
   const size_t off_chunks = off;
@@ -581,7 +578,6 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->start = (uint64_t*)(base + off_start);
   c->enc_descs = (EncDesc*)(base + off_edesc);
   c->dec_descs = (DecDesc*)(base + off_ddesc);
-  c->dec_owner = (uint16_t*)(base + off_ddesc + max_tensors * sizeof(DecDesc));
   c->enc_results = (EncResult*)(base + off_res);
   c->recs = (TileRec*)(base + off_recs);
   c->chunk_agg = (uint64_t*)(base + off_chunks);
@@ -1376,7 +1372,7 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
               c->owner.size() * sizeof(uint16_t));
   if (st) return st;
-  const uint16_t* owner = c->dec_owner;
+  const uint16_t* owner = (const uint16_t*)(c->dec_descs + cnt);
   uint32_t epoch = 0;
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
