@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_index_kernel(
                                  hm.corrupt, sh);
 }
 
-// Reads descriptor t once for the block (it may lie in host memory) and gives
+// Reads descriptor t once for the block (it lies in host memory) and gives
 // every thread its fields as scalars.  Holds a barrier.
 __device__ __forceinline__ DecDesc block_desc(const DecDesc* __restrict__ descs, uint32_t t,
                                               DecDesc* lds) {
@@ -217,28 +217,46 @@ __device__ __forceinline__ DecDesc block_desc(const DecDesc* __restrict__ descs,
   return d;
 }
 
+// The descriptor of the stream that item `key` (a scan tile, a range) of the
+// batch belongs to.  kPinned: owner says whose it is, both in host memory.
+// (With hundreds of streams a search over the descriptors took nine dependent
+// loads.)  Otherwise, few streams, by a search in device memory.
+template <bool kPinned, class F>
+__device__ __forceinline__ DecDesc owner_desc(const DecDesc* __restrict__ descs, uint32_t count,
+                                              const uint16_t* __restrict__ owner, uint32_t key,
+                                              F first, DecDesc* lds) {
+  if constexpr (kPinned) return block_desc(descs, owner[key], lds);
+  DecDesc d = descs[find_desc(descs, count, key, first)];
+  d.C = uniform_ptr(d.C);
+  d.out = uniform_ptr(d.out);
+  return d;
+}
+
 // One scan tile per block.  kOneTile: every stream has one (the common batch),
 // so that block t is stream t's and waits for nobody; otherwise tiles are
-// taken from the ticket, and owner says whose each is.  (A binary search over
-// the descriptors took nine dependent loads.)
-template <bool kOneTile, int kBytes>
+// taken from the ticket.
+template <bool kOneTile, bool kPinned, int kBytes>
 __global__ __launch_bounds__(kThreads) void tlc_zre_index_batch_kernel(
-    const DecDesc* __restrict__ descs, const uint16_t* __restrict__ owner,
+    const DecDesc* __restrict__ descs, uint32_t count, const uint16_t* __restrict__ owner,
     uint64_t* __restrict__ start, uint64_t* __restrict__ status, uint32_t ticket_base,
     uint32_t epoch, Ctrl* __restrict__ ctrl, HostMirror hm) {
   __shared__ IdxShared sh;
   __shared__ uint32_t s_tile;
   __shared__ DecDesc s_desc;
-  uint32_t T = blockIdx.x, t = T;
+  uint32_t T = blockIdx.x;
   if (!kOneTile) {
     if (threadIdx.x == 0) s_tile = take_ticket(&ctrl->dec_ticket) - ticket_base;
     __syncthreads();
     T = uniform32(s_tile);
-    t = owner[T];
   }
-  const DecDesc d = block_desc(descs, t, &s_desc);
-  index_tile<kBytes>(d.C, d.c, d.m, start + d.range0, status, d.tile0,
-                                      T - d.tile0, epoch, ctrl, hm.fault, hm.corrupt, sh);
+  DecDesc d;
+  if constexpr (kOneTile)
+    d = block_desc(descs, T, &s_desc);
+  else
+    d = owner_desc<kPinned>(descs, count, owner, T, [](const DecDesc& e) { return e.tile0; },
+                            &s_desc);
+  index_tile<kBytes>(d.C, d.c, d.m, start + d.range0, status, d.tile0, T - d.tile0, epoch, ctrl,
+                     hm.fault, hm.corrupt, sh);
 }
 
 // ---------------------------------------------------------------- expansion
@@ -633,16 +651,17 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
   }
 }
 
-// One range per block; owner: whose it is.
-template <bool kAcc>
+// One range per block.
+template <bool kAcc, bool kPinned>
 __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_batch_kernel(
-    const DecDesc* __restrict__ descs, const uint16_t* __restrict__ owner,
+    const DecDesc* __restrict__ descs, uint32_t count, const uint16_t* __restrict__ owner,
     const uint64_t* __restrict__ start, uint32_t epoch, const Ctrl* __restrict__ ctrl) {
   __shared__ uint32_t red[kWaves];
   __shared__ DecDesc s_desc;
   __shared__ __align__(16) uint8_t s_q[kDecRange];
   if (ctrl->dec_bad_epoch == epoch) return;  // a corrupt stream: no output written
-  const DecDesc d = block_desc(descs, owner[blockIdx.x], &s_desc);
+  const DecDesc d = owner_desc<kPinned>(descs, count, owner, blockIdx.x,
+                                        [](const DecDesc& e) { return e.range0; }, &s_desc);
   const uint32_t k = blockIdx.x - d.range0;
   const uint64_t q0 = (uint64_t)k * kDecRange;
   const uint32_t qn = (uint32_t)umin64(kDecRange, (uint64_t)d.m - q0);
@@ -904,28 +923,34 @@ hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, const ui
                                   uint32_t tiles, bool wide, uint64_t* start, uint64_t* status,
                                   uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl, HostMirror hm,
                                   hipStream_t st) {
-#define TLC_LAUNCH(O, B)                                                                     \
-  launch_k(tlc_zre_index_batch_kernel<O, B>, tiles, kThreads, st, descs, owner, start, status, \
-           ticket_base, epoch, ctrl, hm)
+#define TLC_LAUNCH(O, P, B)                                                                  \
+  launch_k(tlc_zre_index_batch_kernel<O, P, B>, tiles, kThreads, st, descs, count, owner, start, \
+           status, ticket_base, epoch, ctrl, hm)
+  constexpr int kWide = kZreBytesPerThread, kShort = kZreBatchBytesPerThread;
   if (tiles == count) {
-    if (wide) TLC_LAUNCH(true, kZreBytesPerThread); else TLC_LAUNCH(true, kZreBatchBytesPerThread);
+    if (wide) TLC_LAUNCH(true, true, kWide); else TLC_LAUNCH(true, true, kShort);
+  } else if (owner) {
+    if (wide) TLC_LAUNCH(false, true, kWide); else TLC_LAUNCH(false, true, kShort);
   } else {
-    if (wide) TLC_LAUNCH(false, kZreBytesPerThread); else TLC_LAUNCH(false, kZreBatchBytesPerThread);
+    if (wide) TLC_LAUNCH(false, false, kWide); else TLC_LAUNCH(false, false, kShort);
   }
 #undef TLC_LAUNCH
   return hipGetLastError();
 }
 
-hipError_t launch_expand_dequant_batch(const DecDesc* descs, const uint16_t* owner,
+hipError_t launch_expand_dequant_batch(const DecDesc* descs, uint32_t count, const uint16_t* owner,
                                        uint32_t total_ranges, const uint64_t* start,
                                        int accumulate, uint32_t epoch, const Ctrl* ctrl,
                                        hipStream_t st) {
-  if (accumulate)
-    launch_k(tlc_expand_dequant_batch_kernel<true>, total_ranges, kThreads, st, descs, owner,
-             start, epoch, ctrl);
-  else
-    launch_k(tlc_expand_dequant_batch_kernel<false>, total_ranges, kThreads, st, descs, owner,
-             start, epoch, ctrl);
+#define TLC_LAUNCH(A, P)                                                                      \
+  launch_k(tlc_expand_dequant_batch_kernel<A, P>, total_ranges, kThreads, st, descs, count, owner, \
+           start, epoch, ctrl)
+  if (owner) {
+    if (accumulate) TLC_LAUNCH(true, true); else TLC_LAUNCH(false, true);
+  } else {
+    if (accumulate) TLC_LAUNCH(true, false); else TLC_LAUNCH(false, false);
+  }
+#undef TLC_LAUNCH
   return hipGetLastError();
 }
 

@@ -1160,6 +1160,14 @@ uint32_t place_scan_tiles(std::vector<DecDesc>& d, bool wide) {
   return (uint32_t)tiles;
 }
 
+// Fewer streams than this, some of several scan tiles: their blocks search the
+// descriptors in device memory.  Two dependent reads of host memory per block
+// (owner, descriptor) cost such a batch more than the copy (one stream of 1M
+// values 20.0 against 17.9 us, four of 2.6M 27.0 against 24.4); with more
+// streams, or one scan tile for each, the copy and the search cost more (ten of
+// 2M 36.8 against 35.3, 100 of 2,000 20.1 against 14.5).
+constexpr uint32_t kUploadStreams = 10;
+
 // Appends the stream of each scan tile to the call's owners.
 void add_scan_owners(tlc_ctx* c, const std::vector<DecDesc>& d, uint32_t tiles) {
   for (size_t i = 0; i < d.size(); ++i)
@@ -1292,33 +1300,38 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   st = dev.status();
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
-  // whose each range is, then (unless every stream has one) each scan tile
-  c->owner.clear();
-  for (uint32_t i = 0; i < cnt; ++i)
-    c->owner.insert(c->owner.end(), ceil_div(d[i].m, (size_t)kDecRange), (uint16_t)i);
-  if (tiles != cnt) add_scan_owners(c, d, tiles);
-  const DecDesc* descs = nullptr;
+  const DecDesc* descs = c->dec_descs;
   const uint16_t* owner = nullptr;
-  int slot = 0;
-  st = stage(c, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
-             c->owner.size() * sizeof(uint16_t), (const void**)&descs, (const void**)&owner, &slot);
+  int slot = -1;
+  if (tiles != cnt && cnt < kUploadStreams) {
+    st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc));
+  } else {
+    // whose each range is, then (unless every stream has one) each scan tile
+    c->owner.clear();
+    for (uint32_t i = 0; i < cnt; ++i)
+      c->owner.insert(c->owner.end(), ceil_div(d[i].m, (size_t)kDecRange), (uint16_t)i);
+    if (tiles != cnt) add_scan_owners(c, d, tiles);
+    st = stage(c, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
+               c->owner.size() * sizeof(uint16_t), (const void**)&descs, (const void**)&owner,
+               &slot);
+  }
   if (st) return st;
   uint32_t epoch = 0;
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
   st = timed_launch(c, TLC_KERNEL_ZRE_INDEX_BATCH, [&] {
-    return launch_zre_index_batch(descs, cnt, owner + ranges, tiles, wide, c->start,
+    return launch_zre_index_batch(descs, cnt, owner ? owner + ranges : nullptr, tiles, wide, c->start,
                                   c->dec_status, c->dec_ticket_base, epoch, c->ctrl, fault_mirror(c),
                                   c->stream);
   });
   if (st) return st;
   if (tiles != cnt) c->dec_ticket_base += tiles;
   st = timed_launch(c, TLC_KERNEL_EXPAND_DEQUANT_BATCH, [&] {
-    return launch_expand_dequant_batch(descs, owner, ranges, c->start, accumulate, epoch, c->ctrl,
-                                       c->stream);
+    return launch_expand_dequant_batch(descs, cnt, owner, ranges, c->start, accumulate, epoch,
+                                       c->ctrl, c->stream);
   });
   if (st) return st;
-  return hold_slot(c, slot);
+  return slot < 0 ? TLC_OK : hold_slot(c, slot);
 }
 
 TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* bytes,

@@ -270,7 +270,8 @@ hipError_t launch_expand_dequant(const uint8_t* C, uint32_t c, uint64_t* start,
                                  float scale, float* out, int accumulate, uint32_t epoch,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st);
 // owner: the stream of each scan tile (not read when every stream has one),
-// of each range.  wide: tiles of kZreTile stream bytes where the streams
+// of each range, in host memory as the descriptors; null: few streams, their
+// descriptors in device memory.  wide: tiles of kZreTile stream bytes where the streams
 // average more than four of the smaller tiles (16 streams of 366 KB: 10.1
 // against 15.0 us), else of kZreBatchTile (streams that mostly fit one tile).
 inline bool batch_scan_wide(uint64_t stream_bytes, uint64_t count) {
@@ -280,7 +281,7 @@ hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, const ui
                                   uint32_t tiles, bool wide, uint64_t* start, uint64_t* status,
                                   uint32_t ticket_base, uint32_t epoch, Ctrl* ctrl, HostMirror hm,
                                   hipStream_t st);
-hipError_t launch_expand_dequant_batch(const DecDesc* descs, const uint16_t* owner,
+hipError_t launch_expand_dequant_batch(const DecDesc* descs, uint32_t count, const uint16_t* owner,
                                        uint32_t total_ranges, const uint64_t* start,
                                        int accumulate, uint32_t epoch, const Ctrl* ctrl,
                                        hipStream_t st);

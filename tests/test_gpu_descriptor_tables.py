@@ -52,3 +52,25 @@ def test_capacity_costs_nothing():
         assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32))
     print(took, flush=True)
     assert took[65536] < 1.6 * took[P]
+
+
+@pytest.mark.parametrize("count", [1, 2, 9, 10, 11])
+def test_few_streams_of_several_tiles(count):
+    """Counts on both sides of the line between the two ways, calls of other
+    counts between them on the same context."""
+    import torch
+
+    import gpuutil as g
+    from paper_1802_07389_amd import tlc
+    with tlc.Context(max_n=20_000_000, max_tensors=40) as ctx:
+        for k in (count, 12, count, 1):
+            ns = [300 if t == 1 else 900_001 + 37_003 * t for t in range(k)]
+            data = [stream(20 + t, n) for t, n in enumerate(ns)]
+            o0 = [workloads.normal([112, t], n) for t, n in enumerate(ns)]
+            outs = [g.to_dev(o, t % 4) for t, o in enumerate(o0)]
+            ctx.decompress_batch([torch.from_numpy(c).cuda() for c, _ in data],
+                                 [m for _, m in data], outs, accumulate=True)
+            ctx.sync()
+            for (c, m), n, o, before in zip(data, ns, outs, o0):
+                _, ref = oracle.decompress(c, m, n, before.copy(), True)
+                assert np.array_equal(g.bits(o.cpu().numpy()), g.bits(ref))
