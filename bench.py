@@ -241,7 +241,8 @@ def config_rows(torch, tlc, workloads, dev, parts=PARTS):
         out = torch.zeros_like(x)
         buf = torch.empty(x.numel(), dtype=torch.uint8, device=dev)
         modes = [("No ZRE", tlc.TLC_MODE_NO_ZRE, workloads.C4_S,
-                  (tlc.TLC_KERNEL_QUANT_PACK, tlc.TLC_KERNEL_EXPAND_DEQUANT)),
+                  (tlc.TLC_KERNEL_ACCUM_QUANTIZE, tlc.TLC_KERNEL_QUANT_PACK,
+                   tlc.TLC_KERNEL_EXPAND_DEQUANT)),
                  ("Stoch 3-value + QE", tlc.TLC_MODE_STOCHASTIC, 1.0,
                   (tlc.TLC_KERNEL_QUANT_PACK, tlc.TLC_KERNEL_EXPAND_DEQUANT)),
                  ("8-bit int", tlc.TLC_MODE_INT8, 1.0,

@@ -345,14 +345,14 @@ __device__ __forceinline__ uint32_t expand_range(const uint8_t* __restrict__ C, 
 }
 
 // ---------------------------------------------------------------- Eq. 3
-// Partition K of quartic bytes s_q[0, qn) (global bytes q0 + jl) when out
-// is 16-byte aligned: the partition starts a = (K*m + q0) mod 4 values past
-// a float4 boundary (a = 0 when m % 4 == 0), and cell f of its aligned
-// float4 grid takes digit K of bytes 4f - a .. 4f + 3 - a (two LDS words).
-// Cells shared with a neighbouring range or partition, or reaching past n,
-// are written value by value.  The block sweeps one partition at a time.
-// kNT: the full cells use nontemporal loads and stores.  That pays when out
-// is far larger than the 256 MB last-level cache: on gfx950 the hinted
+// Partition K of quartic bytes s_q[0, qn) (global bytes q0 + jl) of a large
+// output on the 16-byte grid (kNtMinBytes): the partition starts
+// a = (K*m + q0) mod 4 values past a float4 boundary (a = 0 when m % 4 == 0),
+// and cell f of its float4 grid takes digit K of bytes 4f - a .. 4f + 3 - a
+// (two LDS words).  Cells shared with a neighbouring range or partition, or
+// reaching past n, are written value by value.  The block sweeps one partition
+// at a time; the full cells use nontemporal loads and stores.  That pays when
+// out is far larger than the 256 MB last-level cache: on gfx950 the hinted
 // sweep then beat the plain one and five-partition float4 groups, and its
 // stores leave no dirty lines for the next encode to write back.  Outputs
 // that fit the cache decode faster with plain accesses.
@@ -368,7 +368,7 @@ constexpr uint32_t kDenseLiterals = kDecRange / 4;
 // The kAcc loads of partition K's full cells (the cells the sweep below
 // adds to), issued before the range's zero-run expansion so that their
 // latency overlaps it.
-template <int K, bool kNT>
+template <int K>
 __device__ __forceinline__ void sweep_preload(uint64_t q0, uint32_t qn, uint64_t n, uint64_t m,
                                               const float* __restrict__ out,
                                               float4 (&o)[kSweepCells]) {
@@ -380,12 +380,11 @@ __device__ __forceinline__ void sweep_preload(uint64_t q0, uint32_t qn, uint64_t
   for (int i = 0; i < kSweepCells; ++i) {
     const uint32_t f = threadIdx.x + kThreads * i;
     if (f < nf && 4u * f >= a && 4u * f + 4u <= qn + a && e0 + 4ull * f + 4u <= n)
-      o[i] = kNT ? ld_stream(out + e0 + 4ull * f)
-                 : *reinterpret_cast<const float4*>(out + e0 + 4ull * f);
+      o[i] = ld_stream(out + e0 + 4ull * f);
   }
 }
 
-template <int K, bool kAcc, bool kNT, bool kPre = false>
+template <int K, bool kAcc, bool kPre = false>
 __device__ __forceinline__ void dequant_partition_shifted(const uint8_t* s_q, uint64_t q0,
                                                           uint32_t qn, uint64_t n, uint64_t m,
                                                           float M, float* __restrict__ out,
@@ -405,11 +404,7 @@ __device__ __forceinline__ void dequant_partition_shifted(const uint8_t* s_q, ui
     const uint32_t f = threadIdx.x + kThreads * i;
     full[i] = f < nf && 4u * f >= a && 4u * f + 4u <= qn + a && e0 + 4ull * f + 4u <= n;
     if (kAcc && full[i]) {
-      if (kPre)
-        o[i] = pre[i];
-      else
-        o[i] = kNT ? ld_stream(out + e0 + 4ull * f)
-                   : *reinterpret_cast<const float4*>(out + e0 + 4ull * f);
+      o[i] = kPre ? pre[i] : ld_stream(out + e0 + 4ull * f);
     }
   }
 #pragma unroll
@@ -432,12 +427,7 @@ __device__ __forceinline__ void dequant_partition_shifted(const uint8_t* s_q, ui
         o[i] = make_float4(trit_value(d[0], M), trit_value(d[1], M), trit_value(d[2], M),
                            trit_value(d[3], M));
       }
-      if (store) {
-        if (kNT)
-          st_stream(out + e, o[i]);
-        else
-          *reinterpret_cast<float4*>(out + e) = o[i];
-      }
+      if (store) st_stream(out + e, o[i]);
     } else {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -464,11 +454,11 @@ __device__ __forceinline__ void dequant_range(const uint8_t* s_q, uint64_t q0, u
                                               uint64_t n, uint64_t m, float M,
                                               float* __restrict__ out, bool dense) {
   if (kNT) {
-    dequant_partition_shifted<0, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<1, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<2, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<3, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<4, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<0, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<1, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<2, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<3, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<4, kAcc>(s_q, q0, qn, n, m, M, out, dense);
   } else {
 #pragma unroll
     for (int g = 0; g < kDecRange / (4 * kThreads); ++g) {
@@ -609,8 +599,8 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
   // fit the cache gained nothing)
   float4 p0[kPre ? kSweepCells : 1], p1[kPre ? kSweepCells : 1];
   if constexpr (kPre) {
-    sweep_preload<0, kNT>(q0, qn, n, m, out, p0);
-    sweep_preload<1, kNT>(q0, qn, n, m, out, p1);
+    sweep_preload<0>(q0, qn, n, m, out, p0);
+    sweep_preload<1>(q0, qn, n, m, out, p1);
   }
   Slice sl;
   if constexpr (kFused) {
@@ -641,11 +631,11 @@ __global__ __launch_bounds__(kThreads) void tlc_expand_dequant_kernel(
     if (!s_ok) return;  // a corrupt stream: out untouched
   }
   if constexpr (kPre) {
-    dequant_partition_shifted<0, kAcc, kNT, true>(s_q, q0, qn, n, m, M, out, dense, p0);
-    dequant_partition_shifted<1, kAcc, kNT, true>(s_q, q0, qn, n, m, M, out, dense, p1);
-    dequant_partition_shifted<2, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<3, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
-    dequant_partition_shifted<4, kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<0, kAcc, true>(s_q, q0, qn, n, m, M, out, dense, p0);
+    dequant_partition_shifted<1, kAcc, true>(s_q, q0, qn, n, m, M, out, dense, p1);
+    dequant_partition_shifted<2, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<3, kAcc>(s_q, q0, qn, n, m, M, out, dense);
+    dequant_partition_shifted<4, kAcc>(s_q, q0, qn, n, m, M, out, dense);
   } else {
     dequant_range<kAcc, kNT>(s_q, q0, qn, n, m, M, out, dense);
   }

@@ -159,15 +159,16 @@ __device__ __forceinline__ void st_word(uint8_t* p, uint32_t w) {
   *reinterpret_cast<tlc_u4b*>(p) = w;
 }
 
-// The same as streaming accesses, with the
-// nontemporal hint, for tensors read or written once per kernel and far
+// The same as streaming accesses, with the nontemporal hint, for tensors read or written once per kernel and far
 // larger than the caches.  Measured on gfx950: the max reduction reads
 // 25 % faster with it, the 8-bit kernels (contiguous read/write streams,
 // both sides hinted) 10-15 % faster, and the decoder's partition-by-
 // partition sweep gains too (its hinted stores leave no dirty lines for the
-// next encode).  The 3LC encoder hints only its loads of the tensor, which
-// nothing reads again (a C4 round trip 1.5 % faster); hinting its residual
-// loads or stores slowed it or the decode that follows.  The hint changes
+// next encode).  The 3LC encoder's flat passes over large tensors hint
+// their loads and their stores, as nothing in them is read again before the
+// whole tensor has streamed through (the check pass only where the values and
+// the buffer don't fit the last-level cache together); its small tensors,
+// which are read back from the cache, are not hinted.  The hint changes
 // neither values nor visibility: the next kernel on the stream sees the
 // stores.
 __device__ __forceinline__ float4 ld_stream(const float* p) {
@@ -328,16 +329,6 @@ struct SumOp {
   __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a + b; }
 };
 
-__device__ __forceinline__ void unpack16(uint4 v, uint8_t* b) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    b[i] = (uint8_t)(v.x >> (8 * i));
-    b[4 + i] = (uint8_t)(v.y >> (8 * i));
-    b[8 + i] = (uint8_t)(v.z >> (8 * i));
-    b[12 + i] = (uint8_t)(v.w >> (8 * i));
-  }
-}
-
 // Wave scans of segment summaries (zre_scan.hpp), in lane order.
 struct OpRun {
   __device__ __forceinline__ uint64_t operator()(uint64_t a, uint64_t b) const {
@@ -410,9 +401,6 @@ __device__ __forceinline__ void acc_trit_at(float* __restrict__ out, uint64_t e,
   if (__float_as_uint(r) != __float_as_uint(o)) out[e] = r;
 }
 
-// Mask of the non-121 bytes among the 16 quartic bytes q[lo .. lo + cnt)
-// (cnt <= 16; q + lo 16-byte aligned) that one thread holds: bit i for
-// byte lo + i.
 // Four bits: byte i of w differs from 121.  x = w ^ 0x79797979 has a zero
 // byte exactly where w holds 121; bit 7 of ((x & 0x7f..) + 0x7f..) | x is
 // set in every other byte (no carry leaves a byte); the multiply gathers
@@ -424,23 +412,18 @@ __device__ __forceinline__ uint32_t nonzero_byte_mask4(uint32_t w) {
   return ((y >> 7) * 0x00204081u) >> 21 & 0xfu;
 }
 
-__device__ __forceinline__ uint32_t nonzero_mask16(const uint4& w, uint32_t cnt) {
-  static_assert(kZeroGroup == 0x79u, "the mask compares against bytes of 121");
-  const uint32_t nz = nonzero_byte_mask4(w.x) | (nonzero_byte_mask4(w.y) << 4) |
-                      (nonzero_byte_mask4(w.z) << 8) | (nonzero_byte_mask4(w.w) << 12);
-  return cnt >= 16u ? nz : nz & ((1u << cnt) - 1u);
-}
-
-// The same mask in spread form, bit 2i for byte lo + i (rs_gaps_len<2>):
-// the multiply places the four bit-7 flags, shifted to bits 0, 8, 16, 24,
-// at bits 18, 20, 22, 24 (again no two partial products share a bit).
+// The same in spread form, bit 2i for byte i (rs_gaps_len<2>): the multiply
+// places the four bit-7 flags, shifted to bits 0, 8, 16, 24, at bits 18, 20,
+// 22, 24 (again no two partial products share a bit).
 __device__ __forceinline__ uint32_t nonzero_byte_mask4_spread(uint32_t w) {
   const uint32_t x = w ^ 0x79797979u;
   const uint32_t y = (x | ((x & 0x7f7f7f7fu) + 0x7f7f7f7fu)) & 0x80808080u;
   return ((y >> 7) * 0x00041041u) >> 18 & 0x55u;
 }
 
+// The spread mask of the first cnt (<= 16) quartic bytes that one thread holds.
 __device__ __forceinline__ uint32_t nonzero_mask16_spread(const uint4& w, uint32_t cnt) {
+  static_assert(kZeroGroup == 0x79u, "the mask compares against bytes of 121");
   const uint32_t nz = nonzero_byte_mask4_spread(w.x) | (nonzero_byte_mask4_spread(w.y) << 8) |
                       (nonzero_byte_mask4_spread(w.z) << 16) |
                       (nonzero_byte_mask4_spread(w.w) << 24);
@@ -456,11 +439,6 @@ __device__ __forceinline__ uint32_t nonzero_mask_trits(const uint32_t (&d)[5]) {
   const uint32_t z = (d[0] ^ kOnes) | (d[1] ^ kOnes) | (d[2] ^ kOnes) | (d[3] ^ kOnes) |
                      (d[4] ^ kOnes);
   return (z | (z >> 1)) & kOnes;
-}
-
-__device__ __forceinline__ uint32_t nonzero_group_mask(const uint8_t* q, uint32_t lo,
-                                                       uint32_t cnt) {
-  return nonzero_mask16(*reinterpret_cast<const uint4*>(q + lo), cnt);
 }
 
 // Byte i (< 16) of four little-endian words, by selects on the values (an

@@ -1,9 +1,10 @@
 // noalloc.hip -- tlc_compress_noalloc: the encode of tlc_compress for
 // callers that cannot allocate device memory (graph capture, serving
-// loops, harnesses that forbid hipMalloc).  It runs the kernels of the
-// small-tensor path (check pass, then the chained pass that accumulates,
-// quantizes, packs and zero-run encodes; Sections 3.1-3.3) with their
-// scratch in a file-scope device array instead of a context's workspace.
+// loops, harnesses that forbid hipMalloc).  It runs the one launch of the
+// small-tensor path (accumulate, quantize, pack and zero-run encode; Sections
+// 3.1-3.3), for tensors of more than kExchangeTiles tiles after the check pass
+// and chained by look-back, with their scratch in a file-scope device array
+// instead of a context's workspace.
 #include <mutex>
 
 #include "tlc.h"
@@ -15,16 +16,14 @@ namespace tlc {
 namespace {
 
 // Scratch layout: the control block (tile ticket, encode result, fault
-// flag), the check pass's partial maxima (at most kAbsmaxMaxBlocks; the
-// next kAbsmaxMaxBlocks words are spare), then one look-back status word
-// per encoder tile
-// (n <= TLC_NOALLOC_MAX_N gives at most 820 tiles), two spare words and one
-// word per tile for the maxima of at most kExchangeTiles tiles.
+// flag), the check pass's partial maxima (at most kAbsmaxMaxBlocks), then one
+// status word per encoder tile (n <= TLC_NOALLOC_MAX_N gives at most 820
+// tiles), two spare words and one word per tile for the maxima of at most
+// kExchangeTiles tiles.
 constexpr uint32_t kNoallocMaxTiles =
     (uint32_t)(((TLC_NOALLOC_MAX_N + 4) / 5 + kSmallTile - 1) / kSmallTile);
 constexpr size_t kOffPartialsChk = sizeof(Ctrl);
-constexpr size_t kOffPartials = kOffPartialsChk + kAbsmaxMaxBlocks * sizeof(uint32_t);
-constexpr size_t kOffStatus = kOffPartials + kAbsmaxMaxBlocks * sizeof(uint32_t);
+constexpr size_t kOffStatus = kOffPartialsChk + kAbsmaxMaxBlocks * sizeof(uint32_t);
 constexpr size_t kStatusWords = kNoallocMaxTiles + 2;
 constexpr size_t kOffMaxima = kOffStatus + kStatusWords * sizeof(uint64_t);
 constexpr size_t kScratchBytes = 16384;  // the size the header states

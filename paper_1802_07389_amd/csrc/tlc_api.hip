@@ -392,9 +392,10 @@ HostMirror batch_mirror(tlc_ctx* c) {
 // before its launches the host fills each result's err, len and scale words
 // with kPending, which none of their values takes (err is 0 or 1, a length
 // is below 2^31, a scale is finite), and then waits for the words to change
-// rather than for the stream: a tensor's first tile writes err and the
-// scale (and a zero length on error), its last tile, or the compaction's
-// last, the length, a little before the kernels end.
+// rather than for the stream.  Three passes: the writing (or lines) pass's
+// first block writes err and the scale (and a zero length on error), the
+// compaction's last tile the length.  One launch: a tensor's last tile writes
+// all three in one store, on error as soon as M is known, else at its end.
 constexpr uint32_t kPending = 0xffffffffu;
 
 static_assert(offsetof(EncResult, err) == 0 && offsetof(EncResult, len) == 4 &&
@@ -779,22 +780,17 @@ TLC_API int tlc_compress(tlc_ctx* c, const float* tensor, float* residual, size_
   arm_results(&c->rb->enc, 1);
   const uint32_t ntiles = (uint32_t)ceil_div(m, kEncTile);
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
-  if (ntiles < kThreePassMinTiles) {  // small tensor: one chained pass
+  if (ntiles < kThreePassMinTiles) {  // small tensor: one launch
     const uint32_t tiles = small_tiles((uint32_t)m);
-    uint32_t np = 0;
-    if (tiles > kExchangeTiles) {
-      st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
-        return launch_absmax_check(tensor, residual, n, c->partials_chk, &np, c->stream);
-      });
-      if (st) return st;
-    }
+    static_assert((kThreePassMinTiles - 1) * kEncTile <= kExchangeTiles * kSmallTile,
+                  "the tiles exchange their maxima and each takes a ticket");
     uint32_t epoch = 0;
     st = next_epoch(c, &c->enc_epoch, kEncEpochMax, c->enc_status, 2 * c->enc_status_words,
                     nullptr, &epoch);
     if (st) return st;
     st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE_CHAINED, [&] {
       return launch_quant_encode_chained(tensor, residual, n, (uint32_t)m, s, in_place,
-                                         c->partials_chk, np, bytes, c->enc_status,
+                                         nullptr, 0u, bytes, c->enc_status,
                                          c->enc_status + c->enc_status_words, c->enc_ticket_base,
                                          epoch, c->ctrl, enc_mirror(c), c->stream);
     });

@@ -1,7 +1,8 @@
-"""The look-back epoch counters across their wrap, through the C ABI.
+"""The epoch counters of the status words across their wrap, through the C ABI.
 
-Every chained or batched encode and every decode tags its scan's status
-words with the next epoch; at the wrap the words (and, for decodes, the
+Every encode of small tensors, single or batched, tags the words by which its
+tiles exchange maxima and summaries with the next epoch, and every decode those
+of its look-back scan; at the wrap the words (and, for decodes, the
 mark of the launch with a corrupt stream) are cleared.  tlc_ctx_set_epochs
 moves the counters next to the wrap; every call on either side of it must
 still match the oracle bit for bit."""
@@ -29,8 +30,9 @@ def ctx():
     c.close()
 
 
-def chained_encode_check(ctx, n, seed):
-    """A tensor on the chained (look-back) path, against the oracle."""
+def tiles_encode_check(ctx, n, seed):
+    """A tensor of several exchanging tiles (up to 1,310,720 values), or a larger
+    one whose stream serves the decodes, against the oracle."""
     g = G()
     x = workloads.normal([85, seed], n, 1e-3)
     r = workloads.normal([86, seed], n, 1e-4)
@@ -48,12 +50,13 @@ def test_encode_epochs_wrap(ctx):
     E = tlc.TLC_ENC_EPOCH_MAX
     assert tlc.tlc_ctx_set_epochs(ctx.handle, E + 1, 0) == tlc.TLC_E_INVALID
     assert tlc.tlc_ctx_set_epochs(ctx.handle, E - 2, 0) == tlc.TLC_OK
-    # epochs E - 1, E, then the wrap: 1, 2; 600,001 values make 30 tiles
+    # epochs E - 1, E, then the wrap: 1, 2; 600,001 values make 59 tiles,
+    # 1,310,720 the most that exchange
     for k in range(4):
-        chained_encode_check(ctx, 600_001, k)
+        tiles_encode_check(ctx, 600_001 if k % 2 else 5 * 2048 * 128, k)
     # batched encodes: one at E, one after the wrap
     assert tlc.tlc_ctx_set_epochs(ctx.handle, E - 1, 0) == tlc.TLC_OK
-    sizes = [70_001, 5, 400_000, 1_000_003]
+    sizes = [70_001, 5, 400_000, 1_000_003, 5 * 2048 * 128, 1_500_000]
     for step in range(2):
         xs = [workloads.normal([87, step, t], n, 1e-3) for t, n in enumerate(sizes)]
         rs = [workloads.normal([88, step, t], n, 1e-4) for t, n in enumerate(sizes)]
@@ -80,7 +83,7 @@ def test_decode_epochs_wrap_and_corrupt_mark(ctx):
     D = tlc.TLC_DEC_EPOCH_MAX
     assert tlc.tlc_ctx_set_epochs(ctx.handle, 0, D + 1) == tlc.TLC_E_INVALID
     n = 1_500_007
-    streams = [chained_encode_check(ctx, n, 10 + k) for k in range(3)]
+    streams = [tiles_encode_check(ctx, n, 10 + k) for k in range(3)]
     out0 = workloads.normal([89, 0], n, 1e-3)
     bad = np.append(streams[0][0], streams[0][0][-1:])
 

@@ -2,11 +2,13 @@
 the library (libtlc_delay.so, compiled with TLC_DELAY_INJECT) sleeps a
 pseudo-random 0 to about 25 us before every status-word publish.  Each
 user of the status words runs here once against the CPU oracle, bit for
-bit: the chained single-tensor encoder, the three-pass encoder's
-tile-prefix scan, the batched encoder, and the decoder's index scan
-(single, batched and summed decodes; the single decode's blocks also wait
-for their start entries and the stream's verdict).  Every wait is bounded;
-a timeout would surface as TLC_E_DEVICE, not a hang."""
+bit: the tiles of small tensors, alone and in batches, which exchange maxima
+and summaries; the no-allocation encode, whose tiles are chained by look-back
+above that; and the decoder's index scan (single, batched and summed decodes;
+the single decode's blocks also wait for their start entries and the stream's
+verdict).  The three-pass encoders publish no status words; they run here
+because a call mixes them with the others.  Every wait is bounded; a timeout
+would surface as TLC_E_DEVICE, not a hang."""
 import importlib.util
 import os
 
@@ -106,20 +108,46 @@ def test_exchanging_tiles(dt, ctx, few_blocks, blocks, options):
         ctx.set_options(0)
 
 
-def test_chained_and_three_pass_encoders(dt, ctx):
-    # 400 tiles on the chained path (tile tickets + decoupled look-back)
+@pytest.mark.parametrize("n", [5 * 2048 * 128, 5 * 2048 * 128 + 1, 4_000_003, None])
+def test_no_allocation_encode(dt, n):
+    """128 exchanging tiles, then 65 to 410 of twice the size, chained by the
+    block-wide look-back (lookback_block); None: the largest size."""
+    import torch
+    n = n or dt.TLC_NOALLOC_MAX_N
+    x = workloads.normal([97, 0], n, 1e-3)
+    x[n // 3:n // 2] = 0  # runs that cross tiles
+    r = workloads.normal([97, 1], n, 1e-4)
+    r[n // 3:n // 2] = 0
+    m = dt.tlc_max_compressed_bytes(n)
+    xd, rd = torch.from_numpy(x).cuda(), torch.from_numpy(r.copy()).cuda()
+    buf = torch.zeros(m, dtype=torch.uint8, device="cuda")
+    res = torch.zeros(4, dtype=torch.int32, device="cuda")
+    st = dt.tlc_compress_noalloc(xd.data_ptr(), rd.data_ptr(), n, 1.5, buf.data_ptr(), m,
+                                 res.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == dt.TLC_OK
+    torch.cuda.synchronize()
+    got = res.cpu().numpy()
+    st, C_ref, M_ref = oracle.compress(x, r, 1.5)
+    assert st == 0 and got[0] == dt.TLC_OK and got[1] == C_ref.size
+    assert got[2:3].view(F32).tobytes() == F32(M_ref).tobytes()
+    assert np.array_equal(buf[:C_ref.size].cpu().numpy(), C_ref)
+    assert np.array_equal(bits(rd.cpu().numpy()), bits(r))
+    print(f"no-allocation encode of {n} values ok", flush=True)
+
+
+def test_three_pass_encoders(dt, ctx):
+    # 400 tiles: the compaction combines the tiles' summaries itself
     n = 400 * 4096 * 5 - 3
     encode_check(ctx, workloads.normal([91, 0], n, 1e-3), workloads.normal([91, 1], n, 1e-4),
-                 1.0, "chained, 400 tiles")
-    # 1639 tiles on the three-pass path (the last blocks' tile-prefix scan),
-    # the trit path and the in-place bounds path
+                 1.0, "three-pass, 400 tiles")
+    # 1639 tiles: with the chunk pass (its last block scans the chunks)
     n = (1 << 25) + 7
     x = workloads.runs_tensor([91, 2], n)
     encode_check(ctx, x, np.zeros(n, F32), 1.5, "three-pass, 1639 tiles")
     n = 1 << 25
     encode_check(ctx, workloads.normal([91, 3], n, 1e-3), workloads.normal([91, 4], n, 1e-4),
-                 1.0, "three-pass trit path")
-    ctx.set_options(dt.TLC_OPT_IN_PLACE_FEEDBACK)  # bounds and residual lists
+                 1.0, "three-pass, m on the word grid")
+    ctx.set_options(dt.TLC_OPT_IN_PLACE_FEEDBACK)  # line bounds
     try:
         encode_check(ctx, workloads.normal([91, 5], n, 1e-3), workloads.normal([91, 6], n, 1e-4),
                      1.0, "three-pass in place")
@@ -140,6 +168,24 @@ def test_batched_encoder(ctx):
         assert np.array_equal(pays[t][0].cpu().numpy(), C_ref), t
         assert np.array_equal(bits(rd[t].cpu().numpy()), bits(r)), t
     print("batched encoder, 335 tensors ok", flush=True)
+
+
+def test_batch_of_many_tiles(ctx):
+    """Tensors of 128, 127, 2 and 33 exchanging tiles and of one, with one of
+    400 larger tiles, which takes the three passes, in one call."""
+    import torch
+    T = 5 * 2048
+    sizes = [128 * T, 500, 127 * T - 1, 800 * T - 3, T + 1, 33 * T, T]
+    xs = [workloads.normal([98, t], n, 1e-3) for t, n in enumerate(sizes)]
+    rs = [workloads.normal([99, t], n, 1e-4) for t, n in enumerate(sizes)]
+    rd = [torch.from_numpy(r.copy()).cuda() for r in rs]
+    pays = ctx.compress_batch([torch.from_numpy(x).cuda() for x in xs], rd, 1.25)
+    for t, (x, r) in enumerate(zip(xs, rs)):
+        st, C_ref, M_ref = oracle.compress(x, r, 1.25)
+        assert st == 0 and pays[t][1] == M_ref, t
+        assert np.array_equal(pays[t][0].cpu().numpy(), C_ref), t
+        assert np.array_equal(bits(rd[t].cpu().numpy()), bits(r)), t
+    print("batch of many tiles ok", flush=True)
 
 
 def test_decoder_index_scans(ctx):
