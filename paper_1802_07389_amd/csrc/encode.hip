@@ -19,6 +19,9 @@
 //       the quartic pack from the trits and each tile's own zero-run encoding;
 //       then a scan of the tile summaries and the compaction into one stream
 //                                                   (Sections 3.2-3.3)
+//   tlc_quant_encode_bounds_kernel
+//       in place, one large tensor: the tiles quantize what the max pass's
+//       bounds let through themselves, without trits
 //
 // The batch kernels (and the _many_ ones, for the tensors of a batch that are
 // too large for its one launch) run many tensors in one launch: every block
@@ -55,30 +58,31 @@ __device__ __forceinline__ uint32_t line_max(uint32_t v) {
 // which only reduces max|x + r| and writes nothing.
 //
 // kBound (in place, large tensors): also store, for each line of eight
-// float4s (128 bytes) of the buffer, the top 16 bits of the bit pattern of
-// its largest |acc|.  That half-word h bounds the line's values from above
-// (|acc| < (h + 1) * 2^16 as bit patterns), so the pass that follows can skip
-// every line whose h lies below the top half of its threshold U: all its
-// values have q = 0 and keep acc.
+// float4s (128 bytes) of the buffer (8), or for each float4 (1), the top 16
+// bits of the bit pattern of its largest |acc|.  That half-word h bounds the
+// values from above (|acc| < (h + 1) * 2^16 as bit patterns), so the pass that
+// follows can skip every line or float4 whose h lies below the top half of its
+// threshold U: all its values have q = 0 and keep acc.
 //
 // kKeep: plain loads, which leave what they read in the last-level cache for
 // the writing pass (where both tensors fit it).
-template <bool kResid = true, bool kStore = kResid, bool kBound = false, bool kKeep = false>
+template <bool kResid = true, bool kStore = kResid, int kBound = 0, bool kKeep = false>
 __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
                                                 float* __restrict__ r, uint64_t n,
                                                 uint32_t blk, uint32_t nblk,
                                                 uint16_t* __restrict__ bound = nullptr) {
   static_assert(!kStore || kResid, "only a buffer is stored");
-  static_assert(!kBound || kStore, "bounds are of a stored buffer");
+  static_assert(kBound == 0 || (kStore && (kBound == 1 || kBound == 8)),
+                "bounds are of a stored buffer");
   uint32_t mx = 0;
   const uint64_t tid = (uint64_t)blk * kThreads + threadIdx.x;
   const uint64_t stride = (uint64_t)nblk * kThreads;
   const uint64_t nv = n >> 2;
   auto ld = [](const float* p) { return kKeep ? ld4(p) : ld_stream(p); };
   uint64_t i = tid;
-  // with bounds a line's eight lanes leave the loop together: line_max needs
+  // with bounds of lines a line's eight lanes leave the loop together: line_max needs
   // all of them, also where nv % 8 cuts the last line off
-  auto four = [&](uint64_t j) { return (kBound ? j | 7u : j) + 3 * stride < nv; };
+  auto four = [&](uint64_t j) { return (kBound == 8 ? j | 7u : j) + 3 * stride < nv; };
   for (; four(i); i += 4 * stride) {
     float4 a[4], b[4];
 #pragma unroll
@@ -94,7 +98,8 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
       if (kStore) st_stream(r + 4 * (i + u * stride), v);
       const uint32_t m4 =
           max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w)));
-      if (kBound) {
+      if (kBound == 1) bound[i + u * stride] = (uint16_t)(m4 >> 16);
+      if (kBound == 8) {
         const uint32_t lm = line_max(m4);
         if ((threadIdx.x & 7u) == 0u) bound[(i + u * stride) >> 3] = (uint16_t)(lm >> 16);
       }
@@ -112,7 +117,8 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
       }
     }
     const uint32_t m4 = max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w)));
-    if (kBound) {
+    if (kBound == 1 && i < nv) bound[i] = (uint16_t)(m4 >> 16);
+    if (kBound == 8) {
       const uint32_t lm = line_max(m4);
       if ((threadIdx.x & 7u) == 0u && i < nv) bound[i >> 3] = (uint16_t)(lm >> 16);
     }
@@ -186,20 +192,20 @@ __global__ __launch_bounds__(kThreads) void tlc_absmax_check_kernel(
     uint32_t* __restrict__ partials) {
   __shared__ uint32_t lds[kWaves];
   const uint32_t mx = block_max(
-      absmax_part<true, false, false, kKeep>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x),
+      absmax_part<true, false, 0, kKeep>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x),
       lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
-// Step 1 into the buffer and its max pass (in place, large tensors), or the
-// max pass of a tensor without one.
-template <bool kResid>
+// Step 1 into the buffer and its max pass (in place, large tensors; kBound 8 or
+// 1), or the max pass of a tensor without one (0).
+template <int kBound>
 __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_kernel(
     const float* __restrict__ x, float* __restrict__ r, uint64_t n,
     uint32_t* __restrict__ partials, uint16_t* __restrict__ bound) {
   __shared__ uint32_t lds[kWaves];
   const uint32_t mx = block_max(
-      absmax_part<kResid, kResid, kResid>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
+      absmax_part<kBound != 0, kBound != 0, kBound>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(kThreads) void tlc_absmax_check_batch_kernel(
            [&](uint32_t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
                uint32_t nblk) {
              const uint32_t bm = block_max(
-                 absmax_part<true, false, false, kKeep>(uniform_ptr(d.x) + lo,
+                 absmax_part<true, false, 0, kKeep>(uniform_ptr(d.x) + lo,
                                                         uniform_ptr(d.r) + lo, n, blk, nblk),
                  lds);
              if (threadIdx.x == 0) partials[slot] = bm;
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_batch_kernel(
                uint32_t nblk) {
              const uint64_t at = (uint64_t)d.v0 * kManyValues + lo;
              const uint32_t bm =
-                 block_max(absmax_part<true, true, true>(uniform_ptr(d.x) + lo,
+                 block_max(absmax_part<true, true, 8>(uniform_ptr(d.x) + lo,
                                                          uniform_ptr(d.r) + lo, n, blk, nblk,
                                                          bound + at / 32),
                            lds);
@@ -572,55 +578,21 @@ struct TritTileShared {
   uint32_t lut[5][256];
 };
 
-// Tile t of a tensor: its slot and record.  err: the tensor was refused.
+// Section 3.3 from the tile's first non-121 byte on: the thread's quartic bytes
+// w (16 * kHalves, from tile byte lo on) and the masks of the non-121 ones nz
+// (of each piece, spread: bit 2i for its byte i) into the tile's slot and its
+// record.  left: residuals that the tile leaves to the compaction.
 template <int kT>
-__device__ __forceinline__ void encode_trit_tile(uint64_t n, uint32_t m, uint32_t t,
-                                                 const uint8_t* __restrict__ trits,
-                                                 const uint32_t* err, uint8_t* __restrict__ slot,
+__device__ __forceinline__ void encode_tile_runs(const uint4 (&w)[kEncTile / kT / 16],
+                                                 const uint32_t (&nz)[kEncTile / kT / 16],
+                                                 uint32_t tile_bytes, uint8_t* __restrict__ slot,
                                                  TileRec* __restrict__ rec_out,
-                                                 TritTileShared<kT>& shared) {
+                                                 EncShared<kT / 64>& sh, uint32_t left) {
   constexpr int kW = kT / 64;
   constexpr int kHalves = kEncTile / kT / 16;
   constexpr uint32_t kBytes = 16u * kHalves;  // quartic bytes per thread
-  static_assert(kHalves == 1 || kHalves == 2, "one or two pieces of 16 bytes per thread");
-  EncShared<kW>& sh = shared.enc;
-  uint32_t(&s_lut)[5][256] = shared.lut;
-  const uint64_t q0 = (uint64_t)t * kEncTile;
-  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
-  // an interior tile (whole, every value before n): each thread packs its
-  // own quartic bytes in registers; other tiles pack through sh.q
-  const bool own = tile_bytes == (uint32_t)kEncTile && 4ull * m + q0 + kEncTile <= n;
   const uint32_t lo = threadIdx.x * kBytes;
-  uint32_t d[kHalves][5];  // own tile: the trits of the thread's values, 16 per word
-  uint32_t h[kEncTile / 4 / kT][5];
-  if (own)
-    load_trit_words<kHalves>(trits, m, q0, d);
-  else
-    load_trits<kT>(trits, n, m, q0, tile_bytes, h);
-  init_trit_luts<kT>(s_lut);
-  __syncthreads();  // the tables
-  if (*err) return;  // NaN/Inf or overflow: no stream (every block returns)
-  const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
-  uint4 w[kHalves];
-  uint32_t nz[kHalves];  // non-121 bytes of each piece, spread: bit 2i for its byte i
-  if (own) {
-#pragma unroll
-    for (int hf = 0; hf < kHalves; ++hf) {
-      w[hf] = pack_trit_words(d[hf], s_lut);
-      nz[hf] = nonzero_mask_trits(d[hf]);
-    }
-  } else {
-    pack_trits<kT>(h, n, m, q0, tile_bytes, s_lut, sh.q);
-#pragma unroll
-    for (int hf = 0; hf < kHalves; ++hf) {
-      const uint32_t c = cnt > 16u * hf ? umin32(cnt - 16u * hf, 16u) : 0u;
-      w[hf] = c ? *reinterpret_cast<const uint4*>(sh.q + lo + 16u * hf) : make_uint4(0, 0, 0, 0);
-      nz[hf] = c ? nonzero_mask16_spread(w[hf], c) : 0u;
-    }
-  }
-
-  // ---- Section 3.3 from the tile's first non-121 byte on, from the gaps
-  // between non-121 bytes: a max-scan over the threads' last non-121
+  // From the gaps between non-121 bytes: a max-scan over the threads' last non-121
   // positions gives each thread the previous one, a sum-scan of what each
   // thread emits gives its output offset (zre_scan.hpp: rs_gaps_len,
   // rs_gaps_emit; the pieces take turns, as a gap inside one costs exactly
@@ -685,9 +657,58 @@ __device__ __forceinline__ void encode_trit_tile(uint64_t n, uint32_t m, uint32_
       rec.lead = (uint16_t)sh.lead;
       rec.len = (uint16_t)len;
     }
-    rec.pad = 0u;
+    rec.left = left;
     *rec_out = rec;
   }
+}
+
+// Tile t of a tensor: its slot and record.  err: the tensor was refused.
+template <int kT>
+__device__ __forceinline__ void encode_trit_tile(uint64_t n, uint32_t m, uint32_t t,
+                                                 const uint8_t* __restrict__ trits,
+                                                 const uint32_t* err, uint8_t* __restrict__ slot,
+                                                 TileRec* __restrict__ rec_out,
+                                                 TritTileShared<kT>& shared) {
+  constexpr int kHalves = kEncTile / kT / 16;
+  constexpr uint32_t kBytes = 16u * kHalves;  // quartic bytes per thread
+  static_assert(kHalves == 1 || kHalves == 2, "one or two pieces of 16 bytes per thread");
+  EncShared<kT / 64>& enc = shared.enc;
+  uint32_t(&s_lut)[5][256] = shared.lut;
+  const uint64_t q0 = (uint64_t)t * kEncTile;
+  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
+  // an interior tile (whole, every value before n): each thread packs its
+  // own quartic bytes in registers; other tiles pack through sh.q
+  const bool own = tile_bytes == (uint32_t)kEncTile && 4ull * m + q0 + kEncTile <= n;
+  const uint32_t lo = threadIdx.x * kBytes;
+  uint32_t d[kHalves][5];  // own tile: the trits of the thread's values, 16 per word
+  uint32_t h[kEncTile / 4 / kT][5];
+  if (own)
+    load_trit_words<kHalves>(trits, m, q0, d);
+  else
+    load_trits<kT>(trits, n, m, q0, tile_bytes, h);
+  init_trit_luts<kT>(s_lut);
+  __syncthreads();  // the tables
+  if (*err) return;  // NaN/Inf or overflow: no stream (every block returns)
+  const uint32_t cnt = lo < tile_bytes ? umin32(kBytes, tile_bytes - lo) : 0u;
+  uint4 w[kHalves];
+  uint32_t nz[kHalves];  // non-121 bytes of each piece, spread: bit 2i for its byte i
+  if (own) {
+#pragma unroll
+    for (int hf = 0; hf < kHalves; ++hf) {
+      w[hf] = pack_trit_words(d[hf], s_lut);
+      nz[hf] = nonzero_mask_trits(d[hf]);
+    }
+  } else {
+    pack_trits<kT>(h, n, m, q0, tile_bytes, s_lut, enc.q);
+#pragma unroll
+    for (int hf = 0; hf < kHalves; ++hf) {
+      const uint32_t c = cnt > 16u * hf ? umin32(cnt - 16u * hf, 16u) : 0u;
+      w[hf] = c ? *reinterpret_cast<const uint4*>(enc.q + lo + 16u * hf) : make_uint4(0, 0, 0, 0);
+      nz[hf] = c ? nonzero_mask16_spread(w[hf], c) : 0u;
+    }
+  }
+
+  encode_tile_runs<kT>(w, nz, tile_bytes, slot, rec_out, enc, 0u);
 }
 
 template <int kT>
@@ -712,6 +733,225 @@ __global__ __launch_bounds__(kThreads) void tlc_quant_encode_many_kernel(
   encode_trit_tile<kThreads>(d.n, d.m, blockIdx.x - d.tile0,
                              trits + (uint64_t)d.v0 * (kManyValues / 4), &results[t].err,
                              slots + (uint64_t)blockIdx.x * kEncTile, recs + blockIdx.x, sh);
+}
+
+// ---- in place, one large tensor: the first pass from the max pass's bounds of
+// single float4s.  A slice (four values of a partition) of a group of quartic
+// bytes lies in one float4 of the buffer's grid, or with m % 4 != 0 in two, and
+// most have q = 0 throughout: the others alone are read.  The residuals of
+// q != 0 go through LDS into the tile's list, which the compaction writes back:
+// a few scattered stores cost far less in a pass of their own than mixed into a
+// stream of reads.  In place, after many steps (a call; the lines pass, trits and
+// tiles from them | this pass, before and with the compaction's stores): 40M
+// values 143 | 128 us, 2^26 224 | 204, 150M 449 | 397, 2^28 785 | 757, most of
+// them in zero runs 707 | 682.  At s = 1, where most waves are dense, 2^26 265 |
+// 244 and 2^28 1096 | 1057.
+//
+// Residual v of the tile's value `local` (k * kEncTile + position) when `has`:
+// the wave takes consecutive entries of the list with one LDS atomic; what falls
+// past kFixCap is stored at dst at once.
+__device__ __forceinline__ void fix_put(bool has, uint32_t local, float v, float* dst,
+                                        uint32_t* left, uint2* fix) {
+  const uint64_t all = __ballot(has);
+  if (all == 0u) return;
+  const uint32_t leader = (uint32_t)__ffsll((unsigned long long)all) - 1u;
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+      (uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
+  uint32_t base = 0u;
+  if ((threadIdx.x & 63u) == leader) base = atomicAdd(left, (uint32_t)__popcll(all));
+  base = (uint32_t)__shfl((int)base, (int)leader, 64);
+  if (has) {
+    if (base + rank < kFixCap)
+      fix[base + rank] = make_uint2(local, __float_as_uint(v));
+    else
+      *dst = v;
+  }
+}
+
+// Needed slices that a thread loads together.
+constexpr int kSliceBatch = 4;
+
+// Whether every value of group g (quartic bytes 4g .. 4g + 3 of the tile) exists
+// and lies in float4s of the buffer that exist whole, so that they have bounds.
+__device__ __forceinline__ bool group_whole(uint64_t n, uint32_t m, uint64_t q0,
+                                            uint32_t tile_bytes, uint32_t g) {
+  return g * 4u + 4u <= tile_bytes && 4ull * m + q0 + g * 4u + 7u <= n;
+}
+
+// The tile's quartic bytes into q.  h: the bounds of the thread's slices (group
+// it = threadIdx.x + kThreads * it, partition k), the float4's that holds its
+// first value below the next one's.  Where no thread of a wave
+// needs more than two batches, every group starts from the all-zero byte 121
+// and each needed slice moves its bytes by (t - 1) * 3^(4-k); other waves take
+// the groups in turn with their needed slices loaded together, and store those
+// that change at once: the list would not hold them (through the list and what
+// it refused, s = 1, 40M values 170 against 154 us, 2^26 271 against 244).  The
+// groups at the end of the tensor are taken value by value.  Ends with a barrier.
+template <bool kGrid>
+__device__ __forceinline__ void quantize_bounded_tile(
+    float* __restrict__ r, uint64_t n, uint32_t m, const Scale& sc, uint64_t q0,
+    uint32_t tile_bytes, const uint32_t (&h)[kGroupsPerThread][5], uint8_t* q, uint32_t* left,
+    uint2* s_fix) {
+  static_assert(kGroupsPerThread * 5 <= 32, "a thread's slices fit one mask");
+  uint32_t* qw = reinterpret_cast<uint32_t*>(q);
+  const uint32_t hU = __float_as_uint(sc.U) >> 16;
+  auto group_of = [](uint32_t it) { return threadIdx.x + kThreads * it; };
+  auto slice = [&](uint32_t it, uint32_t k) { return r + (uint64_t)k * m + q0 + group_of(it) * 4u; };
+  uint32_t need = 0u;  // bit 5 * it + k
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    // on the grid the second bound is another slice's
+    const uint32_t second = !kGrid && (((uint64_t)k * m + q0) & 3u) ? 0xffffu : 0u;
+#pragma unroll
+    for (int it = 0; it < kGroupsPerThread; ++it) {
+      const uint32_t b =
+          kGrid ? h[it][k] : umax32(h[it][k] & 0xffffu, (h[it][k] >> 16) & second);
+      need |= (group_whole(n, m, q0, tile_bytes, group_of(it)) && b >= hU ? 1u : 0u)
+              << (5 * it + k);
+    }
+  }
+  // the four trits of slice k of group it
+  auto quantize4 = [&](const float4& a, uint32_t (&t)[4]) {
+    float4 o;
+    t[0] = quantize_one(a.x, sc.M, sc.U, o.x);
+    t[1] = quantize_one(a.y, sc.M, sc.U, o.y);
+    t[2] = quantize_one(a.z, sc.M, sc.U, o.z);
+    t[3] = quantize_one(a.w, sc.M, sc.U, o.w);
+    return o;
+  };
+  // the same, its residuals to the list
+  auto quantize = [&](bool has, const float4& a, uint32_t it, uint32_t k, uint32_t (&t)[4]) {
+    const float4 o = quantize4(a, t);
+    const uint32_t local = k * kEncTile + group_of(it) * 4u;
+    float* e = slice(it, k);
+    fix_put(has && t[0] != 1u, local, o.x, e, left, s_fix);
+    fix_put(has && t[1] != 1u, local + 1u, o.y, e + 1, left, s_fix);
+    fix_put(has && t[2] != 1u, local + 2u, o.z, e + 2, left, s_fix);
+    fix_put(has && t[3] != 1u, local + 3u, o.w, e + 3, left, s_fix);
+  };
+  // a group at the end: its existing values one by one
+  auto partial = [&](uint32_t g) {
+    uint32_t w = 0u;
+    for (uint32_t c = 0; c < 4u && g * 4u + c < tile_bytes; ++c) {
+      uint32_t code = 0u;
+      for (uint32_t k = 0; k < 5u; ++k) {
+        const uint64_t e = (uint64_t)k * m + q0 + g * 4u + c;
+        uint32_t t = 0u;  // the padding
+        if (e < n) {
+          float o;
+          t = quantize_one(r[e], sc.M, sc.U, o);
+          r[e] = o;
+        }
+        code = code * 3u + t;
+      }
+      w |= code << (8u * c);
+    }
+    return w;
+  };
+  auto store = [&](uint32_t it, uint32_t w) {
+    const uint32_t g = group_of(it);
+    if (g * 4u < tile_bytes) qw[g] = group_whole(n, m, q0, tile_bytes, g) ? w : partial(g);
+  };
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (wave_max((uint32_t)__popc(need)) <= 2u * kSliceBatch) {
+    uint32_t bytes[kGroupsPerThread];
+#pragma unroll
+    for (int it = 0; it < kGroupsPerThread; ++it) bytes[it] = 0x79797979u;  // five zeros each
+    uint32_t rest = need;
+#pragma unroll 1
+    while (__ballot(rest != 0u)) {  // whole waves (fix_put)
+      float4 a[kSliceBatch];
+      uint32_t sel[kSliceBatch];
+#pragma unroll
+      for (int b = 0; b < kSliceBatch; ++b) {
+        sel[b] = rest ? (uint32_t)__ffs(rest) - 1u : 32u;
+        rest &= rest - 1u;
+        a[b] = sel[b] < 32u ? ld4(slice(sel[b] / 5u, sel[b] % 5u)) : zero;
+      }
+#pragma unroll
+      for (int b = 0; b < kSliceBatch; ++b) {
+        const bool has = sel[b] < 32u;
+        if (__ballot(has) == 0u) break;
+        const uint32_t it = has ? sel[b] / 5u : 0u, k = has ? sel[b] % 5u : 0u;
+        uint32_t t[4];
+        quantize(has, a[b], it, k, t);
+        // each byte stays in 0 .. 242, so the four move as one word
+        const uint32_t by = (t[0] | (t[1] << 8) | (t[2] << 16) | (t[3] << 24)) - 0x01010101u;
+        const uint32_t move = has ? by * trit_weight((int)k) : 0u;
+#pragma unroll
+        for (int gi = 0; gi < kGroupsPerThread; ++gi) bytes[gi] += (uint32_t)gi == it ? move : 0u;
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < kGroupsPerThread; ++it) store(it, bytes[it]);
+  } else {
+#pragma unroll 1
+    for (uint32_t it = 0; it < (uint32_t)kGroupsPerThread; ++it) {
+      float4 a[5];
+#pragma unroll
+      for (int k = 0; k < 5; ++k)
+        a[k] = (need >> (5 * it + k)) & 1u ? ld4(slice(it, k)) : zero;
+      uint32_t w = 0u;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        uint32_t t[4];
+        const float4 o = quantize4(a[k], t);
+        const uint32_t tp = t[0] | (t[1] << 8) | (t[2] << 16) | (t[3] << 24);
+        if ((need >> (5 * it + k)) & 1u && tp != 0x01010101u) st4(slice(it, k), o);
+        w += tp * trit_weight(k);
+      }
+      store(it, w);
+    }
+  }
+  __syncthreads();
+}
+
+// Bound by its scattered reads.  kGrid: m % 4 == 0 (one bound a slice; with two
+// 40M values took 134 us a call, with one 129).
+template <bool kGrid>
+__global__ __launch_bounds__(kThreads) void tlc_quant_encode_bounds_kernel(float* __restrict__ r, uint64_t n, uint32_t m, float s,
+                                    const uint32_t* __restrict__ partials, uint32_t np,
+                                    const uint16_t* __restrict__ bound,
+                                    uint8_t* __restrict__ slots, TileRec* __restrict__ recs,
+                                    uint2* __restrict__ fix, Ctrl* __restrict__ ctrl,
+                                    HostMirror hm) {
+  __shared__ EncShared<kWaves> enc;
+  __shared__ uint2 s_fix[kFixCap];
+  __shared__ uint32_t s_left, s_scale[kWaves];
+  if (threadIdx.x == 0) s_left = 0u;
+  const uint32_t t = blockIdx.x;
+  const uint64_t q0 = (uint64_t)t * kEncTile;
+  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
+  // the bounds don't depend on M: loaded before the block reduces it
+  typedef uint32_t pair __attribute__((aligned(2)));
+  uint32_t h[kGroupsPerThread][5];
+#pragma unroll
+  for (int it = 0; it < kGroupsPerThread; ++it) {
+    const uint32_t g = threadIdx.x + kThreads * it;
+    const bool whole = group_whole(n, m, q0, tile_bytes, g);
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      if (const uint16_t* p = bound + (((uint64_t)k * m + q0 + g * 4u) >> 2); whole)
+        h[it][k] = kGrid ? *p : *reinterpret_cast<const pair*>(p);
+      else
+        h[it][k] = 0u;
+  }
+  const Scale sc = finish_scale(partials, np, s, s_scale);  // holds a barrier
+  if (t == 0 && threadIdx.x == 0) {
+    ctrl->enc.err = sc.bad;
+    ctrl->enc.scale = sc.M;
+    host_put_result(hm.res, sc.bad, sc.M);
+  }
+  if (sc.bad) return;  // the buffer keeps the sums
+  quantize_bounded_tile<kGrid>(r, n, m, sc, q0, tile_bytes, h, enc.q, &s_left, s_fix);
+  const uint32_t left = umin32(s_left, kFixCap);
+  if (threadIdx.x < left) fix[(uint64_t)t * kFixCap + threadIdx.x] = s_fix[threadIdx.x];
+  static_assert(kFixCap <= kThreads, "an entry per thread");
+  const uint32_t lo = 16u * threadIdx.x;
+  const uint32_t cnt = lo < tile_bytes ? umin32(16u, tile_bytes - lo) : 0u;
+  const uint4 w[1] = {cnt ? *reinterpret_cast<const uint4*>(enc.q + lo) : make_uint4(0, 0, 0, 0)};
+  const uint32_t nz[1] = {cnt ? nonzero_mask16_spread(w[0], cnt) : 0u};
+  encode_tile_runs<kThreads>(w, nz, tile_bytes, slots + q0, recs + t, enc, left);
 }
 
 // Pass B: one wave per chunk of 64 tiles: every tile's prefix within its
@@ -782,12 +1022,13 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_chunk_kernel(
 // contains a logic error).
 // kPer > 0 (at most kPer * kThreads tiles): no pass B; the block combines the
 // summaries of all tiles before its first one itself, kPer per thread.
+// fix: the residuals that the bounded first pass left (null: another one ran).
 template <uint32_t kPer>
 __device__ __forceinline__ void compact_tiles(
     const TileRec* __restrict__ recs, const uint64_t* __restrict__ chunk_pre,
     const uint64_t* __restrict__ local_pre, const uint8_t* __restrict__ slots, uint32_t m,
     uint32_t ntiles, uint32_t t0, uint8_t* __restrict__ out, EncResult* __restrict__ res,
-    EncResult* hres) {
+    EncResult* hres, const uint2* __restrict__ fix, float* __restrict__ r, uint64_t n) {
   if (res->err) return;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t t = t0 + (threadIdx.x >> 6);
@@ -850,6 +1091,14 @@ __device__ __forceinline__ void compact_tiles(
         if (i + b < len && at + i + b < m) out[at + i + b] = (uint8_t)(w >> (8u * b));
     }
   }
+  if (fix) {
+    const uint32_t left = umin32(rec.left, kFixCap);
+    for (uint32_t i = lane; i < left; i += 64u) {
+      const uint2 f = fix[(uint64_t)t * kFixCap + i];
+      const uint64_t e = (uint64_t)(f.x / (uint32_t)kEncTile) * m + q0 + f.x % (uint32_t)kEncTile;
+      if (e < n) r[e] = __uint_as_float(f.y);
+    }
+  }
   if (t + 1 == ntiles && lane == 0) {  // a run that ends the stream; the length
     RunSum a;
     a.v = rec.agg;
@@ -866,9 +1115,10 @@ template <uint32_t kPer>
 __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
     const TileRec* __restrict__ recs, const uint64_t* __restrict__ chunk_pre,
     const uint64_t* __restrict__ local_pre, const uint8_t* __restrict__ slots, uint32_t m,
-    uint32_t ntiles, uint8_t* __restrict__ out, Ctrl* __restrict__ ctrl, HostMirror hm) {
+    uint32_t ntiles, uint8_t* __restrict__ out, Ctrl* __restrict__ ctrl, HostMirror hm,
+    const uint2* __restrict__ fix, float* __restrict__ r, uint64_t n) {
   compact_tiles<kPer>(recs, chunk_pre, local_pre, slots, m, ntiles, blockIdx.x * kWaves, out,
-                      &ctrl->enc, hm.res);
+                      &ctrl->enc, hm.res, fix, r, n);
 }
 
 // A batch's middle tensors of at most kPer * kThreads tiles: cblk0 counts the
@@ -882,7 +1132,8 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_many_kernel(
   const EncDesc& d = descs[t];
   compact_tiles<kPer>(recs + d.tile0, nullptr, nullptr, slots + (uint64_t)d.tile0 * kEncTile, d.m,
                       (d.m + kEncTile - 1) / kEncTile, (blockIdx.x - d.cblk0) * kWaves,
-                      uniform_ptr(d.out), results + t, hm.res ? hm.res + t : nullptr);
+                      uniform_ptr(d.out), results + t, hm.res ? hm.res + t : nullptr, nullptr,
+                      nullptr, 0u);
 }
 
 // ---------------------------------------------------------------- small tensors
@@ -1479,12 +1730,14 @@ hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint3
 }
 
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, uint16_t* bound, hipStream_t st) {
+                               uint32_t* nblocks, uint16_t* bound, bool lines, hipStream_t st) {
   *nblocks = absmax_blocks(n);
-  if (r)
-    launch_k(tlc_accum_absmax_kernel<true>, *nblocks, kThreads, st, x, r, n, partials, bound);
+  if (!r)
+    launch_k(tlc_accum_absmax_kernel<0>, *nblocks, kThreads, st, x, r, n, partials, bound);
+  else if (lines)
+    launch_k(tlc_accum_absmax_kernel<8>, *nblocks, kThreads, st, x, r, n, partials, bound);
   else
-    launch_k(tlc_accum_absmax_kernel<false>, *nblocks, kThreads, st, x, r, n, partials, bound);
+    launch_k(tlc_accum_absmax_kernel<1>, *nblocks, kThreads, st, x, r, n, partials, bound);
   return hipGetLastError();
 }
 
@@ -1515,6 +1768,20 @@ hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* 
   else
     launch_k(tlc_quant_encode_kernel<kThreads>, ntiles, kThreads, st, n, m, slots, recs, trits,
              ctrl);
+  return hipGetLastError();
+}
+
+hipError_t launch_quant_encode_bounds(float* r, uint64_t n, uint32_t m, float s,
+                                      const uint32_t* partials, uint32_t np,
+                                      const uint16_t* bound, uint8_t* slots, TileRec* recs,
+                                      uint2* fix, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
+  const uint32_t tiles = (m + kEncTile - 1) / kEncTile;
+  if (m % 4 == 0)
+    launch_k(tlc_quant_encode_bounds_kernel<true>, tiles, kThreads, st, r, n, m, s, partials, np,
+             bound, slots, recs, fix, ctrl, hm);
+  else
+    launch_k(tlc_quant_encode_bounds_kernel<false>, tiles, kThreads, st, r, n, m, s, partials, np,
+             bound, slots, recs, fix, ctrl, hm);
   return hipGetLastError();
 }
 
@@ -1554,14 +1821,16 @@ hipError_t launch_zre_chunks(const TileRec* recs, uint32_t ntiles, uint64_t* loc
 
 hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
                               const uint64_t* local_pre, const uint8_t* slots, uint32_t m,
-                              uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
+                              uint8_t* out, Ctrl* ctrl, HostMirror hm, const uint2* fix, float* r,
+                              uint64_t n, hipStream_t st) {
   const uint32_t ntiles = (uint32_t)((m + kEncTile - 1) / kEncTile);
+  const uint32_t blocks = (ntiles + kWaves - 1) / kWaves;
   if (!zre_chunked(m))
-    launch_k(tlc_zre_compact_kernel<kOwnPrefixTiles / kThreads>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
-             chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
+    launch_k(tlc_zre_compact_kernel<kOwnPrefixTiles / kThreads>, blocks, kThreads, st, recs,
+             chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm, fix, r, n);
   else
-    launch_k(tlc_zre_compact_kernel<0u>, (ntiles + kWaves - 1) / kWaves, kThreads, st, recs,
-             chunk_pre, local_pre, slots, m, ntiles, out, ctrl, hm);
+    launch_k(tlc_zre_compact_kernel<0u>, blocks, kThreads, st, recs, chunk_pre, local_pre, slots,
+             m, ntiles, out, ctrl, hm, fix, r, n);
   return hipGetLastError();
 }
 

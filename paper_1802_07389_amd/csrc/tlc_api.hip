@@ -139,7 +139,8 @@ struct tlc_ctx {
   TileRec* recs = nullptr;
   uint64_t* chunk_agg = nullptr;  // chunk summaries, scanned in place into chunk prefixes
   uint64_t* local_pre = nullptr;  // every tile's prefix within its chunk
-  uint16_t* bound = nullptr;      // per 32 values of the buffer: top half of max |acc|
+  uint16_t* bound = nullptr;      // per 32 or 4 values of the buffer: top half of max |acc|
+  uint2* fix = nullptr;           // per tile: residuals for the compaction (TileRec::left)
   uint8_t* trits = nullptr;       // per four values: their trits
   // pinned host memory: status readback, batch results, descriptor staging
   HostReadback* rb = nullptr;
@@ -474,6 +475,12 @@ int check_usable(tlc_ctx* c, const char* fn) {
   return TLC_OK;
 }
 
+// Below this the writing pass finds the tensor and the buffer in the last-level
+// cache, and the two passes of the default policy are the faster ones in place
+// too (a refused tensor is then left with the sums): 2M values 28 against 33
+// us, 10M 51 against 54, 18M 81 against 83.
+constexpr size_t kInPlaceMinValues = 20000000;
+
 // How a batched encode takes a tensor of m quartic bytes (exchange: the most
 // tiles that exchange their maxima in this call).
 enum BatchKind { kMiddle, kShared, kLone, kLarge };
@@ -534,7 +541,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->slot_bytes = round_up(max_tensors * 64 + c->owner_cap * sizeof(uint16_t), 64);
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
   //         start | enc descs | dec descs, owners | tile records | chunk summaries |
-  //         tile prefixes in their chunks | line bounds | trits | slots
+  //         tile prefixes in their chunks | bounds | residual lists | trits | slots
   // (the batch results follow the control block, so that one copy reads both)
   static_assert(sizeof(Ctrl) % alignof(EncResult) == 0, "results follow the control block");
   const size_t off_res = sizeof(Ctrl);
@@ -560,7 +567,12 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   const size_t off_local = off;
   off = round_up(off + tiles1 * sizeof(uint64_t), 256);
   const size_t off_bound = off;
-  off = round_up(off + ceil_div(values2, (size_t)32) * sizeof(uint16_t), 256);
+  // of lines, or (a large tensor in place) of float4s
+  const bool large = max_n >= kInPlaceMinValues;
+  off = round_up(off + std::max(ceil_div(values2, (size_t)32), large ? max_n / 4 + 2 : 0) *
+                           sizeof(uint16_t), 256);
+  const size_t off_fix = off;
+  off = round_up(off + (large ? tiles1 * (size_t)kFixCap * sizeof(uint2) : 0), 256);
   const size_t off_trits = off;
   off = round_up(off + ceil_div(values2, (size_t)4) + 64, 256);  // 64: whole words past the last
   const size_t off_slots = off;
@@ -584,6 +596,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->chunk_agg = (uint64_t*)(base + off_chunks);
   c->local_pre = (uint64_t*)(base + off_local);
   c->bound = (uint16_t*)(base + off_bound);
+  c->fix = (uint2*)(base + off_fix);
   c->trits = base + off_trits;
   c->slots = base + off_slots;
   e = hipMemset(c->ws, 0, total);
@@ -662,15 +675,9 @@ int launch_max_pass(tlc_ctx* c, const float* x, const float* r, size_t n, uint32
       return launch_absmax_check(x, r, n, c->partials, np, c->stream);
     });
   return timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-    return launch_accum_absmax(x, nullptr, n, c->partials, np, nullptr, c->stream);
+    return launch_accum_absmax(x, nullptr, n, c->partials, np, nullptr, false, c->stream);
   });
 }
-
-// Below this the writing pass finds the tensor and the buffer in the last-level
-// cache, and the two passes of the default policy are the faster ones in place
-// too (a refused tensor is then left with the sums): 2M values 28 against 33
-// us, 10M 51 against 54, 18M 81 against 83.
-constexpr size_t kInPlaceMinValues = 20000000;
 
 // Steps 1, a and b for one tensor: residuals in r, trits in the workspace,
 // err and M in the control block and in hm.  Default policy: the check pass
@@ -683,7 +690,7 @@ int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
   if (in_place && n >= kInPlaceMinValues) {
     st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, c->stream);
+      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, true, c->stream);
     });
     if (st) return st;
     return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
@@ -701,15 +708,30 @@ int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float
   });
 }
 
-// The three passes of one tensor.
+// The three passes of one tensor.  In place, large: the max pass, then tiles
+// that quantize what its bounds let through (tlc_quant_encode_bounds_kernel).
 int launch_three_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint8_t* bytes,
                         HostMirror hm) {
   const uint32_t m = (uint32_t)quartic_len(n);
-  int st = launch_quantize_passes(c, x, r, n, s, hm);
-  if (st) return st;
-  st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
-    return launch_quant_encode(n, m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
-  });
+  const bool bounds = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u && n >= kInPlaceMinValues;
+  int st;
+  if (bounds) {
+    uint32_t np = 0;
+    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
+      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, false, c->stream);
+    });
+    if (st) return st;
+    st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
+      return launch_quant_encode_bounds(r, n, m, s, c->partials, np, c->bound, c->slots, c->recs,
+                                        c->fix, c->ctrl, hm, c->stream);
+    });
+  } else {
+    st = launch_quantize_passes(c, x, r, n, s, hm);
+    if (st) return st;
+    st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
+      return launch_quant_encode(n, m, c->slots, c->recs, c->trits, c->ctrl, c->stream);
+    });
+  }
   if (st) return st;
   if (zre_chunked(m)) {
     st = timed_launch(c, TLC_KERNEL_ZRE_CHUNKS, [&] {
@@ -720,7 +742,7 @@ int launch_three_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s,
   }
   return timed_launch(c, TLC_KERNEL_ZRE_COMPACT, [&] {
     return launch_zre_compact(c->recs, c->chunk_agg, c->local_pre, c->slots, m, bytes, c->ctrl, hm,
-                              c->stream);
+                              bounds ? c->fix : nullptr, r, n, c->stream);
   });
 }
 

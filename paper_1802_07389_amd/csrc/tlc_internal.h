@@ -125,14 +125,18 @@ static_assert(sizeof(EncDesc) == 64, "EncDesc is 64 bytes");
 // Per-tile record of the single-tensor encoder's first pass: the zero-run
 // summary of the whole tile (RunSum bits), the length of its leading run of
 // 121 bytes and how many bytes it wrote into its slot (its encoding from the
-// first non-121 byte on).
+// first non-121 byte on), and how many residuals it left to the compaction
+// (kFixCap at most; from bounds only).
 struct TileRec {
   uint64_t agg;
   uint16_t lead;  // <= kEncTile
   uint16_t len;   // <= kEncTile
-  uint32_t pad;
+  uint32_t left;
 };
 static_assert(sizeof(TileRec) == 16, "TileRec is 16 bytes");
+// A tile's list of residuals for the compaction: (k * kEncTile + position in
+// the tile, value bits) each.  Further ones are stored at once.
+constexpr uint32_t kFixCap = 256;
 
 // One stream of a batched decode or of a decode-sum.
 struct DecDesc {
@@ -179,10 +183,10 @@ inline void launch_k(void (*kernel)(Formals...), dim3 grid, dim3 block, hipStrea
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st);
 // In place: step 1 into the buffer (r NULL: max |x| alone) and the partial
-// maxima; bound (with r): per 32 values of r, the top half of the largest
-// |acc|.
+// maxima; bound (with r): per 32 values of r (lines) or per four, the top half
+// of the largest |acc|.
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, uint16_t* bound, hipStream_t st);
+                               uint32_t* nblocks, uint16_t* bound, bool lines, hipStream_t st);
 // Eq. 2 for a large tensor: final residuals in r and 2-bit trits, one byte per
 // four values.  After the check pass (its partials): from x + r (in_place: a
 // refused tensor is left with the sums); after the in-place max pass (its
@@ -196,6 +200,13 @@ hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* 
 // The tiles' own encodings from the trits.
 hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* recs,
                                const uint8_t* trits, const Ctrl* ctrl, hipStream_t st);
+// The same in place from the max pass's bounds of single float4s, with Eq. 2:
+// residuals of q != 0 go to the tiles' lists, fix.  A bound past the last float4's
+// may be read.
+hipError_t launch_quant_encode_bounds(float* r, uint64_t n, uint32_t m, float s,
+                                      const uint32_t* partials, uint32_t np,
+                                      const uint16_t* bound, uint8_t* slots, TileRec* recs,
+                                      uint2* fix, Ctrl* ctrl, HostMirror hm, hipStream_t st);
 // A small tensor in one launch (after the check pass, its partials, when it
 // has more than kExchangeTiles tiles).  in_place: a refused tensor is left
 // with the sums.  status, maxima: a word per tile each.
@@ -208,7 +219,8 @@ hipError_t launch_zre_chunks(const TileRec* recs, uint32_t ntiles, uint64_t* loc
                              uint64_t* chunk_agg, Ctrl* ctrl, hipStream_t st);
 hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
                               const uint64_t* local_pre, const uint8_t* slots, uint32_t m,
-                              uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st);
+                              uint8_t* out, Ctrl* ctrl, HostMirror hm, const uint2* fix, float* r,
+                              uint64_t n, hipStream_t st);
 // Comparison modes: stochastic trits of x, and the quartic bytes of any trits.
 hipError_t launch_stochastic_trits(const float* x, uint64_t n, float s, uint64_t seed,
                                    uint64_t step, const uint32_t* partials, uint32_t np,

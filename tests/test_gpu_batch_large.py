@@ -73,11 +73,11 @@ def encode_check(ctx, case, options, bad=None):
             assert F32(scales[t]).tobytes() == F32(M_ref).tobytes(), (t, n)
             assert np.array_equal(out[t][:lens[t]].cpu().numpy(), C_ref), (t, n)
         assert np.array_equal(g.bits(rd[t].cpu().numpy()), g.bits(r_ref)), (t, n)
-    # one shared writing pass, and one for each large tensor
+    # one shared tile pass, and one for each large tensor
     edge = WIDE if sum(c[0] for c in case if WIDE < c[0] <= EDGE) > CACHED else EDGE
     large = sum(c[0] > MIDDLE for c in case)
     middle = any(edge < c[0] <= MIDDLE for c in case)
-    assert launches[tlc.TLC_KERNEL_ACCUM_QUANTIZE] == large + middle
+    assert launches[tlc.TLC_KERNEL_QUANT_ENCODE] == large + middle
     assert launches[tlc.TLC_KERNEL_QUANT_ENCODE_BATCH] == any(c[0] <= edge for c in case)
     g.log(f"{[c[0] for c in case]} options {options} bad {bad} ok")
 

@@ -11,14 +11,16 @@ from paper_1802_07389_amd import workloads
 pytestmark = pytest.mark.gpu
 
 F32 = np.float32
-# 512 tiles of 4096 quartic bytes and up take the three passes
-BASE = 5 * 4096 * 512
+# 65 tiles of 4096 quartic bytes and up take the three passes; in place, those of
+# the default policy below 20,000,000 values, then their own
+BASE = {0: 5 * 4096 * 512, 1: 5 * 4096 * 1000}
+LINES = 4 * (20 * 4 * 256 * 256 - 3) + 1  # in place, see test_in_place_line_bounds
 
 
 @pytest.fixture(scope="module")
 def ctx():
     from paper_1802_07389_amd import tlc
-    c = tlc.Context(max_n=BASE + 256)
+    c = tlc.Context(max_n=max(BASE[1] + 256, LINES))
     yield c
     c.close()
 
@@ -32,16 +34,20 @@ def inputs(kind, n):
     if kind == "dense":  # every value is the largest or its negative
         x = np.where(np.arange(n) % 3 == 0, F32(-1.0), F32(1.0)).astype(F32)
         return x, np.zeros(n, F32)
+    if kind == "spread":  # a few in every group of threads, more than a tile's list holds
+        x = workloads.normal([87, n], n, 1e-5)
+        x[::37] = np.where(np.arange(len(x[::37])) % 2 == 0, F32(0.5), F32(-0.5))
+        return x, workloads.normal([88, n], n, 1e-5)
     return np.zeros(n, F32), np.full(n, -0.0, F32)  # "zero": M = 0, -0.0 kept
 
 
 @pytest.mark.parametrize("options", [0, 1], ids=["default", "in_place"])
-@pytest.mark.parametrize("kind", ["sparse", "dense", "zero"])
+@pytest.mark.parametrize("kind", ["sparse", "dense", "zero", "spread"])
 @pytest.mark.parametrize("extra,offset,r_offset", [(0, 0, 0), (1, 1, 0), (2, 0, 3), (3, 2, 2),
                                                    (29, 3, 1), (33, 0, 0), (127, 0, 1)])
 def test_flat_passes(ctx, options, kind, extra, offset, r_offset):
     import gpuutil as g
-    n = BASE + extra
+    n = BASE[options] + extra  # m % 4 = 0 to 3
     x, r = inputs(kind, n)
     r_ref = r.copy()
     st_ref, C_ref, M_ref = oracle.compress(x, r_ref, 1.5)
@@ -55,12 +61,14 @@ def test_flat_passes(ctx, options, kind, extra, offset, r_offset):
     assert np.array_equal(g.bits(r_gpu), g.bits(r_ref))
 
 
-@pytest.mark.parametrize("n", [4 * 1021 + 2, 4 * 524285 + 1])
+@pytest.mark.parametrize("n", [4 * 1021 + 2, 4 * 524285 + 1, LINES])
 @pytest.mark.parametrize("lane", range(8))
 def test_in_place_line_bounds(ctx, n, lane):
     """One float4 of each 128-byte line reaches half the scale: the line's bound
     has to hold it also where n cuts the unrolled loop of the max pass inside a
-    line (n / 4 three short of a multiple of its step, 4 * 256 float4s a block)."""
+    line (n / 4 three short of a multiple of its step, 4 * 256 float4s a block;
+    only LINES is large enough for the in-place max pass: bounds of single float4s
+    in 3LC, of lines in the no-ZRE mode)."""
     import gpuutil as g
     from paper_1802_07389_amd import tlc
     x = workloads.normal([85, n], n, 1e-5)
@@ -86,7 +94,7 @@ def test_in_place_line_bounds(ctx, n, lane):
 def test_refused_tensor_off_the_grid(ctx, options, where):
     """Inf at either end: the buffer as it was, or (in place) the sums."""
     import gpuutil as g
-    n = BASE + 30
+    n = BASE[options] + 30
     x, r = inputs("sparse", n)
     x[where] = np.inf
     r_ref = r.copy()
