@@ -11,17 +11,16 @@
 //       after the check pass, on large tensors: acc = x + r, 3-value
 //       quantization, the residual stored in place and 2-bit trits for the
 //       quartic pack                                (Section 3.1, Eq. 1-2)
-//   tlc_accum_absmax_kernel / _batch_kernel, tlc_quantize_lines_kernel
-//       the same in place: the tensor is added into the buffer with partial
-//       maxima of the sums (Fig. 3, Eq. 1), then the lines that can hold a
-//       q != 0 are quantized
+//   tlc_accum_absmax_kernel / _batch_kernel
+//       in place, large tensors: the tensor is added into the buffer with
+//       partial maxima of the sums (Fig. 3, Eq. 1) and a bound per float4
 //   tlc_quant_encode_kernel, tlc_zre_chunk_kernel, tlc_zre_compact_kernel
 //       the quartic pack from the trits and each tile's own zero-run encoding;
 //       then a scan of the tile summaries and the compaction into one stream
 //                                                   (Sections 3.2-3.3)
-//   tlc_quant_encode_bounds_kernel
-//       in place, one large tensor: the tiles quantize what the max pass's
-//       bounds let through themselves, without trits
+//   tlc_quant_encode_bounds_kernel, tlc_quant_pack_bounds_kernel
+//       after the in-place max pass: the tiles quantize what its bounds let
+//       through themselves, without trits
 //
 // The batch kernels (and the _many_ ones, for the tensors of a batch that are
 // too large for its one launch) run many tensors in one launch: every block
@@ -29,18 +28,11 @@
 // Everything is HBM streaming or bound by latency; nothing is a dense
 // contraction, so there is no MFMA.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 
 namespace tlc {
-
-// Max over the eight lanes of a line (quad_perm 1,0,3,2 and 2,3,0,1, then
-// row_half_mirror), in each of them; all eight lanes active.
-__device__ __forceinline__ uint32_t line_max(uint32_t v) {
-  v = umax32(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true));
-  v = umax32(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true));
-  return umax32(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));
-}
 
 // ---------------------------------------------------------------- Eq. 1
 // Step 1 and Eq. 1 in one read of the tensor: with kResid the buffer
@@ -57,33 +49,28 @@ __device__ __forceinline__ uint32_t line_max(uint32_t v) {
 // kStore false (with kResid): the check pass of the default error policy,
 // which only reduces max|x + r| and writes nothing.
 //
-// kBound (in place, large tensors): also store, for each line of eight
-// float4s (128 bytes) of the buffer (8), or for each float4 (1), the top 16
-// bits of the bit pattern of its largest |acc|.  That half-word h bounds the
-// values from above (|acc| < (h + 1) * 2^16 as bit patterns), so the pass that
-// follows can skip every line or float4 whose h lies below the top half of its
+// kBound (in place, large tensors): also store, for each float4 of the buffer,
+// the top 16 bits of the bit pattern of its largest |acc|.  That half-word h
+// bounds the values from above (|acc| < (h + 1) * 2^16 as bit patterns), so the
+// pass that follows can skip every float4 whose h lies below the top half of its
 // threshold U: all its values have q = 0 and keep acc.
 //
 // kKeep: plain loads, which leave what they read in the last-level cache for
 // the writing pass (where both tensors fit it).
-template <bool kResid = true, bool kStore = kResid, int kBound = 0, bool kKeep = false>
+template <bool kResid = true, bool kStore = kResid, bool kBound = false, bool kKeep = false>
 __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
                                                 float* __restrict__ r, uint64_t n,
                                                 uint32_t blk, uint32_t nblk,
                                                 uint16_t* __restrict__ bound = nullptr) {
   static_assert(!kStore || kResid, "only a buffer is stored");
-  static_assert(kBound == 0 || (kStore && (kBound == 1 || kBound == 8)),
-                "bounds are of a stored buffer");
+  static_assert(!kBound || kStore, "bounds are of a stored buffer");
   uint32_t mx = 0;
   const uint64_t tid = (uint64_t)blk * kThreads + threadIdx.x;
   const uint64_t stride = (uint64_t)nblk * kThreads;
   const uint64_t nv = n >> 2;
   auto ld = [](const float* p) { return kKeep ? ld4(p) : ld_stream(p); };
   uint64_t i = tid;
-  // with bounds of lines a line's eight lanes leave the loop together: line_max needs
-  // all of them, also where nv % 8 cuts the last line off
-  auto four = [&](uint64_t j) { return (kBound == 8 ? j | 7u : j) + 3 * stride < nv; };
-  for (; four(i); i += 4 * stride) {
+  for (; i + 3 * stride < nv; i += 4 * stride) {
     float4 a[4], b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) a[u] = ld(x + 4 * (i + u * stride));
@@ -98,30 +85,19 @@ __device__ __forceinline__ uint32_t absmax_part(const float* __restrict__ x,
       if (kStore) st_stream(r + 4 * (i + u * stride), v);
       const uint32_t m4 =
           max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w)));
-      if (kBound == 1) bound[i + u * stride] = (uint16_t)(m4 >> 16);
-      if (kBound == 8) {
-        const uint32_t lm = line_max(m4);
-        if ((threadIdx.x & 7u) == 0u) bound[(i + u * stride) >> 3] = (uint16_t)(lm >> 16);
-      }
+      if (kBound) bound[i + u * stride] = (uint16_t)(m4 >> 16);
       mx = max(mx, m4);
     }
   }
-  for (; i - (threadIdx.x & 63u) < nv; i += stride) {  // whole waves (line_max)
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < nv) {
-      v = ld(x + 4 * i);
-      if (kResid) {
-        const float4 b = ld(r + 4 * i);
-        v = make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);
-        if (kStore) st_stream(r + 4 * i, v);
-      }
+  for (; i < nv; i += stride) {
+    float4 v = ld(x + 4 * i);
+    if (kResid) {
+      const float4 b = ld(r + 4 * i);
+      v = make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);
+      if (kStore) st_stream(r + 4 * i, v);
     }
     const uint32_t m4 = max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w)));
-    if (kBound == 1 && i < nv) bound[i] = (uint16_t)(m4 >> 16);
-    if (kBound == 8) {
-      const uint32_t lm = line_max(m4);
-      if ((threadIdx.x & 7u) == 0u && i < nv) bound[i >> 3] = (uint16_t)(lm >> 16);
-    }
+    if (kBound) bound[i] = (uint16_t)(m4 >> 16);
     mx = max(mx, m4);
   }
   for (uint64_t e = (nv << 2) + tid; e < n; e += stride) {
@@ -192,20 +168,20 @@ __global__ __launch_bounds__(kThreads) void tlc_absmax_check_kernel(
     uint32_t* __restrict__ partials) {
   __shared__ uint32_t lds[kWaves];
   const uint32_t mx = block_max(
-      absmax_part<true, false, 0, kKeep>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x),
+      absmax_part<true, false, false, kKeep>(x, const_cast<float*>(r), n, blockIdx.x, gridDim.x),
       lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
-// Step 1 into the buffer and its max pass (in place, large tensors; kBound 8 or
-// 1), or the max pass of a tensor without one (0).
-template <int kBound>
+// Step 1 into the buffer and its max pass (in place, large tensors), or the
+// max pass of a tensor without one.
+template <bool kResid>
 __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_kernel(
     const float* __restrict__ x, float* __restrict__ r, uint64_t n,
     uint32_t* __restrict__ partials, uint16_t* __restrict__ bound) {
   __shared__ uint32_t lds[kWaves];
   const uint32_t mx = block_max(
-      absmax_part<kBound != 0, kBound != 0, kBound>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
+      absmax_part<kResid, kResid, kResid>(x, r, n, blockIdx.x, gridDim.x, bound), lds);
   if (threadIdx.x == 0) partials[blockIdx.x] = mx;
 }
 
@@ -231,75 +207,6 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_quantize_kernel(
     return;
   }
   accum_quantize_part(x, r, n, blockIdx.x, gridDim.x, sc.M, sc.U, trits);
-}
-
-// The same in place, after the max pass has left the sums in the buffer and a
-// bound per line: only the lines whose bound reaches U hold a q != 0, so only
-// those are read, and written whole (on gfx950 203 us of single float4s
-// against 178 us of whole lines with 29 % of 2^28 values' lines changed: what
-// a store in a read stream costs is the line, not its bytes).  Trits as
-// above.  A wave takes kLineSlots chunks of 64 float4s at a time and issues
-// their loads before it uses the first.
-constexpr int kLineSlots = 4;
-constexpr uint32_t kLineMaxBlocks = 2048;  // eight per CU, all resident
-
-__device__ __forceinline__ void quantize_lines_part(float* __restrict__ r, uint64_t n,
-                                                    uint32_t blk, uint32_t nblk, const Scale& sc,
-                                                    const uint16_t* __restrict__ bound,
-                                                    uint8_t* __restrict__ trits) {
-  const uint64_t nv = n >> 2;
-  if (blk == 0 && threadIdx.x == 0 && (n & 3u)) {  // the last n % 4 values
-    uint32_t tb = 0u;
-    for (uint64_t e = nv << 2; e < n; ++e) {
-      float o;
-      tb |= quantize_one(r[e], sc.M, sc.U, o) << (2u * (uint32_t)(e & 3u));
-      r[e] = o;
-    }
-    trits[nv] = (uint8_t)tb;
-  }
-  const uint32_t hU = __float_as_uint(sc.U) >> 16;
-  const uint64_t step = (uint64_t)nblk * kThreads * kLineSlots;
-  for (uint64_t i0 = (uint64_t)blk * kThreads * kLineSlots + threadIdx.x; i0 < nv; i0 += step) {
-    bool take[kLineSlots];
-    float4 v[kLineSlots];
-#pragma unroll
-    for (int u = 0; u < kLineSlots; ++u) {
-      const uint64_t i = i0 + u * kThreads;
-      take[u] = i < nv && bound[i >> 3] >= hU;
-    }
-#pragma unroll
-    for (int u = 0; u < kLineSlots; ++u)
-      if (take[u]) v[u] = ld_stream(r + 4 * (i0 + u * kThreads));
-#pragma unroll
-    for (int u = 0; u < kLineSlots; ++u) {
-      const uint64_t i = i0 + u * kThreads;
-      uint32_t tb = 0x55u;  // four times trit 1
-      if (take[u]) {
-        float4 o;
-        tb = quantize_one(v[u].x, sc.M, sc.U, o.x);
-        tb |= quantize_one(v[u].y, sc.M, sc.U, o.y) << 2;
-        tb |= quantize_one(v[u].z, sc.M, sc.U, o.z) << 4;
-        tb |= quantize_one(v[u].w, sc.M, sc.U, o.w) << 6;
-        st_stream(r + 4 * i, o);
-      }
-      if (i < nv) trits[i] = (uint8_t)tb;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void tlc_quantize_lines_kernel(
-    float* __restrict__ r, uint64_t n, uint8_t* __restrict__ trits,
-    const uint16_t* __restrict__ bound, const uint32_t* __restrict__ partials, uint32_t np,
-    float s, Ctrl* __restrict__ ctrl, HostMirror hm) {
-  __shared__ uint32_t lds[kWaves];
-  const Scale sc = finish_scale(partials, np, s, lds);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctrl->enc.err = sc.bad;
-    ctrl->enc.scale = sc.M;
-    host_put_result(hm.res, sc.bad, sc.M);
-  }
-  if (sc.bad) return;
-  quantize_lines_part(r, n, blockIdx.x, gridDim.x, sc, bound, trits);
 }
 
 // The max and the writing passes over a batch's middle tensors, laid end to end
@@ -340,7 +247,7 @@ __global__ __launch_bounds__(kThreads) void tlc_absmax_check_batch_kernel(
            [&](uint32_t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
                uint32_t nblk) {
              const uint32_t bm = block_max(
-                 absmax_part<true, false, 0, kKeep>(uniform_ptr(d.x) + lo,
+                 absmax_part<true, false, false, kKeep>(uniform_ptr(d.x) + lo,
                                                         uniform_ptr(d.r) + lo, n, blk, nblk),
                  lds);
              if (threadIdx.x == 0) partials[slot] = bm;
@@ -356,20 +263,18 @@ __global__ __launch_bounds__(kThreads) void tlc_accum_absmax_batch_kernel(
                uint32_t nblk) {
              const uint64_t at = (uint64_t)d.v0 * kManyValues + lo;
              const uint32_t bm =
-                 block_max(absmax_part<true, true, 8>(uniform_ptr(d.x) + lo,
+                 block_max(absmax_part<true, true, true>(uniform_ptr(d.x) + lo,
                                                          uniform_ptr(d.r) + lo, n, blk, nblk,
-                                                         bound + at / 32),
+                                                         bound + at / 4),
                            lds);
              if (threadIdx.x == 0) partials[slot] = bm;
            });
 }
 
-// kLines: after the in-place max pass.
-template <bool kLines>
 __global__ __launch_bounds__(kThreads) void tlc_quantize_many_kernel(
     const EncDesc* __restrict__ descs, uint32_t count, uint32_t units, uint32_t groups,
-    const uint32_t* __restrict__ partials, bool in_place, const uint16_t* __restrict__ bound,
-    uint8_t* __restrict__ trits, EncResult* __restrict__ results, HostMirror hm) {
+    const uint32_t* __restrict__ partials, bool in_place, uint8_t* __restrict__ trits,
+    EncResult* __restrict__ results, HostMirror hm) {
   __shared__ uint32_t lds[kWaves];
   for_many(descs, count, units, groups,
            [&](uint32_t t, const EncDesc& d, uint64_t lo, uint64_t n, uint32_t slot, uint32_t blk,
@@ -383,15 +288,10 @@ __global__ __launch_bounds__(kThreads) void tlc_quantize_many_kernel(
              const float* x = uniform_ptr(d.x) + lo;
              float* r = uniform_ptr(d.r) + lo;
              const uint64_t at = (uint64_t)d.v0 * kManyValues + lo;
-             if constexpr (kLines) {
-               if (!sc.bad)
-                 quantize_lines_part(r, n, blk, nblk, sc, bound + at / 32, trits + at / 4);
-             } else {
-               if (!sc.bad)
-                 accum_quantize_part(x, r, n, blk, nblk, sc.M, sc.U, trits + at / 4);
-               else if (in_place)
-                 store_sums(x, r, n, blk, nblk);
-             }
+             if (!sc.bad)
+               accum_quantize_part(x, r, n, blk, nblk, sc.M, sc.U, trits + at / 4);
+             else if (in_place)
+               store_sums(x, r, n, blk, nblk);
            });
 }
 
@@ -735,14 +635,14 @@ __global__ __launch_bounds__(kThreads) void tlc_quant_encode_many_kernel(
                              slots + (uint64_t)blockIdx.x * kEncTile, recs + blockIdx.x, sh);
 }
 
-// ---- in place, one large tensor: the first pass from the max pass's bounds of
+// ---- in place, large tensors: the first pass from the max pass's bounds of
 // single float4s.  A slice (four values of a partition) of a group of quartic
 // bytes lies in one float4 of the buffer's grid, or with m % 4 != 0 in two, and
 // most have q = 0 throughout: the others alone are read.  The residuals of
 // q != 0 go through LDS into the tile's list, which the compaction writes back:
 // a few scattered stores cost far less in a pass of their own than mixed into a
-// stream of reads.  In place, after many steps (a call; the lines pass, trits and
-// tiles from them | this pass, before and with the compaction's stores): 40M
+// stream of reads.  After many steps, a call (through a pass over the 128-byte
+// lines that reach the threshold, trits, and tiles from those | this pass): 40M
 // values 143 | 128 us, 2^26 224 | 204, 150M 449 | 397, 2^28 785 | 757, most of
 // them in zero runs 707 | 682.  At s = 1, where most waves are dense, 2^26 265 |
 // 244 and 2^28 1096 | 1057.
@@ -906,22 +806,24 @@ __device__ __forceinline__ void quantize_bounded_tile(
   __syncthreads();
 }
 
+struct BoundShared {
+  EncShared<kWaves> enc;
+  uint2 fix[kFixCap];
+  uint32_t left;  // residuals so far, also those that the list did not hold
+  uint32_t scale[kWaves];
+};
+
+// The tile's quartic bytes in sh.enc.q and its list in sh; false: the tensor is
+// refused, and its buffer keeps the sums.  report is called with the scale.
 // Bound by its scattered reads.  kGrid: m % 4 == 0 (one bound a slice; with two
 // 40M values took 134 us a call, with one 129).
-template <bool kGrid>
-__global__ __launch_bounds__(kThreads) void tlc_quant_encode_bounds_kernel(float* __restrict__ r, uint64_t n, uint32_t m, float s,
-                                    const uint32_t* __restrict__ partials, uint32_t np,
-                                    const uint16_t* __restrict__ bound,
-                                    uint8_t* __restrict__ slots, TileRec* __restrict__ recs,
-                                    uint2* __restrict__ fix, Ctrl* __restrict__ ctrl,
-                                    HostMirror hm) {
-  __shared__ EncShared<kWaves> enc;
-  __shared__ uint2 s_fix[kFixCap];
-  __shared__ uint32_t s_left, s_scale[kWaves];
-  if (threadIdx.x == 0) s_left = 0u;
-  const uint32_t t = blockIdx.x;
-  const uint64_t q0 = (uint64_t)t * kEncTile;
-  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
+template <bool kGrid, class Report>
+__device__ __forceinline__ bool bounded_tile(float* __restrict__ r, uint64_t n, uint32_t m,
+                                             uint64_t q0, uint32_t tile_bytes, float s,
+                                             const uint32_t* __restrict__ partials, uint32_t np,
+                                             const uint16_t* __restrict__ bound, BoundShared& sh,
+                                             Report report) {
+  if (threadIdx.x == 0) sh.left = 0u;
   // the bounds don't depend on M: loaded before the block reduces it
   typedef uint32_t pair __attribute__((aligned(2)));
   uint32_t h[kGroupsPerThread][5];
@@ -930,28 +832,86 @@ __global__ __launch_bounds__(kThreads) void tlc_quant_encode_bounds_kernel(float
     const uint32_t g = threadIdx.x + kThreads * it;
     const bool whole = group_whole(n, m, q0, tile_bytes, g);
 #pragma unroll
-    for (int k = 0; k < 5; ++k)
-      if (const uint16_t* p = bound + (((uint64_t)k * m + q0 + g * 4u) >> 2); whole)
-        h[it][k] = kGrid ? *p : *reinterpret_cast<const pair*>(p);
-      else
-        h[it][k] = 0u;
+    for (int k = 0; k < 5; ++k) {
+      const uint16_t* p = bound + (((uint64_t)k * m + q0 + g * 4u) >> 2);
+      h[it][k] = 0u;
+      if (whole) h[it][k] = kGrid ? *p : *reinterpret_cast<const pair*>(p);
+    }
   }
-  const Scale sc = finish_scale(partials, np, s, s_scale);  // holds a barrier
-  if (t == 0 && threadIdx.x == 0) {
-    ctrl->enc.err = sc.bad;
-    ctrl->enc.scale = sc.M;
-    host_put_result(hm.res, sc.bad, sc.M);
-  }
-  if (sc.bad) return;  // the buffer keeps the sums
-  quantize_bounded_tile<kGrid>(r, n, m, sc, q0, tile_bytes, h, enc.q, &s_left, s_fix);
-  const uint32_t left = umin32(s_left, kFixCap);
-  if (threadIdx.x < left) fix[(uint64_t)t * kFixCap + threadIdx.x] = s_fix[threadIdx.x];
+  const Scale sc = finish_scale(partials, np, s, sh.scale);  // holds a barrier
+  report(sc);
+  if (sc.bad) return false;
+  quantize_bounded_tile<kGrid>(r, n, m, sc, q0, tile_bytes, h, sh.enc.q, &sh.left, sh.fix);
+  return true;
+}
+
+template <bool kGrid, class Report>
+__device__ __forceinline__ void encode_bounded_tile(float* __restrict__ r, uint64_t n, uint32_t m,
+                                                    uint32_t t, float s,
+                                                    const uint32_t* __restrict__ partials,
+                                                    uint32_t np,
+                                                    const uint16_t* __restrict__ bound,
+                                                    uint8_t* __restrict__ slot,
+                                                    TileRec* __restrict__ rec,
+                                                    uint2* __restrict__ fix, BoundShared& sh,
+                                                    Report report) {
+  const uint64_t q0 = (uint64_t)t * kEncTile;
+  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
+  if (!bounded_tile<kGrid>(r, n, m, q0, tile_bytes, s, partials, np, bound, sh, report)) return;
+  const uint32_t left = umin32(sh.left, kFixCap);
+  if (threadIdx.x < left) fix[threadIdx.x] = sh.fix[threadIdx.x];
   static_assert(kFixCap <= kThreads, "an entry per thread");
   const uint32_t lo = 16u * threadIdx.x;
   const uint32_t cnt = lo < tile_bytes ? umin32(16u, tile_bytes - lo) : 0u;
-  const uint4 w[1] = {cnt ? *reinterpret_cast<const uint4*>(enc.q + lo) : make_uint4(0, 0, 0, 0)};
+  const uint4 w[1] = {cnt ? *reinterpret_cast<const uint4*>(sh.enc.q + lo)
+                          : make_uint4(0, 0, 0, 0)};
   const uint32_t nz[1] = {cnt ? nonzero_mask16_spread(w[0], cnt) : 0u};
-  encode_tile_runs<kThreads>(w, nz, tile_bytes, slots + q0, recs + t, enc, left);
+  encode_tile_runs<kThreads>(w, nz, tile_bytes, slot, rec, sh.enc, left);
+}
+
+template <bool kGrid>
+__global__ __launch_bounds__(kThreads) void tlc_quant_encode_bounds_kernel(
+    float* __restrict__ r, uint64_t n, uint32_t m, float s, const uint32_t* __restrict__ partials,
+    uint32_t np, const uint16_t* __restrict__ bound, uint8_t* __restrict__ slots,
+    TileRec* __restrict__ recs, uint2* __restrict__ fix, Ctrl* __restrict__ ctrl, HostMirror hm) {
+  __shared__ BoundShared sh;
+  const uint32_t t = blockIdx.x;
+  encode_bounded_tile<kGrid>(r, n, m, t, s, partials, np, bound, slots + (uint64_t)t * kEncTile,
+                             recs + t, fix + (uint64_t)t * kFixCap, sh, [&](const Scale& sc) {
+                               if (t == 0 && threadIdx.x == 0) {
+                                 ctrl->enc.err = sc.bad;
+                                 ctrl->enc.scale = sc.M;
+                                 host_put_result(hm.res, sc.bad, sc.M);
+                               }
+                             });
+}
+
+// The tiles of a batch's middle tensors.
+__global__ __launch_bounds__(kThreads) void tlc_quant_encode_bounds_many_kernel(
+    const EncDesc* __restrict__ descs, uint32_t count, const uint32_t* __restrict__ partials,
+    const uint16_t* __restrict__ bound, uint8_t* __restrict__ slots, TileRec* __restrict__ recs,
+    uint2* __restrict__ fix, EncResult* __restrict__ results, HostMirror hm) {
+  __shared__ BoundShared sh;
+  const uint32_t T = blockIdx.x;
+  const uint32_t t = find_desc(descs, count, T, [](const EncDesc& d) { return d.tile0; });
+  const EncDesc& d = descs[t];
+  auto report = [&](const Scale& sc) {
+    if (T == d.tile0 && threadIdx.x == 0) {
+      results[t].err = sc.bad;
+      results[t].scale = sc.M;
+      host_put_result(hm.res ? hm.res + t : nullptr, sc.bad, sc.M);
+    }
+  };
+  auto tile = [&](auto grid) {
+    encode_bounded_tile<decltype(grid)::value>(
+        uniform_ptr(d.r), d.n, d.m, T - d.tile0, d.s, partials + d.blk0, d.nblk,
+        bound + (uint64_t)d.v0 * (kManyValues / 4), slots + (uint64_t)T * kEncTile, recs + T,
+        fix + (uint64_t)T * kFixCap, sh, report);
+  };
+  if (d.m % 4u == 0u)
+    tile(std::true_type{});
+  else
+    tile(std::false_type{});
 }
 
 // Pass B: one wave per chunk of 64 tiles: every tile's prefix within its
@@ -1126,14 +1086,15 @@ __global__ __launch_bounds__(kThreads) void tlc_zre_compact_kernel(
 template <uint32_t kPer>
 __global__ __launch_bounds__(kThreads) void tlc_zre_compact_many_kernel(
     const EncDesc* __restrict__ descs, uint32_t count, const TileRec* __restrict__ recs,
-    const uint8_t* __restrict__ slots, EncResult* __restrict__ results, HostMirror hm) {
+    const uint8_t* __restrict__ slots, EncResult* __restrict__ results, HostMirror hm,
+    const uint2* __restrict__ fix) {
   const uint32_t t =
       find_desc(descs, count, blockIdx.x, [](const EncDesc& d) { return d.cblk0; });
   const EncDesc& d = descs[t];
   compact_tiles<kPer>(recs + d.tile0, nullptr, nullptr, slots + (uint64_t)d.tile0 * kEncTile, d.m,
                       (d.m + kEncTile - 1) / kEncTile, (blockIdx.x - d.cblk0) * kWaves,
-                      uniform_ptr(d.out), results + t, hm.res ? hm.res + t : nullptr, nullptr,
-                      nullptr, 0u);
+                      uniform_ptr(d.out), results + t, hm.res ? hm.res + t : nullptr,
+                      fix ? fix + (uint64_t)d.tile0 * kFixCap : nullptr, uniform_ptr(d.r), d.n);
 }
 
 // ---------------------------------------------------------------- small tensors
@@ -1660,6 +1621,9 @@ __global__ __launch_bounds__(kThreads) void tlc_stochastic_trits_kernel(
   }
 }
 
+// Sixteen bytes at any address.
+typedef uint32_t tlc_u4x1 __attribute__((ext_vector_type(4), aligned(1)));
+
 // The quartic bytes of all values from their trits, one tile per block.
 __global__ __launch_bounds__(kThreads) void tlc_quant_pack_kernel(
     uint64_t n, uint32_t m, const uint8_t* __restrict__ trits, uint8_t* __restrict__ out,
@@ -1680,13 +1644,12 @@ __global__ __launch_bounds__(kThreads) void tlc_quant_pack_kernel(
     init_trit_luts(s_lut);
     __syncthreads();
     const uint4 w = pack_trit_words(d[0], s_lut);
-    typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(1)));
-    u4 o;
+    tlc_u4x1 o;
     o.x = w.x;
     o.y = w.y;
     o.z = w.z;
     o.w = w.w;
-    *reinterpret_cast<u4*>(out + q0 + 16u * threadIdx.x) = o;
+    *reinterpret_cast<tlc_u4x1*>(out + q0 + 16u * threadIdx.x) = o;
   } else {
     uint32_t h[kGroupsPerThread][5];
     load_trits(trits, n, m, q0, tile_bytes, h);
@@ -1695,6 +1658,41 @@ __global__ __launch_bounds__(kThreads) void tlc_quant_pack_kernel(
     pack_trits(h, n, m, q0, tile_bytes, s_lut, s_q);
     for (uint32_t i = threadIdx.x; i < tile_bytes; i += kThreads) out[q0 + i] = s_q[i];
   }
+}
+
+// The same after the in-place max pass; the residuals that the tile's list holds
+// are stored once its reads are through.  (40M values, a call, with a pass over
+// lines and trits in between | this one: 132 | 119 us at s = 1.75, 153 | 143 at
+// s = 1.)
+template <bool kGrid>
+__global__ __launch_bounds__(kThreads) void tlc_quant_pack_bounds_kernel(
+    float* __restrict__ r, uint64_t n, uint32_t m, float s, const uint32_t* __restrict__ partials,
+    uint32_t np, const uint16_t* __restrict__ bound, uint8_t* __restrict__ out,
+    Ctrl* __restrict__ ctrl, HostMirror hm) {
+  __shared__ BoundShared sh;
+  const uint64_t q0 = (uint64_t)blockIdx.x * kEncTile;
+  const uint32_t tile_bytes = (uint32_t)umin64(kEncTile, (uint64_t)m - q0);
+  if (!bounded_tile<kGrid>(r, n, m, q0, tile_bytes, s, partials, np, bound, sh,
+                           [&](const Scale& sc) {
+                             if (blockIdx.x == 0 && threadIdx.x == 0) {
+                               const uint32_t len = sc.bad ? 0u : m;
+                               ctrl->enc.err = sc.bad;
+                               ctrl->enc.scale = sc.M;
+                               ctrl->enc.len = len;
+                               host_put_all(hm.res, sc.bad, len, sc.M);
+                             }
+                           }))
+    return;
+  if (threadIdx.x < umin32(sh.left, kFixCap)) {
+    const uint2 f = sh.fix[threadIdx.x];
+    r[(uint64_t)(f.x / (uint32_t)kEncTile) * m + q0 + f.x % (uint32_t)kEncTile] =
+        __uint_as_float(f.y);
+  }
+  if (tile_bytes == (uint32_t)kEncTile)
+    *reinterpret_cast<tlc_u4x1*>(out + q0 + 16u * threadIdx.x) =
+        *reinterpret_cast<const tlc_u4x1*>(sh.enc.q + 16u * threadIdx.x);
+  else
+    for (uint32_t i = threadIdx.x; i < tile_bytes; i += kThreads) out[q0 + i] = sh.enc.q[i];
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1730,14 +1728,12 @@ hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint3
 }
 
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, uint16_t* bound, bool lines, hipStream_t st) {
+                               uint32_t* nblocks, uint16_t* bound, hipStream_t st) {
   *nblocks = absmax_blocks(n);
-  if (!r)
-    launch_k(tlc_accum_absmax_kernel<0>, *nblocks, kThreads, st, x, r, n, partials, bound);
-  else if (lines)
-    launch_k(tlc_accum_absmax_kernel<8>, *nblocks, kThreads, st, x, r, n, partials, bound);
+  if (r)
+    launch_k(tlc_accum_absmax_kernel<true>, *nblocks, kThreads, st, x, r, n, partials, bound);
   else
-    launch_k(tlc_accum_absmax_kernel<1>, *nblocks, kThreads, st, x, r, n, partials, bound);
+    launch_k(tlc_accum_absmax_kernel<false>, *nblocks, kThreads, st, x, r, n, partials, bound);
   return hipGetLastError();
 }
 
@@ -1746,16 +1742,6 @@ hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s,
                                  uint8_t* trits, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   launch_k(tlc_accum_quantize_kernel, absmax_blocks(n), kThreads, st, x, r, n, trits, partials,
            np, s, in_place, ctrl, hm);
-  return hipGetLastError();
-}
-
-hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* partials,
-                                 uint32_t np, const uint16_t* bound, uint8_t* trits, Ctrl* ctrl,
-                                 HostMirror hm, hipStream_t st) {
-  constexpr uint64_t per = kThreads * kLineSlots;
-  const uint64_t want = std::max<uint64_t>(1, ((n >> 2) + per - 1) / per);
-  launch_k(tlc_quantize_lines_kernel, (uint32_t)std::min<uint64_t>(want, kLineMaxBlocks), kThreads,
-           st, r, n, trits, bound, partials, np, s, ctrl, hm);
   return hipGetLastError();
 }
 
@@ -1836,11 +1822,11 @@ hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
 
 hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_place,
                               uint32_t* partials, uint16_t* bound, uint8_t* trits, uint8_t* slots,
-                              TileRec* recs, EncResult* results, HostMirror hm, int pass,
+                              TileRec* recs, uint2* fix, EncResult* results, HostMirror hm, int pass,
                               hipStream_t st) {
   constexpr uint32_t kBlocks = kAbsmaxMaxBlocks;  // one per CU, as for a tensor alone
   if (pass == 0) {
-    if (p.lines)
+    if (p.bounds)
       launch_k(tlc_accum_absmax_batch_kernel, kBlocks, kThreads, st, descs, p.count, p.units,
                p.groups, partials, bound);
     else if (p.values * 2 * sizeof(float) <= kCacheBytes)
@@ -1849,22 +1835,22 @@ hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_p
     else
       launch_k(tlc_absmax_check_batch_kernel<false>, kBlocks, kThreads, st, descs, p.count,
                p.units, p.groups, partials);
-  } else if (pass == 1) {
-    if (p.lines)
-      launch_k(tlc_quantize_many_kernel<true>, kLineMaxBlocks, kThreads, st, descs, p.count,
-               p.units, p.groups, partials, in_place, bound, trits, results, hm);
-    else
-      launch_k(tlc_quantize_many_kernel<false>, kBlocks, kThreads, st, descs, p.count, p.units,
-               p.groups, partials, in_place, bound, trits, results, hm);
+  } else if (pass == 1) {  // not with bounds: the tiles quantize
+    launch_k(tlc_quantize_many_kernel, kBlocks, kThreads, st, descs, p.count, p.units, p.groups,
+             partials, in_place, trits, results, hm);
   } else if (pass == 2) {
-    launch_k(tlc_quant_encode_many_kernel, p.tiles, kThreads, st, descs, p.count, slots, recs,
-             trits, results);
+    if (p.bounds)
+      launch_k(tlc_quant_encode_bounds_many_kernel, p.tiles, kThreads, st, descs, p.count,
+               partials, bound, slots, recs, fix, results, hm);
+    else
+      launch_k(tlc_quant_encode_many_kernel, p.tiles, kThreads, st, descs, p.count, slots, recs,
+               trits, results);
   } else if (p.most_tiles <= kOwnPrefixTiles) {
     launch_k(tlc_zre_compact_many_kernel<kOwnPrefixTiles / kThreads>, p.compact_blocks, kThreads,
-             st, descs, p.count, recs, slots, results, hm);
+             st, descs, p.count, recs, slots, results, hm, p.bounds ? fix : nullptr);
   } else {
     launch_k(tlc_zre_compact_many_kernel<kManyMaxTiles / kThreads>, p.compact_blocks, kThreads, st,
-             descs, p.count, recs, slots, results, hm);
+             descs, p.count, recs, slots, results, hm, p.bounds ? fix : nullptr);
   }
   return hipGetLastError();
 }
@@ -1894,6 +1880,19 @@ hipError_t launch_quant_pack(uint64_t n, uint32_t m, const uint8_t* trits, uint8
                              Ctrl* ctrl, HostMirror hm, hipStream_t st) {
   const uint32_t blocks = (uint32_t)((m + kEncTile - 1) / kEncTile);
   launch_k(tlc_quant_pack_kernel, blocks, kThreads, st, n, m, trits, out, ctrl, hm);
+  return hipGetLastError();
+}
+
+hipError_t launch_quant_pack_bounds(float* r, uint64_t n, uint32_t m, float s,
+                                    const uint32_t* partials, uint32_t np, const uint16_t* bound,
+                                    uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st) {
+  const uint32_t blocks = (m + kEncTile - 1) / kEncTile;
+  if (m % 4 == 0)
+    launch_k(tlc_quant_pack_bounds_kernel<true>, blocks, kThreads, st, r, n, m, s, partials, np,
+             bound, out, ctrl, hm);
+  else
+    launch_k(tlc_quant_pack_bounds_kernel<false>, blocks, kThreads, st, r, n, m, s, partials, np,
+             bound, out, ctrl, hm);
   return hipGetLastError();
 }
 

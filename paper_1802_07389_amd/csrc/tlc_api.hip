@@ -139,7 +139,7 @@ struct tlc_ctx {
   TileRec* recs = nullptr;
   uint64_t* chunk_agg = nullptr;  // chunk summaries, scanned in place into chunk prefixes
   uint64_t* local_pre = nullptr;  // every tile's prefix within its chunk
-  uint16_t* bound = nullptr;      // per 32 or 4 values of the buffer: top half of max |acc|
+  uint16_t* bound = nullptr;      // per four values of the buffer: top half of max |acc|
   uint2* fix = nullptr;           // per tile: residuals for the compaction (TileRec::left)
   uint8_t* trits = nullptr;       // per four values: their trits
   // pinned host memory: status readback, batch results, descriptor staging
@@ -393,8 +393,8 @@ HostMirror batch_mirror(tlc_ctx* c) {
 // before its launches the host fills each result's err, len and scale words
 // with kPending, which none of their values takes (err is 0 or 1, a length
 // is below 2^31, a scale is finite), and then waits for the words to change
-// rather than for the stream.  Three passes: the writing (or lines) pass's
-// first block writes err and the scale (and a zero length on error), the
+// rather than for the stream.  Three passes: the first block of the pass that
+// quantizes writes err and the scale (and a zero length on error), the
 // compaction's last tile the length.  One launch: a tensor's last tile writes
 // all three in one store, on error as soon as M is known, else at its end.
 constexpr uint32_t kPending = 0xffffffffu;
@@ -567,12 +567,10 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   const size_t off_local = off;
   off = round_up(off + tiles1 * sizeof(uint64_t), 256);
   const size_t off_bound = off;
-  // of lines, or (a large tensor in place) of float4s
-  const bool large = max_n >= kInPlaceMinValues;
-  off = round_up(off + std::max(ceil_div(values2, (size_t)32), large ? max_n / 4 + 2 : 0) *
-                           sizeof(uint16_t), 256);
+  const bool large = max_n >= kInPlaceMinValues;  // one tensor, or a batch's middle ones
+  off = round_up(off + (large ? values2 / 4 + 2 : 0) * sizeof(uint16_t), 256);
   const size_t off_fix = off;
-  off = round_up(off + (large ? tiles1 * (size_t)kFixCap * sizeof(uint2) : 0), 256);
+  off = round_up(off + (large ? tiles2 * (size_t)kFixCap * sizeof(uint2) : 0), 256);
   const size_t off_trits = off;
   off = round_up(off + ceil_div(values2, (size_t)4) + 64, 256);  // 64: whole words past the last
   const size_t off_slots = off;
@@ -675,29 +673,30 @@ int launch_max_pass(tlc_ctx* c, const float* x, const float* r, size_t n, uint32
       return launch_absmax_check(x, r, n, c->partials, np, c->stream);
     });
   return timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-    return launch_accum_absmax(x, nullptr, n, c->partials, np, nullptr, false, c->stream);
+    return launch_accum_absmax(x, nullptr, n, c->partials, np, nullptr, c->stream);
   });
 }
 
-// Steps 1, a and b for one tensor: residuals in r, trits in the workspace,
-// err and M in the control block and in hm.  Default policy: the check pass
-// (8n bytes), then the writing pass (12n).  In place, from kInPlaceMinValues on:
-// the sums with the max pass (12n), then the lines that can hold a q != 0.
+// Whether a call takes one tensor of n values through the in-place max pass.
+bool sums_in_place(const tlc_ctx* c, size_t n) {
+  return (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u && n >= kInPlaceMinValues;
+}
+
+// Step 1 into the buffer (12n bytes), with partial maxima and bounds.
+int launch_sums_pass(tlc_ctx* c, const float* x, float* r, size_t n, uint32_t* np) {
+  return timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
+    return launch_accum_absmax(x, r, n, c->partials, np, c->bound, c->stream);
+  });
+}
+
+// Steps 1, a and b for one tensor: residuals in r, trits in the workspace, err
+// and M in the control block and in hm, by the check pass (8n bytes), then the
+// writing pass (12n).
 int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s,
                            HostMirror hm) {
   uint32_t np = 0;
   int st;
   const bool in_place = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u;
-  if (in_place && n >= kInPlaceMinValues) {
-    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, true, c->stream);
-    });
-    if (st) return st;
-    return timed_launch(c, TLC_KERNEL_ACCUM_QUANTIZE, [&] {
-      return launch_quantize_lines(r, n, s, c->partials, np, c->bound, c->trits, c->ctrl, hm,
-                                   c->stream);
-    });
-  }
   st = timed_launch(c, TLC_KERNEL_ABSMAX_CHECK, [&] {
     return launch_absmax_check(x, r, n, c->partials_chk, &np, c->stream);
   });
@@ -713,13 +712,11 @@ int launch_quantize_passes(tlc_ctx* c, const float* x, float* r, size_t n, float
 int launch_three_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s, uint8_t* bytes,
                         HostMirror hm) {
   const uint32_t m = (uint32_t)quartic_len(n);
-  const bool bounds = (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u && n >= kInPlaceMinValues;
+  const bool bounds = sums_in_place(c, n);
   int st;
   if (bounds) {
     uint32_t np = 0;
-    st = timed_launch(c, TLC_KERNEL_ABSMAX, [&] {
-      return launch_accum_absmax(x, r, n, c->partials, &np, c->bound, false, c->stream);
-    });
+    st = launch_sums_pass(c, x, r, n, &np);
     if (st) return st;
     st = timed_launch(c, TLC_KERNEL_QUANT_ENCODE, [&] {
       return launch_quant_encode_bounds(r, n, m, s, c->partials, np, c->bound, c->slots, c->recs,
@@ -749,12 +746,13 @@ int launch_three_passes(tlc_ctx* c, const float* x, float* r, size_t n, float s,
 // The three passes of a batch's middle tensors (descriptors d[0 .. plan.count)
 // in device memory).
 int launch_many_passes(tlc_ctx* c, const ManyPlan& plan, bool in_place, HostMirror hm) {
-  const int ids[4] = {plan.lines ? TLC_KERNEL_ABSMAX_BATCH : TLC_KERNEL_ABSMAX_CHECK_BATCH,
+  const int ids[4] = {plan.bounds ? TLC_KERNEL_ABSMAX_BATCH : TLC_KERNEL_ABSMAX_CHECK_BATCH,
                       TLC_KERNEL_ACCUM_QUANTIZE, TLC_KERNEL_QUANT_ENCODE, TLC_KERNEL_ZRE_COMPACT};
   for (int pass = 0; pass < 4; ++pass) {
+    if (pass == 1 && plan.bounds) continue;  // the tiles quantize
     const int st = timed_launch(c, ids[pass], [&] {
       return launch_encode_many(c->enc_descs, plan, in_place, c->partials_chk, c->bound, c->trits,
-                                c->slots, c->recs, c->enc_results, hm, pass, c->stream);
+                                c->slots, c->recs, c->fix, c->enc_results, hm, pass, c->stream);
     });
     if (st) return st;
   }
@@ -913,6 +911,14 @@ TLC_API int tlc_compress_ex(tlc_ctx* c, int mode, const float* tensor, float* re
       return launch_quant_pack(n, (uint32_t)m, c->trits, bytes, c->ctrl, enc_mirror(c),
                                c->stream);
     });
+  } else if (sums_in_place(c, n)) {
+    uint32_t np = 0;
+    st = launch_sums_pass(c, tensor, residual, n, &np);
+    if (st) return st;
+    st = timed_launch(c, TLC_KERNEL_QUANT_PACK, [&] {
+      return launch_quant_pack_bounds(residual, n, (uint32_t)m, s, c->partials, np, c->bound,
+                                      bytes, c->ctrl, enc_mirror(c), c->stream);
+    });
   } else {
     st = launch_quantize_passes(c, tensor, residual, n, s, HostMirror{});
     if (st) return st;
@@ -1032,7 +1038,7 @@ TLC_API int tlc_compress_batch(tlc_ctx* c, size_t count, const float* const* ten
   const bool join = wide * 2 * sizeof(float) > kCacheBytes;
   const uint32_t exchange = join ? kManyMinTiles : kExchangeTiles;
   if (join) plan.values += wide;
-  plan.lines =
+  plan.bounds =
       (c->options & TLC_OPT_IN_PLACE_FEEDBACK) != 0u && plan.values >= kInPlaceMinValues;
   uint32_t tiles = 0, shared = 0;
   c->owner.clear();

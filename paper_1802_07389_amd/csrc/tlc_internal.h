@@ -183,26 +183,21 @@ inline void launch_k(void (*kernel)(Formals...), dim3 grid, dim3 block, hipStrea
 hipError_t launch_absmax_check(const float* x, const float* r, uint64_t n, uint32_t* partials,
                                uint32_t* nblocks, hipStream_t st);
 // In place: step 1 into the buffer (r NULL: max |x| alone) and the partial
-// maxima; bound (with r): per 32 values of r (lines) or per four, the top half
-// of the largest |acc|.
+// maxima; bound (with r): per four values of r, the top half of the largest
+// |acc|.
 hipError_t launch_accum_absmax(const float* x, float* r, uint64_t n, uint32_t* partials,
-                               uint32_t* nblocks, uint16_t* bound, bool lines, hipStream_t st);
-// Eq. 2 for a large tensor: final residuals in r and 2-bit trits, one byte per
-// four values.  After the check pass (its partials): from x + r (in_place: a
-// refused tensor is left with the sums); after the in-place max pass (its
-// partials and bounds): from r.
+                               uint32_t* nblocks, uint16_t* bound, hipStream_t st);
+// Eq. 2 for a large tensor after the check pass (its partials): final residuals
+// in r and 2-bit trits, one byte per four values (in_place: a refused tensor is
+// left with the sums).
 hipError_t launch_accum_quantize(const float* x, float* r, uint64_t n, float s, bool in_place,
                                  const uint32_t* partials, uint32_t np, uint8_t* trits,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st);
-hipError_t launch_quantize_lines(float* r, uint64_t n, float s, const uint32_t* partials,
-                                 uint32_t np, const uint16_t* bound, uint8_t* trits, Ctrl* ctrl,
-                                 HostMirror hm, hipStream_t st);
 // The tiles' own encodings from the trits.
 hipError_t launch_quant_encode(uint64_t n, uint32_t m, uint8_t* slots, TileRec* recs,
                                const uint8_t* trits, const Ctrl* ctrl, hipStream_t st);
-// The same in place from the max pass's bounds of single float4s, with Eq. 2:
-// residuals of q != 0 go to the tiles' lists, fix.  A bound past the last float4's
-// may be read.
+// The same after the in-place max pass, from its bounds, with Eq. 2: residuals of
+// q != 0 go to the tiles' lists, fix.  A bound past the last float4's may be read.
 hipError_t launch_quant_encode_bounds(float* r, uint64_t n, uint32_t m, float s,
                                       const uint32_t* partials, uint32_t np,
                                       const uint16_t* bound, uint8_t* slots, TileRec* recs,
@@ -227,23 +222,28 @@ hipError_t launch_stochastic_trits(const float* x, uint64_t n, float s, uint64_t
                                    uint8_t* trits, Ctrl* ctrl, hipStream_t st);
 hipError_t launch_quant_pack(uint64_t n, uint32_t m, const uint8_t* trits, uint8_t* out,
                              Ctrl* ctrl, HostMirror hm, hipStream_t st);
+// The quartic bytes after the in-place max pass, with Eq. 2.
+hipError_t launch_quant_pack_bounds(float* r, uint64_t n, uint32_t m, float s,
+                                    const uint32_t* partials, uint32_t np, const uint16_t* bound,
+                                    uint8_t* out, Ctrl* ctrl, HostMirror hm, hipStream_t st);
 // x + r after the check pass (its partials), or x alone (r NULL).
 hipError_t launch_int8_quant(const float* x, float* r, uint64_t n, float s, bool in_place,
                              const uint32_t* partials, uint32_t npartials, uint8_t* out,
                              Ctrl* ctrl, HostMirror hm, hipStream_t st);
 hipError_t launch_int8_dequant(const uint8_t* C, uint64_t n, float M, float* out,
                                int accumulate, hipStream_t st);
-// Pass 0 (max), 1 (quantize), 2 (tiles) or 3 (compaction) of a batch's middle
-// tensors; descs in device memory, results by descriptor.
+// Pass 0 (max), 1 (quantize; not with bounds), 2 (tiles) or 3 (compaction) of a
+// batch's middle tensors; descs in device memory, results by descriptor.
 struct ManyPlan {
   uint32_t count, tiles, compact_blocks, most_tiles;
   uint32_t units, groups;  // kManyValues each; equal shares of them (a power of two)
   uint64_t values;
-  bool lines;  // the in-place max pass and lines, not the check and writing pass
+  bool bounds;  // the in-place max pass and tiles from its bounds
 };
 hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_place,
                               uint32_t* partials, uint16_t* bound, uint8_t* trits, uint8_t* slots,
-                              TileRec* recs, EncResult* results, HostMirror hm, int pass,
+                              TileRec* recs, uint2* fix, EncResult* results, HostMirror hm,
+                              int pass,
                               hipStream_t st);
 // owner: the tensor of each of the `tiles` tiles; the first `shared` are those
 // of tensors of more than one.
