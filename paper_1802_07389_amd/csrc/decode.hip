@@ -749,10 +749,13 @@ __device__ __forceinline__ void wave_expand(const SumSlice& sl, const SliceWords
 // wave into its own LDS range, with one block barrier per group; the next
 // group's bytes load while the current group is summed, and the groups'
 // LDS ranges alternate between two sets.
-// (Four blocks per CU, which the compiler would otherwise miss by six
-// registers: 37.0 against 38.1 us for 16 streams of 25.6M values.)
-template <bool kAcc>
-__global__ __launch_bounds__(kThreads, 4) void tlc_expand_sum_kernel(
+// kResident: blocks per CU that the registers have to allow.  Four, which the
+// compiler would otherwise miss by six registers, pay where the grid needs them
+// (37.0 against 38.1 us for 16 streams of 25.6M values); the few spilled ones
+// cost every launch a microsecond of scratch setup (one stream of 2,000 values
+// 14.9 against 13.9 us a call), so that smaller grids are compiled for three.
+template <bool kAcc, int kResident>
+__global__ __launch_bounds__(kThreads, kResident) void tlc_expand_sum_kernel(
     const DecDesc* __restrict__ descs, uint32_t count, const uint64_t* __restrict__ start,
     uint64_t n, uint64_t m, float* __restrict__ out, uint32_t epoch,
     const Ctrl* __restrict__ ctrl) {
@@ -952,12 +955,15 @@ hipError_t launch_expand_sum(const DecDesc* descs, uint32_t count, const uint64_
                              uint64_t n, uint64_t m, float* out, int accumulate, uint32_t epoch,
                              const Ctrl* ctrl, hipStream_t st) {
   const uint32_t blocks = (uint32_t)((m + kDecRange - 1) / kDecRange);
-  if (accumulate)
-    launch_k(tlc_expand_sum_kernel<true>, blocks, kThreads, st, descs, count, start, n, m, out,
-             epoch, ctrl);
-  else
-    launch_k(tlc_expand_sum_kernel<false>, blocks, kThreads, st, descs, count, start, n, m, out,
-             epoch, ctrl);
+#define TLC_LAUNCH(A, R)                                                                         \
+  launch_k(tlc_expand_sum_kernel<A, R>, blocks, kThreads, st, descs, count, start, n, m, out, epoch, \
+           ctrl)
+  if (blocks > 3u * kCus) {
+    if (accumulate) TLC_LAUNCH(true, 4); else TLC_LAUNCH(false, 4);
+  } else {
+    if (accumulate) TLC_LAUNCH(true, 3); else TLC_LAUNCH(false, 3);
+  }
+#undef TLC_LAUNCH
   return hipGetLastError();
 }
 

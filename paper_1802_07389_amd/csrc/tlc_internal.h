@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "tlc.h"
 
 namespace tlc {
@@ -35,6 +37,7 @@ inline uint32_t small_tiles(uint32_t m) { return (m + kSmallTile - 1) / kSmallTi
 // need (kExchangeTiles of half the size), a single launch.
 constexpr uint32_t kThreePassMinTiles = kExchangeTiles / 2 + 1;
 constexpr uint64_t kCacheBytes = 256ull << 20;  // the last-level cache
+constexpr uint32_t kCus = 256;
 constexpr uint32_t kAbsmaxMaxBlocks = 256;  // partial maxima per encode (one block per CU)
 // Up to this many tiles the compaction finds its prefixes without the chunk
 // pass: two summaries per thread.
@@ -283,11 +286,14 @@ hipError_t launch_expand_dequant(const uint8_t* C, uint32_t c, uint64_t* start,
                                  Ctrl* ctrl, HostMirror hm, hipStream_t st);
 // owner: the stream of each scan tile (not read when every stream has one),
 // of each range, in host memory as the descriptors; null: few streams, their
-// descriptors in device memory.  wide: tiles of kZreTile stream bytes where the streams
-// average more than four of the smaller tiles (16 streams of 366 KB: 10.1
-// against 15.0 us), else of kZreBatchTile (streams that mostly fit one tile).
+// descriptors in device memory.  wide: tiles of kZreTile stream bytes where the
+// streams average more than four of the smaller tiles and are long enough
+// together that fewer, longer tiles don't leave the chip idle (16 streams of 366
+// KB: 10.1 against 15.0 us; a call of 12 streams, 619 KB together 45.0 us with
+// the smaller tiles and 45.1 with these, 1.2 MB 46.1 and 46.0, 2.9 MB 53.4 and
+// 50.7; two of 52 KB 20.3 and 20.6), else of kZreBatchTile.
 inline bool batch_scan_wide(uint64_t stream_bytes, uint64_t count) {
-  return stream_bytes > 4u * count * (uint64_t)kZreBatchTile;
+  return stream_bytes > 4u * std::max<uint64_t>(count, 32u) * kZreBatchTile;
 }
 hipError_t launch_zre_index_batch(const DecDesc* descs, uint32_t count, const uint16_t* owner,
                                   uint32_t tiles, bool wide, uint64_t* start, uint64_t* status,
