@@ -318,7 +318,8 @@ int take_slot(tlc_ctx* c, const void* src, size_t bytes, int* slot) {
   return TLC_OK;
 }
 
-// own (may be NULL): owners to follow the descriptors in the same copy.
+// own (may be NULL): owners to follow the descriptors in the same copy, which is
+// a whole number of 64 bytes (copies of 70 or 74 took 1 to 2 us longer).
 int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes, const void* own = nullptr,
            size_t own_bytes = 0) {
   int slot = 0;
@@ -326,7 +327,7 @@ int upload(tlc_ctx* c, void* dst, const void* src, size_t bytes, const void* own
   if (st) return st;
   if (own_bytes) {
     memcpy(c->staging + (size_t)slot * c->slot_bytes + bytes, own, own_bytes);
-    bytes += own_bytes;
+    bytes = round_up(bytes + own_bytes, 64);
   }
   const uint8_t* host = c->staging + (size_t)slot * c->slot_bytes;
   hipError_t e = hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, c->stream);
@@ -1184,13 +1185,21 @@ uint32_t place_scan_tiles(std::vector<DecDesc>& d, bool wide) {
   return (uint32_t)tiles;
 }
 
-// Fewer streams than this, some of several scan tiles: their blocks search the
-// descriptors in device memory.  Two dependent reads of host memory per block
-// (owner, descriptor) cost such a batch more than the copy (one stream of 1M
-// values 20.0 against 17.9 us, four of 2.6M 27.0 against 24.4); with more
-// streams, or one scan tile for each, the copy and the search cost more (ten of
-// 2M 36.8 against 35.3, 100 of 2,000 20.1 against 14.5).
-constexpr uint32_t kUploadStreams = 10;
+// Whether the blocks of a batched decode, some of whose streams have several
+// scan tiles, search the descriptors in device memory, rather than read their
+// stream's number and descriptor in host memory.  The two dependent reads over
+// the bus cost every block, the copy and the search grow with the streams, so
+// that the line runs where the average stream has 3 KB for each stream there is
+// (in device | host memory: two streams of 20 KB 16.6 | 18.9 us, eight of 16 KB
+// 21.5 | 20.0 and of 39 KB 18.7 | 19.8, 16 of 41 KB 24.5 | 22.5 and of 51 KB
+// 27.3 | 27.9, 24 of 48 KB 33.3 | 32.2 and of 109 KB 44.8 | 46.7).
+bool search_on_device(uint64_t stream_bytes, uint64_t streams) {
+  return stream_bytes > 3072u * streams * streams;
+}
+// From this many streams on, the scan of a summed decode finds its stream in a
+// table of owners instead of a search (24 streams: 74.9 us with the search, 74.5
+// with the table).
+constexpr uint32_t kSumOwnerStreams = 32;
 
 // Appends the stream of each scan tile to the call's owners.
 void add_scan_owners(tlc_ctx* c, const std::vector<DecDesc>& d, uint32_t tiles) {
@@ -1327,7 +1336,7 @@ TLC_API int tlc_decompress_batch(tlc_ctx* c, size_t count, const uint8_t* const*
   const DecDesc* descs = c->dec_descs;
   const uint16_t* owner = nullptr;
   int slot = -1;
-  if (tiles != cnt && cnt < kUploadStreams) {
+  if (tiles != cnt && search_on_device(stream_bytes, cnt)) {
     st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc));
   } else {
     // whose each range is, then (unless every stream has one) each scan tile
@@ -1404,12 +1413,13 @@ TLC_API int tlc_decompress_sum(tlc_ctx* c, size_t count, const uint8_t* const* b
   if (st) return st;
   const uint32_t cnt = (uint32_t)d.size();
   c->owner.clear();
-  if (tiles != cnt) add_scan_owners(c, d, tiles);
+  const bool table = tiles != cnt && cnt >= kSumOwnerStreams;
+  if (table) add_scan_owners(c, d, tiles);
   // to device memory: every block of the sum reads the descriptors
   st = upload(c, c->dec_descs, d.data(), cnt * sizeof(DecDesc), c->owner.data(),
               c->owner.size() * sizeof(uint16_t));
   if (st) return st;
-  const uint16_t* owner = (const uint16_t*)(c->dec_descs + cnt);
+  const uint16_t* owner = table ? (const uint16_t*)(c->dec_descs + cnt) : nullptr;
   uint32_t epoch = 0;
   st = next_dec_epoch(c, &epoch);
   if (st) return st;
