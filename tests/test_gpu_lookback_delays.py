@@ -51,7 +51,7 @@ def dt():
 
 @pytest.fixture(scope="module")
 def ctx(dt):
-    c = dt.Context(max_n=(1 << 25) + 64, max_tensors=400)
+    c = dt.Context(max_n=2051 * 4096 * 5, max_tensors=400)
     yield c
     c.close()
 
@@ -140,14 +140,14 @@ def test_three_pass_encoders(dt, ctx):
     n = 400 * 4096 * 5 - 3
     encode_check(ctx, workloads.normal([91, 0], n, 1e-3), workloads.normal([91, 1], n, 1e-4),
                  1.0, "three-pass, 400 tiles")
-    # 1639 tiles: with the chunk pass (its last block scans the chunks)
-    n = (1 << 25) + 7
+    # 2051 tiles: with the chunk pass (its last block scans the chunks)
+    n = 2051 * 4096 * 5 - 7
     x = workloads.runs_tensor([91, 2], n)
-    encode_check(ctx, x, np.zeros(n, F32), 1.5, "three-pass, 1639 tiles")
+    encode_check(ctx, x, np.zeros(n, F32), 1.5, "three-pass, 2051 tiles")
     n = 1 << 25
     encode_check(ctx, workloads.normal([91, 3], n, 1e-3), workloads.normal([91, 4], n, 1e-4),
                  1.0, "three-pass, m on the word grid")
-    ctx.set_options(dt.TLC_OPT_IN_PLACE_FEEDBACK)  # line bounds
+    ctx.set_options(dt.TLC_OPT_IN_PLACE_FEEDBACK)  # bounds
     try:
         encode_check(ctx, workloads.normal([91, 5], n, 1e-3), workloads.normal([91, 6], n, 1e-4),
                      1.0, "three-pass in place")

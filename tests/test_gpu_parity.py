@@ -175,13 +175,16 @@ def test_partitions_off_float4_grid(ctx, n, offset):
     check_encode_decode(ctx, x, np.zeros(n, F32), 1.0, offset=offset, tag=f"shift dense n={n}")
 
 
-# tensors of 520 encoder tiles and more take the three-pass encoder (each
+# tensors of 65 encoder tiles and more take the three-pass encoder (each
 # tile encoded into its own slot, then the tile summaries scanned and the
 # stream compacted); the patterns below stress its tile boundaries.  The
-# last two have m % 4 = 0 and n % 4 = 3 or 1: the float4 path with a
-# partial last float4, whose values the max pass quantizes one by one.
+# first five take eight summaries per thread of the compaction, the fourth and
+# fifth with m % 4 = 0 and n % 4 = 3 or 1 (a partial last float4, whose values
+# are quantized one by one); then two summaries, and a chunk pass before.
 THREE_PASS_N = [5 * 4096 * 520, 5 * 4096 * 520 + 13, 5 * (4096 * 531 + 2) - 1,
-                5 * 4096 * 520 - 1, 5 * 4096 * 520 - 3]
+                5 * 4096 * 520 - 1, 5 * 4096 * 520 - 3,
+                5 * 4096 * 65 + 1, 5 * 4096 * 200 - 3, 5 * 4096 * 512, 5 * 4096 * 512 + 1,
+                5 * 4096 * 2048, 5 * 4096 * 2048 + 1]
 
 
 @pytest.mark.parametrize("n", THREE_PASS_N)
@@ -653,8 +656,8 @@ def test_c5_aggregation_and_reencode(ctx):
 # ------------------------------------------------------------------ seeded shapes
 def _seeded_cases(count=40, seed=20261202):
     """(index, kind, n, offset, s, accumulate) draws: n log-uniform up to 3M
-    values, every tenth past the three-pass threshold (512 tiles of 4096
-    quartic bytes); offsets 0-4 values (alignment); s in [1, 2) as fp32."""
+    values, every tenth of 512 to 516 tiles of 4096 quartic bytes (the
+    three-pass encoder); offsets 0-4 values (alignment); s in [1, 2) as fp32."""
     rng = np.random.default_rng(seed)
     cases = []
     for i in range(count):
