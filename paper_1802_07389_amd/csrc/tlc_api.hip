@@ -555,7 +555,7 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   c->slot_bytes = round_up(max_tensors * 64 + c->owner_cap * sizeof(uint16_t), 64);
   // layout: ctrl | enc results | partials | check partials | enc status | dec status |
   //         start | enc descs | dec descs, owners | tile records | chunk summaries |
-  //         tile prefixes in their chunks | bounds | residual lists | trits | slots
+  //         tile prefixes in their chunks | bounds or trits | residual lists | slots
   // (the batch results follow the control block, so that one copy reads both)
   static_assert(sizeof(Ctrl) % alignof(EncResult) == 0, "results follow the control block");
   const size_t off_res = sizeof(Ctrl);
@@ -580,13 +580,15 @@ TLC_API int tlc_ctx_create_batch(tlc_ctx** out, size_t max_n, size_t max_tensors
   off = round_up(off + (tiles1 / 64 + 1) * sizeof(uint64_t), 256);
   const size_t off_local = off;
   off = round_up(off + tiles1 * sizeof(uint64_t), 256);
-  const size_t off_bound = off;
+  // bounds and trits share their place: a tensor's passes use one of them, and
+  // passes follow each other on the stream
+  const size_t off_bound = off, off_trits = off;
   const bool large = max_n >= kInPlaceMinValues;  // one tensor, or a batch's middle ones
-  off = round_up(off + (large ? values2 / 4 + 2 : 0) * sizeof(uint16_t), 256);
+  off = round_up(off + std::max((large ? values2 / 4 + 2 : 0) * sizeof(uint16_t),
+                                ceil_div(values2, (size_t)4) + 64),  // whole words past the last
+                 256);
   const size_t off_fix = off;
   off = round_up(off + (large ? tiles2 * (size_t)kFixCap * sizeof(uint2) : 0), 256);
-  const size_t off_trits = off;
-  off = round_up(off + ceil_div(values2, (size_t)4) + 64, 256);  // 64: whole words past the last
   const size_t off_slots = off;
   const size_t total = round_up(off + tiles2 * (size_t)kEncTile, 256);
   e = hipMalloc(&c->ws, total);
