@@ -1816,10 +1816,8 @@ hipError_t launch_zre_compact(const TileRec* recs, const uint64_t* chunk_pre,
            ntiles, out, ctrl, hm, fix, r, n)
   if (zre_chunked(m))
     TLC_LAUNCH(0u);
-  else if (ntiles > kFewPrefixTiles)
-    TLC_LAUNCH(kOwnPrefixTiles / kThreads);
   else
-    TLC_LAUNCH(kFewPrefixTiles / kThreads);
+    TLC_LAUNCH(kOwnPrefixTiles / kThreads);
 #undef TLC_LAUNCH
   return hipGetLastError();
 }
@@ -1829,7 +1827,6 @@ hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_p
                               TileRec* recs, uint2* fix, EncResult* results, HostMirror hm, int pass,
                               hipStream_t st) {
   constexpr uint32_t kBlocks = kAbsmaxMaxBlocks;  // one per CU, as for a tensor alone
-  static_assert(kManyMaxTiles <= kOwnPrefixTiles, "there is no chunk pass");
   if (pass == 0) {
     if (p.bounds)
       launch_k(tlc_accum_absmax_batch_kernel, kBlocks, kThreads, st, descs, p.count, p.units,
@@ -1850,11 +1847,11 @@ hipError_t launch_encode_many(const EncDesc* descs, const ManyPlan& p, bool in_p
     else
       launch_k(tlc_quant_encode_many_kernel, p.tiles, kThreads, st, descs, p.count, slots, recs,
                trits, results);
-  } else if (p.most_tiles <= kFewPrefixTiles) {
-    launch_k(tlc_zre_compact_many_kernel<kFewPrefixTiles / kThreads>, p.compact_blocks, kThreads,
+  } else if (p.most_tiles <= kOwnPrefixTiles) {
+    launch_k(tlc_zre_compact_many_kernel<kOwnPrefixTiles / kThreads>, p.compact_blocks, kThreads,
              st, descs, p.count, recs, slots, results, hm, p.bounds ? fix : nullptr);
   } else {
-    launch_k(tlc_zre_compact_many_kernel<kOwnPrefixTiles / kThreads>, p.compact_blocks, kThreads, st,
+    launch_k(tlc_zre_compact_many_kernel<kManyMaxTiles / kThreads>, p.compact_blocks, kThreads, st,
              descs, p.count, recs, slots, results, hm, p.bounds ? fix : nullptr);
   }
   return hipGetLastError();

@@ -40,12 +40,11 @@ constexpr uint64_t kCacheBytes = 256ull << 20;  // the last-level cache
 constexpr uint32_t kCus = 256;
 constexpr uint32_t kAbsmaxMaxBlocks = 256;  // partial maxima per encode (one block per CU)
 // Up to this many tiles the compaction finds its prefixes without the chunk
-// pass, eight summaries per thread, or two up to kFewPrefixTiles (a call with the
-// chunk pass | without: 11M values, 538 tiles, 62.5 | 59.0 us, 25.6M 108.8 |
-// 106.3, 41M, 2002 tiles, 162.7 | 162.0; with sixteen summaries 60M 222 | 222,
-// 80M, 3907 tiles, 284 | 287).
-constexpr uint32_t kFewPrefixTiles = 512;
-constexpr uint32_t kOwnPrefixTiles = 2048;
+// pass, two summaries per thread (9M values, 440 tiles, a call with the chunk
+// pass | without: 56.0 | 52.1 us).  With eight summaries, as a batch's middle
+// tensors have them, 11M values (538 tiles) would take 59.0 instead of 62.5 us,
+// 25.6M 106.3 instead of 108.8 and 41M 162.0 instead of 162.7.
+constexpr uint32_t kOwnPrefixTiles = 512;
 inline bool zre_chunked(uint32_t m) {
   return (m + (uint32_t)kEncTile - 1) / kEncTile > kOwnPrefixTiles;
 }

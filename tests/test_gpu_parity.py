@@ -178,9 +178,9 @@ def test_partitions_off_float4_grid(ctx, n, offset):
 # tensors of 65 encoder tiles and more take the three-pass encoder (each
 # tile encoded into its own slot, then the tile summaries scanned and the
 # stream compacted); the patterns below stress its tile boundaries.  The
-# first five take eight summaries per thread of the compaction, the fourth and
-# fifth with m % 4 = 0 and n % 4 = 3 or 1 (a partial last float4, whose values
-# are quantized one by one); then two summaries, and a chunk pass before.
+# fourth and fifth have m % 4 = 0 and n % 4 = 3 or 1 (a partial last float4,
+# whose values are quantized one by one); those of up to 512 tiles have no chunk
+# pass before the compaction.
 THREE_PASS_N = [5 * 4096 * 520, 5 * 4096 * 520 + 13, 5 * (4096 * 531 + 2) - 1,
                 5 * 4096 * 520 - 1, 5 * 4096 * 520 - 3,
                 5 * 4096 * 65 + 1, 5 * 4096 * 200 - 3, 5 * 4096 * 512, 5 * 4096 * 512 + 1,
