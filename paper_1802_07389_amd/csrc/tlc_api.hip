@@ -490,9 +490,12 @@ int check_usable(tlc_ctx* c, const char* fn) {
 }
 
 // Below this the writing pass finds the tensor and the buffer in the last-level
-// cache, and the two passes of the default policy are the faster ones in place
-// too (a refused tensor is then left with the sums): 2M values 28 against 33
-// us, 10M 51 against 54, 18M 81 against 83.
+// cache, and the two passes of the default policy are used in place too (a
+// refused tensor is then left with the sums).  Where most float4s change (s = 1)
+// they are the faster ones up to here, where few do (s = 1.75) up to 10M values
+// (theirs | the sums and bounds: 5M values 37.3 | 45.0 and 35.1 | 39.3 us, 10M 56.7
+// | 61.9 and 52.5 | 54.0, 14M 75.3 | 80.0 and 70.2 | 65.6, 20M 92.5 | 96.2 and 88.4
+// | 81.7; off the grid 98.0 | 98.7 and 94.1 | 83.4).
 constexpr size_t kInPlaceMinValues = 20000000;
 
 // How a batched encode takes a tensor of m quartic bytes (exchange: the most
