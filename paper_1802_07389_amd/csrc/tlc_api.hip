@@ -419,17 +419,18 @@ bool result_pending(const EncResult* r) {
   return err == kPending || w[2] == kPending || (err == 0u && w[1] == kPending);
 }
 
-// Encodes of at least this many values take long enough (58 us) to hide a query
-// of the stream.
-constexpr size_t kQueryMinValues = 10000000;
+// Encodes of at least this many values are long enough to hide a query of the
+// stream behind their kernels, also for calls that follow each other.
+constexpr size_t kQueryMinValues = 40000000;
 
 // Polls the armed results; falls back to waiting for the stream once the
 // stream has finished (or a look-back fault was flagged) without them.
 // A caller that then waits for the stream waits 12 us for the runtime to put its
 // signal behind the kernels, unless a query has done so while they ran: values
-// says how many they are (a call and a wait, without | with the query: 11M
-// values 68.3 | 64.2 us, 41M 170.7 | 165.2, 80M 292.9 | 287.4; a call alone is
-// no slower, 59.0 | 59.3, but at 5M 36.6 | 40.3).
+// says how many they are (a call and a wait, without | with the query: 41M
+// values 171.9 | 166.5 us, 60M 232 | 226, 80M 294 | 287; a call among others
+// 162.7 | 161.0, 222 | 221 and 284 | 282, but 25.6M 104.0 | 107.9 and 5M 36.6 |
+// 40.3).
 int wait_results(tlc_ctx* c, const EncResult* r, uint32_t count, size_t values) {
   if (values >= kQueryMinValues) {
     const hipError_t q = hipStreamQuery(c->stream);
