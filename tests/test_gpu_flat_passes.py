@@ -65,8 +65,9 @@ def test_flat_passes(ctx, options, kind, extra, offset, r_offset):
 @pytest.mark.parametrize("lane", range(8))
 def test_in_place_line_bounds(ctx, n, lane):
     """One float4 of each 128-byte line reaches half the scale: its bound has to
-    hold also where n cuts the unrolled loop of the max pass inside a line (n / 4 three short of a multiple of its step, 4 * 256 float4s a block;
-    only LINES is large enough for the in-place max pass)."""
+    hold also where n cuts the unrolled loop of the max pass inside a line (n / 4
+    three short of a multiple of its step, 4 * 256 float4s a block; only LINES is
+    large enough for the in-place max pass)."""
     import gpuutil as g
     from paper_1802_07389_amd import tlc
     x = workloads.normal([85, n], n, 1e-5)
